@@ -15,6 +15,8 @@ namespace sparq {
 constexpr int kChunk = 16;        // bytes one lane feeds to an int8 matrix instruction
 constexpr int kStepK = 64;        // reduction bytes per main-loop step
 constexpr int kPadN = 256;        // packed output channels are padded to this
+// bytes read + written from which a streaming kernel takes the non-temporal form: the last-level cache holds 256 MiB
+constexpr int64_t kStreamedBytes = (int64_t)256 << 20;
 
 inline int64_t round_up(int64_t v, int64_t m) { return (v + m - 1) / m * m; }
 

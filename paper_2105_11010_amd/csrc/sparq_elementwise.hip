@@ -11,8 +11,6 @@ constexpr int kEwThreads = 256;
 typedef unsigned int v4u __attribute__((ext_vector_type(4)));
 typedef int v4s __attribute__((ext_vector_type(4)));
 typedef float v4f __attribute__((ext_vector_type(4)));
-// bytes read + written from which a streaming kernel takes the non-temporal form: the last-level cache holds 256 MiB
-constexpr int64_t kStreamedBytes = (int64_t)256 << 20;
 
 static int ew_grid(int64_t work_items, int per_block) {
     int64_t blocks = (work_items + per_block - 1) / per_block;

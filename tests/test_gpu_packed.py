@@ -123,3 +123,47 @@ def test_convolution_on_packed_input(sq, oracle, layer, group):
         wsb = sq.sparq_workspace_bytes(d, m)
         sq.sparq_conv_gemm(xd, pw, d, m, acc=acc2, workspace=torch.empty(wsb, dtype=torch.uint8, device=dev) if wsb else None)
         assert torch.equal(acc, acc2)
+
+
+@pytest.mark.parametrize("mode,group", [((4, S.OPT5, 1, 1), 1), ((4, S.OPT3, 0, 1), 1), ((4, S.OPT5, 1, 0), 8)], ids=str)
+def test_calls_larger_than_the_last_level_cache(sq, mode, group):
+    """More than 256 MiB moved: unpacking goes through LDS; the last wavefront holds fewer than 64 records."""
+    m = sq.mode(*mode)
+    rows, C = 42037, 4064                                                    # 127 records a row
+    x = torch.randint(0, 256, (rows, C), dtype=torch.uint8, device="cuda")
+    x.mul_((torch.rand(rows, C, device="cuda") < 0.5).to(torch.uint8))
+    packed = torch.empty(sq.sparq_packed_act_bytes(rows, C, m, group), dtype=torch.uint8, device="cuda")
+    assert x.numel() + packed.numel() >= 256 << 20 and rows * (C // 32) % 64
+    sq.sparq_pack_act(x, packed, m, group)
+    y = torch.full_like(x, 0xCD)
+    sq.sparq_unpack_act(packed, y, m, group)
+    part = torch.empty_like(x)
+    step = 5000                                                              # small calls take the other form
+    for r in range(0, rows, step):
+        n = min(step, rows - r)
+        rec = packed.numel() // rows
+        sq.sparq_unpack_act(packed[r * rec:(r + n) * rec], part[r:r + n], m, group)
+    assert torch.equal(y, part)
+    if group == 1:
+        sq.sparq_trim(x, part, m)
+        assert torch.equal(y, part)
+
+
+@pytest.mark.parametrize("offset,C", [(1, 33), (3, 64), (4, 40), (2, 31)])
+def test_activations_that_start_anywhere(sq, oracle, offset, C):
+    """Activations at an odd address, ragged rows, and a last record that ends with the tensor."""
+    mode = (4, S.OPT5, 1, 1)
+    x = S.gen_activations((67, C), 0.5, S.rng_for(7, 300 + offset))
+    m = sq.mode(*mode)
+    buf = torch.zeros(x.size + 16, dtype=torch.uint8, device="cuda")
+    xd = buf[offset:offset + x.size].view(x.shape)
+    xd.copy_(torch.from_numpy(x))
+    packed = torch.empty(sq.sparq_packed_act_bytes(67, C, m), dtype=torch.uint8, device="cuda")
+    sq.sparq_pack_act(xd, packed, m)
+    out = torch.full((x.size + 16,), 0xCD, dtype=torch.uint8, device="cuda")
+    sq.sparq_unpack_act(packed, out[offset:offset + x.size].view(x.shape), m)
+    ref = oracle.pack_act(x, **kw(mode))
+    assert np.array_equal(packed.cpu().numpy().reshape(ref.shape), ref)
+    o = out.cpu().numpy()
+    assert np.array_equal(o[offset:offset + x.size].reshape(x.shape), oracle.trim(x, **kw(mode)))
+    assert (o[:offset] == 0xCD).all() and (o[offset + x.size:] == 0xCD).all()
