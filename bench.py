@@ -525,10 +525,10 @@ def main():
             ms6 = time_calls(torch, lambda i: sq.sparq_conv_gemm_sparse24(dom["x"], sp, dom["d"], pm, scale=dom["sc"], out=dom["out"],
                                                                           workspace=ws), args.warmup, args.steps)
             e = entry(wl_name + ", 2:4 pruned weights (activations picked by the kept weights, then paired: an expanded problem "
-                                "with 4x the channels whose weights are again 2:4 sparse)", [L], ms6, 4)
+                                "with 3x the channels whose weights are again 2:4 sparse)", [L], ms6, 4)
             e["plan"] = sq.sparq_sparse24_plan(dom["d"], pm)
-            e["note"] = ("value counts the dense layer's operations; with pairing on the expanded problem holds 4x the channels, "
-                         "on the sparse matrix instruction (plan ends in sparse_mfma) that is 2x the dense layer's matrix instructions")
+            e["note"] = ("value counts the dense layer's operations; with pairing on the expanded problem holds 3x the channels, "
+                         "on the sparse matrix instruction (plan ends in sparse_mfma) that is 1.5x the dense layer's matrix instructions")
             also.append(e)
             del sp, ws
             # the same pruned weights with vSPARQ off: no expansion, the layer itself on the sparse matrix instruction

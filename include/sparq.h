@@ -240,14 +240,16 @@ sparq_status sparq_conv_gemm_packed(const void *packed_x, size_t packed_x_bytes,
  *   (ta, tb) = the pair rule of Eq. 2 on the two picked activations (each
  *   trimmed on its own when mode->pair is 0).
  * MI355X has no datapath that trims after a sparse selection; with vSPARQ on
- * the result is computed exactly over an expanded problem (16 expanded channels
- * per group of four, in which the kept weights are again 2:4 sparse); with it
+ * the result is computed exactly over an expanded problem (12 expanded channels
+ * per group of four, one per activation and partner, in which the kept weights
+ * are again 2:4 sparse; the buffers are sized for 16); with it
  * off the problem is the layer itself.  Where the layer's plan is the
  * wave-specialised input-patch kernel the weights go to the sparse matrix
  * instruction as its sparse operand; otherwise the decompressed weights run
  * on the dense path.
  * sparq_sparse24_plan reports which (a text line as from sparq_conv_plan plus
- * "expanded_x4" and "sparse_mfma" / "dense_mfma").
+ * "expanded_x4", the problem over expanded groups of four, and "sparse_mfma" /
+ * "dense_mfma").
  * packed: 256-byte aligned, sparq_sparse24_packed_bytes() bytes, filled once
  * by sparq_pack_weights_sparse24 for the same desc and mode; workspace:
  * 256-byte aligned, sparq_sparse24_workspace_bytes() bytes.  Everything else

@@ -51,6 +51,11 @@ enum TrimKind : int {
     kTrimKinds
 };
 
+// The variants that look at two neighbouring activations (vSPARQ).
+constexpr bool trim_kind_pairs(int kind) {
+    return kind == kTrimFloorPair || kind == kTrimFloorPairWide || kind == kTrimRoundPairWide || kind == kTrimRoundPair4;
+}
+
 inline TrimKind trim_kind(const sparq_mode* m) {
     if (m->window_bits == 8) return kTrimNone;
     const bool wide = m->pair && m->window_bits < 4;
@@ -237,11 +242,16 @@ sparq_status launch_trim_pad(const uint8_t* x, uint8_t* xp, int64_t pixels, int 
                              const sparq_mode* mode, hipStream_t stream);
 
 
-// Implemented in sparq_sparse24.hip: the expanded activation tensor (16 bytes per group of four channels) and the
-// dense (expand: 16 bytes per group, else 4) form of 2:4 compressed weights.
+// 2:4 pruned weights with vSPARQ on: the expanded channels of C (sparq_sparse24.hip).  Blocked: the order the sparse
+// form of the input-patch kernel expands by itself; a fifth of padding costs less there than the expanded tensor does.
+inline bool sparse24_blocked(int C) { return C % 16 == 0 && round_up(C, 64) * 5 <= (int64_t)C * 6; }
+inline int64_t sparse24_channels(int C) { return sparse24_blocked(C) ? 3 * round_up(C, 64) : round_up(3 * (int64_t)C, 16); }
+
+// Implemented in sparq_sparse24.hip: the expanded activation tensor and the dense (expand: sparse24_channels(C) per
+// row of C, else C) form of 2:4 compressed weights, rows = output channels x taps.
 sparq_status launch_sparse24_expand_act(const uint8_t* x, uint8_t* xe, int64_t pixels, int C, const sparq_mode* mode,
                                         hipStream_t stream);
-sparq_status launch_sparse24_expand_weights(const int8_t* vals, const uint8_t* idx, int8_t* dense, int64_t groups, bool expand,
+sparq_status launch_sparse24_expand_weights(const int8_t* vals, const uint8_t* idx, int8_t* dense, int64_t rows, int C, bool expand,
                                             hipStream_t stream);
 // ... and the operands of the sparse matrix instruction (16 kept bytes + one word of positions per 32 reduction
 // indices) from dense weights [N][taps][C] with at most two non-zeros per aligned group of four channels.

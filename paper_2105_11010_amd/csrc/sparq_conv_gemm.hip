@@ -217,8 +217,8 @@ ConvPlan make_plan(const ConvGeom& g, const Tuning& tune) {
 }
 
 // 2:4 pruned weights run on the sparse matrix instruction when the layer's plan is the wave-specialised
-// input-patch kernel and the trim looks at one activation at a time (with pairing on, the caller expands the
-// problem and `kind` is the plain one; with it off the staging wavefronts trim as in the dense form).
+// input-patch kernel and the trim looks at one activation at a time (with pairing on, the problem is the expanded
+// one and `kind` is the plain one; with it off the staging wavefronts trim as in the dense form).
 bool sparse_plan(const ConvPlan& pl, TrimKind kind) {
     const bool single = kind == kTrimNone || kind == kTrimFloor || kind == kTrimRound || kind == kTrimRound4;
     return pl.patch && pl.ws && pl.variant->fn_sp && single;
@@ -306,7 +306,9 @@ void set_row_division(GemmParams& p) {
 // requantisation factors) as in sparq_conv_gemm_u8.
 // sp: the weights as operands of the sparse matrix instruction as well (2:4 pruned layers); used when the plan is
 // the wave-specialised input-patch kernel, ignored otherwise.
-struct SparseOperand { const uint8_t* vals; const uint32_t* pos; };
+// expand_mode: desc is the expanded layer (blocked order) but x is the tensor itself, with x_channels channels; the
+// sparse kernel expands it under that mode.  Where that kernel does not apply the call returns SPARQ_EUNSUPPORTED.
+struct SparseOperand { const uint8_t* vals; const uint32_t* pos; const sparq_mode* expand_mode = nullptr; int x_channels = 0; };
 sparq_status conv_launch(const uint8_t* x, const void* packed_w, const sparq_conv_desc* desc, const sparq_mode* mode,
                          int32_t* acc, const float* scale, float* out, uint8_t* y, const sparq_mode* out_mode,
                          void* workspace, size_t workspace_bytes, void* stream, const SparseOperand* sp = nullptr) {
@@ -420,16 +422,24 @@ sparq_status conv_launch(const uint8_t* x, const void* packed_w, const sparq_con
             qs.wpk = sp->vals;
             qs.widx = sp->pos;
             qs.w_bytes = (uint32_t)((size_t)g.Kp * g.Np / 2);
-            const sparq_status st = pl.variant->fn_sp(kind, qs, pl.npix, s);
-            if (st != SPARQ_EUNSUPPORTED) return st;
+            TrimKind skind = kind;
+            if (sp->expand_mode) {
+                skind = trim_kind(sp->expand_mode);
+                qs.luts = make_luts(sp->expand_mode->window_bits, sp->expand_mode->shift_mask);
+                qs.C = sp->x_channels;
+                qs.x_bytes = (uint32_t)((size_t)g.B * g.H * g.W * sp->x_channels);
+            }
+            const sparq_status st = pl.variant->fn_sp(skind, qs, pl.npix, s);
+            if (st != SPARQ_EUNSUPPORTED || sp->expand_mode) return st;
         }
-        {
+        if (!(sp && sp->expand_mode)) {
             const PatchLauncher fn = use_ws ? pl.variant->fn_ws : pl.variant->fn;
             const sparq_status st = fn(pkind, q, pl.npix, s);
             if (st != SPARQ_EUNSUPPORTED) return finish(st, pfused);
         }
     }
 
+    if (sp && sp->expand_mode) return SPARQ_EUNSUPPORTED;
     GemmParams p{};
     p.x = xin;
     p.wpk = static_cast<const uint8_t*>(packed_w) + g.w_off;
@@ -540,16 +550,24 @@ extern "C" sparq_status sparq_conv_gemm_packed(const void* packed_x, size_t pack
 
 // ---- 2:4 pruned weights (Section 4, sparse tensor core; Section 5.3): see sparq_sparse24.hip ----
 namespace {
-// The dense problem that is actually contracted: with vSPARQ on, 16 expanded channels per group of four.
-bool sparse24_geometry(const sparq_conv_desc* desc, const sparq_mode* mode, sparq_conv_desc* eff, bool* expand) {
+// What the entry points accept, and the size of their buffers, is that of a layer with four expanded channels per
+// channel (the form this path had first); the contracted layer never needs more than that.
+bool sparse24_bound(const sparq_conv_desc* desc, const sparq_mode* mode, sparq_conv_desc* bound, bool* expand) {
     ConvGeom g;
     if (!desc || desc->C % 4 != 0 || !conv_geom(desc, &g) || !mode_valid(mode)) return false;
     *expand = mode->pair && mode->window_bits != 8;
-    *eff = *desc;
+    *bound = *desc;
     if (*expand) {
         if ((int64_t)desc->C * 4 > 0x7FFFFFFF) return false;
-        eff->C = desc->C * 4;
+        bound->C = desc->C * 4;
     }
+    return conv_geom(bound, &g);
+}
+// The dense problem that is actually contracted: with vSPARQ on, 12 expanded channels per group of four.
+bool sparse24_geometry(const sparq_conv_desc* desc, const sparq_mode* mode, sparq_conv_desc* eff, bool* expand) {
+    ConvGeom g;
+    if (!sparse24_bound(desc, mode, eff, expand)) return false;
+    if (*expand) eff->C = (int)sparse24_channels(desc->C);
     return conv_geom(eff, &g);
 }
 const sparq_mode kNoPairPlain = {8, 1, 0, 0};
@@ -572,10 +590,10 @@ Sparse24Layout sparse24_layout(const sparq_conv_desc& eff) {
 }  // namespace
 
 extern "C" size_t sparq_sparse24_packed_bytes(const sparq_conv_desc* desc, const sparq_mode* mode) {
-    sparq_conv_desc eff;
+    sparq_conv_desc bound;
     bool expand;
-    if (!sparse24_geometry(desc, mode, &eff, &expand)) return 0;
-    const Sparse24Layout L = sparse24_layout(eff);
+    if (!sparse24_bound(desc, mode, &bound, &expand)) return 0;
+    const Sparse24Layout L = sparse24_layout(bound);
     return L.tiles + L.dense + L.vals + L.pos;
 }
 
@@ -587,8 +605,8 @@ extern "C" sparq_status sparq_pack_weights_sparse24(const int8_t* w_vals, const 
     if (packed_bytes < sparq_sparse24_packed_bytes(desc, mode)) return SPARQ_EWORKSPACE;
     const Sparse24Layout L = sparse24_layout(eff);
     int8_t* dense = static_cast<int8_t*>(packed) + L.tiles;
-    const int64_t groups = (int64_t)desc->N * desc->KH * desc->KW * (desc->C / 4);
-    sparq_status st = launch_sparse24_expand_weights(w_vals, w_idx, dense, groups, expand, static_cast<hipStream_t>(stream));
+    sparq_status st = launch_sparse24_expand_weights(w_vals, w_idx, dense, (int64_t)desc->N * desc->KH * desc->KW, desc->C, expand,
+                                                     static_cast<hipStream_t>(stream));
     if (st != SPARQ_OK) return st;
     st = sparq_pack_weights(dense, &eff, packed, L.tiles, stream);
     if (st != SPARQ_OK || !L.sparse) return st;
@@ -600,11 +618,11 @@ extern "C" sparq_status sparq_pack_weights_sparse24(const int8_t* w_vals, const 
 }
 
 extern "C" size_t sparq_sparse24_workspace_bytes(const sparq_conv_desc* desc, const sparq_mode* mode) {
-    sparq_conv_desc eff;
+    sparq_conv_desc bound;
     bool expand;
-    if (!sparse24_geometry(desc, mode, &eff, &expand)) return 0;
+    if (!sparse24_bound(desc, mode, &bound, &expand)) return 0;
     if (!expand) return sparq_workspace_bytes(desc, mode);
-    return (size_t)round_up((int64_t)eff.B * eff.H * eff.W * eff.C, 256) + sparq_workspace_bytes(&eff, &kNoPairPlain);
+    return (size_t)round_up((int64_t)bound.B * bound.H * bound.W * bound.C, 256) + sparq_workspace_bytes(&bound, &kNoPairPlain);
 }
 
 extern "C" sparq_status sparq_conv_gemm_sparse24(const uint8_t* x, const void* packed, const sparq_conv_desc* desc,
@@ -615,13 +633,24 @@ extern "C" sparq_status sparq_conv_gemm_sparse24(const uint8_t* x, const void* p
     if (!x || !packed || (!acc && !out) || !sparse24_geometry(desc, mode, &eff, &expand)) return SPARQ_EINVAL;
     const Sparse24Layout L = sparse24_layout(eff);
     const uint8_t* sp_vals = static_cast<const uint8_t*>(packed) + L.tiles + L.dense;
-    const SparseOperand sp_op = {sp_vals, reinterpret_cast<const uint32_t*>(sp_vals + L.vals)};
+    SparseOperand sp_op;
+    sp_op.vals = sp_vals;
+    sp_op.pos = reinterpret_cast<const uint32_t*>(sp_vals + L.vals);
     const SparseOperand* sp = L.sparse ? &sp_op : nullptr;
     if (!expand)      // nothing depends on the partner: the decompressed weights, the ordinary path
         return conv_launch(x, packed, desc, mode, acc, scale, out, nullptr, nullptr, workspace, workspace_bytes, stream, sp);
     if (!aligned(x, 4) || !workspace || !aligned(workspace, 256)) return SPARQ_EINVAL;
     if (workspace_bytes < sparq_sparse24_workspace_bytes(desc, mode)) return SPARQ_EWORKSPACE;
     const int64_t pixels = (int64_t)desc->B * desc->H * desc->W;
+    if (pixels * desc->C * 4 >= (int64_t)kInvalidOffset) return SPARQ_EUNSUPPORTED;
+    if (sp && sparse24_blocked(desc->C) && aligned(x, 16)) {      // the staging wavefronts expand what they load
+        SparseOperand fused = sp_op;
+        fused.expand_mode = mode;
+        fused.x_channels = desc->C;
+        const sparq_status st = conv_launch(x, packed, &eff, &kNoPairPlain, acc, scale, out, nullptr, nullptr, workspace,
+                                            workspace_bytes, stream, &fused);
+        if (st != SPARQ_EUNSUPPORTED) return st;
+    }
     const size_t x_room = (size_t)round_up(pixels * eff.C, 256);
     uint8_t* xe = static_cast<uint8_t*>(workspace);
     const sparq_status st = launch_sparse24_expand_act(x, xe, pixels, desc->C, mode, static_cast<hipStream_t>(stream));

@@ -6,16 +6,19 @@
 // coordinates; the coordinates pick two of the four activations, and the picked two form that output channel's
 // vSPARQ pair (Eq. 2).  The trim of an activation therefore depends on WHICH other activation the output channel
 // picks with it -- but only through one bit: whether that partner is zero.  With
-//     T_i = bSPARQ(x_i)              (partner non-zero)
-//     W_i = x_i with 2n bits kept    (partner zero; n = 4: x_i itself)
-//     B_i = min(T_i, W_i),
-// the value channel n sees is  B_i + F_ij,  F_ij = (x_j == 0 ? W_i : T_i) - B_i >= 0,  j = its partner.  So a
-// group of four input channels is expanded into 16 unsigned bytes -- B_0..B_3 and the twelve F_ij (i, then j
-// ascending) -- and an output channel's two kept weights are written at the four matching places of a
-// 16-byte weight group (w_i at B_i and at F_ij).  The plain-8-bit contraction of the expanded tensors is
-// then exactly the sparse, pair-trimmed dot product.  The expanded weights are again 2:4 sparse (two non-zeros in
-// 16), so they also go, as kept bytes plus positions, to the sparse matrix instruction (the SP form of the
-// input-patch kernel): two instructions' worth of work per kept weight pair instead of four dense ones.
+//     A(i|j) = x_i trimmed as the pair rule trims it beside x_j,
+// a group of four input channels has twelve such values, in three words of two pairs each:
+//     G_0 = A(0|1) A(1|0) A(2|3) A(3|2)    G_1 = A(0|2) A(2|0) A(1|3) A(3|1)    G_2 = A(0|3) A(3|0) A(1|2) A(2|1)
+// -- G_j is the ordinary trim of the group's bytes brought into another order.  Whatever two positions an output
+// channel keeps, both its values sit in one of the three words, so its two weights go to their two places there and
+// zeros everywhere else: the plain-8-bit contraction over 3C channels is exactly the sparse, pair-trimmed dot product.
+// (Three bytes per channel are also the least: the twelve values are independent of each other.)  Every expanded
+// aligned group of four again holds two non-zeros or none, so the weights also go, as kept bytes plus positions, to
+// the sparse matrix instruction (the SP form of the input-patch kernel).
+// Blocked order (sparse24_blocked: C a multiple of 16 that wastes at most a fifth on whole 64-channel blocks): a block
+// of 64 channels becomes three blocks of 64, all its G_0, all its G_1, all its G_2.  Then the SP kernel's staging
+// wavefronts read the tensor itself and trim each block three times, in three byte orders, and no expanded tensor is
+// written at all.  Otherwise the three words of a group follow each other and the pixel is padded to 16 channels.
 // With vSPARQ off (or a plain 8-bit layer) nothing depends on the partner: the problem is the layer itself.
 #include "sparq_common.h"
 
@@ -31,60 +34,59 @@ int sp_grid(int64_t items) {
     return (int)(blocks < 1 ? 1 : blocks);
 }
 
-// One lane per group of four channels of one pixel: 4 bytes in, 16 bytes out.
-__global__ __launch_bounds__(kSpThreads) void expand_act_kernel(const uint32_t* __restrict__ x, uint4* __restrict__ xe,
-                                                                 int64_t groups, TrimLuts Ln, TrimLuts Lw, int wide,
-                                                                 int round_nearest) {
+// Word of the expanded pixel (or weight row) that holds G_j of group `grp`.
+__device__ __forceinline__ int expanded_word(int grp, int j, bool blocked) {
+    return blocked ? (grp >> 4) * 48 + j * 16 + (grp & 15) : 3 * grp + j;
+}
+
+// One lane per group of four channels of one pixel: 4 bytes in, 12 out (groups past C: the zeros that fill the last block).
+__global__ __launch_bounds__(kSpThreads) void expand_act_kernel(const uint32_t* __restrict__ x, uint32_t* __restrict__ xe,
+                                                                 int64_t items, int groups, int groups_out, int words_out,
+                                                                 int blocked, TrimLuts L, int round_nearest) {
     const int64_t stride = (int64_t)gridDim.x * kSpThreads;
-    for (int64_t i = (int64_t)blockIdx.x * kSpThreads + threadIdx.x; i < groups; i += stride) {
-        const uint32_t v = x[i];
-        const uint32_t t = trim4_any(v, Ln, round_nearest != 0, false);              // every byte trimmed on its own
-        const uint32_t w = wide ? trim4_any(v, Lw, round_nearest != 0, false) : v;   // 2n-bit windows (n < 4) or untouched
-        uint32_t T[4], W[4], B[4], Z[4];
+    for (int64_t i = (int64_t)blockIdx.x * kSpThreads + threadIdx.x; i < items; i += stride) {
+        const int64_t pix = i / groups_out;
+        const int grp = (int)(i - pix * groups_out);
+        const uint32_t v = grp < groups ? x[pix * groups + grp] : 0u;
+        uint32_t* dst = xe + pix * words_out;
 #pragma unroll
-        for (int k = 0; k < 4; ++k) {
-            T[k] = (t >> (8 * k)) & 255u;
-            W[k] = (w >> (8 * k)) & 255u;
-            B[k] = T[k] < W[k] ? T[k] : W[k];
-            Z[k] = ((v >> (8 * k)) & 255u) == 0u;
-        }
-        uint32_t o[4] = {B[0] | (B[1] << 8) | (B[2] << 16) | (B[3] << 24), 0, 0, 0};
-#pragma unroll
-        for (int a = 0; a < 4; ++a) {
-            int r = 0;
-#pragma unroll
-            for (int b = 0; b < 4; ++b) {
-                if (b == a) continue;
-                const uint32_t f = (Z[b] ? W[a] : T[a]) - B[a];
-                const int e = 4 + 3 * a + r++;
-                o[e >> 2] |= f << (8 * (e & 3));
-            }
-        }
-        xe[i] = make_uint4(o[0], o[1], o[2], o[3]);
+        for (int j = 0; j < 3; ++j)
+            dst[expanded_word(grp, j, blocked != 0)] = trim4_any(perm(0, v, sparse24_pair_order(j)), L, round_nearest != 0, true);
+        if (!blocked && grp == groups_out - 1)
+            for (int k = 3 * groups_out; k < words_out; ++k) dst[k] = 0u;
     }
 }
 
 // One lane per (output channel, tap, group): two kept weights and their coordinates -> a dense group.
-// EXPAND: 16 bytes (w_i at B_i and at F_ij); otherwise the four bytes of the decompressed group.
+// EXPAND: three words, the weights at the places of their pair (words_out per tap, groups past `groups` are zeros);
+// otherwise the four bytes of the decompressed group.
 template <bool EXPAND>
 __global__ __launch_bounds__(kSpThreads) void expand_weights_kernel(const int8_t* __restrict__ vals, const uint8_t* __restrict__ idx,
-                                                                     uint32_t* __restrict__ dense, int64_t groups) {
+                                                                     uint32_t* __restrict__ dense, int64_t items, int groups,
+                                                                     int groups_out, int words_out, int blocked) {
     const int64_t stride = (int64_t)gridDim.x * kSpThreads;
-    for (int64_t i = (int64_t)blockIdx.x * kSpThreads + threadIdx.x; i < groups; i += stride) {
-        const uint32_t w0 = (uint8_t)vals[2 * i], w1 = (uint8_t)vals[2 * i + 1];
-        const int i0 = idx[2 * i] & 3, i1 = idx[2 * i + 1] & 3;                   // (coordinates are a precondition; masked for safety)
-        uint32_t o[4] = {0, 0, 0, 0};
-        o[0] = (w0 << (8 * i0)) | (w1 << (8 * i1));
+    for (int64_t i = (int64_t)blockIdx.x * kSpThreads + threadIdx.x; i < items; i += stride) {
+        const int64_t tap = i / groups_out;
+        const int grp = (int)(i - tap * groups_out);
+        uint32_t w0 = 0, w1 = 0;
+        int i0 = 0, i1 = 0;
+        if (grp < groups) {
+            const int64_t s = tap * groups + grp;
+            w0 = (uint8_t)vals[2 * s]; w1 = (uint8_t)vals[2 * s + 1];
+            i0 = idx[2 * s] & 3; i1 = idx[2 * s + 1] & 3;                         // (coordinates are a precondition; masked for safety)
+        }
         if (EXPAND) {
-            const int e0 = 4 + 3 * i0 + (i1 < i0 ? i1 : i1 - 1);                  // F_{i0,i1}: rank of i1 among the others
-            const int e1 = 4 + 3 * i1 + (i0 < i1 ? i0 : i0 - 1);
-            if (i0 != i1) {
-                o[e0 >> 2] |= w0 << (8 * (e0 & 3));
-                o[e1 >> 2] |= w1 << (8 * (e1 & 3));
-            }
-            reinterpret_cast<uint4*>(dense)[i] = make_uint4(o[0], o[1], o[2], o[3]);
+            uint32_t* dst = dense + tap * words_out;
+            const int word = (i0 ^ i1) - 1;                                       // which of G_0..G_2 holds the pair
+            // place of channel i inside G_j: nibble i of the table
+            const uint32_t place = word == 0 ? 0x3210u : word == 1 ? 0x3120u : 0x1320u;
+            const uint32_t o = (w0 << (8 * ((place >> (4 * i0)) & 3))) | (w1 << (8 * ((place >> (4 * i1)) & 3)));
+#pragma unroll
+            for (int j = 0; j < 3; ++j) dst[expanded_word(grp, j, blocked != 0)] = j == word ? o : 0u;
+            if (!blocked && grp == groups_out - 1)
+                for (int k = 3 * groups_out; k < words_out; ++k) dst[k] = 0u;
         } else {
-            dense[i] = o[0];
+            dense[i] = (w0 << (8 * i0)) | (w1 << (8 * i1));
         }
     }
 }
@@ -142,24 +144,28 @@ sparq_status launch_sparse24_pack_operand(const int8_t* dense, uint8_t* vals, ui
 
 sparq_status launch_sparse24_expand_act(const uint8_t* x, uint8_t* xe, int64_t pixels, int C, const sparq_mode* mode,
                                         hipStream_t s) {
-    const int n = mode->window_bits;
-    const int64_t groups = pixels * (C / 4);
-    if (groups == 0) return SPARQ_OK;
-    const TrimLuts Ln = make_luts(n, mode->shift_mask);
-    const bool wide = 2 * n < 8;
-    const TrimLuts Lw = wide ? make_luts(2 * n, wide_shift_mask(n, mode->shift_mask)) : Ln;
-    expand_act_kernel<<<sp_grid(groups), kSpThreads, 0, s>>>(reinterpret_cast<const uint32_t*>(x), reinterpret_cast<uint4*>(xe),
-                                                            groups, Ln, Lw, wide ? 1 : 0, mode->round_nearest);
+    const bool blocked = sparse24_blocked(C);
+    const int groups_out = blocked ? (int)round_up(C, 64) / 4 : C / 4;
+    const int64_t items = pixels * groups_out;
+    if (items == 0) return SPARQ_OK;
+    expand_act_kernel<<<sp_grid(items), kSpThreads, 0, s>>>(reinterpret_cast<const uint32_t*>(x), reinterpret_cast<uint32_t*>(xe), items,
+                                                           C / 4, groups_out, (int)(sparse24_channels(C) / 4), blocked ? 1 : 0,
+                                                           make_luts(mode->window_bits, mode->shift_mask), mode->round_nearest);
     return launch_status();
 }
 
-sparq_status launch_sparse24_expand_weights(const int8_t* vals, const uint8_t* idx, int8_t* dense, int64_t groups, bool expand,
+sparq_status launch_sparse24_expand_weights(const int8_t* vals, const uint8_t* idx, int8_t* dense, int64_t rows, int C, bool expand,
                                             hipStream_t s) {
-    if (groups == 0) return SPARQ_OK;
+    const bool blocked = expand && sparse24_blocked(C);
+    const int groups_out = blocked ? (int)round_up(C, 64) / 4 : C / 4;
+    const int64_t items = rows * groups_out;
+    if (items == 0) return SPARQ_OK;
+    uint32_t* d = reinterpret_cast<uint32_t*>(dense);
     if (expand)
-        expand_weights_kernel<true><<<sp_grid(groups), kSpThreads, 0, s>>>(vals, idx, reinterpret_cast<uint32_t*>(dense), groups);
+        expand_weights_kernel<true><<<sp_grid(items), kSpThreads, 0, s>>>(vals, idx, d, items, C / 4, groups_out,
+                                                                         (int)(sparse24_channels(C) / 4), blocked ? 1 : 0);
     else
-        expand_weights_kernel<false><<<sp_grid(groups), kSpThreads, 0, s>>>(vals, idx, reinterpret_cast<uint32_t*>(dense), groups);
+        expand_weights_kernel<false><<<sp_grid(items), kSpThreads, 0, s>>>(vals, idx, d, items, C / 4, groups_out, C / 4, 0);
     return launch_status();
 }
 

@@ -131,6 +131,10 @@ SPARQ_HD uint32_t lerp(uint32_t a, uint32_t b, uint32_t c) {
 }
 #endif
 
+// Byte order (a selector for perm(0, v, .)) that makes bytes (0,1) and (2,3) of a group of four channels its pairs of
+// partition j: j = 0: 01|23, 1: 02|13, 2: 03|12.
+SPARQ_HD uint32_t sparse24_pair_order(int j) { return j == 0 ? 0x03020100u : j == 1 ? 0x03010200u : 0x02010300u; }
+
 SPARQ_HD uint32_t bfi(uint32_t mask, uint32_t a, uint32_t b) { return (mask & a) | (~mask & b); }
 
 // 0xFF in every byte whose bit 7 is set in f

@@ -134,6 +134,34 @@ def test_sparse_instruction_kernel_with_one_output(sq, oracle, layer):
     assert np.all(np.abs(out.cpu().numpy().astype(np.float64) - ref_out) <= 1e-6 * np.abs(ref_out))
 
 
+# expansion inside the staging wavefronts: a last 64-channel block that is partly padding, units of several blocks
+# (1x1), every pairing trim
+BLOCKED_LAYERS = [
+    S.ConvLayer("blk_3x3_112_72", 2, 13, 11, 112, 72, 3, 3, (1, 1), (1, 1), 0.5, M45),
+    S.ConvLayer("blk_1x1_176_136", 2, 15, 15, 176, 136, 1, 1, (1, 1), (0, 0), 0.5, S.Mode(4, S.OPT3, 0, 1)),
+    S.ConvLayer("blk_1x1_256_70", 2, 15, 15, 256, 70, 1, 1, (1, 1), (0, 0), 0.4, S.Mode(3, S.OPT6_3B, 1, 1)),
+    S.ConvLayer("blk_1x1s2_128_300", 2, 15, 15, 128, 300, 1, 1, (2, 2), (0, 0), 0.5, S.Mode(2, S.OPT7_2B, 0, 1)),
+    S.ConvLayer("blk_5x5_64_65_2bit", 1, 12, 12, 64, 65, 5, 5, (1, 1), (2, 2), 0.6, S.Mode(2, S.OPT7_2B, 1, 1)),
+]
+
+
+@pytest.mark.parametrize("layer", BLOCKED_LAYERS, ids=lambda l: l.name)
+def test_sparse24_expanded_while_staging(sq, oracle, layer):
+    rng = S.rng_for(10, 300 + BLOCKED_LAYERS.index(layer))
+    x = S.gen_activations(layer.x_shape(), layer.zf, rng)
+    wv, wi = S.gen_sparse24_weights(layer.w_shape(), rng)
+    sc = S.gen_scales(layer.N, rng)
+    ref_acc, ref_out = oracle.conv_gemm_sparse24(x, wv, wi, layer.stride, layer.pad, scale=sc, **layer.mode.kwargs())
+    try:
+        for spec in FORMS:                       # the gather kernel reads the same expansion from memory
+            sq.sparq_set_tuning(spec)
+            acc, out = run_sparse(sq, layer, x, wv, wi, sc)
+            assert np.array_equal(acc, ref_acc), f"{layer.name} [{spec}]: int32 accumulators differ from the oracle"
+            assert np.all(np.abs(out.astype(np.float64) - ref_out) <= 1e-6 * np.abs(ref_out)), spec
+    finally:
+        sq.sparq_set_tuning(None)
+
+
 def test_extreme_values(sq, oracle):
     """All activations 255 or 0 in a pattern that makes every partner case occur, weights at -127 / 127."""
     layer = S.ConvLayer("sp_extreme", 1, 6, 6, 64, 32, 3, 3, (1, 1), (1, 1), 0.5, M45)
