@@ -76,6 +76,16 @@ __device__ __forceinline__ uint32_t trim4_kind(uint32_t x, const TrimLuts& L) {
     else return trim4<true, true, true>(x, L);
 }
 
+// The same with the partners' bytes given (pairing kinds only).
+template <int KIND>
+__device__ __forceinline__ uint32_t trim4_kind_beside(uint32_t x, uint32_t pm, const TrimLuts& L) {
+    static_assert(trim_kind_pairs(KIND), "a pairing trim");
+    if constexpr (KIND == kTrimFloorPair) return trim4_beside<false, true, false>(x, pm, L);
+    else if constexpr (KIND == kTrimFloorPairWide) return trim4_beside<false, true, true>(x, pm, L);
+    else if constexpr (KIND == kTrimRoundPair4) return trim4_round_n4_beside<true>(x, pm, L);
+    else return trim4_beside<true, true, true>(x, pm, L);
+}
+
 // ---- convolution geometry and packed weights --------------------------------
 struct ConvGeom {
     int B, H, W, C, N, KH, KW, sh, sw, ph, pw;

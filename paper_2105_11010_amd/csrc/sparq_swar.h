@@ -152,16 +152,15 @@ SPARQ_HD uint32_t low_mask(uint32_t selA, uint32_t selB, uint32_t a_hi, uint32_t
 // Trim four packed activations.  ROUND: "+R".  PAIR: vSPARQ on.  WIDE: a zero
 // partner grants a 2n-bit window with 2n < 8 (n = 2, 3); with n = 4 the value
 // simply stays as it is.
+// `pm`: 0xFF in bytes whose partner is non-zero (PAIR only).
 template <bool ROUND, bool PAIR, bool WIDE>
-SPARQ_HD uint32_t trim4(uint32_t x, const TrimLuts& L) {
+SPARQ_HD uint32_t trim4_beside(uint32_t x, uint32_t pm, const TrimLuts& L) {
     const uint32_t selA = (x >> 5) & 0x07070707u;
     const uint32_t selB = (x >> 2) & 0x07070707u;
     const uint32_t low_n = low_mask(selA, selB, L.a_hi, L.a_lo, L.b_hi, L.b_lo);
     uint32_t low = low_n;
     uint32_t wtop = 0;          // all bits up to the window top, per byte (only needed for ROUND)
     if (PAIR) {
-        // pm: bytes whose partner is non-zero (they are trimmed to n bits)
-        const uint32_t pm = expand_bit7_swapped(nonzero_flag(x));
         if (WIDE) {
             const uint32_t low_w = low_mask(selA, selB, L.wa_hi, L.wa_lo, L.wb_hi, L.wb_lo);
             low = bfi(pm, low_n, low_w);
@@ -182,19 +181,50 @@ SPARQ_HD uint32_t trim4(uint32_t x, const TrimLuts& L) {
     const uint32_t r = x & half & may_round;
     return fl + (r << 1);
 }
+template <bool ROUND, bool PAIR, bool WIDE>
+SPARQ_HD uint32_t trim4(uint32_t x, const TrimLuts& L) {
+    return trim4_beside<ROUND, PAIR, WIDE>(x, PAIR ? expand_bit7_swapped(nonzero_flag(x)) : 0u, L);
+}
 
 // n = 4 with rounding: the saturation test is a byte-wise compare against a per-region
 // threshold (one table lookup + v_lerp_u8), and rounding is "add the half bit, then drop the
 // residual": x + 2^(s-1) cannot leave the byte unless the value saturates.
 template <bool PAIR>
-SPARQ_HD uint32_t trim4_round_n4(uint32_t x, const TrimLuts& L) {
+SPARQ_HD uint32_t trim4_round_n4_beside(uint32_t x, uint32_t pm, const TrimLuts& L) {
     const uint32_t selA = (x >> 5) & 0x07070707u;
     const uint32_t selB = (x >> 2) & 0x07070707u;
     uint32_t low = low_mask(selA, selB, L.a_hi, L.a_lo, L.b_hi, L.b_lo);
-    if (PAIR) low &= expand_bit7_swapped(nonzero_flag(x));
+    if (PAIR) low &= pm;
     const uint32_t half = low & ~(low >> 1);
     const uint32_t sat = expand_bit7(lerp(x, perm(L.ncap_hi, L.ncap_lo, selA), 0u));   // x + (256 - cap) >= 256
     return (x + (half & ~sat)) & ~low;
+}
+template <bool PAIR>
+SPARQ_HD uint32_t trim4_round_n4(uint32_t x, const TrimLuts& L) {
+    return trim4_round_n4_beside<PAIR>(x, PAIR ? expand_bit7_swapped(nonzero_flag(x)) : 0u, L);
+}
+
+// ---- rows of an odd number of channels as one stream of 16-byte words ----
+// Pairs restart with every row, so a word's bytes can pair across its edges and the last byte of a row has no partner.
+// col: channel of the word's first byte (C >= 16: at most one row ends inside).  w: the word; nz[k]: 0xFF in the non-zero
+// bytes of w[k]; before / after: the same for the byte before the word (bits 31..24) and after it (bits 7..0).  pm[k]: 0xFF
+// in the bytes of w[k] whose partner is non-zero.
+SPARQ_HD void odd_row_partners(uint32_t col, uint32_t C, const uint32_t (&nz)[4], uint32_t before, uint32_t after, uint32_t (&pm)[4]) {
+    const uint32_t left = C - col;                           // bytes up to the end of the row
+    const uint32_t b = left < 17u ? left : 17u;              // first byte of the next row (past the word: none inside)
+    // bytes that are the first of their pair; the row's parity holds up to b, the next row's from there on
+    const uint32_t here = (col & 1u) ? 0xFF00FF00u : 0x00FF00FFu, next = (b & 1u) ? 0xFF00FF00u : 0x00FF00FFu;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        const uint32_t lo = k ? nz[k - 1] : before, hi = k < 3 ? nz[k + 1] : after;
+        const uint32_t up = (nz[k] >> 8) | (hi << 24), down = (nz[k] << 8) | (lo >> 24);
+        const int sh = (int)b - 4 * k;                       // bytes of this word that belong to the first row
+        const uint32_t mine = sh <= 0 ? 0u : sh >= 4 ? 0xFFFFFFFFu : (1u << (8 * sh)) - 1u;
+        const uint32_t first = bfi(mine, here, next);
+        const int e = (int)b - 1 - 4 * k;                    // the row's last byte (an even channel: no partner)
+        const uint32_t last = (e >= 0 && e < 4) ? 0xFFu << (8 * e) : 0u;
+        pm[k] = bfi(first, up, down) & ~last;
+    }
 }
 
 // Runtime-dispatched form for code that is not performance critical.

@@ -103,6 +103,23 @@ def test_trim_streamed_form(sq, oracle):
     assert np.array_equal(yd.cpu().numpy(), oracle.trim(x, **mode.kwargs()))
 
 
+@pytest.mark.parametrize("C", [17, 19, 31, 1023])
+@pytest.mark.parametrize("mode", [S.Mode(4, S.OPT5, 1, 1), S.Mode(4, S.OPT3, 0, 1), S.Mode(3, S.OPT6_3B, 1, 1),
+                                  S.Mode(2, S.OPT7_2B, 0, 1), S.Mode(4, S.OPT5, 1, 0)], ids=lambda m: m.label)
+def test_trim_odd_rows_as_one_stream(sq, oracle, C, mode):
+    """Odd channel counts of at least 16: pairs across words, wavefronts and workgroups, row ends at every place of a
+    word, tensors that end inside a word; more than one round per wavefront."""
+    rng = S.rng_for(8, 220 + C)
+    for rows in (1, 2, 61, 64, 999, 1 + (18 << 20) // C):
+        x = S.gen_activations((rows, C), 0.5, rng)
+        y = torch.full((rows * C + 16,), 77, dtype=torch.uint8, device="cuda:0")
+        sq.sparq_trim(dev(x), y[:rows * C].view(rows, C), sq.mode(*mode.astuple()))
+        torch.cuda.synchronize()
+        got = y.cpu().numpy()
+        assert np.array_equal(got[:rows * C].reshape(rows, C), oracle.trim(x, **mode.kwargs())), (rows, C)
+        assert np.all(got[rows * C:] == 77), "bytes past the tensor were written"
+
+
 # ------------------------------------------------------------- dequant ------
 
 @pytest.mark.parametrize("M,N", [(1, 1), (37, 19), (513, 64), (1000, 160)])
