@@ -110,8 +110,15 @@ def out_rows(d: SparqConvDesc) -> int:
     return d.B * Ho * Wo
 
 
-def _stream() -> ctypes.c_void_p:
-    return ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+# Address of a device's current stream, without the Stream object torch.cuda.current_stream() builds for it (2.9 us of a
+# 9 us call; 0.1 this way).
+_current_raw_stream = torch._C._cuda_getCurrentRawStream if hasattr(torch._C, "_cuda_getCurrentRawStream") else None
+
+
+def _stream() -> int:
+    if _current_raw_stream is None:
+        return torch.cuda.current_stream().cuda_stream
+    return _current_raw_stream(torch.cuda.current_device())
 
 
 def _dev(t: Optional[torch.Tensor], dtype, name: str) -> Optional[int]:
