@@ -270,6 +270,32 @@ def test_conv_shapes(sq, oracle, layer, mode, path):
     check_layer(sq, oracle, layer, mode, seed_cfg=8)
 
 
+# The split-reduction form (small layers): its three tiles; fewer reduction steps than wavefronts, shares of unequal
+# length, ragged tiles, padded channels, images that share a tile, a patch that fills most of LDS.
+SPLIT_SHAPES = [
+    ("32x32", S.ConvLayer("s_1x1_c128_m1", 1, 1, 1, 128, 33)),
+    ("32x32", S.ConvLayer("s_1x1_c160", 1, 33, 1, 160, 70)),
+    ("32x32", S.ConvLayer("s_3x3_7x7_c512", 1, 7, 7, 512, 96, 3, 3, (1, 1), (1, 1))),
+    ("32x32", S.ConvLayer("s_3x3_3x3_c80", 9, 3, 3, 80, 50, 3, 3, (1, 1), (1, 1))),
+    ("32x32", S.ConvLayer("s_1x1_c4608", 1, 40, 1, 4608, 40)),
+    ("32x32", S.ConvLayer("s_2x2_c72", 2, 10, 10, 72, 16, 2, 2, (1, 1), (0, 0))),
+    ("32x64", S.ConvLayer("s_3x3_28_c64_n130", 3, 28, 28, 64, 130, 3, 3, (1, 1), (1, 1))),
+    ("64x64", S.ConvLayer("s_3x3_56_c64", 4, 56, 56, 64, 64, 3, 3, (1, 1), (1, 1))),
+    ("64x64", S.ConvLayer("s_3x3_s2_c96_n70", 6, 60, 60, 96, 70, 3, 3, (2, 2), (1, 1))),
+]
+
+
+@pytest.mark.parametrize("tile,layer", SPLIT_SHAPES, ids=lambda v: v if isinstance(v, str) else v.name)
+@pytest.mark.parametrize("mode", [S.Mode(4, S.OPT5, 1, 1), S.Mode(4, S.OPT5, 1, 0), S.Mode(4, S.OPT3, 0, 1), S.Mode(4, S.OPT3, 0, 0),
+                                  S.Mode(3, S.OPT6_3B, 1, 0), S.Mode(2, S.OPT7_2B, 1, 1), S.Mode(2, S.OPT7_2B, 0, 1), S.PLAIN8],
+                         ids=lambda m: m.label)
+def test_conv_split_reduction(sq, oracle, tile, layer, mode):
+    d = sq.conv_desc(layer.B, layer.H, layer.W, layer.C, layer.N, layer.KH, layer.KW, layer.stride, layer.pad)
+    assert f"split_reduction tile={tile}" in sq.sparq_conv_plan(d, sq.mode(*mode.astuple()))
+    check_layer(sq, oracle, layer, mode, seed_cfg=8)
+    check_layer_u8(sq, oracle, layer, mode, seed_cfg=8)
+
+
 # Shapes chosen for the input-patch kernel: tiles that span several image rows and several images,
 # one-row tiles, every staging variant (64/128/256-channel units), several output-channel tiles.
 PATCH_SHAPES = [
