@@ -2,6 +2,7 @@
 // pre-pass for channel counts that are not a multiple of 16, and the choice of tile shape.
 #include "sparq_conv_gemm_kernel.h"
 #include "sparq_conv_patch_kernel.h"
+#include "sparq_conv_rows_kernel.h"
 #include "sparq_conv_split_kernel.h"
 
 #include <stdio.h>
@@ -217,9 +218,37 @@ const SplitVariant* pick_split(const ConvGeom& g, PatchGeom* pg, int* npix) {
     return nullptr;
 }
 
+// ---- 1x1 layers with the activations in registers --------------------------------------------
+struct RowsVariant { int steps; const char* name; RowsLauncher fn; };       // 32-index reduction steps it holds
+const RowsVariant kRowsVariants[] = {
+    {2, "64", launch_rows_k64}, {4, "128", launch_rows_k128}, {6, "192", launch_rows_k192}, {8, "256", launch_rows_k256},
+    {10, "320", launch_rows_k320}, {12, "384", launch_rows_k384}, {16, "512", launch_rows_k512}, {24, "768", launch_rows_k768}, {32, "1024", launch_rows_k1024},
+};
+
+bool prefer_gather(const ConvGeom& g);
+
+// Activations in registers: 1x1 layers without padding.  `bytes`: requantised results (16 of them leave together).
+// Up to 512 channels it beats the tile kernels nearly everywhere, by 1.1-1.6 x on small tensors and up to 2.2 x on large ones
+// (256 -> 64 channels, 802816 pixels 80 -> 69 us; 64 -> 256 bytes 106 -> 58; 128 -> 512 bytes 60 -> 35), except where four-byte
+// results larger than the last-level cache leave in rows of 1 KB or more (64 -> 256, 802816 pixels: 154 against 170 us: the
+// tile kernels write whole rows at a time).  Up to 768 channels many pixels are needed (768 -> 160, 36992 pixels 25.5 -> 22;
+// 768 -> 320, 8192 pixels 14 -> 16), up to 1024 it is ahead only where bytes would go to the gather kernel (1024 -> 512,
+// 50176 pixels 65 -> 53 us; four-byte results have the 128 x 512 tile there: 54 against 55).
+const RowsVariant* pick_rows(const ConvGeom& g, bool bytes) {
+    if (g.KH != 1 || g.KW != 1 || g.ph || g.pw || g.Cq % kStepK || g.M >= kPatchMaxDividend ||
+        (size_t)g.Kp * g.Np >= kPatchInvalidOffset || (int64_t)g.B * g.H * g.W >= kPatchMaxDividend)
+        return nullptr;
+    if (bytes ? g.N % 16 != 0 : (g.N >= 256 && g.M * g.N * 4 >= kStreamedBytes)) return nullptr;
+    if (g.K > 768 ? !(bytes && prefer_gather(g)) : g.K > 512 && !prefer_gather(g) && g.M < 32 * 1024) return nullptr;
+    for (const RowsVariant& v : kRowsVariants)
+        if (g.Cq / 32 <= v.steps) return &v;
+    return nullptr;
+}
+
 // Everything the entry points decide before launching.
 struct ConvPlan {
     const SplitVariant* split = nullptr;   // split-reduction form (then pg and npix are its own)
+    const RowsVariant* rows = nullptr;     // activations in registers; what follows is for calls it does not take
     bool patch = false;
     const PatchVariant* variant = nullptr;
     PatchGeom pg{};
@@ -229,7 +258,8 @@ struct ConvPlan {
 };
 
 // split: the split-reduction form may be taken (never for 2:4 pruned weights, nor when the tuning hook is in use).
-ConvPlan make_plan(const ConvGeom& g, const Tuning& tune, bool split = true) {
+// bytes: requantised results.
+ConvPlan make_plan(const ConvGeom& g, const Tuning& tune, bool split = true, bool bytes = false) {
     ConvPlan pl;
     if (g.fold) {               // at most 4 channels: 4-channel padded copy, pixel-folded, gather kernel
         pl.pad_bytes = (size_t)round_up((int64_t)g.B * g.H * g.W * 4, 256);
@@ -239,7 +269,12 @@ ConvPlan make_plan(const ConvGeom& g, const Tuning& tune, bool split = true) {
     const bool force_gather = tune.path == 1, force_patch = tune.path == 2;
     ConvGeom gk = g;
     gk.C = gk.Cp;                                                // what the kernel sees after the padding pre-pass
-    if (split && !tune.set() && (pl.split = pick_split(gk, &pl.pg, &pl.npix)) != nullptr) return pl;
+    if (split && !tune.set()) {
+        // (up to 256 channels the registers form is ahead of the split form at every size, beyond that behind it:
+        // 256 -> 256, 784 pixels 5.3 against 5.7 us; 512 -> 256 7.9 against 6.0)
+        pl.rows = pick_rows(gk, bytes);
+        if ((!pl.rows || g.K > 256) && (pl.split = pick_split(gk, &pl.pg, &pl.npix)) != nullptr) return pl;
+    }
     if (!force_gather && (force_patch || !prefer_gather(g)) && plan_patch(gk, &pl.pg, &pl.npix, &pl.ac, &pl.cbs)) {
         pl.variant = pick_patch(g, tune, pl.ac, pl.cbs, pl.npix, force_patch, &pl.ws);
         pl.patch = pl.variant != nullptr;
@@ -310,6 +345,8 @@ sparq_status plan_text(const sparq_conv_desc* desc, const sparq_mode* mode, char
     if (pl.split) {
         snprintf(text, text_bytes, "conv_patch_kernel split_reduction tile=%s patch_pixels=%d%s", pl.split->name, pl.npix,
                  pl.pad_bytes ? " padded_copy" : "");
+    } else if (pl.rows) {
+        snprintf(text, text_bytes, "conv_patch_kernel in_registers channels=%s%s", pl.rows->name, pl.pad_bytes ? " padded_copy" : "");
     } else if (pl.patch) {
         snprintf(text, text_bytes, "conv_patch_kernel tile=128x%d chunks=%d unit_channels=%d patch_pixels=%d%s%s",
                  pl.variant->tn, pl.ac, 64 * pl.cbs, pl.npix, pl.ws ? " wave_specialised" : "",
@@ -369,7 +406,7 @@ sparq_status conv_launch(const uint8_t* x, const void* packed_w, const sparq_con
         return SPARQ_EINVAL;
     hipStream_t s = static_cast<hipStream_t>(stream);
     const Tuning tune = current_tuning();
-    const ConvPlan pl = make_plan(g, tune, sp == nullptr);
+    const ConvPlan pl = make_plan(g, tune, sp == nullptr, y != nullptr);
     const size_t need = pl.pad_bytes;
     if (need) {
         if (!workspace || !aligned(workspace, 256)) return SPARQ_EINVAL;
@@ -425,9 +462,11 @@ sparq_status conv_launch(const uint8_t* x, const void* packed_w, const sparq_con
         return sparq_trim(y, y, g.M, g.N, out_mode, stream);
     };
 
-    // Small layers: the reduction split over a workgroup's wavefronts.
-    if (pl.split) {
-        SplitParams q{};
+    // An input that arrives trimmed (plain 8 bits) with an output to be trimmed for the next layer: the variants of the
+    // OUTPUT mode, told not to trim their input, do it in their epilogue (the two forms below; the third says why not always).
+    const bool out_only = trim_y && !fused_trim && kind == kTrimNone && mode->window_bits == 8 && g.N % 4 == 0 && g.Cp == g.C;
+    const sparq_mode* kmode = out_only ? out_mode : mode;
+    const auto fill = [&](auto& q) {
         q.x = xin;
         q.wpk = static_cast<const uint8_t*>(packed_w) + g.w_off;
         q.colsum = static_cast<const int32_t*>(packed_w);
@@ -435,6 +474,16 @@ sparq_status conv_launch(const uint8_t* x, const void* packed_w, const sparq_con
         q.x_bytes = (uint32_t)x_bytes;
         q.w_bytes = (uint32_t)((size_t)g.Kp * g.Np);
         q.N = g.N; q.Np = g.Np; q.C = g.Cp;
+        q.luts = make_luts(kmode->window_bits, kmode->shift_mask);
+        q.trim_in = out_only ? 0 : 1;
+        q.trim_out = fused_trim || out_only ? 1 : 0;
+    };
+    const TrimKind okind = out_only ? trim_kind(out_mode) : kind;
+
+    // Small layers: the reduction split over a workgroup's wavefronts.
+    if (pl.split) {
+        SplitParams q{};
+        fill(q);
         q.planes = g.Cq / kChunk;
         q.steps_tap = g.Cq / 32;
         q.steps = g.KH * g.KW * q.steps_tap;
@@ -442,13 +491,18 @@ sparq_status conv_launch(const uint8_t* x, const void* packed_w, const sparq_con
         q.div_steps_tap = make_fastdiv((uint32_t)q.steps_tap);
         q.div_kw = make_fastdiv((uint32_t)g.KW);
         q.g = pl.pg;
-        // an input that arrives trimmed with an output to be trimmed: the OUTPUT mode's variant, not trimming its input
-        const bool out_only = trim_y && !fused_trim && kind == kTrimNone && mode->window_bits == 8 && g.N % 4 == 0 && g.Cp == g.C;
-        const sparq_mode* kmode = out_only ? out_mode : mode;
-        q.luts = make_luts(kmode->window_bits, kmode->shift_mask);
-        q.trim_in = out_only ? 0 : 1;
-        q.trim_out = fused_trim || out_only ? 1 : 0;
-        return finish(pl.split->fn(out_only ? trim_kind(out_mode) : kind, q, pl.npix, s), q.trim_out != 0);
+        return finish(pl.split->fn(okind, q, pl.npix, s), q.trim_out != 0);
+    }
+
+    // 1x1 layers with a short reduction: activations in registers.
+    if (pl.rows) {
+        RowsParams q{};
+        fill(q);
+        q.M = (int)g.M;
+        q.steps = g.Cq / 32;
+        q.g = make_patch_geom(g.B, g.H, g.W, 1, 1, g.sh, g.sw, 0, 0);
+        const sparq_status st = pl.rows->fn(okind, q, s);
+        if (st != SPARQ_EUNSUPPORTED) return finish(st, q.trim_out != 0);
     }
 
     // Preferred: the input-patch kernel (activations loaded and trimmed once per tile and channel block).

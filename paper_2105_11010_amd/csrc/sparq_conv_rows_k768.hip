@@ -1,0 +1,6 @@
+// 1x1 SPARQ convolution with the activations in registers: up to 768 channels, every trim variant and output.
+#include "sparq_conv_rows_kernel.h"
+
+namespace sparq {
+SPARQ_DECLARE_ROWS(launch_rows_k768) { return launch_rows_kind<RowsCfg<24, 1, false, 2>>(kind, p, s); }
+}  // namespace sparq

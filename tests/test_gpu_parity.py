@@ -273,8 +273,9 @@ def test_conv_shapes(sq, oracle, layer, mode, path):
 # The split-reduction form (small layers): its three tiles; fewer reduction steps than wavefronts, shares of unequal
 # length, ragged tiles, padded channels, images that share a tile, a patch that fills most of LDS.
 SPLIT_SHAPES = [
-    ("32x32", S.ConvLayer("s_1x1_c128_m1", 1, 1, 1, 128, 33)),
-    ("32x32", S.ConvLayer("s_1x1_c160", 1, 33, 1, 160, 70)),
+    ("32x32", S.ConvLayer("s_1x3_c64", 1, 5, 5, 64, 33, 1, 3, (1, 1), (0, 1))),
+    ("32x32", S.ConvLayer("s_1x1_c320", 1, 33, 1, 320, 70)),
+    ("32x32", S.ConvLayer("s_1x1_c528_m1", 1, 1, 1, 528, 33)),
     ("32x32", S.ConvLayer("s_3x3_7x7_c512", 1, 7, 7, 512, 96, 3, 3, (1, 1), (1, 1))),
     ("32x32", S.ConvLayer("s_3x3_3x3_c80", 9, 3, 3, 80, 50, 3, 3, (1, 1), (1, 1))),
     ("32x32", S.ConvLayer("s_1x1_c4608", 1, 40, 1, 4608, 40)),
@@ -294,6 +295,34 @@ def test_conv_split_reduction(sq, oracle, tile, layer, mode):
     assert f"split_reduction tile={tile}" in sq.sparq_conv_plan(d, sq.mode(*mode.astuple()))
     check_layer(sq, oracle, layer, mode, seed_cfg=8)
     check_layer_u8(sq, oracle, layer, mode, seed_cfg=8)
+
+
+# The form with the activations in registers (1x1 layers): every number of reduction steps it holds and numbers in between,
+# pixels and channels that fill no fragment, strides, odd channel counts, runs of fewer than 128 result bytes, shares of the
+# output channels, 64 pixels per wavefront (many pixels and channels).
+ROWS_SHAPES = [
+    S.ConvLayer("r_c64_m3", 1, 3, 1, 64, 64), S.ConvLayer("r_c64_n33", 1, 65, 1, 64, 33), S.ConvLayer("r_c48_n48", 1, 9, 7, 48, 48),
+    S.ConvLayer("r_c128_n80_s2", 3, 15, 13, 128, 80, 1, 1, (2, 2), (0, 0)), S.ConvLayer("r_c65_n144", 2, 11, 11, 65, 144),
+    S.ConvLayer("r_c192_n272", 5, 20, 20, 192, 272), S.ConvLayer("r_c176_n400", 1, 3000, 1, 176, 400),
+    S.ConvLayer("r_c256_n1024_s3x2", 4, 17, 19, 256, 1024, 1, 1, (3, 2), (0, 0)), S.ConvLayer("r_c288_n96", 20, 35, 35, 288, 96),
+    S.ConvLayer("r_c384_n160", 1, 9001, 1, 384, 160), S.ConvLayer("r_c512_n144", 1, 12555, 1, 512, 144),
+    S.ConvLayer("r_c192_n512_wide", 1, 49169, 1, 192, 512), S.ConvLayer("r_c448_n528_wide", 1, 49169, 1, 448, 528),
+    S.ConvLayer("r_c768_n48", 1, 32799, 1, 768, 48),
+]
+
+
+@pytest.mark.parametrize("layer", ROWS_SHAPES, ids=lambda l: l.name)
+@pytest.mark.parametrize("mode", [S.Mode(4, S.OPT5, 1, 1), S.Mode(3, S.OPT6_3B, 0, 1), S.PLAIN8], ids=lambda m: m.label)
+def test_conv_activations_in_registers(sq, oracle, layer, mode):
+    d = sq.conv_desc(layer.B, layer.H, layer.W, layer.C, layer.N, layer.KH, layer.KW, layer.stride, layer.pad)
+    assert "in_registers" in sq.sparq_conv_plan(d, sq.mode(*mode.astuple()))
+    check_layer(sq, oracle, layer, mode, seed_cfg=8)
+    check_layer_u8(sq, oracle, layer, mode, seed_cfg=8, out_mode=S.Mode(4, S.OPT5, 1, 1))
+
+
+def test_conv_activations_in_registers_1024_channels(sq, oracle):
+    """More than 768 channels: requantised results of layers that fill the chip only."""
+    check_layer_u8(sq, oracle, S.ConvLayer("r_c1024_n128", 1, 32799, 1, 1024, 128), S.Mode(4, S.OPT5, 1, 1), seed_cfg=8)
 
 
 # Shapes chosen for the input-patch kernel: tiles that span several image rows and several images,
