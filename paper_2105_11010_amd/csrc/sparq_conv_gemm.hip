@@ -4,6 +4,7 @@
 #include "sparq_conv_patch_kernel.h"
 #include "sparq_conv_rows_kernel.h"
 #include "sparq_conv_split_kernel.h"
+#include "sparq_conv_wide_kernel.h"
 
 #include <stdio.h>
 #include <stdlib.h>
@@ -222,33 +223,56 @@ const SplitVariant* pick_split(const ConvGeom& g, PatchGeom* pg, int* npix) {
 struct RowsVariant { int steps; const char* name; RowsLauncher fn; };       // 32-index reduction steps it holds
 const RowsVariant kRowsVariants[] = {
     {2, "64", launch_rows_k64}, {4, "128", launch_rows_k128}, {6, "192", launch_rows_k192}, {8, "256", launch_rows_k256},
-    {10, "320", launch_rows_k320}, {12, "384", launch_rows_k384}, {16, "512", launch_rows_k512}, {24, "768", launch_rows_k768}, {32, "1024", launch_rows_k1024},
+    {10, "320", launch_rows_k320}, {12, "384", launch_rows_k384}, {16, "512", launch_rows_k512},
 };
-
-bool prefer_gather(const ConvGeom& g);
 
 // Activations in registers: 1x1 layers without padding.  `bytes`: requantised results (16 of them leave together).
 // Up to 512 channels it beats the tile kernels nearly everywhere, by 1.1-1.6 x on small tensors and up to 2.2 x on large ones
 // (256 -> 64 channels, 802816 pixels 80 -> 69 us; 64 -> 256 bytes 106 -> 58; 128 -> 512 bytes 60 -> 35), except where four-byte
 // results larger than the last-level cache leave in rows of 1 KB or more (64 -> 256, 802816 pixels: 154 against 170 us: the
-// tile kernels write whole rows at a time).  Up to 768 channels many pixels are needed (768 -> 160, 36992 pixels 25.5 -> 22;
-// 768 -> 320, 8192 pixels 14 -> 16), up to 1024 it is ahead only where bytes would go to the gather kernel (1024 -> 512,
-// 50176 pixels 65 -> 53 us; four-byte results have the 128 x 512 tile there: 54 against 55).
+// tile kernels write whole rows at a time).  (Holding 768 or 1024 channels was built too: behind the form below.)
 const RowsVariant* pick_rows(const ConvGeom& g, bool bytes) {
     if (g.KH != 1 || g.KW != 1 || g.ph || g.pw || g.Cq % kStepK || g.M >= kPatchMaxDividend ||
         (size_t)g.Kp * g.Np >= kPatchInvalidOffset || (int64_t)g.B * g.H * g.W >= kPatchMaxDividend)
         return nullptr;
     if (bytes ? g.N % 16 != 0 : (g.N >= 256 && g.M * g.N * 4 >= kStreamedBytes)) return nullptr;
-    if (g.K > 768 ? !(bytes && prefer_gather(g)) : g.K > 512 && !prefer_gather(g) && g.M < 32 * 1024) return nullptr;
     for (const RowsVariant& v : kRowsVariants)
         if (g.Cq / 32 <= v.steps) return &v;
     return nullptr;
+}
+
+// ---- 1x1 layers with a long reduction: eight wavefronts per tile ------------------------------
+struct WideVariant { const char* name; int tn; WideLauncher fn; };
+const WideVariant kWideVariants[] = {{"128x512", 512, launch_wide_512}, {"128x256", 256, launch_wide_256}};
+
+// Eight wavefronts per tile: 1x1 layers without padding and with more than 512 channels, whatever their size (what the split
+// form does not take), except many pixels with few output channels, where the 256-wide tile multiplies mostly padding.  Over
+// 220 shapes of 768 to 4608 channels (128..2048 outputs, 784..50176 pixels) 1.02 to 2 x faster than the kernels it replaced:
+// 65536 x 4608 x 512 int32 197 -> 172 us, bytes 233 -> 154; 50176 x 4608 x 320 207 -> 118; 50176 x 1024 -> 256 bytes 34 -> 28.
+// With 449 to 512 channels the activations fit in registers, and that form is ahead once there are many rounds of
+// tiles; in one well-filled round (196 tiles: 12544 x 512 -> 512 14.1 against 11.9 us), or two for bytes, this one is.
+// The 512-wide tile costs about 1.35 times the 256-wide one's round and does twice the work.
+const WideVariant* pick_wide(const ConvGeom& g, bool bytes) {
+    if (g.KH != 1 || g.KW != 1 || g.ph || g.pw || g.Cq % kStepK || g.Cq < 512 || g.M >= kPatchMaxDividend ||
+        (size_t)g.Kp * g.Np >= kPatchInvalidOffset || (int64_t)g.B * g.H * g.W >= kPatchMaxDividend || (bytes && g.N % 16))
+        return nullptr;
+    if (g.N <= 128 && g.M >= 32 * 1024) return nullptr;
+    const int64_t cus = device_cu_count(), tiles_m = (g.M + 127) / 128;
+    const int64_t t512 = tiles_m * ((g.N + 511) / 512), t256 = tiles_m * ((g.N + 255) / 256);
+    const int64_t r512 = (t512 + cus - 1) / cus, r256 = (t256 + cus - 1) / cus;
+    const bool wider = g.N > 256 && r512 * 27 <= r256 * 20 && round_up(g.N, 512) <= g.Np;
+    if (g.Cq == 512) {
+        const bool fills = wider ? bytes && r512 <= 2 && t512 * 10 >= r512 * cus * 7 : r256 == 1 && t256 * 8 >= cus * 3;
+        if (!fills || round_up(g.N, wider ? 512 : 256) * 4 > (int64_t)g.N * 5) return nullptr;     // (or pads N by over a quarter)
+    }
+    return &kWideVariants[wider ? 0 : 1];
 }
 
 // Everything the entry points decide before launching.
 struct ConvPlan {
     const SplitVariant* split = nullptr;   // split-reduction form (then pg and npix are its own)
     const RowsVariant* rows = nullptr;     // activations in registers; what follows is for calls it does not take
+    const WideVariant* wide = nullptr;     // eight wavefronts per tile; what follows is for calls it does not take
     bool patch = false;
     const PatchVariant* variant = nullptr;
     PatchGeom pg{};
@@ -274,6 +298,7 @@ ConvPlan make_plan(const ConvGeom& g, const Tuning& tune, bool split = true, boo
         // 256 -> 256, 784 pixels 5.3 against 5.7 us; 512 -> 256 7.9 against 6.0)
         pl.rows = pick_rows(gk, bytes);
         if ((!pl.rows || g.K > 256) && (pl.split = pick_split(gk, &pl.pg, &pl.npix)) != nullptr) return pl;
+        pl.wide = pick_wide(gk, bytes);
     }
     if (!force_gather && (force_patch || !prefer_gather(g)) && plan_patch(gk, &pl.pg, &pl.npix, &pl.ac, &pl.cbs)) {
         pl.variant = pick_patch(g, tune, pl.ac, pl.cbs, pl.npix, force_patch, &pl.ws);
@@ -345,6 +370,8 @@ sparq_status plan_text(const sparq_conv_desc* desc, const sparq_mode* mode, char
     if (pl.split) {
         snprintf(text, text_bytes, "conv_patch_kernel split_reduction tile=%s patch_pixels=%d%s", pl.split->name, pl.npix,
                  pl.pad_bytes ? " padded_copy" : "");
+    } else if (pl.wide) {
+        snprintf(text, text_bytes, "conv_gemm_kernel tile=%s eight_wavefronts%s", pl.wide->name, pl.pad_bytes ? " padded_copy" : "");
     } else if (pl.rows) {
         snprintf(text, text_bytes, "conv_patch_kernel in_registers channels=%s%s", pl.rows->name, pl.pad_bytes ? " padded_copy" : "");
     } else if (pl.patch) {
@@ -479,6 +506,18 @@ sparq_status conv_launch(const uint8_t* x, const void* packed_w, const sparq_con
         q.trim_out = fused_trim || out_only ? 1 : 0;
     };
     const TrimKind okind = out_only ? trim_kind(out_mode) : kind;
+
+    // 1x1 layers with a long reduction: eight wavefronts per tile.  (They always trim their input: a call
+    // with only its output to be trimmed goes to the forms below.)
+    if (pl.wide && !out_only) {
+        WideParams q{};
+        fill(q);
+        q.M = (int)g.M;
+        q.steps = g.Cq / kStepK;
+        q.g = make_patch_geom(g.B, g.H, g.W, 1, 1, g.sh, g.sw, 0, 0);
+        const sparq_status st = pl.wide->fn(okind, q, s);
+        if (st != SPARQ_EUNSUPPORTED) return finish(st, q.trim_out != 0);
+    }
 
     // Small layers: the reduction split over a workgroup's wavefronts.
     if (pl.split) {

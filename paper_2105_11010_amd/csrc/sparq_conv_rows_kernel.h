@@ -310,7 +310,5 @@ SPARQ_DECLARE_ROWS(launch_rows_k256);
 SPARQ_DECLARE_ROWS(launch_rows_k320);
 SPARQ_DECLARE_ROWS(launch_rows_k384);
 SPARQ_DECLARE_ROWS(launch_rows_k512);
-SPARQ_DECLARE_ROWS(launch_rows_k768);
-SPARQ_DECLARE_ROWS(launch_rows_k1024);
 
 }  // namespace sparq

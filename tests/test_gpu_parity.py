@@ -307,7 +307,6 @@ ROWS_SHAPES = [
     S.ConvLayer("r_c256_n1024_s3x2", 4, 17, 19, 256, 1024, 1, 1, (3, 2), (0, 0)), S.ConvLayer("r_c288_n96", 20, 35, 35, 288, 96),
     S.ConvLayer("r_c384_n160", 1, 9001, 1, 384, 160), S.ConvLayer("r_c512_n144", 1, 12555, 1, 512, 144),
     S.ConvLayer("r_c192_n512_wide", 1, 49169, 1, 192, 512), S.ConvLayer("r_c448_n528_wide", 1, 49169, 1, 448, 528),
-    S.ConvLayer("r_c768_n48", 1, 32799, 1, 768, 48),
 ]
 
 
@@ -320,9 +319,22 @@ def test_conv_activations_in_registers(sq, oracle, layer, mode):
     check_layer_u8(sq, oracle, layer, mode, seed_cfg=8, out_mode=S.Mode(4, S.OPT5, 1, 1))
 
 
-def test_conv_activations_in_registers_1024_channels(sq, oracle):
-    """More than 768 channels: requantised results of layers that fill the chip only."""
-    check_layer_u8(sq, oracle, S.ConvLayer("r_c1024_n128", 1, 32799, 1, 1024, 128), S.Mode(4, S.OPT5, 1, 1), seed_cfg=8)
+# Eight wavefronts per tile (1x1 layers with long reductions): steps that are padded to a multiple of four, an odd channel
+# count, strides, ragged pixels and channels, one tile, more tiles than CUs with two tiles of channels each.
+WIDE_SHAPES = [
+    ("128x256", S.ConvLayer("w_c520_n48", 1, 19999, 1, 520, 48)), ("128x256", S.ConvLayer("w_c575_n272_s2", 3, 99, 101, 575, 272, 1, 1, (2, 2), (0, 0))),
+    ("128x256", S.ConvLayer("w_c512_n512", 1, 12544, 1, 512, 512)), ("128x256", S.ConvLayer("w_c528_n528", 1, 33001, 1, 528, 528)),
+    ("128x512", S.ConvLayer("w_c1024_n320", 1, 32769, 1, 1024, 320)), ("128x256", S.ConvLayer("w_c4608_n130", 1, 9000, 1, 4608, 130)),
+]
+
+
+@pytest.mark.parametrize("tile,layer", WIDE_SHAPES, ids=lambda v: v if isinstance(v, str) else v.name)
+@pytest.mark.parametrize("mode", [S.Mode(4, S.OPT5, 1, 1), S.Mode(3, S.OPT6_3B, 0, 1), S.PLAIN8], ids=lambda m: m.label)
+def test_conv_eight_wavefronts(sq, oracle, tile, layer, mode):
+    d = sq.conv_desc(layer.B, layer.H, layer.W, layer.C, layer.N, layer.KH, layer.KW, layer.stride, layer.pad)
+    assert f"tile={tile} eight_wavefronts" in sq.sparq_conv_plan(d, sq.mode(*mode.astuple()))
+    check_layer(sq, oracle, layer, mode, seed_cfg=8)
+    check_layer_u8(sq, oracle, layer, mode, seed_cfg=8, out_mode=S.Mode(4, S.OPT5, 1, 1))
 
 
 # Shapes chosen for the input-patch kernel: tiles that span several image rows and several images,
