@@ -1,6 +1,7 @@
 // Host entry point of the fused SPARQ convolution: validation, the channel-padding
 // pre-pass for channel counts that are not a multiple of 16, and the choice of tile shape.
 #include "sparq_conv_gemm_kernel.h"
+#include "sparq_conv_block_kernel.h"
 #include "sparq_conv_patch_kernel.h"
 #include "sparq_conv_rows_kernel.h"
 #include "sparq_conv_split_kernel.h"
@@ -82,13 +83,16 @@ const PatchVariant kPatchVariants[] = {
 // are cached because the same layers are launched over and over.
 int patch_npix_max(const PatchGeom& g) {
     struct Key { int v[13]; int npix; };
-    static Key cache[64];
-    static int used = 0, next = 0;
+    static Key cache[512];                        // direct-mapped (a layer table asks for up to two tile heights per layer)
     static std::mutex mu;
     const int key[13] = {g.tm, g.M, g.B, g.H, g.W, g.KH, g.KW, g.sh, g.sw, g.ph, g.pw, g.Ho, g.Wo};
-    std::lock_guard<std::mutex> lock(mu);
-    for (int i = 0; i < used; ++i)
-        if (!memcmp(cache[i].v, key, sizeof(key))) return cache[i].npix;
+    uint32_t hash = 0;
+    for (int v : key) hash = (hash ^ (uint32_t)v) * 0x9E3779B1u, hash ^= hash >> 15;
+    Key& slot = cache[hash & 511];
+    {
+        std::lock_guard<std::mutex> lock(mu);
+        if (!memcmp(slot.v, key, sizeof(key))) return slot.npix;      // (an empty slot's tile height is 0)
+    }
     const int64_t img = (int64_t)g.Ho * g.Wo;
     int64_t a = g.tm, b = img;
     while (b) { const int64_t t = a % b; a = b; b = t; }
@@ -101,7 +105,7 @@ int patch_npix_max(const PatchGeom& g) {
     }
     const int n_last = tile_patch(g, (int)((tiles - 1) * g.tm)).npix;
     npix = n_last > npix ? n_last : npix;
-    Key& slot = cache[used < 64 ? used++ : (next++ & 63)];
+    std::lock_guard<std::mutex> lock(mu);
     memcpy(slot.v, key, sizeof(key));
     slot.npix = npix;
     return npix;
@@ -268,11 +272,35 @@ const WideVariant* pick_wide(const ConvGeom& g, bool bytes) {
     return &kWideVariants[wider ? 0 : 1];
 }
 
+// ---- multi-tap layers as many small workgroups -----------------------------------------------
+// Small workgroups: multi-tap layers with tiles for every slot of the chip (300 and more) and
+//   up to 64 channels, if they have at most 64 outputs or a patch of less than 450 pixels per tile (1.0-1.5 x faster there:
+//   56 x 56 x 64 -> 64 3x3, batch 32 16.5 -> 13.1 us, batch 256 78 -> 58; wider rows trim too much per 64 outputs),
+//   or 113 to 128 with such a patch, for bytes (28 x 28 x 128 -> 128, batch 256 47 -> 42; 35 x 35 x 96 -> 96 fp32 35 against 37),
+//   or a patch too large for the tile kernel's staging, which the gather kernel would trim once per tap (1.5-3 x:
+//   56 x 56 x 64 -> 64 5x5, batch 32).
+// With fewer tiles, or more channels, the tile kernel's pipelining is ahead (14 x 14 x 256, batch 256: 35 against 44 us).
+bool pick_block(const ConvGeom& g, bool bytes, bool gather, PatchGeom* pg, int* npix) {
+    const int taps = g.KH * g.KW;
+    if (taps == 1 || (bytes && g.N % 16) || (g.M + BlockCfg::kTM - 1) / BlockCfg::kTM * ((g.N + 63) / 64) < 300) return false;
+    if (g.Cq > 128 && !gather) return false;
+    PatchGeom q;
+    int n;
+    if (!patch_geom_for(g, BlockCfg::kTM, &q, &n) || block_lds_bytes(n) < 0 || block_lds_bytes(n) > 64 * 1024) return false;
+    // patch pixels of a tile that starts and ends anywhere in its rows (the largest one may cross two images)
+    const bool small = ((int64_t)BlockCfg::kTM + (int64_t)g.KH * g.Wo) * ((int64_t)(g.Wo - 1) * g.sw + g.KW) < 450ll * g.Wo;
+    if (!gather && !(g.Cq == 64 ? g.N <= 64 || small : small && bytes && g.C > 112)) return false;
+    *pg = q;
+    *npix = n;
+    return true;
+}
+
 // Everything the entry points decide before launching.
 struct ConvPlan {
     const SplitVariant* split = nullptr;   // split-reduction form (then pg and npix are its own)
     const RowsVariant* rows = nullptr;     // activations in registers; what follows is for calls it does not take
     const WideVariant* wide = nullptr;     // eight wavefronts per tile; what follows is for calls it does not take
+    bool block = false;                    // small workgroups (then pg and npix are its own)
     bool patch = false;
     const PatchVariant* variant = nullptr;
     PatchGeom pg{};
@@ -304,6 +332,7 @@ ConvPlan make_plan(const ConvGeom& g, const Tuning& tune, bool split = true, boo
         pl.variant = pick_patch(g, tune, pl.ac, pl.cbs, pl.npix, force_patch, &pl.ws);
         pl.patch = pl.variant != nullptr;
     }
+    if (split && !tune.set()) pl.block = pick_block(gk, bytes, !pl.patch, &pl.pg, &pl.npix);
     return pl;
 }
 
@@ -370,6 +399,8 @@ sparq_status plan_text(const sparq_conv_desc* desc, const sparq_mode* mode, char
     if (pl.split) {
         snprintf(text, text_bytes, "conv_patch_kernel split_reduction tile=%s patch_pixels=%d%s", pl.split->name, pl.npix,
                  pl.pad_bytes ? " padded_copy" : "");
+    } else if (pl.block) {
+        snprintf(text, text_bytes, "conv_patch_kernel small_workgroups tile=256x64 patch_pixels=%d%s", pl.npix, pl.pad_bytes ? " padded_copy" : "");
     } else if (pl.wide) {
         snprintf(text, text_bytes, "conv_gemm_kernel tile=%s eight_wavefronts%s", pl.wide->name, pl.pad_bytes ? " padded_copy" : "");
     } else if (pl.rows) {
@@ -531,6 +562,15 @@ sparq_status conv_launch(const uint8_t* x, const void* packed_w, const sparq_con
         q.div_kw = make_fastdiv((uint32_t)g.KW);
         q.g = pl.pg;
         return finish(pl.split->fn(okind, q, pl.npix, s), q.trim_out != 0);
+    }
+
+    // Multi-tap layers as many small workgroups.
+    if (pl.block) {
+        BlockParams q{};
+        fill(q);
+        q.ncb = g.Cq / kStepK;
+        q.g = pl.pg;
+        return finish(launch_block(okind, q, pl.npix, s), q.trim_out != 0);
     }
 
     // 1x1 layers with a short reduction: activations in registers.

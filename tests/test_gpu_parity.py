@@ -337,6 +337,26 @@ def test_conv_eight_wavefronts(sq, oracle, tile, layer, mode):
     check_layer_u8(sq, oracle, layer, mode, seed_cfg=8, out_mode=S.Mode(4, S.OPT5, 1, 1))
 
 
+# Small workgroups (multi-tap layers with many tiles): several 64-channel blocks, padded channels, an odd channel count, ragged
+# pixels and outputs, images that share a tile, wide rows, patches the tile kernel cannot stage.
+BLOCK_SHAPES = [
+    S.ConvLayer("b_3x3_56_c64", 25, 56, 56, 64, 64, 3, 3, (1, 1), (1, 1)), S.ConvLayer("b_3x3_p0_c48_n32", 105, 30, 29, 48, 32, 3, 3),
+    S.ConvLayer("b_3x3_17_c128_n272", 61, 17, 17, 128, 272, 3, 3, (1, 1), (1, 1)), S.ConvLayer("b_3x3_28_c120_n80", 53, 28, 28, 120, 80, 3, 3, (1, 1), (1, 1)),
+    S.ConvLayer("b_5x5_57_c130_n33", 25, 57, 55, 130, 33, 5, 5, (1, 1), (2, 2)), S.ConvLayer("b_2x2_c40_n96", 33, 36, 36, 40, 96, 2, 2, (1, 1), (0, 0)),
+    S.ConvLayer("b_3x3_wide_rows_c60_n33", 7, 112, 111, 60, 33, 3, 3, (1, 1), (1, 1)),
+]
+
+
+@pytest.mark.parametrize("layer", BLOCK_SHAPES, ids=lambda l: l.name)
+@pytest.mark.parametrize("mode", [S.Mode(4, S.OPT5, 1, 1), S.Mode(3, S.OPT6_3B, 0, 1), S.PLAIN8], ids=lambda m: m.label)
+def test_conv_small_workgroups(sq, oracle, layer, mode):
+    d = sq.conv_desc(layer.B, layer.H, layer.W, layer.C, layer.N, layer.KH, layer.KW, layer.stride, layer.pad)
+    # (113 to 128 channels: requantised results only, which the plan line does not speak of)
+    assert ("small_workgroups" in sq.sparq_conv_plan(d, sq.mode(*mode.astuple()))) == (layer.C <= 64 or layer.KH == 5)
+    check_layer(sq, oracle, layer, mode, seed_cfg=8)
+    check_layer_u8(sq, oracle, layer, mode, seed_cfg=8, out_mode=S.Mode(4, S.OPT5, 1, 1))
+
+
 # Shapes chosen for the input-patch kernel: tiles that span several image rows and several images,
 # one-row tiles, every staging variant (64/128/256-channel units), several output-channel tiles.
 PATCH_SHAPES = [
