@@ -240,6 +240,9 @@ const RowsVariant* pick_rows(const ConvGeom& g, bool bytes) {
         (size_t)g.Kp * g.Np >= kPatchInvalidOffset || (int64_t)g.B * g.H * g.W >= kPatchMaxDividend)
         return nullptr;
     if (bytes ? g.N % 16 != 0 : (g.N >= 256 && g.M * g.N * 4 >= kStreamedBytes)) return nullptr;
+    // (four-byte rows that start off a 64-byte border: its 128-byte runs are two partial lines each, the tile kernels' rows are
+    // not; 196 -> 948, 28187 pixels 57 against 85 us.  Up to 8 MiB the shorter chain is worth more.)
+    if (!bytes && g.N % 16 != 0 && g.M * g.N * 4 > (8 << 20)) return nullptr;
     for (const RowsVariant& v : kRowsVariants)
         if (g.Cq / 32 <= v.steps) return &v;
     return nullptr;
@@ -250,7 +253,7 @@ struct WideVariant { const char* name; int tn; WideLauncher fn; };
 const WideVariant kWideVariants[] = {{"128x512", 512, launch_wide_512}, {"128x256", 256, launch_wide_256}};
 
 // Eight wavefronts per tile: 1x1 layers without padding and with more than 512 channels, whatever their size (what the split
-// form does not take), except many pixels with few output channels, where the 256-wide tile multiplies mostly padding.  Over
+// form does not take), except few output channels, where the 256-wide tile multiplies mostly padding (784 -> 48: 12 against 15 us).  Over
 // 220 shapes of 768 to 4608 channels (128..2048 outputs, 784..50176 pixels) 1.02 to 2 x faster than the kernels it replaced:
 // 65536 x 4608 x 512 int32 197 -> 172 us, bytes 233 -> 154; 50176 x 4608 x 320 207 -> 118; 50176 x 1024 -> 256 bytes 34 -> 28.
 // With 449 to 512 channels the activations fit in registers, and that form is ahead once there are many rounds of
@@ -260,7 +263,7 @@ const WideVariant* pick_wide(const ConvGeom& g, bool bytes) {
     if (g.KH != 1 || g.KW != 1 || g.ph || g.pw || g.Cq % kStepK || g.Cq < 512 || g.M >= kPatchMaxDividend ||
         (size_t)g.Kp * g.Np >= kPatchInvalidOffset || (int64_t)g.B * g.H * g.W >= kPatchMaxDividend || (bytes && g.N % 16))
         return nullptr;
-    if (g.N <= 128 && g.M >= 32 * 1024) return nullptr;
+    if (g.N <= 96 || (g.N <= 128 && g.M >= 32 * 1024)) return nullptr;
     const int64_t cus = device_cu_count(), tiles_m = (g.M + 127) / 128;
     const int64_t t512 = tiles_m * ((g.N + 511) / 512), t256 = tiles_m * ((g.N + 255) / 256);
     const int64_t r512 = (t512 + cus - 1) / cus, r256 = (t256 + cus - 1) / cus;
@@ -277,12 +280,13 @@ const WideVariant* pick_wide(const ConvGeom& g, bool bytes) {
 //   up to 64 channels, if they have at most 64 outputs or a patch of less than 450 pixels per tile (1.0-1.5 x faster there:
 //   56 x 56 x 64 -> 64 3x3, batch 32 16.5 -> 13.1 us, batch 256 78 -> 58; wider rows trim too much per 64 outputs),
 //   or 113 to 128 with such a patch, for bytes (28 x 28 x 128 -> 128, batch 256 47 -> 42; 35 x 35 x 96 -> 96 fp32 35 against 37),
-//   or a patch too large for the tile kernel's staging, which the gather kernel would trim once per tap (1.5-3 x:
-//   56 x 56 x 64 -> 64 5x5, batch 32).
+//   or a patch too large for the tile kernel's staging, which the gather kernel would trim once per tap, if they have 15 taps
+//   and more or few channels on either side (1.5-3 x: 56 x 56 x 64 -> 64 5x5, batch 32; 98 x 98 x 539 -> 128 3x3 67 against 78).
 // With fewer tiles, or more channels, the tile kernel's pipelining is ahead (14 x 14 x 256, batch 256: 35 against 44 us).
 bool pick_block(const ConvGeom& g, bool bytes, bool gather, PatchGeom* pg, int* npix) {
     const int taps = g.KH * g.KW;
     if (taps == 1 || (bytes && g.N % 16) || (g.M + BlockCfg::kTM - 1) / BlockCfg::kTM * ((g.N + 63) / 64) < 300) return false;
+    gather = gather && (g.Cq == 64 || g.N <= 64 || taps >= 15) && g.Cq <= 256;
     if (g.Cq > 128 && !gather) return false;
     PatchGeom q;
     int n;
@@ -842,7 +846,13 @@ extern "C" sparq_status sparq_conv_gemm_sparse24(const uint8_t* x, const void* p
     if (workspace_bytes < sparq_sparse24_workspace_bytes(desc, mode)) return SPARQ_EWORKSPACE;
     const int64_t pixels = (int64_t)desc->B * desc->H * desc->W;
     if (pixels * desc->C * 4 >= (int64_t)kInvalidOffset) return SPARQ_EUNSUPPORTED;
-    if (sp && sparse24_blocked(desc->C) && aligned(x, 16)) {      // the staging wavefronts expand what they load
+    // The staging wavefronts expand what they load where a tile's patch is small beside its taps: each patch pixel is then
+    // trimmed three times per 64 channels and channel tile, which the matrix instructions of its taps have to cover (3x3 on 32 x
+    // 32 pixels, 204 patch pixels: 357 -> 241 us; strided 1x7 on 12 x 12 54 -> 108).  Elsewhere the expanded tensor is written first.
+    ConvGeom ge;
+    conv_geom(&eff, &ge);
+    const ConvPlan pe = make_plan(ge, current_tuning(), false);
+    if (sp && sparse24_blocked(desc->C) && aligned(x, 16) && pe.patch && pe.npix <= 32 * desc->KH * desc->KW) {
         SparseOperand fused = sp_op;
         fused.expand_mode = mode;
         fused.x_channels = desc->C;

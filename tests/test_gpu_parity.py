@@ -322,7 +322,7 @@ def test_conv_activations_in_registers(sq, oracle, layer, mode):
 # Eight wavefronts per tile (1x1 layers with long reductions): steps that are padded to a multiple of four, an odd channel
 # count, strides, ragged pixels and channels, one tile, more tiles than CUs with two tiles of channels each.
 WIDE_SHAPES = [
-    ("128x256", S.ConvLayer("w_c520_n48", 1, 19999, 1, 520, 48)), ("128x256", S.ConvLayer("w_c575_n272_s2", 3, 99, 101, 575, 272, 1, 1, (2, 2), (0, 0))),
+    ("128x256", S.ConvLayer("w_c520_n112", 1, 19999, 1, 520, 112)), ("128x256", S.ConvLayer("w_c575_n272_s2", 3, 99, 101, 575, 272, 1, 1, (2, 2), (0, 0))),
     ("128x256", S.ConvLayer("w_c512_n512", 1, 12544, 1, 512, 512)), ("128x256", S.ConvLayer("w_c528_n528", 1, 33001, 1, 528, 528)),
     ("128x512", S.ConvLayer("w_c1024_n320", 1, 32769, 1, 1024, 320)), ("128x256", S.ConvLayer("w_c4608_n130", 1, 9000, 1, 4608, 130)),
 ]
