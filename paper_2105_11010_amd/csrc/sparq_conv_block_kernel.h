@@ -257,6 +257,16 @@ inline int block_lds_bytes(int npix_max) {
     return need > kLdsPerCu ? -1 : (int)need;
 }
 
+inline int64_t block_tiles(int64_t M, int64_t N) {
+    return (M + BlockCfg::kTM - 1) / BlockCfg::kTM * ((N + BlockCfg::kTN - 1) / BlockCfg::kTN);
+}
+// What the kernel can be launched for: LDS (64 KB: what a launch may use without asking), 32-bit offsets inside a tile of
+// results, tile numbers.  The rule that picks this form asks the same, so that other layers go on to the other kernels.
+inline bool block_launchable(int64_t M, int64_t N, int npix_max) {
+    const int lds_bytes = block_lds_bytes(npix_max);
+    return lds_bytes >= 0 && lds_bytes <= 64 * 1024 && N * 4 * BlockCfg::kTM < 0x7FFFFFFF && block_tiles(M, N) <= 0x0FFFFFFF;
+}
+
 // `p` carries everything except plane_stride and the tile counts; npix_max bounds TilePatch::npix.
 template <int KIND, bool U8>
 sparq_status launch_block_cfg(const BlockParams& p, int npix_max, hipStream_t s) {
@@ -264,13 +274,9 @@ sparq_status launch_block_cfg(const BlockParams& p, int npix_max, hipStream_t s)
     BlockParams q = p;
     q.plane_stride = patch_plane_stride(npix_max, 4);
     const int lds_bytes = block_lds_bytes(npix_max);
-    // (64 KB: what a launch may use without asking)
-    if (lds_bytes < 0 || lds_bytes > 64 * 1024 || p.g.tm != Cfg::kTM || p.g.rm_wo || (int64_t)p.N * 4 * Cfg::kTM >= 0x7FFFFFFF)
-        return SPARQ_EUNSUPPORTED;
+    if (p.g.tm != Cfg::kTM || p.g.rm_wo || !block_launchable(p.g.M, p.N, npix_max)) return SPARQ_EUNSUPPORTED;
     q.tiles_n = (p.N + Cfg::kTN - 1) / Cfg::kTN;
-    const int64_t tiles = (int64_t)((p.g.M + Cfg::kTM - 1) / Cfg::kTM) * q.tiles_n;
-    if (tiles > 0x0FFFFFFF) return SPARQ_EUNSUPPORTED;
-    q.tiles = (int)tiles;
+    q.tiles = (int)block_tiles(p.g.M, p.N);
     q.tiles_xcd = (q.tiles + 7) / 8;
     conv_block_kernel<KIND, U8><<<(unsigned)(8 * q.tiles_xcd), Cfg::kThreads, lds_bytes, s>>>(q);
     return launch_status();

@@ -285,12 +285,12 @@ const WideVariant* pick_wide(const ConvGeom& g, bool bytes) {
 // With fewer tiles, or more channels, the tile kernel's pipelining is ahead (14 x 14 x 256, batch 256: 35 against 44 us).
 bool pick_block(const ConvGeom& g, bool bytes, bool gather, PatchGeom* pg, int* npix) {
     const int taps = g.KH * g.KW;
-    if (taps == 1 || (bytes && g.N % 16) || (g.M + BlockCfg::kTM - 1) / BlockCfg::kTM * ((g.N + 63) / 64) < 300) return false;
+    if (taps == 1 || (bytes && g.N % 16) || block_tiles(g.M, g.N) < 300) return false;
     gather = gather && (g.Cq == 64 || g.N <= 64 || taps >= 15) && g.Cq <= 256;
     if (g.Cq > 128 && !gather) return false;
     PatchGeom q;
     int n;
-    if (!patch_geom_for(g, BlockCfg::kTM, &q, &n) || block_lds_bytes(n) < 0 || block_lds_bytes(n) > 64 * 1024) return false;
+    if (!patch_geom_for(g, BlockCfg::kTM, &q, &n) || !block_launchable(g.M, g.N, n)) return false;
     // patch pixels of a tile that starts and ends anywhere in its rows (the largest one may cross two images)
     const bool small = ((int64_t)BlockCfg::kTM + (int64_t)g.KH * g.Wo) * ((int64_t)(g.Wo - 1) * g.sw + g.KW) < 450ll * g.Wo;
     if (!gather && !(g.Cq == 64 ? g.N <= 64 || small : small && bytes && g.C > 112)) return false;

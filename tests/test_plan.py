@@ -100,6 +100,16 @@ def test_widest_gather_tile_only_with_step_aligned_taps(lib):
         assert lib.sparq_set_tuning(None) == 0
 
 
+def test_small_workgroups_only_where_they_can_be_launched(lib):
+    """A tile of 256 rows of results is addressed in 32 bits: from 2^21 output channels on a few-channel layer is planned
+    for the kernels that still take it (the call would otherwise return "unsupported")."""
+    mode = S.Mode(4, S.OPT5, 1, 1)
+    for n, small in (((1 << 21) - 64, True), (1 << 21, False)):
+        for layer in (S.ConvLayer("n_3x3", 1, 8, 8, 64, n, 3, 3, (1, 1), (1, 1)), S.ConvLayer("n_1x3", 1, 1, 16, 64, n, 1, 3, (1, 1), (0, 1))):
+            text = plan(lib, layer, mode)[0]
+            assert ("small_workgroups" in text) == small, text
+
+
 def test_plan_rejects_bad_arguments(lib):
     buf = ctypes.create_string_buffer(64)
     m = Mode(4, 0x1F, 1, 1)
