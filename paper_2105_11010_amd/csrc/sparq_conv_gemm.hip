@@ -83,15 +83,19 @@ const PatchVariant kPatchVariants[] = {
 // are cached because the same layers are launched over and over.
 int patch_npix_max(const PatchGeom& g) {
     struct Key { int v[13]; int npix; };
-    static Key cache[512];                        // direct-mapped (a layer table asks for up to two tile heights per layer)
+    // 128 sets of four geometries (a layer table asks for up to two tile heights per layer).  Four ways, because two layers that
+    // push each other out pay the walk on every call: 12 us at 35 x 35 pixels, 193 at 147 x 147, against 0.1 for a look-up.
+    struct Set { Key way[4]; unsigned next; };
+    static Set cache[128];
     static std::mutex mu;
     const int key[13] = {g.tm, g.M, g.B, g.H, g.W, g.KH, g.KW, g.sh, g.sw, g.ph, g.pw, g.Ho, g.Wo};
     uint32_t hash = 0;
     for (int v : key) hash = (hash ^ (uint32_t)v) * 0x9E3779B1u, hash ^= hash >> 15;
-    Key& slot = cache[hash & 511];
+    Set& set = cache[hash & 127];
     {
         std::lock_guard<std::mutex> lock(mu);
-        if (!memcmp(slot.v, key, sizeof(key))) return slot.npix;      // (an empty slot's tile height is 0)
+        for (const Key& k : set.way)
+            if (!memcmp(k.v, key, sizeof(key))) return k.npix;       // (an empty way's tile height is 0)
     }
     const int64_t img = (int64_t)g.Ho * g.Wo;
     int64_t a = g.tm, b = img;
@@ -106,6 +110,7 @@ int patch_npix_max(const PatchGeom& g) {
     const int n_last = tile_patch(g, (int)((tiles - 1) * g.tm)).npix;
     npix = n_last > npix ? n_last : npix;
     std::lock_guard<std::mutex> lock(mu);
+    Key& slot = set.way[set.next++ & 3];
     memcpy(slot.v, key, sizeof(key));
     slot.npix = npix;
     return npix;

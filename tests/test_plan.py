@@ -110,6 +110,23 @@ def test_small_workgroups_only_where_they_can_be_launched(lib):
             assert ("small_workgroups" in text) == small, text
 
 
+def test_layers_in_turn_do_not_walk_their_tiles_again(lib):
+    """The largest patch of a layer comes from a walk over its tile positions (193 us for 147 x 147 pixels) and is kept per
+    geometry.  These two geometries share the low nine bits of the cache's hash: called in turn, neither pushes the other out."""
+    import time
+    mode = S.Mode(4, S.OPT5, 1, 1)
+    layers = [S.ConvLayer(f"b{b}", b, 147, 147, 256, 256, 3, 3, (1, 1), (1, 1)) for b in (136, 140)]
+
+    def us(l):
+        t = time.perf_counter()
+        plan(lib, l, mode)
+        return (time.perf_counter() - t) * 1e6
+
+    first = min(us(l) for l in layers)
+    again = sorted(us(l) for _ in range(50) for l in layers)[50]
+    assert again < first / 3, (first, again)
+
+
 def test_plan_rejects_bad_arguments(lib):
     buf = ctypes.create_string_buffer(64)
     m = Mode(4, 0x1F, 1, 1)
