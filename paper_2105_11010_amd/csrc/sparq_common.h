@@ -193,6 +193,11 @@ __device__ __forceinline__ uint32_t requant_u8x4(int32_t r0, int32_t r1, int32_t
     return __builtin_amdgcn_cvt_pk_u8_f32(__fmul_rn((float)r3, factor), 3, w);
 }
 
+// Stands between a wavefront's LDS writes and its lanes' reads of what OTHER lanes wrote, and between those reads and the next
+// writes.  A wavefront's LDS queue is in order, so the hardware needs nothing and no instruction is emitted; the fence keeps
+// the compiler, which sees one lane's addresses only, from reordering the two sides.
+__device__ __forceinline__ void wavefront_lds_fence() { __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront"); }
+
 // Cache policy of the int32 / fp32 result stores of the convolution kernels: non-temporal.  These results are four
 // bytes per output, written once and not read again by the int8 path (the next layer reads the requantised bytes,
 // which keep the ordinary policy); layers bound by this stream run 6-15 % faster, the others do not change.

@@ -623,6 +623,7 @@ __global__ __launch_bounds__(Cfg::kThreads, Cfg::kWgPerCu * Cfg::kThreads / 256)
                                 const v4i r = {c[i][j][4 * q], c[i][j][4 * q + 1], c[i][j][4 * q + 2], c[i][j][4 * q + 3]};
                                 *reinterpret_cast<v4i*>(xw + (j * 32 + 8 * q) * 4) = r;
                             }
+                        wavefront_lds_fence();
 #pragma unroll
                         for (int k = 0; k < 8; ++k) {
                             v4i r = *reinterpret_cast<const v4i*>(xrd + 4 * k * kSparseRowPitch);
@@ -646,6 +647,7 @@ __global__ __launch_bounds__(Cfg::kThreads, Cfg::kWgPerCu * Cfg::kThreads / 256)
                                 }
                             }
                         }
+                        wavefront_lds_fence();
                     }
                 };
                 if constexpr (SP) {

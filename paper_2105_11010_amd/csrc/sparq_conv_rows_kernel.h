@@ -199,6 +199,7 @@ __global__ __launch_bounds__(kRowsThreads, Cfg::kOcc) void conv_rows_kernel(cons
                     *reinterpret_cast<v4u*>(turn_w + i * 32 * kRowsPitch + 32 * part) = v4u{s02[0], s02[1], s13[0], s13[1]};
                 }
                 if (part == 3 || n0 + 32 >= n_end) {                 // uniform: 128 channels gathered, or the last ones
+                    wavefront_lds_fence();
                     const __amdgpu_buffer_rsrc_t orsrc =
                         __builtin_amdgcn_make_buffer_rsrc((void*)(p.out_u8 + base), 0, rows * p.N, 0x00020000);
                     const int no = n0 - 32 * part + 16 * (lane & 7);
@@ -208,6 +209,7 @@ __global__ __launch_bounds__(kRowsThreads, Cfg::kOcc) void conv_rows_kernel(cons
                         const v4u o = *reinterpret_cast<const v4u*>(turn_r + 8 * r * kRowsPitch);
                         __builtin_amdgcn_raw_buffer_store_b128(o, orsrc, lane_off + 8 * r * p.N, 0, 0);
                     }
+                    wavefront_lds_fence();
                 }
             } else {
                 const int pitch = p.N * 4, bytes = rows * pitch;

@@ -226,6 +226,7 @@ __global__ __launch_bounds__(kWideThreads, 2) void conv_wide_kernel(const WidePa
                     const auto s13 = __builtin_amdgcn_permlane32_swap(w[1], w[3], false, false);
                     *reinterpret_cast<v4u*>(turn + l32 * kWidePitch + 32 * j + 16 * lhi) = v4u{s02[0], s02[1], s13[0], s13[1]};
                 }
+                wavefront_lds_fence();
 #pragma unroll
                 for (int r = 0; r < 2; ++r) {
                     const int row = 16 * r + (lane >> 2);
@@ -233,6 +234,7 @@ __global__ __launch_bounds__(kWideThreads, 2) void conv_wide_kernel(const WidePa
                     const int off = col < p.N ? ((wm * FM + i) * 32 + row) * p.N + col : (int)kPatchInvalidOffset;
                     __builtin_amdgcn_raw_buffer_store_b128(o, orsrc, off, 0, 0);
                 }
+                wavefront_lds_fence();
             }
         } else {
             const int pitch = p.N * 4, bytes = rows * pitch;

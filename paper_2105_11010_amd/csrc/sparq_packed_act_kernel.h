@@ -100,8 +100,7 @@ __device__ __forceinline__ void load_words(const uint32_t* src, uint32_t (&r)[WO
 // A wavefront's 64 records are WORDS * 256 contiguous bytes, and so are their 2 KB of channels when rows are whole
 // records, but a lane's own share is 16 to 36 bytes: read or written straight from the lanes, an instruction touches a
 // part of each line.  These two turn the shares through the wavefront's own piece of LDS, so that lane l moves 16-byte
-// chunks l, l + 64, ... with non-temporal accesses.  (The LDS queue of a wavefront is in order; the fences keep the
-// compiler from reordering the two sides.)
+// chunks l, l + 64, ... with non-temporal accesses.
 template <int WORDS>
 __device__ __forceinline__ void turn_load(const uint32_t* src, int nwords, uint32_t* area, int lane, uint32_t (&r)[WORDS]) {
 #pragma unroll
@@ -110,23 +109,23 @@ __device__ __forceinline__ void turn_load(const uint32_t* src, int nwords, uint3
         if (4 * c + 4 <= nwords) *reinterpret_cast<v4u*>(area + 4 * c) = __builtin_nontemporal_load(reinterpret_cast<const v4u_w*>(src + 4 * c));
         else for (int i = 4 * c; i < nwords; ++i) area[i] = src[i];
     }
-    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    wavefront_lds_fence();
 #pragma unroll
     for (int i = 0; i < WORDS; ++i) r[i] = area[lane * WORDS + i];
-    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    wavefront_lds_fence();
 }
 template <int WORDS>
 __device__ __forceinline__ void turn_store(uint32_t* dst, int nwords, uint32_t* area, int lane, const uint32_t (&r)[WORDS]) {
 #pragma unroll
     for (int i = 0; i < WORDS; ++i) area[lane * WORDS + i] = r[i];
-    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    wavefront_lds_fence();
 #pragma unroll
     for (int k = 0; k < (WORDS + 3) / 4; ++k) {
         const int c = lane + 64 * k;
         if (4 * c + 4 <= nwords) __builtin_nontemporal_store(*reinterpret_cast<const v4u*>(area + 4 * c), reinterpret_cast<v4u_w*>(dst + 4 * c));
         else for (int i = 4 * c; i < nwords; ++i) dst[i] = area[i];
     }
-    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    wavefront_lds_fence();
 }
 
 // N window bits, SB ShiftCtrl bits, G channels per ShiftCtrl field.
