@@ -106,8 +106,11 @@ size_t sparq_workspace_bytes(const sparq_conv_desc *desc, const sparq_mode *mode
 
 /* Which kernel and tiling sparq_conv_gemm would use for this descriptor and mode
  * on the current device, as a short human-readable line (for logs and profiles;
- * the wording is not an interface).  text receives at most text_bytes bytes
- * including the terminator. */
+ * the wording is not an interface): the kernel family with its form and tile,
+ * then kernel=<the kernel that is launched> and u8_kernel=<the one that
+ * sparq_conv_gemm_u8 launches for its byte results>.  (A call whose input arrives
+ * trimmed and whose output is to be trimmed leaves conv_wide_kernel to the
+ * others.)  text receives at most text_bytes bytes including the terminator. */
 sparq_status sparq_conv_plan(const sparq_conv_desc *desc, const sparq_mode *mode,
                              char *text, size_t text_bytes);
 
@@ -247,7 +250,7 @@ sparq_status sparq_conv_gemm_packed(const void *packed_x, size_t packed_x_bytes,
  * wave-specialised input-patch kernel the weights go to the sparse matrix
  * instruction as its sparse operand; otherwise the decompressed weights run
  * on the dense path.
- * sparq_sparse24_plan reports which (a text line as from sparq_conv_plan plus
+ * sparq_sparse24_plan reports which (a text line as from sparq_conv_plan, without u8_kernel, plus
  * "expanded_x4", the problem over expanded groups of four, and "sparse_mfma" /
  * "dense_mfma").
  * packed: 256-byte aligned, sparq_sparse24_packed_bytes() bytes, filled once

@@ -229,11 +229,17 @@ const SplitVariant* pick_split(const ConvGeom& g, PatchGeom* pg, int* npix) {
 }
 
 // ---- 1x1 layers with the activations in registers --------------------------------------------
-struct RowsVariant { int steps; const char* name; RowsLauncher fn; };       // 32-index reduction steps it holds
+struct RowsVariant { int steps; const char* name; RowsLauncher fn; int rm, rm_large; };   // 32-index reduction steps it holds, pixels per wavefront
 const RowsVariant kRowsVariants[] = {
-    {2, "64", launch_rows_k64}, {4, "128", launch_rows_k128}, {6, "192", launch_rows_k192}, {8, "256", launch_rows_k256},
-    {10, "320", launch_rows_k320}, {12, "384", launch_rows_k384}, {16, "512", launch_rows_k512},
+    {2, "64", launch_rows_k64, 32, 32}, {4, "128", launch_rows_k128, 32, 32}, {6, "192", launch_rows_k192, 32, 64},
+    {8, "256", launch_rows_k256, 32, 64}, {10, "320", launch_rows_k320, 32, 64}, {12, "384", launch_rows_k384, 32, 64},
+    {16, "512", launch_rows_k512, 32, 64},
 };
+// What its launcher takes beyond the rule below (else the call goes on to the tile kernels).
+bool rows_launchable(const RowsVariant& v, const ConvGeom& g, bool bytes) {
+    const int rm = rows_large(g.M, g.N) ? v.rm_large : v.rm;
+    return g.N * 4ll * rm < 0x7FFFFFFF && rows_lds_bytes(rm, g.N, bytes) <= 64 * 1024;
+}
 
 // Activations in registers: 1x1 layers without padding.  `bytes`: requantised results (16 of them leave together).
 // Up to 512 channels it beats the tile kernels nearly everywhere, by 1.1-1.6 x on small tensors and up to 2.2 x on large ones
@@ -400,40 +406,61 @@ extern "C" size_t sparq_workspace_bytes(const sparq_conv_desc* desc, const sparq
 }
 
 namespace {
-sparq_status plan_text(const sparq_conv_desc* desc, const sparq_mode* mode, char* text, size_t text_bytes, bool split) {
+// Which of the plan's forms is launched, in the order conv_launch tries them.
+enum PlanForm { kFormWide, kFormSplit, kFormBlock, kFormRows, kFormPatch, kFormGather };
+PlanForm plan_form(const ConvGeom& g, const ConvPlan& pl, bool bytes) {
+    if (pl.wide) return kFormWide;
+    if (pl.split) return kFormSplit;
+    if (pl.block) return kFormBlock;
+    if (pl.rows && rows_launchable(*pl.rows, g, bytes)) return kFormRows;
+    return pl.patch ? kFormPatch : kFormGather;
+}
+const char* const kFormKernels[] = {"conv_wide_kernel", "conv_split_kernel", "conv_block_kernel", "conv_rows_kernel", "conv_patch_kernel", "conv_gemm_kernel"};
+
+const char* gather_tile_name(const ConvGeom& g, const Tuning& tune, bool bytes) {
+    ConvGeom gt = g.fold ? folded_view(g) : g;
+    gt.Np = g.Np;
+    const TileLauncher fn = pick_tile(gt, tune, bytes);
+    for (const TileEntry& t : kTiles)
+        if (t.fn == fn) return t.name;
+    return "?";
+}
+
+// The line starts with the kernel family and the form, then names the kernel itself; `forms`: not the 2:4 layers, which keep to
+// the tile kernels and have no byte results.
+sparq_status plan_text(const sparq_conv_desc* desc, const sparq_mode* mode, char* text, size_t text_bytes, bool forms, bool u8_too) {
     ConvGeom g;
     if (!text || text_bytes == 0 || !conv_geom(desc, &g) || !mode_valid(mode)) return SPARQ_EINVAL;
     const Tuning tune = current_tuning();
-    const ConvPlan pl = make_plan(g, tune, split);
-    if (pl.split) {
-        snprintf(text, text_bytes, "conv_patch_kernel split_reduction tile=%s patch_pixels=%d%s", pl.split->name, pl.npix,
-                 pl.pad_bytes ? " padded_copy" : "");
-    } else if (pl.block) {
-        snprintf(text, text_bytes, "conv_patch_kernel small_workgroups tile=256x64 patch_pixels=%d%s", pl.npix, pl.pad_bytes ? " padded_copy" : "");
-    } else if (pl.wide) {
-        snprintf(text, text_bytes, "conv_gemm_kernel tile=%s eight_wavefronts%s", pl.wide->name, pl.pad_bytes ? " padded_copy" : "");
-    } else if (pl.rows) {
-        snprintf(text, text_bytes, "conv_patch_kernel in_registers channels=%s%s", pl.rows->name, pl.pad_bytes ? " padded_copy" : "");
-    } else if (pl.patch) {
-        snprintf(text, text_bytes, "conv_patch_kernel tile=128x%d chunks=%d unit_channels=%d patch_pixels=%d%s%s",
-                 pl.variant->tn, pl.ac, 64 * pl.cbs, pl.npix, pl.ws ? " wave_specialised" : "",
-                 pl.pad_bytes ? " padded_copy" : "");
-    } else {
-        const char* name = "?";
-        ConvGeom gt = g.fold ? folded_view(g) : g;
-        gt.Np = g.Np;
-        const TileLauncher fn = pick_tile(gt, tune);
-        for (const TileEntry& t : kTiles)
-            if (t.fn == fn) name = t.name;
-        snprintf(text, text_bytes, "conv_gemm_kernel tile=%s%s%s", name, pl.pad_bytes ? " padded_copy" : "",
-                 g.fold ? " pixel_folded" : "");
+    const ConvPlan pl = make_plan(g, tune, forms);
+    const PlanForm form = plan_form(g, pl, false);
+    const char* copy = pl.pad_bytes ? " padded_copy" : "";
+    char u8[64] = "";
+    if (u8_too) {
+        const ConvPlan p8 = make_plan(g, tune, forms, true);
+        const PlanForm f8 = plan_form(g, p8, true);
+        const char* tile = f8 == kFormWide ? p8.wide->name : f8 == kFormSplit ? p8.split->name : f8 == kFormGather ? gather_tile_name(g, tune, true) : nullptr;
+        snprintf(u8, sizeof(u8), " u8_kernel=%s%s%s", kFormKernels[f8], tile ? ":" : "", tile ? tile : "");
     }
+    char line[160];
+    switch (form) {
+        case kFormSplit: snprintf(line, sizeof(line), "conv_patch_kernel split_reduction tile=%s patch_pixels=%d", pl.split->name, pl.npix); break;
+        case kFormBlock: snprintf(line, sizeof(line), "conv_patch_kernel small_workgroups tile=256x64 patch_pixels=%d", pl.npix); break;
+        case kFormWide: snprintf(line, sizeof(line), "conv_gemm_kernel tile=%s eight_wavefronts", pl.wide->name); break;
+        case kFormRows: snprintf(line, sizeof(line), "conv_patch_kernel in_registers channels=%s", pl.rows->name); break;
+        case kFormPatch:
+            snprintf(line, sizeof(line), "conv_patch_kernel tile=128x%d chunks=%d unit_channels=%d patch_pixels=%d%s", pl.variant->tn, pl.ac,
+                     64 * pl.cbs, pl.npix, pl.ws ? " wave_specialised" : "");
+            break;
+        case kFormGather: snprintf(line, sizeof(line), "conv_gemm_kernel tile=%s", gather_tile_name(g, tune, false)); break;
+    }
+    snprintf(text, text_bytes, "%s%s%s kernel=%s%s", line, copy, g.fold ? " pixel_folded" : "", kFormKernels[form], u8);
     return SPARQ_OK;
 }
 }  // namespace
 
 extern "C" sparq_status sparq_conv_plan(const sparq_conv_desc* desc, const sparq_mode* mode, char* text, size_t text_bytes) {
-    return plan_text(desc, mode, text, text_bytes, true);
+    return plan_text(desc, mode, text, text_bytes, true, true);
 }
 
 namespace {
@@ -879,7 +906,7 @@ extern "C" sparq_status sparq_sparse24_plan(const sparq_conv_desc* desc, const s
     if (!text || text_bytes == 0 || !sparse24_geometry(desc, mode, &eff, &expand)) return SPARQ_EINVAL;
     const sparq_mode* m = expand ? &kNoPairPlain : mode;
     char line[200];
-    const sparq_status st = plan_text(&eff, m, line, sizeof(line), !sparse24_layout(eff).sparse);
+    const sparq_status st = plan_text(&eff, m, line, sizeof(line), !sparse24_layout(eff).sparse, false);
     if (st != SPARQ_OK) return st;
     ConvGeom g;
     conv_geom(&eff, &g);

@@ -241,6 +241,11 @@ __global__ __launch_bounds__(kRowsThreads, Cfg::kOcc) void conv_rows_kernel(cons
     }
 }
 
+// Dynamic LDS of a launch with rm pixels per wavefront.
+inline int64_t rows_lds_bytes(int rm, int64_t N, bool bytes) {
+    return bytes ? (kRowsThreads / 64) * rm * kRowsPitch + (N + 31) / 32 * 32 * 8 : 0;
+}
+
 // `p` carries everything except the item counts.
 template <class Cfg, int KIND, bool U8>
 sparq_status launch_rows_cfg(const RowsParams& p, hipStream_t s) {
@@ -271,19 +276,19 @@ sparq_status launch_rows_cfg(const RowsParams& p, hipStream_t s) {
     // (the loop's cursor runs past the last item by less than two strides)
     if (items > (1 << 30) || (int64_t)p.N * 4 * Cfg::kRM >= 0x7FFFFFFF || p.steps > Cfg::kKS) return SPARQ_EUNSUPPORTED;
     q.items = (int)items;
-    const int turn_bytes = (kRowsThreads / 64) * Cfg::kRM * kRowsPitch;
-    const int lds_bytes = U8 ? turn_bytes + blocks * 32 * 8 : 0;
+    const int64_t lds_bytes = rows_lds_bytes(Cfg::kRM, p.N, U8);
     if (lds_bytes > 64 * 1024) return SPARQ_EUNSUPPORTED;    // (what a launch may use without asking)
     const int64_t wgs = (items + 3) / 4, resident = slots / 4;
-    conv_rows_kernel<Cfg, KIND, U8><<<(unsigned)(wgs < resident ? wgs : resident), kRowsThreads, lds_bytes, s>>>(q);
+    conv_rows_kernel<Cfg, KIND, U8><<<(unsigned)(wgs < resident ? wgs : resident), kRowsThreads, (size_t)lds_bytes, s>>>(q);
     return launch_status();
 }
 
 // Cfg1: 32 pixels per wavefront, Cfg2: 64.  Sixty-four halve the weight traffic and win once both sides of the product are
 // large (K 256, N 1024, M 200704: 75 against 83 us); otherwise the shorter items do (K 256, N 256, M 12544: 7.2 against 9.9).
+inline bool rows_large(int64_t M, int64_t N) { return N >= 512 && M >= 48 * 1024; }
 template <class Cfg1, class Cfg2, int KIND>
 sparq_status launch_rows_out(const RowsParams& p, hipStream_t s) {
-    if (!std::is_same_v<Cfg1, Cfg2> && p.N >= 512 && p.M >= 48 * 1024)
+    if (!std::is_same_v<Cfg1, Cfg2> && rows_large(p.M, p.N))
         return p.out_u8 ? launch_rows_cfg<Cfg2, KIND, true>(p, s) : launch_rows_cfg<Cfg2, KIND, false>(p, s);
     return p.out_u8 ? launch_rows_cfg<Cfg1, KIND, true>(p, s) : launch_rows_cfg<Cfg1, KIND, false>(p, s);
 }

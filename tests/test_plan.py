@@ -66,6 +66,34 @@ def test_plan_of_the_headline_shapes(lib):
     assert text.startswith("conv_gemm_kernel tile=128x512") and ws == 0
 
 
+def words(text, key):
+    return [w[len(key):] for w in text.split() if w.startswith(key)]
+
+
+@pytest.mark.parametrize("shape,kernel,u8_kernel", [
+    ((64, 32, 32, 512, 512, 3, 1), "conv_patch_kernel", "conv_patch_kernel"),
+    ((1, 65536, 1, 4608, 512, 1, 0), "conv_wide_kernel", "conv_wide_kernel:128x512"),
+    ((256, 56, 56, 64, 256, 1, 0), "conv_patch_kernel", "conv_rows_kernel"),            # large four-byte rows / byte rows
+    ((256, 14, 14, 256, 1024, 1, 0), "conv_rows_kernel", "conv_rows_kernel"),
+    ((256, 56, 56, 64, 64, 3, 1), "conv_block_kernel", "conv_block_kernel"),
+    ((256, 28, 28, 128, 128, 3, 1), "conv_patch_kernel", "conv_block_kernel"),          # 113 to 128 channels: bytes only
+    ((128, 35, 35, 96, 96, 3, 1), "conv_patch_kernel", "conv_patch_kernel"),
+    ((1, 56, 56, 64, 64, 3, 1), "conv_split_kernel", "conv_split_kernel:32x32"),
+    ((1, 7, 7, 512, 514, 3, 1), "conv_split_kernel", "conv_split_kernel:32x32"),        # this form takes any N for bytes
+    ((64, 28, 28, 64, 250, 1, 0), "conv_patch_kernel", "conv_patch_kernel"),            # rows off a 64-byte border, bytes not 16
+    ((2, 9, 9, 32, 300, 3, 1), "conv_gemm_kernel", "conv_gemm_kernel:128x256"),
+    ((64, 32, 32, 512, 514, 1, 0), "conv_patch_kernel", "conv_patch_kernel"),
+    ((1, 65536, 1, 4608, 508, 1, 0), "conv_wide_kernel", "conv_gemm_kernel:128x256"),   # bytes: N off 16
+    ((1, 4000, 1, 64, 6000, 1, 0), "conv_rows_kernel", "conv_patch_kernel"),            # bytes: more channels than its LDS constants hold
+], ids=str)
+def test_plan_names_the_kernel_of_either_result(lib, shape, kernel, u8_kernel):
+    """kernel=: what sparq_conv_gemm launches; u8_kernel=: what sparq_conv_gemm_u8 does (with the gather kernel's, the split and
+    the eight-wavefront form's tile)."""
+    B, H, W, C, N, k, pad = shape
+    text = plan(lib, S.ConvLayer("p", B, H, W, C, N, k, k, (1, 1), (pad, pad)), S.Mode(4, S.OPT5, 1, 1))[0]
+    assert words(text, "kernel=") == [kernel] and words(text, "u8_kernel=") == [u8_kernel], text
+
+
 def test_tuning_hook_forces_and_clears_the_choice(lib):
     """sparq_set_tuning: the documented keys change the plan, NULL restores the rules, junk is refused and changes nothing."""
     conv = S.ConvLayer("conv3x3", 64, 32, 32, 512, 512, 3, 3, (1, 1), (1, 1), 0.5, S.Mode(4, S.OPT5, 1, 1))
