@@ -251,8 +251,10 @@ sparq_status sparq_conv_gemm_packed(const void *packed_x, size_t packed_x_bytes,
  * instruction as its sparse operand; otherwise the decompressed weights run
  * on the dense path.
  * sparq_sparse24_plan reports which (a text line as from sparq_conv_plan, without u8_kernel, plus
- * "expanded_x4", the problem over expanded groups of four, and "sparse_mfma" /
- * "dense_mfma").
+ * "expanded_x4", the problem over expanded groups of four,
+ * "expanded_while_staging" where the kernel expands x itself instead of reading
+ * an expanded tensor from the workspace (x then 16-byte aligned), and
+ * "sparse_mfma" / "dense_mfma").
  * packed: 256-byte aligned, sparq_sparse24_packed_bytes() bytes, filled once
  * by sparq_pack_weights_sparse24 for the same desc and mode; workspace:
  * 256-byte aligned, sparq_sparse24_workspace_bytes() bytes.  Everything else

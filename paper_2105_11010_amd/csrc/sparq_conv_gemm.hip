@@ -807,6 +807,14 @@ bool sparse24_geometry(const sparq_conv_desc* desc, const sparq_mode* mode, spar
 }
 const sparq_mode kNoPairPlain = {8, 1, 0, 0};
 
+// The staging wavefronts expand what they load where a tile's patch is small beside its taps: each patch pixel is then
+// trimmed three times per 64 channels and channel tile, which the matrix instructions of its taps have to cover (3x3 on 32 x
+// 32 pixels, 204 patch pixels: 357 -> 241 us; strided 1x7 on 12 x 12 54 -> 108).  Elsewhere the expanded tensor is written first.
+// `pl`: the plan of the expanded layer.
+bool expands_while_staging(const sparq_conv_desc& desc, const ConvPlan& pl) {
+    return sparse24_blocked(desc.C) && sparse_plan(pl, kTrimNone) && pl.npix <= 32 * desc.KH * desc.KW;
+}
+
 // Layout of the buffer sparq_pack_weights_sparse24 fills: the dense packed tiles of the contracted problem, room
 // to decompress into, then the same weights as operands of the sparse matrix instruction (kept bytes, positions)
 // when the contracted problem's taps are 64-byte aligned (otherwise those two parts are empty).
@@ -878,13 +886,9 @@ extern "C" sparq_status sparq_conv_gemm_sparse24(const uint8_t* x, const void* p
     if (workspace_bytes < sparq_sparse24_workspace_bytes(desc, mode)) return SPARQ_EWORKSPACE;
     const int64_t pixels = (int64_t)desc->B * desc->H * desc->W;
     if (pixels * desc->C * 4 >= (int64_t)kInvalidOffset) return SPARQ_EUNSUPPORTED;
-    // The staging wavefronts expand what they load where a tile's patch is small beside its taps: each patch pixel is then
-    // trimmed three times per 64 channels and channel tile, which the matrix instructions of its taps have to cover (3x3 on 32 x
-    // 32 pixels, 204 patch pixels: 357 -> 241 us; strided 1x7 on 12 x 12 54 -> 108).  Elsewhere the expanded tensor is written first.
     ConvGeom ge;
     conv_geom(&eff, &ge);
-    const ConvPlan pe = make_plan(ge, current_tuning(), false);
-    if (sp && sparse24_blocked(desc->C) && aligned(x, 16) && pe.patch && pe.npix <= 32 * desc->KH * desc->KW) {
+    if (sp && aligned(x, 16) && expands_while_staging(*desc, make_plan(ge, current_tuning(), false))) {
         SparseOperand fused = sp_op;
         fused.expand_mode = mode;
         fused.x_channels = desc->C;
@@ -913,7 +917,8 @@ extern "C" sparq_status sparq_sparse24_plan(const sparq_conv_desc* desc, const s
     const ConvPlan pl = make_plan(g, current_tuning(), false);
     const TrimKind kind = (g.fold || g.Cp != g.C) ? kTrimNone : trim_kind(m);     // a padded copy is trimmed by its pre-pass
     const bool smfmac = sparse24_layout(eff).sparse && sparse_plan(pl, kind);
-    snprintf(text, text_bytes, "%s%s%s", line, expand ? " expanded_x4" : "", smfmac ? " sparse_mfma" : " dense_mfma");
+    snprintf(text, text_bytes, "%s%s%s%s", line, expand ? " expanded_x4" : "",
+             expand && smfmac && expands_while_staging(*desc, pl) ? " expanded_while_staging" : "", smfmac ? " sparse_mfma" : " dense_mfma");
     return SPARQ_OK;
 }
 

@@ -134,32 +134,56 @@ def test_sparse_instruction_kernel_with_one_output(sq, oracle, layer):
     assert np.all(np.abs(out.cpu().numpy().astype(np.float64) - ref_out) <= 1e-6 * np.abs(ref_out))
 
 
-# expansion inside the staging wavefronts: a last 64-channel block that is partly padding, units of several blocks
-# (1x1), every pairing trim
-BLOCKED_LAYERS = [
-    S.ConvLayer("blk_3x3_112_72", 2, 13, 11, 112, 72, 3, 3, (1, 1), (1, 1), 0.5, M45),
+# Channel counts in blocked order.  Staging: the kernel expands x itself (small patches beside the taps) -- a last 64-channel
+# block that is partly padding, units of one, two and four blocks (1x1 layers of few pixels), every pairing trim.  Written: the
+# same order, expanded into the workspace first.
+STAGING_LAYERS = [
+    (64, S.ConvLayer("blk_3x3_112_72", 2, 13, 11, 112, 72, 3, 3, (1, 1), (1, 1), 0.5, M45)),
+    (64, S.ConvLayer("blk_5x5_64_65_2bit", 1, 12, 12, 64, 65, 5, 5, (1, 1), (2, 2), 0.6, S.Mode(2, S.OPT7_2B, 1, 1))),
+    (64, S.ConvLayer("blk_3x3_176_100_floor", 2, 13, 11, 176, 100, 3, 3, (1, 1), (1, 1), 0.5, S.Mode(4, S.OPT3, 0, 1))),
+    (64, S.ConvLayer("blk_3x3_64_40_floor3", 1, 9, 9, 64, 40, 3, 3, (1, 1), (1, 1), 0.5, S.Mode(3, S.OPT6_3B, 0, 1))),
+    (128, S.ConvLayer("blk_1x1_128_40_floor", 1, 5, 6, 128, 40, 1, 1, (1, 1), (0, 0), 0.5, S.Mode(4, S.OPT5, 0, 1))),
+    (128, S.ConvLayer("blk_1x1_112_70_round3", 1, 1, 1, 112, 70, 1, 1, (1, 1), (0, 0), 0.3, S.Mode(3, S.OPT6_3B, 1, 1))),
+    (256, S.ConvLayer("blk_1x1_256_136", 2, 4, 4, 256, 136, 1, 1, (1, 1), (0, 0), 0.5, M45)),
+    (256, S.ConvLayer("blk_1x1s2_240_300_2bit", 1, 9, 9, 240, 300, 1, 1, (2, 2), (0, 0), 0.5, S.Mode(2, S.OPT7_2B, 0, 1))),
+    (256, S.ConvLayer("blk_1x1_512_64_floor", 1, 31, 1, 512, 64, 1, 1, (1, 1), (0, 0), 0.4, S.Mode(4, S.OPT2, 0, 1))),
+]
+WRITTEN_LAYERS = [
     S.ConvLayer("blk_1x1_176_136", 2, 15, 15, 176, 136, 1, 1, (1, 1), (0, 0), 0.5, S.Mode(4, S.OPT3, 0, 1)),
     S.ConvLayer("blk_1x1_256_70", 2, 15, 15, 256, 70, 1, 1, (1, 1), (0, 0), 0.4, S.Mode(3, S.OPT6_3B, 1, 1)),
     S.ConvLayer("blk_1x1s2_128_300", 2, 15, 15, 128, 300, 1, 1, (2, 2), (0, 0), 0.5, S.Mode(2, S.OPT7_2B, 0, 1)),
-    S.ConvLayer("blk_5x5_64_65_2bit", 1, 12, 12, 64, 65, 5, 5, (1, 1), (2, 2), 0.6, S.Mode(2, S.OPT7_2B, 1, 1)),
 ]
 
 
-@pytest.mark.parametrize("layer", BLOCKED_LAYERS, ids=lambda l: l.name)
-def test_sparse24_expanded_while_staging(sq, oracle, layer):
-    rng = S.rng_for(10, 300 + BLOCKED_LAYERS.index(layer))
+def check_blocked_layer(sq, oracle, layer, stream, staging, unit=None):
+    """Through the rules' choice, the gather kernel (which reads the same expansion from memory) and every tile width."""
+    rng = S.rng_for(10, stream)
     x = S.gen_activations(layer.x_shape(), layer.zf, rng)
     wv, wi = S.gen_sparse24_weights(layer.w_shape(), rng)
     sc = S.gen_scales(layer.N, rng)
     ref_acc, ref_out = oracle.conv_gemm_sparse24(x, wv, wi, layer.stride, layer.pad, scale=sc, **layer.mode.kwargs())
+    d = sq.conv_desc(layer.B, layer.H, layer.W, layer.C, layer.N, layer.KH, layer.KW, layer.stride, layer.pad)
     try:
-        for spec in FORMS:                       # the gather kernel reads the same expansion from memory
+        for spec in FORMS:
             sq.sparq_set_tuning(spec)
+            plan = sq.sparq_sparse24_plan(d, sq.mode(*layer.mode.astuple()))
+            assert ("expanded_while_staging" in plan) == (staging and spec != "path=gather"), plan
+            assert spec == "path=gather" or unit is None or f"unit_channels={unit} " in plan, plan
             acc, out = run_sparse(sq, layer, x, wv, wi, sc)
-            assert np.array_equal(acc, ref_acc), f"{layer.name} [{spec}]: int32 accumulators differ from the oracle"
-            assert np.all(np.abs(out.astype(np.float64) - ref_out) <= 1e-6 * np.abs(ref_out)), spec
+            assert np.array_equal(acc, ref_acc), f"{layer.name} [{plan}]: int32 accumulators differ from the oracle"
+            assert np.all(np.abs(out.astype(np.float64) - ref_out) <= 1e-6 * np.abs(ref_out)), plan
     finally:
         sq.sparq_set_tuning(None)
+
+
+@pytest.mark.parametrize("unit,layer", STAGING_LAYERS, ids=lambda v: v.name if isinstance(v, S.ConvLayer) else f"unit{v}")
+def test_sparse24_expanded_while_staging(sq, oracle, unit, layer):
+    check_blocked_layer(sq, oracle, layer, 300 + [l for _, l in STAGING_LAYERS].index(layer), True, unit)
+
+
+@pytest.mark.parametrize("layer", WRITTEN_LAYERS, ids=lambda l: l.name)
+def test_sparse24_blocked_expansion_written_first(sq, oracle, layer):
+    check_blocked_layer(sq, oracle, layer, 320 + WRITTEN_LAYERS.index(layer), False)
 
 
 def test_extreme_values(sq, oracle):

@@ -195,3 +195,15 @@ def test_sparse24_plan_names_the_matrix_instruction(lib):
     assert lib.sparq_sparse24_packed_bytes(ctypes.byref(conv), ctypes.byref(m)) >= dense_tiles + kp_np + kp_np // 2 + kp_np // 8
     buf = ctypes.create_string_buffer(64)
     assert lib.sparq_sparse24_plan(ctypes.byref(Desc(1, 4, 4, 6, 8, 1, 1, 1, 1, 0, 0)), ctypes.byref(m), buf, len(buf)) == 1   # C % 4
+
+
+def test_sparse24_plan_says_where_the_expansion_happens(lib):
+    """While staging: blocked channel counts, vSPARQ on, the sparse instruction, at most 32 patch pixels per tap."""
+    m = Mode(4, 0x1F, 0, 1)
+    for d, staging in (((2, 13, 11, 176, 100, 3, 3, 1, 1, 1, 1), True), ((2, 4, 4, 256, 136, 1, 1, 1, 1, 0, 0), True),
+                       ((1, 3, 11, 256, 136, 1, 1, 1, 1, 0, 0), False), ((2, 15, 15, 256, 70, 1, 1, 1, 1, 0, 0), False),
+                       ((2, 13, 11, 96, 100, 3, 3, 1, 1, 1, 1), False)):          # 96 channels: a third of padding
+        text = sparse_plan(lib, Desc(*d), m)
+        assert ("expanded_while_staging" in text) == staging and text.endswith("sparse_mfma"), text
+    for m in (Mode(4, 0x1F, 0, 0), Mode(8, 1, 0, 0)):
+        assert "expanded" not in sparse_plan(lib, Desc(2, 13, 11, 176, 100, 3, 3, 1, 1, 1, 1), m)
