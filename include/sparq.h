@@ -273,12 +273,18 @@ sparq_status sparq_sparse24_plan(const sparq_conv_desc *desc, const sparq_mode *
 
 /* Test and tuning hook: overrides, for the whole process and until changed
  * again, which kernel and tiling the convolution entry points choose (the
- * tests use it to drive every kernel over every shape; results never depend
- * on it).  spec is a comma-separated list of key=value, NULL or "" clears it:
- *   path=gather|patch        one of the two convolution kernels, where eligible
+ * tests use it to drive every kernel over every shape it can run; results never
+ * depend on it).  spec is a comma-separated list of key=value, NULL or "" clears it:
+ *   path=gather|patch        one of the two tile kernels, where eligible
  *   tile=128x128|128x256|128x512   gather kernel tile
  *   patch_tn=64|128|256      input-patch kernel: output channels per tile
  *   patch_ws=0|1             input-patch kernel: plain / wave-specialised form
+ *   form=split|rows|wide|block   conv_split_kernel, conv_rows_kernel,
+ *                            conv_wide_kernel or conv_block_kernel wherever the
+ *                            layer fits it, the tile kernels elsewhere (2:4
+ *                            layers that run on the sparse instruction's plan
+ *                            keep to the tile kernels)
+ * Any of the keys switches the rules of the four other forms off.
  * Anything else returns SPARQ_EINVAL and leaves the override as it was.
  * Changing it while convolution calls are in flight on other threads makes
  * those calls pick either setting. */

@@ -322,5 +322,5 @@ def sparq_conv_gemm_sparse24(x: torch.Tensor, packed: torch.Tensor, d: SparqConv
 
 
 def sparq_set_tuning(spec: Optional[str] = None) -> None:
-    """Test / tuning hook: force the kernel choice ("path=patch,patch_tn=128,patch_ws=1", ...); None clears it."""
+    """Test / tuning hook: force the kernel choice ("path=patch,patch_tn=128,patch_ws=1", "form=rows", ...); None clears it."""
     _check(lib.sparq_set_tuning(spec.encode() if spec else None), "sparq_set_tuning")

@@ -18,11 +18,14 @@ using namespace sparq;
 namespace {
 
 // ---- the one test / tuning hook (sparq_set_tuning): process-wide overrides of the kernel choice ----
+enum TunedForm { kTunedSplit = 1, kTunedRows, kTunedWide, kTunedBlock };
 struct Tuning {
     int path = 0;             // 0: rules decide, 1: gather kernel, 2: input-patch kernel
     char tile[16] = "";       // gather kernel tile "128x128" | "128x256" | "128x512"
     int patch_tn = 0;         // input-patch kernel: output channels per tile (64 / 128 / 256), 0: rules decide
     int patch_ws = -1;        // 1 / 0: wave-specialised / plain form, -1: rules decide
+    int form = 0;             // 0: rules decide, else a TunedForm
+    // one of the two tile kernels is asked for: the rules of the other forms do not apply
     bool set() const { return path || tile[0] || patch_tn || patch_ws >= 0; }
 };
 Tuning g_tuning;
@@ -227,8 +230,19 @@ const SplitVariant* pick_split(const ConvGeom& g, PatchGeom* pg, int* npix) {
     }
     return nullptr;
 }
+// The smallest tile that holds the layer's patch.
+const SplitVariant* fit_split(const ConvGeom& g, PatchGeom* pg, int* npix) {
+    for (const SplitVariant& v : kSplitVariants)
+        if (patch_geom_for(g, v.tm, pg, npix) && v.lds_bytes(*npix, g.Cq / kChunk) > 0) return &v;
+    return nullptr;
+}
 
 // ---- 1x1 layers with the activations in registers --------------------------------------------
+// 1x1 layers without padding, inside the index arithmetic of the two forms made for them; `bytes`: 16 results leave together.
+bool one_tap(const ConvGeom& g, bool bytes) {
+    return g.KH == 1 && g.KW == 1 && !g.ph && !g.pw && g.Cq % kStepK == 0 && g.M < kPatchMaxDividend &&
+           (size_t)g.Kp * g.Np < kPatchInvalidOffset && (int64_t)g.B * g.H * g.W < kPatchMaxDividend && !(bytes && g.N % 16);
+}
 struct RowsVariant { int steps; const char* name; RowsLauncher fn; int rm, rm_large; };   // 32-index reduction steps it holds, pixels per wavefront
 const RowsVariant kRowsVariants[] = {
     {2, "64", launch_rows_k64, 32, 32}, {4, "128", launch_rows_k128, 32, 32}, {6, "192", launch_rows_k192, 32, 64},
@@ -241,27 +255,30 @@ bool rows_launchable(const RowsVariant& v, const ConvGeom& g, bool bytes) {
     return g.N * 4ll * rm < 0x7FFFFFFF && rows_lds_bytes(rm, g.N, bytes) <= 64 * 1024;
 }
 
-// Activations in registers: 1x1 layers without padding.  `bytes`: requantised results (16 of them leave together).
+const RowsVariant* fit_rows(const ConvGeom& g, bool bytes) {
+    if (one_tap(g, bytes))
+        for (const RowsVariant& v : kRowsVariants)
+            if (g.Cq / 32 <= v.steps) return &v;
+    return nullptr;
+}
+
+// Activations in registers: 1x1 layers without padding.  `bytes`: requantised results.
 // Up to 512 channels it beats the tile kernels nearly everywhere, by 1.1-1.6 x on small tensors and up to 2.2 x on large ones
 // (256 -> 64 channels, 802816 pixels 80 -> 69 us; 64 -> 256 bytes 106 -> 58; 128 -> 512 bytes 60 -> 35), except where four-byte
 // results larger than the last-level cache leave in rows of 1 KB or more (64 -> 256, 802816 pixels: 154 against 170 us: the
 // tile kernels write whole rows at a time).  (Holding 768 or 1024 channels was built too: behind the form below.)
 const RowsVariant* pick_rows(const ConvGeom& g, bool bytes) {
-    if (g.KH != 1 || g.KW != 1 || g.ph || g.pw || g.Cq % kStepK || g.M >= kPatchMaxDividend ||
-        (size_t)g.Kp * g.Np >= kPatchInvalidOffset || (int64_t)g.B * g.H * g.W >= kPatchMaxDividend)
-        return nullptr;
-    if (bytes ? g.N % 16 != 0 : (g.N >= 256 && g.M * g.N * 4 >= kStreamedBytes)) return nullptr;
+    if (!bytes && g.N >= 256 && g.M * g.N * 4 >= kStreamedBytes) return nullptr;
     // (four-byte rows that start off a 64-byte border: its 128-byte runs are two partial lines each, the tile kernels' rows are
     // not; 196 -> 948, 28187 pixels 57 against 85 us.  Up to 8 MiB the shorter chain is worth more.)
     if (!bytes && g.N % 16 != 0 && g.M * g.N * 4 > (8 << 20)) return nullptr;
-    for (const RowsVariant& v : kRowsVariants)
-        if (g.Cq / 32 <= v.steps) return &v;
-    return nullptr;
+    return fit_rows(g, bytes);
 }
 
 // ---- 1x1 layers with a long reduction: eight wavefronts per tile ------------------------------
 struct WideVariant { const char* name; int tn; WideLauncher fn; };
 const WideVariant kWideVariants[] = {{"128x512", 512, launch_wide_512}, {"128x256", 256, launch_wide_256}};
+bool fit_wide(const ConvGeom& g, bool bytes) { return one_tap(g, bytes) && g.Cq > 4 * kStepK; }      // (its requests run six steps ahead)
 
 // Eight wavefronts per tile: 1x1 layers without padding and with more than 512 channels, whatever their size (what the split
 // form does not take), except few output channels, where the 256-wide tile multiplies mostly padding (784 -> 48: 12 against 15 us).  Over
@@ -270,16 +287,15 @@ const WideVariant kWideVariants[] = {{"128x512", 512, launch_wide_512}, {"128x25
 // With 449 to 512 channels the activations fit in registers, and that form is ahead once there are many rounds of
 // tiles; in one well-filled round (196 tiles: 12544 x 512 -> 512 14.1 against 11.9 us), or two for bytes, this one is.
 // The 512-wide tile costs about 1.35 times the 256-wide one's round and does twice the work.
-const WideVariant* pick_wide(const ConvGeom& g, bool bytes) {
-    if (g.KH != 1 || g.KW != 1 || g.ph || g.pw || g.Cq % kStepK || g.Cq < 512 || g.M >= kPatchMaxDividend ||
-        (size_t)g.Kp * g.Np >= kPatchInvalidOffset || (int64_t)g.B * g.H * g.W >= kPatchMaxDividend || (bytes && g.N % 16))
-        return nullptr;
-    if (g.N <= 96 || (g.N <= 128 && g.M >= 32 * 1024)) return nullptr;
+// forced: by the tuning hook, only the tile is chosen.
+const WideVariant* pick_wide(const ConvGeom& g, bool bytes, bool forced = false) {
+    if (!fit_wide(g, bytes)) return nullptr;
+    if (!forced && (g.Cq < 512 || g.N <= 96 || (g.N <= 128 && g.M >= 32 * 1024))) return nullptr;
     const int64_t cus = device_cu_count(), tiles_m = (g.M + 127) / 128;
     const int64_t t512 = tiles_m * ((g.N + 511) / 512), t256 = tiles_m * ((g.N + 255) / 256);
     const int64_t r512 = (t512 + cus - 1) / cus, r256 = (t256 + cus - 1) / cus;
     const bool wider = g.N > 256 && r512 * 27 <= r256 * 20 && round_up(g.N, 512) <= g.Np;
-    if (g.Cq == 512) {
+    if (g.Cq == 512 && !forced) {
         const bool fills = wider ? bytes && r512 <= 2 && t512 * 10 >= r512 * cus * 7 : r256 == 1 && t256 * 8 >= cus * 3;
         if (!fills || round_up(g.N, wider ? 512 : 256) * 4 > (int64_t)g.N * 5) return nullptr;     // (or pads N by over a quarter)
     }
@@ -287,6 +303,15 @@ const WideVariant* pick_wide(const ConvGeom& g, bool bytes) {
 }
 
 // ---- multi-tap layers as many small workgroups -----------------------------------------------
+bool fit_block(const ConvGeom& g, bool bytes, PatchGeom* pg, int* npix) {
+    PatchGeom q;
+    int n;
+    if (g.KH * g.KW == 1 || (bytes && g.N % 16) || !patch_geom_for(g, BlockCfg::kTM, &q, &n) || !block_launchable(g.M, g.N, n)) return false;
+    *pg = q;
+    *npix = n;
+    return true;
+}
+
 // Small workgroups: multi-tap layers with tiles for every slot of the chip (300 and more) and
 //   up to 64 channels, if they have at most 64 outputs or a patch of less than 450 pixels per tile (1.0-1.5 x faster there:
 //   56 x 56 x 64 -> 64 3x3, batch 32 16.5 -> 13.1 us, batch 256 78 -> 58; wider rows trim too much per 64 outputs),
@@ -296,18 +321,13 @@ const WideVariant* pick_wide(const ConvGeom& g, bool bytes) {
 // With fewer tiles, or more channels, the tile kernel's pipelining is ahead (14 x 14 x 256, batch 256: 35 against 44 us).
 bool pick_block(const ConvGeom& g, bool bytes, bool gather, PatchGeom* pg, int* npix) {
     const int taps = g.KH * g.KW;
-    if (taps == 1 || (bytes && g.N % 16) || block_tiles(g.M, g.N) < 300) return false;
+    if (taps == 1 || block_tiles(g.M, g.N) < 300) return false;
     gather = gather && (g.Cq == 64 || g.N <= 64 || taps >= 15) && g.Cq <= 256;
     if (g.Cq > 128 && !gather) return false;
-    PatchGeom q;
-    int n;
-    if (!patch_geom_for(g, BlockCfg::kTM, &q, &n) || !block_launchable(g.M, g.N, n)) return false;
     // patch pixels of a tile that starts and ends anywhere in its rows (the largest one may cross two images)
     const bool small = ((int64_t)BlockCfg::kTM + (int64_t)g.KH * g.Wo) * ((int64_t)(g.Wo - 1) * g.sw + g.KW) < 450ll * g.Wo;
     if (!gather && !(g.Cq == 64 ? g.N <= 64 || small : small && bytes && g.C > 112)) return false;
-    *pg = q;
-    *npix = n;
-    return true;
+    return fit_block(g, bytes, pg, npix);
 }
 
 // Everything the entry points decide before launching.
@@ -324,9 +344,10 @@ struct ConvPlan {
     size_t pad_bytes = 0;       // channel-padded copy of x (channel counts that are not a multiple of 16)
 };
 
-// split: the split-reduction form may be taken (never for 2:4 pruned weights, nor when the tuning hook is in use).
+// forms: the forms other than the two tile kernels may be taken (never for 2:4 pruned weights; where the tuning hook asks for
+// a tile kernel, no rule takes them; where it asks for one of them, that one wherever the layer fits it).
 // bytes: requantised results.
-ConvPlan make_plan(const ConvGeom& g, const Tuning& tune, bool split = true, bool bytes = false) {
+ConvPlan make_plan(const ConvGeom& g, const Tuning& tune, bool forms = true, bool bytes = false) {
     ConvPlan pl;
     if (g.fold) {               // at most 4 channels: 4-channel padded copy, pixel-folded, gather kernel
         pl.pad_bytes = (size_t)round_up((int64_t)g.B * g.H * g.W * 4, 256);
@@ -336,7 +357,13 @@ ConvPlan make_plan(const ConvGeom& g, const Tuning& tune, bool split = true, boo
     const bool force_gather = tune.path == 1, force_patch = tune.path == 2;
     ConvGeom gk = g;
     gk.C = gk.Cp;                                                // what the kernel sees after the padding pre-pass
-    if (split && !tune.set()) {
+    const bool rules = forms && !tune.form && !tune.set();
+    if (forms && tune.form) {
+        if (tune.form == kTunedRows && (pl.rows = fit_rows(gk, bytes)) != nullptr && !rows_launchable(*pl.rows, gk, bytes)) pl.rows = nullptr;
+        if (tune.form == kTunedSplit && (pl.split = fit_split(gk, &pl.pg, &pl.npix)) != nullptr) return pl;
+        if (tune.form == kTunedWide) pl.wide = pick_wide(gk, bytes, true);
+    }
+    if (rules) {
         // (up to 256 channels the registers form is ahead of the split form at every size, beyond that behind it:
         // 256 -> 256, 784 pixels 5.3 against 5.7 us; 512 -> 256 7.9 against 6.0)
         pl.rows = pick_rows(gk, bytes);
@@ -347,7 +374,8 @@ ConvPlan make_plan(const ConvGeom& g, const Tuning& tune, bool split = true, boo
         pl.variant = pick_patch(g, tune, pl.ac, pl.cbs, pl.npix, force_patch, &pl.ws);
         pl.patch = pl.variant != nullptr;
     }
-    if (split && !tune.set()) pl.block = pick_block(gk, bytes, !pl.patch, &pl.pg, &pl.npix);
+    if (rules) pl.block = pick_block(gk, bytes, !pl.patch, &pl.pg, &pl.npix);
+    else if (forms && tune.form == kTunedBlock) pl.block = fit_block(gk, bytes, &pl.pg, &pl.npix);
     return pl;
 }
 
@@ -389,6 +417,12 @@ extern "C" sparq_status sparq_set_tuning(const char* spec) {
         } else if (!strcmp(key, "patch_ws")) {
             if (strcmp(val, "0") && strcmp(val, "1")) return SPARQ_EINVAL;
             t.patch_ws = val[0] - '0';
+        } else if (!strcmp(key, "form")) {
+            if (!strcmp(val, "split")) t.form = kTunedSplit;
+            else if (!strcmp(val, "rows")) t.form = kTunedRows;
+            else if (!strcmp(val, "wide")) t.form = kTunedWide;
+            else if (!strcmp(val, "block")) t.form = kTunedBlock;
+            else return SPARQ_EINVAL;
         } else {
             return SPARQ_EINVAL;
         }

@@ -357,6 +357,44 @@ def test_conv_small_workgroups(sq, oracle, layer, mode):
     check_layer_u8(sq, oracle, layer, mode, seed_cfg=8, out_mode=S.Mode(4, S.OPT5, 1, 1))
 
 
+# Each of these forms, forced by the tuning hook, in every trim variant it is built for and every form of its results: int32
+# alone, fp32 alone, both, bytes, bytes trimmed with the layer's own mode, and bytes trimmed where the input already is.
+FORM_SHAPES = [
+    ("split", S.ConvLayer("f_3x3_c80_n32", 2, 9, 11, 80, 32, 3, 3, (1, 1), (1, 1))),
+    ("split", S.ConvLayer("f_1x1_c208_n48_s2", 2, 9, 11, 208, 48, 1, 1, (2, 2), (0, 0))),
+    ("rows", S.ConvLayer("f_c64_n48", 1, 71, 1, 64, 48)), ("rows", S.ConvLayer("f_c128_n80", 3, 9, 7, 128, 80)),
+    ("rows", S.ConvLayer("f_c176_n144_s2", 3, 15, 13, 176, 144, 1, 1, (2, 2), (0, 0))), ("rows", S.ConvLayer("f_c256_n272", 1, 100, 1, 256, 272)),
+    ("rows", S.ConvLayer("f_c304_n64", 1, 333, 1, 304, 64)), ("rows", S.ConvLayer("f_c384_n160", 1, 130, 1, 384, 160)),
+    ("rows", S.ConvLayer("f_c512_n16", 1, 67, 1, 512, 16)), ("rows", S.ConvLayer("f_c192_n512_wide", 1, 49169, 1, 192, 512)),
+    ("wide", S.ConvLayer("f_c336_n48", 1, 200, 1, 336, 48)), ("wide", S.ConvLayer("f_c576_n272_s2", 3, 21, 19, 576, 272, 1, 1, (2, 2), (0, 0))),
+    ("wide", S.ConvLayer("f_c528_n320", 1, 16500, 1, 528, 320)),          # the 512-wide tile
+    ("block", S.ConvLayer("f_3x3_c80_n80", 2, 13, 11, 80, 80, 3, 3, (1, 1), (1, 1))), ("block", S.ConvLayer("f_5x5_c144_n48", 1, 20, 20, 144, 48, 5, 5, (1, 1), (2, 2))),
+]
+FORM_MODES = [S.Mode(4, S.OPT5, 1, 1), S.Mode(4, S.OPT5, 1, 0), S.Mode(4, S.OPT3, 0, 1), S.Mode(4, S.OPT3, 0, 0),
+              S.Mode(3, S.OPT6_3B, 1, 0), S.Mode(2, S.OPT7_2B, 1, 1), S.Mode(2, S.OPT7_2B, 0, 1), S.PLAIN8]
+
+
+@pytest.mark.parametrize("form,layer", FORM_SHAPES, ids=lambda v: v if isinstance(v, str) else v.name)
+@pytest.mark.parametrize("mode", FORM_MODES, ids=lambda m: m.label)
+def test_conv_every_variant_of_a_form(sq, oracle, tuning, form, layer, mode):
+    tuning(f"form={form}")
+    d = sq.conv_desc(layer.B, layer.H, layer.W, layer.C, layer.N, layer.KH, layer.KW, layer.stride, layer.pad)
+    words = sq.sparq_conv_plan(d, sq.mode(*mode.astuple())).split()
+    assert f"kernel=conv_{form}_kernel" in words and any(w.startswith(f"u8_kernel=conv_{form}_kernel") for w in words), words
+    x, w, sc = S.gen_layer(8, layer)
+    ref_acc, ref_out = oracle.conv_gemm(x, w, layer.stride, layer.pad, scale=sc, **mode.kwargs())
+    for want_acc, want_out in ((True, False), (False, True), (True, True)):
+        acc, out = run_conv(sq, x, w, sc, layer, mode, want_acc, want_out)
+        assert acc is None or np.array_equal(acc, ref_acc)
+        assert out is None or np.all(np.abs(out.astype(np.float64) - ref_out) <= 1e-6 * np.abs(ref_out))
+    f = S.gen_requant(layer, S.rng_for(8, 900 + layer.index))
+    ref = oracle.requant(ref_acc, f)
+    assert np.array_equal(run_conv_u8(sq, x, w, f, layer, mode), ref)
+    assert np.array_equal(run_conv_u8(sq, x, w, f, layer, mode, out_mode=mode), oracle.trim(ref, **mode.kwargs()))
+    plain = oracle.requant(oracle.conv_gemm(x, w, layer.stride, layer.pad, **S.PLAIN8.kwargs())[0], f)
+    assert np.array_equal(run_conv_u8(sq, x, w, f, layer, S.PLAIN8, out_mode=mode), oracle.trim(plain, **mode.kwargs()))
+
+
 # Shapes chosen for the input-patch kernel: tiles that span several image rows and several images,
 # one-row tiles, every staging variant (64/128/256-channel units), several output-channel tiles.
 PATCH_SHAPES = [

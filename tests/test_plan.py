@@ -113,6 +113,35 @@ def test_tuning_hook_forces_and_clears_the_choice(lib):
     assert plan(lib, conv)[0] == base
 
 
+def test_tuning_hook_forces_the_other_forms(lib):
+    """form=: wherever the layer fits the form, for four-byte and byte results; the tile kernels where it does not."""
+    lib.sparq_set_tuning.argtypes = [ctypes.c_char_p]
+    mode = S.Mode(4, S.OPT5, 1, 1)
+    big = S.ConvLayer("conv3x3", 64, 32, 32, 512, 512, 3, 3, (1, 1), (1, 1))
+    taps = S.ConvLayer("t", 2, 13, 11, 72, 80, 3, 3, (1, 1), (1, 1))
+    one = S.ConvLayer("o", 1, 100, 1, 330, 48)
+    odd = S.ConvLayer("n", 1, 100, 1, 330, 50)
+    few = S.ConvLayer("c32", 2, 13, 11, 32, 80, 3, 3, (1, 1), (1, 1))
+    tiles = ("conv_patch_kernel", "conv_gemm_kernel")
+    cases = {"split": ((taps, True, True), (one, True, True), (odd, True, True), (few, False, False)),
+             "rows": ((one, True, True), (odd, True, False), (taps, False, False), (big, False, False)),
+             "wide": ((one, True, True), (odd, True, False), (taps, False, False), (S.ConvLayer("k", 1, 100, 1, 256, 48), False, False)),
+             "block": ((taps, True, True), (big, True, True), (one, False, False), (few, False, False))}
+    base = [plan(lib, l, mode)[0] for l in (big, taps, one, odd, few)]
+    try:
+        for form, layers in cases.items():
+            assert lib.sparq_set_tuning(f"form={form}".encode()) == 0
+            for layer, acc, u8 in layers:
+                text = plan(lib, layer, mode)[0]
+                k, k8 = words(text, "kernel=")[0], words(text, "u8_kernel=")[0].split(":")[0]
+                assert (k == f"conv_{form}_kernel") == acc and (acc or k in tiles), text
+                assert (k8 == f"conv_{form}_kernel") == u8 and (u8 or k8 in tiles), text
+        assert lib.sparq_set_tuning(b"form=fast") == 1
+    finally:
+        assert lib.sparq_set_tuning(None) == 0
+    assert [plan(lib, l, mode)[0] for l in (big, taps, one, odd, few)] == base
+
+
 def test_widest_gather_tile_only_with_step_aligned_taps(lib):
     """The 128 x 512 tile tracks a step's filter tap in scalar registers, so every 64-byte reduction step must lie
     inside one tap (more than 32 channels); otherwise, and when 512 columns would read past the padded weights, the
