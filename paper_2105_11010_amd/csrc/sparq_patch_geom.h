@@ -1,6 +1,6 @@
 // Index arithmetic of the input-patch convolution kernel, shared by device and host code.
 //
-// A tile is PatchGeom::tm (128 or 256) consecutive output pixels in (b, oy, ox) order.  All input pixels that any
+// A tile is PatchGeom::tm (32 to 256) consecutive output pixels in (b, oy, ox) order.  All input pixels that any
 // filter tap of any of those outputs touches form a rectangle of "virtual rows" x columns:
 //
 //   virtual row  v = b * Hv + (iy + pad_h),  Hv = H + 2 * pad_h     (padding rows included)

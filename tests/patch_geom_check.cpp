@@ -2,7 +2,7 @@
 // convolution shape, every output pixel and every filter tap, the patch pixel the kernel would
 // read must hold exactly the input pixel the convolution's definition names (or padding), lie
 // inside the patch, and the patch must not exceed the closed-form size bound.
-// Both tile heights the kernels use (128 and 256 output pixels) are walked.
+// Every tile height the kernels use (32 and 64 output pixels in the split form, 128, and 256 in small workgroups) is walked.
 //   usage: patch_geom_check B H W KH KW stride_h stride_w pad_h pad_w   -> prints "ok <tiles> <max npix> <bound>" (of the 128-pixel walk)
 #include <stdio.h>
 #include <stdlib.h>
@@ -48,6 +48,7 @@ int main(int argc, char** argv) {
     if (argc < 10) return 2;
     const int B = atoi(argv[1]), H = atoi(argv[2]), W = atoi(argv[3]), KH = atoi(argv[4]), KW = atoi(argv[5]);
     const int sh = atoi(argv[6]), sw = atoi(argv[7]), ph = atoi(argv[8]), pw = atoi(argv[9]);
-    if (int rc = walk(B, H, W, KH, KW, sh, sw, ph, pw, 256, false)) return rc;
+    for (int tm : {32, 64, 256})
+        if (int rc = walk(B, H, W, KH, KW, sh, sw, ph, pw, tm, false)) return rc;
     return walk(B, H, W, KH, KW, sh, sw, ph, pw, 128, true);
 }
