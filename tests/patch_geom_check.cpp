@@ -7,6 +7,8 @@
 #include <stdio.h>
 #include <stdlib.h>
 
+#include <initializer_list>
+
 #include "../paper_2105_11010_amd/csrc/sparq_patch_geom.h"
 
 using namespace sparq;
