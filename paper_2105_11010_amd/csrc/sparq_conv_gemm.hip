@@ -287,14 +287,27 @@ bool fit_wide(const ConvGeom& g, bool bytes) { return one_tap(g, bytes) && g.Cq 
 // With 449 to 512 channels the activations fit in registers, and that form is ahead once there are many rounds of
 // tiles; in one well-filled round (196 tiles: 12544 x 512 -> 512 14.1 against 11.9 us), or two for bytes, this one is.
 // The 512-wide tile costs about 1.35 times the 256-wide one's round and does twice the work.
+// With tiles for less than half the CUs the tile kernels' narrower tiles use more of the chip, unless a long reduction is trimmed
+// (3123 timed layers, 8 to 1200 tiles of 128 x 256: the kernels it replaced are 1.1-1.3 x faster up to 64 tiles below 1024 channels, up to 1.48 x
+// faster where nothing is trimmed -- 867 x 4336 -> 960, untrimmed, 21 against 30 us; 0.89-0.94 x at 1024 channels and more with a trim).  Without
+// a trim there is less to share out, so neither up to 128 outputs (18828 x 4608 -> 128 bytes 23 against 34) nor where more than a fifth of
+// the columns are padding and the rounds are not full (9408 x 2688 -> 288 bytes 18 against 23); with one, such padding needs 640
+// channels (9218 x 576 -> 272 bytes 10.2 against 12.0).  With these lines 23 of the 3123 are more than 6 % slower than the kernels it replaced, before 563.
 // forced: by the tuning hook, only the tile is chosen.
-const WideVariant* pick_wide(const ConvGeom& g, bool bytes, bool forced = false) {
+const WideVariant* pick_wide(const ConvGeom& g, bool bytes, bool plain, bool forced = false) {
     if (!fit_wide(g, bytes)) return nullptr;
     if (!forced && (g.Cq < 512 || g.N <= 96 || (g.N <= 128 && g.M >= 32 * 1024))) return nullptr;
     const int64_t cus = device_cu_count(), tiles_m = (g.M + 127) / 128;
     const int64_t t512 = tiles_m * ((g.N + 511) / 512), t256 = tiles_m * ((g.N + 255) / 256);
     const int64_t r512 = (t512 + cus - 1) / cus, r256 = (t256 + cus - 1) / cus;
     const bool wider = g.N > 256 && r512 * 27 <= r256 * 20 && round_up(g.N, 512) <= g.Np;
+    if (!forced) {
+        const bool half = t256 * 2 >= cus, padded = round_up(g.N, 256) * 4 > (int64_t)g.N * 5;
+        if (plain ? !half || g.N <= 128 || (padded && !wider && t256 * 4 < r256 * cus * 3)
+                  : padded && g.Cq < 704 ? t256 <= cus
+                                         : !half && (g.Cq < 1024 || (bytes && t256 * 4 < cus)))
+            return nullptr;
+    }
     if (g.Cq == 512 && !forced) {
         const bool fills = wider ? bytes && r512 <= 2 && t512 * 10 >= r512 * cus * 7 : r256 == 1 && t256 * 8 >= cus * 3;
         if (!fills || round_up(g.N, wider ? 512 : 256) * 4 > (int64_t)g.N * 5) return nullptr;     // (or pads N by over a quarter)
@@ -346,9 +359,10 @@ struct ConvPlan {
 
 // forms: the forms other than the two tile kernels may be taken (never for 2:4 pruned weights; where the tuning hook asks for
 // a tile kernel, no rule takes them; where it asks for one of them, that one wherever the layer fits it).
-// bytes: requantised results.
-ConvPlan make_plan(const ConvGeom& g, const Tuning& tune, bool forms = true, bool bytes = false) {
+// bytes: requantised results.  trims: the layer's mode trims (its size queries and descriptors without one do not care).
+ConvPlan make_plan(const ConvGeom& g, const Tuning& tune, bool forms = true, bool bytes = false, bool trims = true) {
     ConvPlan pl;
+    const bool plain = !trims || g.Cp != g.C;                    // the kernel itself does not trim (a padded copy is trimmed already)
     if (g.fold) {               // at most 4 channels: 4-channel padded copy, pixel-folded, gather kernel
         pl.pad_bytes = (size_t)round_up((int64_t)g.B * g.H * g.W * 4, 256);
         return pl;
@@ -361,14 +375,14 @@ ConvPlan make_plan(const ConvGeom& g, const Tuning& tune, bool forms = true, boo
     if (forms && tune.form) {
         if (tune.form == kTunedRows && (pl.rows = fit_rows(gk, bytes)) != nullptr && !rows_launchable(*pl.rows, gk, bytes)) pl.rows = nullptr;
         if (tune.form == kTunedSplit && (pl.split = fit_split(gk, &pl.pg, &pl.npix)) != nullptr) return pl;
-        if (tune.form == kTunedWide) pl.wide = pick_wide(gk, bytes, true);
+        if (tune.form == kTunedWide) pl.wide = pick_wide(gk, bytes, plain, true);
     }
     if (rules) {
         // (up to 256 channels the registers form is ahead of the split form at every size, beyond that behind it:
         // 256 -> 256, 784 pixels 5.3 against 5.7 us; 512 -> 256 7.9 against 6.0)
         pl.rows = pick_rows(gk, bytes);
         if ((!pl.rows || g.K > 256) && (pl.split = pick_split(gk, &pl.pg, &pl.npix)) != nullptr) return pl;
-        pl.wide = pick_wide(gk, bytes);
+        pl.wide = pick_wide(gk, bytes, plain);
     }
     if (!force_gather && (force_patch || !prefer_gather(g)) && plan_patch(gk, &pl.pg, &pl.npix, &pl.ac, &pl.cbs)) {
         pl.variant = pick_patch(g, tune, pl.ac, pl.cbs, pl.npix, force_patch, &pl.ws);
@@ -466,12 +480,13 @@ sparq_status plan_text(const sparq_conv_desc* desc, const sparq_mode* mode, char
     ConvGeom g;
     if (!text || text_bytes == 0 || !conv_geom(desc, &g) || !mode_valid(mode)) return SPARQ_EINVAL;
     const Tuning tune = current_tuning();
-    const ConvPlan pl = make_plan(g, tune, forms);
+    const bool trims = mode->window_bits != 8;
+    const ConvPlan pl = make_plan(g, tune, forms, false, trims);
     const PlanForm form = plan_form(g, pl, false);
     const char* copy = pl.pad_bytes ? " padded_copy" : "";
     char u8[64] = "";
     if (u8_too) {
-        const ConvPlan p8 = make_plan(g, tune, forms, true);
+        const ConvPlan p8 = make_plan(g, tune, forms, true, trims);
         const PlanForm f8 = plan_form(g, p8, true);
         const char* tile = f8 == kFormWide ? p8.wide->name : f8 == kFormSplit ? p8.split->name : f8 == kFormGather ? gather_tile_name(g, tune, true) : nullptr;
         snprintf(u8, sizeof(u8), " u8_kernel=%s%s%s", kFormKernels[f8], tile ? ":" : "", tile ? tile : "");
@@ -534,7 +549,7 @@ sparq_status conv_launch(const uint8_t* x, const void* packed_w, const sparq_con
         return SPARQ_EINVAL;
     hipStream_t s = static_cast<hipStream_t>(stream);
     const Tuning tune = current_tuning();
-    const ConvPlan pl = make_plan(g, tune, sp == nullptr, y != nullptr);
+    const ConvPlan pl = make_plan(g, tune, sp == nullptr, y != nullptr, mode->window_bits != 8);
     const size_t need = pl.pad_bytes;
     if (need) {
         if (!workspace || !aligned(workspace, 256)) return SPARQ_EINVAL;

@@ -330,7 +330,8 @@ WIDE_SHAPES = [
 
 @pytest.mark.parametrize("tile,layer", WIDE_SHAPES, ids=lambda v: v if isinstance(v, str) else v.name)
 @pytest.mark.parametrize("mode", [S.Mode(4, S.OPT5, 1, 1), S.Mode(3, S.OPT6_3B, 0, 1), S.PLAIN8], ids=lambda m: m.label)
-def test_conv_eight_wavefronts(sq, oracle, tile, layer, mode):
+def test_conv_eight_wavefronts(sq, oracle, tuning, tile, layer, mode):
+    tuning("form=wide")                    # (the rules give some of these to the tile kernels: few tiles, mostly padding)
     d = sq.conv_desc(layer.B, layer.H, layer.W, layer.C, layer.N, layer.KH, layer.KW, layer.stride, layer.pad)
     assert f"tile={tile} eight_wavefronts" in sq.sparq_conv_plan(d, sq.mode(*mode.astuple()))
     check_layer(sq, oracle, layer, mode, seed_cfg=8)

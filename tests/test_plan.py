@@ -94,6 +94,28 @@ def test_plan_names_the_kernel_of_either_result(lib, shape, kernel, u8_kernel):
     assert words(text, "kernel=") == [kernel] and words(text, "u8_kernel=") == [u8_kernel], text
 
 
+M45, PLAIN = S.Mode(4, S.OPT5, 1, 1), S.PLAIN8
+
+
+@pytest.mark.parametrize("form,shape,mode,takes", [
+    # eight wavefronts: tiles for less than half the CUs, untrimmed layers of few outputs or half-empty rounds, mostly padding
+    ("wide", (1, 867, 1, 4336, 960, 1, 0), PLAIN, (False, False)), ("wide", (1, 12544, 1, 4432, 128, 1, 0), PLAIN, (False, False)),
+    ("wide", (1, 2000, 1, 832, 816, 1, 0), M45, (False, False)), ("wide", (1, 1500, 1, 1040, 816, 1, 0), M45, (True, False)),
+    ("wide", (1, 2500, 1, 1040, 816, 1, 0), M45, (True, True)), ("wide", (1, 9408, 1, 2688, 288, 1, 0), PLAIN, (False, False)),
+    ("wide", (1, 9408, 1, 2688, 288, 1, 0), M45, (True, True)), ("wide", (1, 9218, 1, 576, 272, 1, 0), M45, (False, False)),
+    ("wide", (1, 65536, 1, 4608, 512, 1, 0), PLAIN, (True, True)), ("wide", (2, 33, 33, 4336, 960, 1, 0), M45, (True, True)),
+    ("wide", (2, 33, 33, 4337, 960, 1, 0), M45, (False, False)),                     # an odd channel count: the padded copy is trimmed already
+], ids=str)
+def test_rules_leave_layers_to_the_tile_kernels(lib, form, shape, mode, takes):
+    """Both sides of the lines at which a form stops being ahead of the tile kernels; takes: (four-byte results, bytes)."""
+    B, H, W, C, N, k, pad = shape
+    kh, kw = k if isinstance(k, tuple) else (k, k)
+    text = plan(lib, S.ConvLayer("p", B, H, W, C, N, kh, kw, (1, 1), pad if isinstance(pad, tuple) else (pad, pad)), mode)[0]
+    tiles = ("conv_patch_kernel", "conv_gemm_kernel")
+    for got, want in ((words(text, "kernel=")[0], takes[0]), (words(text, "u8_kernel=")[0].split(":")[0], takes[1])):
+        assert got == f"conv_{form}_kernel" if want else got in tiles, text
+
+
 def test_tuning_hook_forces_and_clears_the_choice(lib):
     """sparq_set_tuning: the documented keys change the plan, NULL restores the rules, junk is refused and changes nothing."""
     conv = S.ConvLayer("conv3x3", 64, 32, 32, 512, 512, 3, 3, (1, 1), (1, 1), 0.5, S.Mode(4, S.OPT5, 1, 1))
