@@ -332,11 +332,21 @@ bool fit_block(const ConvGeom& g, bool bytes, PatchGeom* pg, int* npix) {
 //   or a patch too large for the tile kernel's staging, which the gather kernel would trim once per tap, if they have 15 taps
 //   and more or few channels on either side (1.5-3 x: 56 x 56 x 64 -> 64 5x5, batch 32; 98 x 98 x 539 -> 128 3x3 67 against 78).
 // With fewer tiles, or more channels, the tile kernel's pipelining is ahead (14 x 14 x 256, batch 256: 35 against 44 us).
-bool pick_block(const ConvGeom& g, bool bytes, bool gather, PatchGeom* pg, int* npix) {
+// Its four-byte results leave in runs of 128 bytes, so rows off a 64-byte border are for the tile kernel beyond 64 outputs (112 x 112 x 48 ->
+// 86 1x3 19 against 38 us), and fewer than nine taps (seven up to 64 outputs) do not pay for them (1x3 40 x 40 x 48 -> 126 30 against 42); it trims
+// a patch once per 64 outputs, the tile kernel per 128 or 256, which decides where images are narrow (8 x 8 x 64 -> 160 fp32
+// 10.4 against 12.7; bytes beyond 128 outputs 12 x 12 x 48 -> 192 7x1 81 against 95) and with 113 to 128 channels beyond 64 outputs (35 x 35 x 128 -> 256
+// bytes 55 against 61; 14 x 14 x 128 -> 96 14 against 16; up to 128 outputs on rows of 28 pixels and more it stays 1.02-1.15 x ahead).  With
+// these lines 58 of 3002 timed layers are more than 6 % slower than on the tile kernels, before 217.
+bool pick_block(const ConvGeom& g, bool bytes, bool plain, bool gather, PatchGeom* pg, int* npix) {
     const int taps = g.KH * g.KW;
     if (taps == 1 || block_tiles(g.M, g.N) < 300) return false;
     gather = gather && (g.Cq == 64 || g.N <= 64 || taps >= 15) && g.Cq <= 256;
-    if (g.Cq > 128 && !gather) return false;
+    if (!gather) {
+        if (g.Cq > 128) return false;
+        if (!bytes && (g.N <= 64 ? taps < 7 : taps < 9 || g.N % 16 || (!plain && g.Wo <= 8))) return false;
+        if (bytes && !plain && (g.Cq == 64 ? g.N > 128 && g.Wo <= 14 : g.N > 128 || (g.N > 64 && (g.Wo < 28 || taps < 9)))) return false;
+    }
     // patch pixels of a tile that starts and ends anywhere in its rows (the largest one may cross two images)
     const bool small = ((int64_t)BlockCfg::kTM + (int64_t)g.KH * g.Wo) * ((int64_t)(g.Wo - 1) * g.sw + g.KW) < 450ll * g.Wo;
     if (!gather && !(g.Cq == 64 ? g.N <= 64 || small : small && bytes && g.C > 112)) return false;
@@ -388,7 +398,7 @@ ConvPlan make_plan(const ConvGeom& g, const Tuning& tune, bool forms = true, boo
         pl.variant = pick_patch(g, tune, pl.ac, pl.cbs, pl.npix, force_patch, &pl.ws);
         pl.patch = pl.variant != nullptr;
     }
-    if (rules) pl.block = pick_block(gk, bytes, !pl.patch, &pl.pg, &pl.npix);
+    if (rules) pl.block = pick_block(gk, bytes, plain, !pl.patch, &pl.pg, &pl.npix);
     else if (forms && tune.form == kTunedBlock) pl.block = fit_block(gk, bytes, &pl.pg, &pl.npix);
     return pl;
 }

@@ -105,6 +105,13 @@ M45, PLAIN = S.Mode(4, S.OPT5, 1, 1), S.PLAIN8
     ("wide", (1, 9408, 1, 2688, 288, 1, 0), M45, (True, True)), ("wide", (1, 9218, 1, 576, 272, 1, 0), M45, (False, False)),
     ("wide", (1, 65536, 1, 4608, 512, 1, 0), PLAIN, (True, True)), ("wide", (2, 33, 33, 4336, 960, 1, 0), M45, (True, True)),
     ("wide", (2, 33, 33, 4337, 960, 1, 0), M45, (False, False)),                     # an odd channel count: the padded copy is trimmed already
+    # small workgroups: rows off a 64-byte border, few taps, narrow images, more than 64 outputs at 113 to 128 channels
+    ("block", (56, 56, 56, 48, 86, 3, 1), M45, (False, False)), ("block", (56, 56, 56, 48, 96, 3, 1), M45, (True, True)),
+    ("block", (72, 40, 40, 48, 80, (1, 3), (0, 1)), M45, (False, True)), ("block", (72, 40, 40, 48, 48, (1, 3), (0, 1)), M45, (False, True)),
+    ("block", (72, 40, 40, 48, 48, (1, 7), (0, 3)), M45, (True, True)), ("block", (409, 8, 8, 64, 160, 3, 1), M45, (False, False)),
+    ("block", (409, 8, 8, 64, 160, 3, 1), PLAIN, (True, True)), ("block", (400, 12, 12, 48, 192, 3, 1), M45, (True, False)),
+    ("block", (128, 35, 35, 128, 256, 3, 1), M45, (False, False)), ("block", (128, 35, 35, 128, 256, 3, 1), PLAIN, (False, True)),
+    ("block", (256, 14, 14, 128, 96, 3, 1), M45, (False, False)), ("block", (256, 28, 28, 128, 128, 3, 1), M45, (False, True)),
 ], ids=str)
 def test_rules_leave_layers_to_the_tile_kernels(lib, form, shape, mode, takes):
     """Both sides of the lines at which a form stops being ahead of the tile kernels; takes: (four-byte results, bytes)."""
@@ -184,7 +191,7 @@ def test_small_workgroups_only_where_they_can_be_launched(lib):
     for the kernels that still take it (the call would otherwise return "unsupported")."""
     mode = S.Mode(4, S.OPT5, 1, 1)
     for n, small in (((1 << 21) - 64, True), (1 << 21, False)):
-        for layer in (S.ConvLayer("n_3x3", 1, 8, 8, 64, n, 3, 3, (1, 1), (1, 1)), S.ConvLayer("n_1x3", 1, 1, 16, 64, n, 1, 3, (1, 1), (0, 1))):
+        for layer in (S.ConvLayer("n_3x3", 1, 16, 16, 64, n, 3, 3, (1, 1), (1, 1)), S.ConvLayer("n_1x9", 1, 1, 16, 64, n, 1, 9, (1, 1), (0, 4))):
             text = plan(lib, layer, mode)[0]
             assert ("small_workgroups" in text) == small, text
 
