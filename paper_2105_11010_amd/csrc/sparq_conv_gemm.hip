@@ -265,12 +265,16 @@ const RowsVariant* fit_rows(const ConvGeom& g, bool bytes) {
 // Activations in registers: 1x1 layers without padding.  `bytes`: requantised results.
 // Up to 512 channels it beats the tile kernels nearly everywhere, by 1.1-1.6 x on small tensors and up to 2.2 x on large ones
 // (256 -> 64 channels, 802816 pixels 80 -> 69 us; 64 -> 256 bytes 106 -> 58; 128 -> 512 bytes 60 -> 35), except where four-byte
-// results larger than the last-level cache leave in rows of 1 KB or more (64 -> 256, 802816 pixels: 154 against 170 us: the
-// tile kernels write whole rows at a time).  (Holding 768 or 1024 channels was built too: behind the form below.)
-const RowsVariant* pick_rows(const ConvGeom& g, bool bytes) {
-    if (!bytes && g.N >= 256 && g.M * g.N * 4 >= kStreamedBytes) return nullptr;
+// results beyond the last-level cache leave in rows of 400 bytes or more (64 -> 256, 802816 pixels: 154 against 170 us: the
+// tile kernels write whole rows at a time).  Where little arithmetic stands beside the stores -- up to 192 channels, 256 without a
+// trim -- that begins at half its size (128 -> 448, 144611 pixels, 247 MiB 49 against 57; 128 -> 560, 92466 pixels, untrimmed, 198 MiB
+// 48 against 54; 110 timed layers of more than 96 outputs between 128 and 256 MiB: 1.03 x of the tile kernels' time up to
+// that many channels, 0.84 x beyond).  (Holding 768 or 1024 channels was built too: behind the form below.)
+const RowsVariant* pick_rows(const ConvGeom& g, bool bytes, bool plain) {
+    if (!bytes && g.N > 96 && g.M * g.N * 4 >= (g.Cq <= (plain ? 256 : 192) ? kStreamedBytes / 2 : kStreamedBytes)) return nullptr;
     // (four-byte rows that start off a 64-byte border: its 128-byte runs are two partial lines each, the tile kernels' rows are
-    // not; 196 -> 948, 28187 pixels 57 against 85 us.  Up to 8 MiB the shorter chain is worth more.)
+    // not; 196 -> 948, 28187 pixels 57 against 85 us.  Up to 8 MiB the shorter chain is worth more: 1.0-1.5 x faster at 2 to 8 MiB over 75
+    // layers of 64 to 512 channels, between 1.6 x faster and 1.3 x slower at 12 to 16, 1.1-2.2 x slower at 32 to 64.)
     if (!bytes && g.N % 16 != 0 && g.M * g.N * 4 > (8 << 20)) return nullptr;
     return fit_rows(g, bytes);
 }
@@ -390,7 +394,7 @@ ConvPlan make_plan(const ConvGeom& g, const Tuning& tune, bool forms = true, boo
     if (rules) {
         // (up to 256 channels the registers form is ahead of the split form at every size, beyond that behind it:
         // 256 -> 256, 784 pixels 5.3 against 5.7 us; 512 -> 256 7.9 against 6.0)
-        pl.rows = pick_rows(gk, bytes);
+        pl.rows = pick_rows(gk, bytes, plain);
         if ((!pl.rows || g.K > 256) && (pl.split = pick_split(gk, &pl.pg, &pl.npix)) != nullptr) return pl;
         pl.wide = pick_wide(gk, bytes, plain);
     }

@@ -112,6 +112,10 @@ M45, PLAIN = S.Mode(4, S.OPT5, 1, 1), S.PLAIN8
     ("block", (409, 8, 8, 64, 160, 3, 1), PLAIN, (True, True)), ("block", (400, 12, 12, 48, 192, 3, 1), M45, (True, False)),
     ("block", (128, 35, 35, 128, 256, 3, 1), M45, (False, False)), ("block", (128, 35, 35, 128, 256, 3, 1), PLAIN, (False, True)),
     ("block", (256, 14, 14, 128, 96, 3, 1), M45, (False, False)), ("block", (256, 28, 28, 128, 128, 3, 1), M45, (False, True)),
+    # activations in registers: four-byte results of half the last-level cache and more beside little arithmetic
+    ("rows", (1, 144611, 1, 128, 448, 1, 0), M45, (False, True)), ("rows", (1, 144611, 1, 256, 448, 1, 0), M45, (True, True)),
+    ("rows", (1, 144611, 1, 256, 448, 1, 0), PLAIN, (False, True)), ("rows", (1, 70000, 1, 128, 448, 1, 0), M45, (True, True)),
+    ("rows", (1, 802816, 1, 256, 64, 1, 0), M45, (True, True)), ("rows", (1, 802816, 1, 256, 128, 1, 0), M45, (False, True)),
 ], ids=str)
 def test_rules_leave_layers_to_the_tile_kernels(lib, form, shape, mode, takes):
     """Both sides of the lines at which a form stops being ahead of the tile kernels; takes: (four-byte results, bytes)."""
