@@ -260,13 +260,25 @@ sparq_status launch_trim_pad(const uint8_t* x, uint8_t* xp, int64_t pixels, int 
 // 2:4 pruned weights with vSPARQ on: the expanded channels of C (sparq_sparse24.hip).  Blocked: the order the sparse
 // form of the input-patch kernel expands by itself; a fifth of padding costs less there than the expanded tensor does.
 inline bool sparse24_blocked(int C) { return C % 16 == 0 && round_up(C, 64) * 5 <= (int64_t)C * 6; }
-inline int64_t sparse24_channels(int C) { return sparse24_blocked(C) ? 3 * round_up(C, 64) : round_up(3 * (int64_t)C, 16); }
+// One tap: filled up with zero channels to whole 256- or 128-channel units of the input-patch kernel if that adds no more than a
+// twelfth -- 27 single blocks of a 576-channel layer cost 27 barriers, 28 in units of four cost seven (49 pixels 16.7 -> 13.3 us) -- or
+// a 24th where units of two fit already (640 channels, 12544 pixels: 29.0 against 30.2 filled up).  (Filling 64 or 128 channels
+// up by a third as well: 12544 pixels 10 to 18 % slower.)
+inline int64_t sparse24_channels(int C, int taps) {
+    const int64_t used = sparse24_blocked(C) ? 3 * round_up(C, 64) : 3 * (int64_t)C;
+    if (taps == 1)
+        for (int unit : {256, 128}) {
+            const int64_t more = round_up(used, unit) - used;
+            if (used + more <= 4 * (int64_t)C && more * (used % 128 ? 12 : 24) <= used) return used + more;
+        }
+    return round_up(used, 16);
+}
 
-// Implemented in sparq_sparse24.hip: the expanded activation tensor and the dense (expand: sparse24_channels(C) per
-// row of C, else C) form of 2:4 compressed weights, rows = output channels x taps.
-sparq_status launch_sparse24_expand_act(const uint8_t* x, uint8_t* xe, int64_t pixels, int C, const sparq_mode* mode,
+// Implemented in sparq_sparse24.hip: the expanded activation tensor (Ce = sparse24_channels) and the dense form of 2:4
+// compressed weights (rows of Ce channels; Ce == C: decompressed only), rows = output channels x taps.
+sparq_status launch_sparse24_expand_act(const uint8_t* x, uint8_t* xe, int64_t pixels, int C, int Ce, const sparq_mode* mode,
                                         hipStream_t stream);
-sparq_status launch_sparse24_expand_weights(const int8_t* vals, const uint8_t* idx, int8_t* dense, int64_t rows, int C, bool expand,
+sparq_status launch_sparse24_expand_weights(const int8_t* vals, const uint8_t* idx, int8_t* dense, int64_t rows, int C, int Ce,
                                             hipStream_t stream);
 // ... and the operands of the sparse matrix instruction (16 kept bytes + one word of positions per 32 reduction
 // indices) from dense weights [N][taps][C] with at most two non-zeros per aligned group of four channels.

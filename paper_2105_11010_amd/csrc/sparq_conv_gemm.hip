@@ -865,7 +865,7 @@ bool sparse24_bound(const sparq_conv_desc* desc, const sparq_mode* mode, sparq_c
 bool sparse24_geometry(const sparq_conv_desc* desc, const sparq_mode* mode, sparq_conv_desc* eff, bool* expand) {
     ConvGeom g;
     if (!sparse24_bound(desc, mode, eff, expand)) return false;
-    if (*expand) eff->C = (int)sparse24_channels(desc->C);
+    if (*expand) eff->C = (int)sparse24_channels(desc->C, desc->KH * desc->KW);
     return conv_geom(eff, &g);
 }
 const sparq_mode kNoPairPlain = {8, 1, 0, 0};
@@ -911,7 +911,7 @@ extern "C" sparq_status sparq_pack_weights_sparse24(const int8_t* w_vals, const 
     if (packed_bytes < sparq_sparse24_packed_bytes(desc, mode)) return SPARQ_EWORKSPACE;
     const Sparse24Layout L = sparse24_layout(eff);
     int8_t* dense = static_cast<int8_t*>(packed) + L.tiles;
-    sparq_status st = launch_sparse24_expand_weights(w_vals, w_idx, dense, (int64_t)desc->N * desc->KH * desc->KW, desc->C, expand,
+    sparq_status st = launch_sparse24_expand_weights(w_vals, w_idx, dense, (int64_t)desc->N * desc->KH * desc->KW, desc->C, eff.C,
                                                      static_cast<hipStream_t>(stream));
     if (st != SPARQ_OK) return st;
     st = sparq_pack_weights(dense, &eff, packed, L.tiles, stream);
@@ -961,7 +961,7 @@ extern "C" sparq_status sparq_conv_gemm_sparse24(const uint8_t* x, const void* p
     }
     const size_t x_room = (size_t)round_up(pixels * eff.C, 256);
     uint8_t* xe = static_cast<uint8_t*>(workspace);
-    const sparq_status st = launch_sparse24_expand_act(x, xe, pixels, desc->C, mode, static_cast<hipStream_t>(stream));
+    const sparq_status st = launch_sparse24_expand_act(x, xe, pixels, desc->C, eff.C, mode, static_cast<hipStream_t>(stream));
     if (st != SPARQ_OK) return st;
     return conv_launch(xe, packed, &eff, &kNoPairPlain, acc, scale, out, nullptr, nullptr, xe + x_room,
                        workspace_bytes - x_room, stream, sp);

@@ -18,7 +18,8 @@
 // Blocked order (sparse24_blocked: C a multiple of 16 that wastes at most a fifth on whole 64-channel blocks): a block
 // of 64 channels becomes three blocks of 64, all its G_0, all its G_1, all its G_2.  Then the SP kernel's staging
 // wavefronts read the tensor itself and trim each block three times, in three byte orders, and no expanded tensor is
-// written at all.  Otherwise the three words of a group follow each other and the pixel is padded to 16 channels.
+// written at all.  Otherwise the three words of a group follow each other.  Zero channels fill the pixel up to a multiple
+// of 16, of 1x1 layers to whole units of the input-patch kernel (sparse24_channels).
 // With vSPARQ off (or a plain 8-bit layer) nothing depends on the partner: the problem is the layer itself.
 #include "sparq_common.h"
 
@@ -52,8 +53,7 @@ __global__ __launch_bounds__(kSpThreads) void expand_act_kernel(const uint32_t* 
 #pragma unroll
         for (int j = 0; j < 3; ++j)
             dst[expanded_word(grp, j, blocked != 0)] = trim4_any(perm(0, v, sparse24_pair_order(j)), L, round_nearest != 0, true);
-        if (!blocked && grp == groups_out - 1)
-            for (int k = 3 * groups_out; k < words_out; ++k) dst[k] = 0u;
+        for (int k = 3 * groups_out + grp; k < words_out; k += groups_out) dst[k] = 0u;       // channels that fill the pixel up
     }
 }
 
@@ -83,8 +83,7 @@ __global__ __launch_bounds__(kSpThreads) void expand_weights_kernel(const int8_t
             const uint32_t o = (w0 << (8 * ((place >> (4 * i0)) & 3))) | (w1 << (8 * ((place >> (4 * i1)) & 3)));
 #pragma unroll
             for (int j = 0; j < 3; ++j) dst[expanded_word(grp, j, blocked != 0)] = j == word ? o : 0u;
-            if (!blocked && grp == groups_out - 1)
-                for (int k = 3 * groups_out; k < words_out; ++k) dst[k] = 0u;
+            for (int k = 3 * groups_out + grp; k < words_out; k += groups_out) dst[k] = 0u;
         } else {
             dense[i] = (w0 << (8 * i0)) | (w1 << (8 * i1));
         }
@@ -142,20 +141,21 @@ sparq_status launch_sparse24_pack_operand(const int8_t* dense, uint8_t* vals, ui
     return launch_status();
 }
 
-sparq_status launch_sparse24_expand_act(const uint8_t* x, uint8_t* xe, int64_t pixels, int C, const sparq_mode* mode,
+sparq_status launch_sparse24_expand_act(const uint8_t* x, uint8_t* xe, int64_t pixels, int C, int Ce, const sparq_mode* mode,
                                         hipStream_t s) {
     const bool blocked = sparse24_blocked(C);
     const int groups_out = blocked ? (int)round_up(C, 64) / 4 : C / 4;
     const int64_t items = pixels * groups_out;
     if (items == 0) return SPARQ_OK;
     expand_act_kernel<<<sp_grid(items), kSpThreads, 0, s>>>(reinterpret_cast<const uint32_t*>(x), reinterpret_cast<uint32_t*>(xe), items,
-                                                           C / 4, groups_out, (int)(sparse24_channels(C) / 4), blocked ? 1 : 0,
+                                                           C / 4, groups_out, Ce / 4, blocked ? 1 : 0,
                                                            make_luts(mode->window_bits, mode->shift_mask), mode->round_nearest);
     return launch_status();
 }
 
-sparq_status launch_sparse24_expand_weights(const int8_t* vals, const uint8_t* idx, int8_t* dense, int64_t rows, int C, bool expand,
+sparq_status launch_sparse24_expand_weights(const int8_t* vals, const uint8_t* idx, int8_t* dense, int64_t rows, int C, int Ce,
                                             hipStream_t s) {
+    const bool expand = Ce != C;                             // (at least three expanded channels per channel)
     const bool blocked = expand && sparse24_blocked(C);
     const int groups_out = blocked ? (int)round_up(C, 64) / 4 : C / 4;
     const int64_t items = rows * groups_out;
@@ -163,7 +163,7 @@ sparq_status launch_sparse24_expand_weights(const int8_t* vals, const uint8_t* i
     uint32_t* d = reinterpret_cast<uint32_t*>(dense);
     if (expand)
         expand_weights_kernel<true><<<sp_grid(items), kSpThreads, 0, s>>>(vals, idx, d, items, C / 4, groups_out,
-                                                                         (int)(sparse24_channels(C) / 4), blocked ? 1 : 0);
+                                                                         Ce / 4, blocked ? 1 : 0);
     else
         expand_weights_kernel<false><<<sp_grid(items), kSpThreads, 0, s>>>(vals, idx, d, items, C / 4, groups_out, C / 4, 0);
     return launch_status();

@@ -146,9 +146,11 @@ STAGING_LAYERS = [
     (128, S.ConvLayer("blk_1x1_112_70_round3", 1, 1, 1, 112, 70, 1, 1, (1, 1), (0, 0), 0.3, S.Mode(3, S.OPT6_3B, 1, 1))),
     (256, S.ConvLayer("blk_1x1_256_136", 2, 4, 4, 256, 136, 1, 1, (1, 1), (0, 0), 0.5, M45)),
     (256, S.ConvLayer("blk_1x1s2_240_300_2bit", 1, 9, 9, 240, 300, 1, 1, (2, 2), (0, 0), 0.5, S.Mode(2, S.OPT7_2B, 0, 1))),
+    (256, S.ConvLayer("blk_1x1_576_40", 1, 3, 9, 576, 40, 1, 1, (1, 1), (0, 0), 0.5, M45)),         # 27 blocks and one of zeros
     (256, S.ConvLayer("blk_1x1_512_64_floor", 1, 31, 1, 512, 64, 1, 1, (1, 1), (0, 0), 0.4, S.Mode(4, S.OPT2, 0, 1))),
 ]
 WRITTEN_LAYERS = [
+    S.ConvLayer("blk_1x1_576_70", 1, 9, 11, 576, 70, 1, 1, (1, 1), (0, 0), 0.5, M45),           # 27 blocks and one of zeros
     S.ConvLayer("blk_1x1_176_136", 2, 15, 15, 176, 136, 1, 1, (1, 1), (0, 0), 0.5, S.Mode(4, S.OPT3, 0, 1)),
     S.ConvLayer("blk_1x1_256_70", 2, 15, 15, 256, 70, 1, 1, (1, 1), (0, 0), 0.4, S.Mode(3, S.OPT6_3B, 1, 1)),
     S.ConvLayer("blk_1x1s2_128_300", 2, 15, 15, 128, 300, 1, 1, (2, 2), (0, 0), 0.5, S.Mode(2, S.OPT7_2B, 0, 1)),

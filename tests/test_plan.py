@@ -269,3 +269,12 @@ def test_sparse24_plan_says_where_the_expansion_happens(lib):
         assert ("expanded_while_staging" in text) == staging and text.endswith("sparse_mfma"), text
     for m in (Mode(4, 0x1F, 0, 0), Mode(8, 1, 0, 0)):
         assert "expanded" not in sparse_plan(lib, Desc(2, 13, 11, 176, 100, 3, 3, 1, 1, 1, 1), m)
+
+
+def test_one_tap_sparse24_layers_take_whole_units(lib):
+    """Expanded 1x1 layers are filled up with zero channels to units of four or two 64-channel blocks where that adds little: their
+    number of blocks is a multiple of three, and a unit of one costs a barrier per block."""
+    lib.sparq_sparse24_packed_bytes.restype = ctypes.c_size_t
+    for c, unit in ((64, 64), (96, 64), (128, 128), (192, 64), (256, 256), (320, 256), (448, 128), (640, 128), (576, 256), (832, 256), (1216, 256)):
+        text = sparse_plan(lib, Desc(1, 14, 14, c, 256, 1, 1, 1, 1, 0, 0), Mode(4, 0x1F, 1, 1))
+        assert f"unit_channels={unit} " in text and text.endswith("sparse_mfma"), (c, text)
