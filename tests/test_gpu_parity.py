@@ -120,6 +120,30 @@ def test_trim_odd_rows_as_one_stream(sq, oracle, C, mode):
         assert np.all(got[rows * C:] == 77), "bytes past the tensor were written"
 
 
+@pytest.mark.parametrize("C", [35, 36, 7, 16])
+@pytest.mark.parametrize("mode", [S.Mode(4, S.OPT5, 1, 1), S.Mode(4, S.OPT3, 0, 0)], ids=lambda m: m.label)
+def test_trim_is_one_launch(sq, oracle, C, mode):
+    """Also where the tensor ends inside a 16-byte word: captured calls hold one node, and replays give the oracle's bytes."""
+    import ctypes
+    x = S.gen_activations((333, C), 0.5, S.rng_for(8, 240 + C))
+    m = sq.mode(*mode.astuple())
+    xd = dev(x)
+    y = torch.zeros_like(xd)
+    sq.sparq_trim(xd, y, m)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph(keep_graph=True)
+    with torch.cuda.graph(graph):
+        sq.sparq_trim(xd, y, m)
+    nodes = ctypes.c_size_t(0)
+    assert sq.lib.hipGraphGetNodes(ctypes.c_void_p(graph.raw_cuda_graph()), None, ctypes.byref(nodes)) == 0
+    assert nodes.value == 1
+    for _ in range(2):
+        y.zero_()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert np.array_equal(y.cpu().numpy(), oracle.trim(x, **mode.kwargs()))
+
+
 # ------------------------------------------------------------- dequant ------
 
 @pytest.mark.parametrize("M,N", [(1, 1), (37, 19), (513, 64), (1000, 160)])
