@@ -260,13 +260,14 @@ sparq_status launch_trim_pad(const uint8_t* x, uint8_t* xp, int64_t pixels, int 
 // 2:4 pruned weights with vSPARQ on: the expanded channels of C (sparq_sparse24.hip).  Blocked: the order the sparse
 // form of the input-patch kernel expands by itself; a fifth of padding costs less there than the expanded tensor does.
 inline bool sparse24_blocked(int C) { return C % 16 == 0 && round_up(C, 64) * 5 <= (int64_t)C * 6; }
-// One tap: filled up with zero channels to whole 256- or 128-channel units of the input-patch kernel if that adds no more than a
-// twelfth -- 27 single blocks of a 576-channel layer cost 27 barriers, 28 in units of four cost seven (49 pixels 16.7 -> 13.3 us) -- or
-// a 24th where units of two fit already (640 channels, 12544 pixels: 29.0 against 30.2 filled up).  (Filling 64 or 128 channels
-// up by a third as well: 12544 pixels 10 to 18 % slower.)
-inline int64_t sparse24_channels(int C, int taps) {
+// One tap and pixels (M of them) for one round of tiles at most: filled up with zero channels to whole 256- or 128-channel units of
+// the input-patch kernel if that adds no more than a twelfth -- 27 single blocks of a 576-channel layer cost 27 barriers, 28 in units of
+// four cost seven (49 pixels 16.7 -> 13.3 us) -- or a 24th where units of two fit already (640 channels, 12544 pixels: 29.0 against
+// 30.2 filled up).  (Filling 64 or 128 channels up by a third as well: 12544 pixels 10 to 18 % slower; with several rounds of tiles
+// single blocks leave LDS for two workgroups per CU: 1216 channels, 50176 pixels 95 against 111.)
+inline int64_t sparse24_channels(int C, int taps, int64_t M) {
     const int64_t used = sparse24_blocked(C) ? 3 * round_up(C, 64) : 3 * (int64_t)C;
-    if (taps == 1)
+    if (taps == 1 && M <= 32 * 1024)
         for (int unit : {256, 128}) {
             const int64_t more = round_up(used, unit) - used;
             if (used + more <= 4 * (int64_t)C && more * (used % 128 ? 12 : 24) <= used) return used + more;

@@ -864,8 +864,8 @@ bool sparse24_bound(const sparq_conv_desc* desc, const sparq_mode* mode, sparq_c
 // The dense problem that is actually contracted: with vSPARQ on, 12 expanded channels per group of four.
 bool sparse24_geometry(const sparq_conv_desc* desc, const sparq_mode* mode, sparq_conv_desc* eff, bool* expand) {
     ConvGeom g;
-    if (!sparse24_bound(desc, mode, eff, expand)) return false;
-    if (*expand) eff->C = (int)sparse24_channels(desc->C, desc->KH * desc->KW);
+    if (!sparse24_bound(desc, mode, eff, expand) || !conv_geom(eff, &g)) return false;
+    if (*expand) eff->C = (int)sparse24_channels(desc->C, desc->KH * desc->KW, g.M);
     return conv_geom(eff, &g);
 }
 const sparq_mode kNoPairPlain = {8, 1, 0, 0};
