@@ -133,8 +133,8 @@ bool patch_geom_for(const ConvGeom& g, int tm, PatchGeom* pg, int* npix) {
     return true;
 }
 
-// Fills `pg`, `npix`, and picks staging (chunks per lane, channel block); false: not eligible.
-bool plan_patch(const ConvGeom& g, PatchGeom* pg, int* npix, int* ac, int* cbs) {
+// Fills `pg`, `npix`, and picks staging (chunks per lane, channel block of at most 64 max_unit channels); false: not eligible.
+bool plan_patch(const ConvGeom& g, int max_unit, PatchGeom* pg, int* npix, int* ac, int* cbs) {
     PatchGeom q;
     int n;
     if (!patch_geom_for(g, kPatchTM, &q, &n)) return false;
@@ -145,7 +145,7 @@ bool plan_patch(const ConvGeom& g, PatchGeom* pg, int* npix, int* ac, int* cbs) 
     static const int cand[6][2] = {{8, 4}, {4, 2}, {2, 1}, {4, 1}, {8, 1}, {12, 1}};
     for (const auto& c : cand) {
         const int a = c[0], cb = c[1];
-        if (ksteps % cb) continue;
+        if (ksteps % cb || cb > max_unit) continue;
         if (n * 4 * cb > a * 256) continue;                      // patch does not fit the staging registers
         if (cb > 1 && taps > 1) continue;                        // multi-tap layers: 64-channel units
         const int as = a / 2, steps = taps * cb;
@@ -398,7 +398,10 @@ ConvPlan make_plan(const ConvGeom& g, const Tuning& tune, bool forms = true, boo
         if ((!pl.rows || g.K > 256) && (pl.split = pick_split(gk, &pl.pg, &pl.npix)) != nullptr) return pl;
         pl.wide = pick_wide(gk, bytes, plain);
     }
-    if (!force_gather && (force_patch || !prefer_gather(g)) && plan_patch(gk, &pl.pg, &pl.npix, &pl.ac, &pl.cbs)) {
+    // (units of four blocks and the sparse form's result rows leave LDS for one workgroup per CU, where narrow layers with more tiles
+    // than CUs want two: 72 -> 16, expanded to four blocks, 401408 pixels 63 against 54 us in units of two)
+    const int max_unit = !forms && g.N <= 64 && (g.M + kPatchTM - 1) / kPatchTM > device_cu_count() ? 2 : 4;
+    if (!force_gather && (force_patch || !prefer_gather(g)) && plan_patch(gk, max_unit, &pl.pg, &pl.npix, &pl.ac, &pl.cbs)) {
         pl.variant = pick_patch(g, tune, pl.ac, pl.cbs, pl.npix, force_patch, &pl.ws);
         pl.patch = pl.variant != nullptr;
     }

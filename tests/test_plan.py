@@ -278,6 +278,6 @@ def test_one_tap_sparse24_layers_take_whole_units(lib):
     for c, unit in ((64, 64), (96, 64), (128, 128), (192, 64), (256, 256), (320, 256), (448, 128), (640, 128), (576, 256), (832, 256), (1216, 256)):
         text = sparse_plan(lib, Desc(1, 14, 14, c, 256, 1, 1, 1, 1, 0, 0), Mode(4, 0x1F, 1, 1))
         assert f"unit_channels={unit} " in text and text.endswith("sparse_mfma"), (c, text)
-    for m, c, n, unit in ((32768, 576, 300, 256), (33000, 576, 300, 64)):
+    for m, c, n, unit in ((32768, 576, 300, 256), (33000, 576, 300, 64), (32768, 72, 16, 256), (33000, 72, 16, 128), (33000, 72, 80, 256)):
         text = sparse_plan(lib, Desc(1, m, 1, c, n, 1, 1, 1, 1, 0, 0), Mode(4, 0x1F, 1, 1))
         assert f"unit_channels={unit} " in text, (m, c, n, text)
