@@ -133,8 +133,7 @@ sparq_status sparq_conv_gemm(const uint8_t *x, const void *packed_w,
  * workspace around: code under HIP graph capture, tight serving loops,
  * harnesses that forbid hipMalloc.  Same arguments and results as
  * sparq_conv_gemm without the workspace: whatever scratch the layer needs (the
- * channel-padded copy, split-reduction sums) is taken from an array inside the
- * library's device image, SPARQ_STATIC_WORKSPACE_BYTES per GPU, held from the
+ * channel-padded copy) is taken from an array inside the library's device image, SPARQ_STATIC_WORKSPACE_BYTES per GPU, held from the
  * library's first use on that GPU until the process ends.  A layer whose
  * sparq_workspace_bytes() exceeds that size returns SPARQ_EWORKSPACE before
  * anything is launched.  The call allocates and frees nothing (no hipMalloc,
@@ -166,8 +165,9 @@ sparq_status sparq_dequant(const int32_t *acc, const float *scale, float *out,
  * layer would on loading it, y = T(y) with pairs (2j, 2j+1) of one pixel's N
  * channels (Sections 3.1-3.2), so that the next layer can run with
  * window_bits = 8 and every activation is trimmed once.  This happens inside
- * the convolution's epilogue when out_mode equals mode and N is a multiple of
- * 4, and as one in-place sparq_trim pass over y otherwise; the result is the
+ * the convolution's epilogue where the kernel can (N a multiple of 4, and
+ * out_mode equal to mode or an input that is not trimmed), and as one in-place
+ * sparq_trim pass over y otherwise; the result is the
  * same.  factor and y (both device memory) must be 16-byte aligned;
  * everything else as for sparq_conv_gemm with acc == NULL, including the
  * workspace. */
@@ -245,7 +245,8 @@ sparq_status sparq_conv_gemm_packed(const void *packed_x, size_t packed_x_bytes,
  * MI355X has no datapath that trims after a sparse selection; with vSPARQ on
  * the result is computed exactly over an expanded problem (12 expanded channels
  * per group of four, one per activation and partner, in which the kept weights
- * are again 2:4 sparse; the buffers are sized for 16); with it
+ * are again 2:4 sparse, filled up with zero channels to the kernels' units; the
+ * buffers are sized for 16 per group); with it
  * off the problem is the layer itself.  Where the layer's plan is the
  * wave-specialised input-patch kernel the weights go to the sparse matrix
  * instruction as its sparse operand; otherwise the decompressed weights run

@@ -7,7 +7,8 @@
 // stores.  A tile is 256 pixels x 64 channels: of a 56-pixel-wide 3x3 layer 256 pixels need 1.6 patch pixels each, 128 need
 // 2.6, and the trim of the patch is the largest item of such a layer.  A patch pixel's address is worked out once per tile, into
 // LDS.  Requantised results: weights as the row operand (see sparq_conv_rows_kernel.h), rows leave through LDS.
-// Bound by vector issue and the phases' waits: 56 x 56 x 64 -> 64 3x3, batch 256, bytes: 78 -> 58 us (memory alone 21, the
+// Bound by vector issue (60 % of the cycles by the counters, the matrix pipeline 30) and the phases' waits (40 % of a wavefront's
+// life): 56 x 56 x 64 -> 64 3x3, batch 256, bytes: 78 -> 58 us (memory alone 21, the
 // matrix instructions 18); three workgroups per CU with twice the weights requested ahead: 63; 128 pixels per tile: 77.
 #pragma once
 #include "sparq_conv_patch_kernel.h"

@@ -162,8 +162,7 @@ bool plan_patch(const ConvGeom& g, int max_unit, PatchGeom* pg, int* npix, int* 
 //   64 for narrow layers (wave-specialised, two workgroups of 8 wavefronts per CU: the accumulators are small
 //   enough for 128 registers per lane), and for layers so small that 128-wide tiles would leave half the chip idle.
 //   256 (wave-specialised: 4 matrix + 4 staging wavefronts, one workgroup per CU) when it pads N to no more columns
-//   than 128-wide tiles would and either fills three quarters of the chip or the layer is small anyway (then one
-//   larger tile per CU beats a split reduction with its two extra launches); also for patches so large that LDS
+//   than 128-wide tiles would and either fills three quarters of the chip or the layer is small anyway; also for patches so large that LDS
 //   holds one workgroup per CU anyway (strided 3x3 layers on large images) when the layer is wide and fills the chip.
 //   128 otherwise: two plain workgroups per CU that hide each other's latencies for 1x1 layers with many tiles,
 //   wave-specialised for multi-tap layers and for layers with no more tiles than CUs.
@@ -175,7 +174,7 @@ const PatchVariant* pick_patch(const ConvGeom& g, const Tuning& tune, int ac, in
     int tn = g.N <= 64 ? 64 : 128;
     const bool same_columns = round_up(g.N, 256) == round_up(g.N, 128);
     if (g.N > 128 && same_columns && (t256 * 4 >= (int64_t)cus * 3 || (t128 <= cus && t256 * 8 >= cus))) tn = 256;
-    if (g.N > 64 && t128 * 2 <= cus) tn = 64;      // a small layer: more, narrower tiles fill more CUs, and need no split reduction
+    if (g.N > 64 && t128 * 2 <= cus) tn = 64;      // a small layer: more, narrower tiles fill more CUs
     if (2 * 4 * cbs * patch_plane_stride(npix, 4 * cbs) > kLdsPerCu / 2) {
         if (g.N >= 256 && t256 >= cus) tn = 256;
         else if (g.N < 256 && t128 >= cus && !forced) return nullptr;   // narrow: gather kernel
@@ -285,7 +284,8 @@ const WideVariant kWideVariants[] = {{"128x512", 512, launch_wide_512}, {"128x25
 bool fit_wide(const ConvGeom& g, bool bytes) { return one_tap(g, bytes) && g.Cq > 4 * kStepK; }      // (its requests run six steps ahead)
 
 // Eight wavefronts per tile: 1x1 layers without padding and with more than 512 channels, whatever their size (what the split
-// form does not take), except few output channels, where the 256-wide tile multiplies mostly padding (784 -> 48: 12 against 15 us).  Over
+// form does not take), except few output channels, where the 256-wide tile multiplies mostly padding (784 -> 48: 12 against 15 us; 97 to 128
+// outputs are ahead in one round of tiles, 24576 x 768 -> 128 1.17 x, and behind in two, 36992 x 768 -> 128 0.97 x, bytes 0.87 x).  Over
 // 220 shapes of 768 to 4608 channels (128..2048 outputs, 784..50176 pixels) 1.02 to 2 x faster than the kernels it replaced:
 // 65536 x 4608 x 512 int32 197 -> 172 us, bytes 233 -> 154; 50176 x 4608 x 320 207 -> 118; 50176 x 1024 -> 256 bytes 34 -> 28.
 // With 449 to 512 channels the activations fit in registers, and that form is ahead once there are many rounds of
@@ -329,7 +329,8 @@ bool fit_block(const ConvGeom& g, bool bytes, PatchGeom* pg, int* npix) {
     return true;
 }
 
-// Small workgroups: multi-tap layers with tiles for every slot of the chip (300 and more) and
+// Small workgroups: multi-tap layers with tiles for every CU (300 and more: from 250 to 310 tiles of 56 x 56 x 64 it is within
+// 5 % of the tile kernel, with 147 10.9 against 10.5 us, with 392 13.0 against 15.4) and
 //   up to 64 channels, if they have at most 64 outputs or a patch of less than 450 pixels per tile (1.0-1.5 x faster there:
 //   56 x 56 x 64 -> 64 3x3, batch 32 16.5 -> 13.1 us, batch 256 78 -> 58; wider rows trim too much per 64 outputs),
 //   or 113 to 128 with such a patch, for bytes (28 x 28 x 128 -> 128, batch 256 47 -> 42; 35 x 35 x 96 -> 96 fp32 35 against 37),
@@ -554,7 +555,7 @@ sparq_status conv_launch(const uint8_t* x, const void* packed_w, const sparq_con
     if (!acc && !out && !y) return SPARQ_EINVAL;
     if ((out || y) && !scale) return SPARQ_EINVAL;
     // y trimmed for the next layer: in the epilogue when that layer's mode is this layer's own and the kernel
-    // packs the bytes (N a multiple of 4, no split reduction, not a plain 8-bit layer); otherwise one in-place
+    // packs the bytes (N a multiple of 4, not a plain 8-bit layer); otherwise one in-place
     // pass of the standalone trim over y afterwards.  Either way y = trim(requantised result), pairs (2j, 2j+1) of a row.
     const bool trim_y = y && out_mode && out_mode->window_bits != 8;
     if (trim_y && !mode_valid(out_mode)) return SPARQ_EINVAL;

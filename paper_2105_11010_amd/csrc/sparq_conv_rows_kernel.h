@@ -14,7 +14,8 @@
 // are the row operand and a store writes whole runs.
 // Up to 128 channels bound by memory (64 -> 256, 802816 pixels, bytes: 106 -> 58 us, 4.4 TB/s; 128 -> 512, 200704 pixels:
 // 60 -> 35); from 256 channels on by the trim's vector instructions and the weights from L2 (256 -> 64, 802816 pixels:
-// 80 -> 69, 56 without a trim; 256 -> 1024, 50176 pixels: 42 -> 29; 512 -> 1024: 69 -> 47).
+// 80 -> 69, 56 without a trim; 256 -> 1024, 50176 pixels: 42 -> 29; 512 -> 1024: 69 -> 47).  Counters, bytes: with 64 channels 55 % of
+// a wavefront's life in waits, with 256 25 % and vector issue at 45 to 53 % of the cycles.
 #pragma once
 #include "sparq_conv_patch_kernel.h"
 

@@ -76,7 +76,7 @@ __global__ __launch_bounds__(kEwThreads) void trim_pair_kernel(const uint8_t* x,
 // word learns from its neighbours (lanes, at a wavefront's ends memory) whether the bytes next to it are zero.  Bound by
 // memory and its arithmetic about equally (35 vector instructions per four activations).  156800 x 289: 49.8 -> 20.4 us
 // (4.4 TB/s; one lane per pair, byte accesses and a 64-bit division before).
-// col_step: channel by which a wavefront's position in its row moves per round.  bytes <= 2^31 * 16.
+// col_step: channel by which a wavefront's position in its row moves per round.
 template <int KIND>
 __global__ __launch_bounds__(kEwThreads) void trim_odd_rows_kernel(const uint8_t* __restrict__ x, uint8_t* __restrict__ y,
                                                                    int64_t bytes, uint32_t C, FastDiv divC, uint32_t col_step,
