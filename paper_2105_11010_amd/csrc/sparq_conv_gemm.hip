@@ -334,7 +334,7 @@ bool fit_block(const ConvGeom& g, bool bytes, PatchGeom* pg, int* npix) {
 //   up to 64 channels, if they have at most 64 outputs or a patch of less than 450 pixels per tile (1.0-1.5 x faster there:
 //   56 x 56 x 64 -> 64 3x3, batch 32 16.5 -> 13.1 us, batch 256 78 -> 58; wider rows trim too much per 64 outputs),
 //   or 113 to 128 with such a patch, for bytes (28 x 28 x 128 -> 128, batch 256 47 -> 42; 65 to 112 channels: fp32
-//   0.86-1.04 x, bytes 0.78-0.97 x on rows up to 17 pixels and 1.0-1.26 x up to 128 outputs from 28 on, which the tile kernel keeps),
+//   0.86-1.04 x, bytes 0.78-1.10 x on rows up to 17 pixels and 0.93-1.26 x up to 128 outputs from 28 on, which the tile kernel keeps),
 //   or a patch too large for the tile kernel's staging, which the gather kernel would trim once per tap, if they have 15 taps
 //   and more or few channels on either side (1.5-3 x: 56 x 56 x 64 -> 64 5x5, batch 32; 98 x 98 x 539 -> 128 3x3 67 against 78).
 // With fewer tiles, or more channels, the tile kernel's pipelining is ahead (14 x 14 x 256, batch 256: 35 against 44 us).
