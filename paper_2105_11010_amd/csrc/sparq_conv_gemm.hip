@@ -337,6 +337,11 @@ bool fit_block(const ConvGeom& g, bool bytes, PatchGeom* pg, int* npix) {
 //   0.86-1.04 x, bytes 0.78-1.10 x on rows up to 17 pixels and 0.93-1.26 x up to 128 outputs from 28 on, which the tile kernel keeps),
 //   or a patch too large for the tile kernel's staging, which the gather kernel would trim once per tap, if they have 15 taps
 //   and more or few channels on either side (1.5-3 x: 56 x 56 x 64 -> 64 5x5, batch 32; 98 x 98 x 539 -> 128 3x3 67 against 78).
+//   Of 65 to 128 outputs the gather kernel makes one column tile: with fewer than 15 taps it then trims hardly more, and a
+//   filter one column wide makes the patch tall (untrimmed fp32 3x1 0.95-1.37 x of the gather kernel's time, 1.12 on average; 40 x 40 x 48 -> 96
+//   7x1 untrimmed bytes 41 against 50 us; trimmed fp32 up to 131072 pixels 1.05-1.12 x, beyond 0.92-1.0; 129 outputs and more 0.56-0.92 x).
+//   Rows of fp32 off a 64-byte border cost the gather kernel more: untrimmed 0.67-0.9 x from 100 outputs on, but 1.05-1.16 x from 72 to 92
+//   (70 x 70 x 64 -> 88 3x2 39 against 44).  2x2 and 2x4 0.88-1.08 x, 4x4 and 5x5 0.5-0.9 x.
 // With fewer tiles, or more channels, the tile kernel's pipelining is ahead (14 x 14 x 256, batch 256: 35 against 44 us).
 // Its four-byte results leave in runs of 128 bytes, so rows off a 64-byte border are for the tile kernel beyond 64 outputs (112 x 112 x 48 ->
 // 86 1x3 19 against 38 us), and fewer than nine taps (seven up to 64 outputs) do not pay for them (1x3 40 x 40 x 48 -> 126 30 against 42); it trims
@@ -348,6 +353,11 @@ bool pick_block(const ConvGeom& g, bool bytes, bool plain, bool gather, PatchGeo
     const int taps = g.KH * g.KW;
     if (taps == 1 || block_tiles(g.M, g.N) < 300) return false;
     gather = gather && (g.Cq == 64 || g.N <= 64 || taps >= 15) && g.Cq <= 256;
+    if (gather && g.N > 64 && g.N <= 128 && taps < 15) {
+        const bool column = g.KW == 1, aligned = g.N % 16 == 0;
+        if (bytes ? plain && column && taps >= 5 : plain ? (aligned ? column : g.N >= 72 && g.N < 96) : aligned && column && g.M <= 128 * 1024)
+            return false;
+    }
     if (!gather) {
         if (g.Cq > 128) return false;
         if (!bytes && (g.N <= 64 ? taps < 7 : taps < 9 || g.N % 16 || (!plain && g.Wo <= 8))) return false;

@@ -112,6 +112,13 @@ M45, PLAIN = S.Mode(4, S.OPT5, 1, 1), S.PLAIN8
     ("block", (409, 8, 8, 64, 160, 3, 1), PLAIN, (True, True)), ("block", (400, 12, 12, 48, 192, 3, 1), M45, (True, False)),
     ("block", (128, 35, 35, 128, 256, 3, 1), M45, (False, False)), ("block", (128, 35, 35, 128, 256, 3, 1), PLAIN, (False, True)),
     ("block", (256, 14, 14, 128, 96, 3, 1), M45, (False, False)), ("block", (256, 28, 28, 128, 128, 3, 1), M45, (False, True)),
+    # small workgroups on layers whose patch the tile kernel cannot stage: one 128-wide column tile of the gather kernel, filters one column wide
+    ("block", (51, 56, 56, 64, 112, (3, 1), (1, 0)), PLAIN, (False, True)), ("block", (51, 56, 56, 64, 144, (3, 1), (1, 0)), PLAIN, (True, True)),
+    ("block", (51, 56, 56, 64, 64, (3, 1), (1, 0)), PLAIN, (True, True)), ("block", (51, 56, 56, 64, 112, (3, 1), (1, 0)), M45, (True, True)),
+    ("block", (33, 56, 56, 64, 112, (3, 1), (1, 0)), M45, (False, True)), ("block", (202, 40, 40, 64, 112, (7, 1), (3, 0)), PLAIN, (False, False)),
+    ("block", (202, 40, 40, 64, 112, (7, 1), (3, 0)), M45, (True, True)), ("block", (51, 56, 56, 64, 112, 4, 2), PLAIN, (True, True)),
+    ("block", (206, 32, 32, 64, 72, 2, 1), PLAIN, (False, False)), ("block", (206, 32, 32, 64, 80, 2, 1), PLAIN, (True, True)),
+    ("block", (51, 56, 56, 64, 100, (3, 1), (1, 0)), PLAIN, (True, False)), ("block", (33, 56, 56, 64, 100, (3, 1), (1, 0)), M45, (True, False)),
     # activations in registers: four-byte results of half the last-level cache and more beside little arithmetic
     ("rows", (1, 144611, 1, 128, 448, 1, 0), M45, (False, True)), ("rows", (1, 144611, 1, 256, 448, 1, 0), M45, (True, True)),
     ("rows", (1, 144611, 1, 256, 448, 1, 0), PLAIN, (False, True)), ("rows", (1, 70000, 1, 128, 448, 1, 0), M45, (True, True)),
