@@ -1,0 +1,6 @@
+// SPARQ convolution of layers with four channels: every filter height, stride and output.
+#include "sparq_conv_few_kernel.h"
+
+namespace sparq {
+sparq_status launch_few_c4(const FewParams& p, hipStream_t s) { return launch_few_channels<4>(p, s); }
+}  // namespace sparq

@@ -2,6 +2,7 @@
 // pre-pass for channel counts that are not a multiple of 16, and the choice of tile shape.
 #include "sparq_conv_gemm_kernel.h"
 #include "sparq_conv_block_kernel.h"
+#include "sparq_conv_few_kernel.h"
 #include "sparq_conv_patch_kernel.h"
 #include "sparq_conv_rows_kernel.h"
 #include "sparq_conv_split_kernel.h"
@@ -375,6 +376,7 @@ struct ConvPlan {
     const RowsVariant* rows = nullptr;     // activations in registers; what follows is for calls it does not take
     const WideVariant* wide = nullptr;     // eight wavefronts per tile; what follows is for calls it does not take
     bool block = false;                    // small workgroups (then pg and npix are its own)
+    FewGeom few{};                         // at most four channels (steps != 0)
     bool patch = false;
     const PatchVariant* variant = nullptr;
     PatchGeom pg{};
@@ -389,8 +391,9 @@ struct ConvPlan {
 ConvPlan make_plan(const ConvGeom& g, const Tuning& tune, bool forms = true, bool bytes = false, bool trims = true) {
     ConvPlan pl;
     const bool plain = !trims || g.Cp != g.C;                    // the kernel itself does not trim (a padded copy is trimmed already)
-    if (g.fold) {               // at most 4 channels: 4-channel padded copy, pixel-folded, gather kernel
+    if (g.fold) {               // at most 4 channels: their own kernel, or 4-channel padded copy, pixel-folded, gather kernel
         pl.pad_bytes = (size_t)round_up((int64_t)g.B * g.H * g.W * 4, 256);
+        if (forms && !tune.form && !tune.set()) pl.few = few_geom(g, bytes, device_cu_count());
         return pl;
     }
     if (g.Cp != g.C) pl.pad_bytes = (size_t)round_up((int64_t)g.B * g.H * g.W * g.Cp, 256);
@@ -484,15 +487,16 @@ extern "C" size_t sparq_workspace_bytes(const sparq_conv_desc* desc, const sparq
 
 namespace {
 // Which of the plan's forms is launched, in the order conv_launch tries them.
-enum PlanForm { kFormWide, kFormSplit, kFormBlock, kFormRows, kFormPatch, kFormGather };
+enum PlanForm { kFormFew, kFormWide, kFormSplit, kFormBlock, kFormRows, kFormPatch, kFormGather };
 PlanForm plan_form(const ConvGeom& g, const ConvPlan& pl, bool bytes) {
+    if (pl.few.steps) return kFormFew;
     if (pl.wide) return kFormWide;
     if (pl.split) return kFormSplit;
     if (pl.block) return kFormBlock;
     if (pl.rows && rows_launchable(*pl.rows, g, bytes)) return kFormRows;
     return pl.patch ? kFormPatch : kFormGather;
 }
-const char* const kFormKernels[] = {"conv_wide_kernel", "conv_split_kernel", "conv_block_kernel", "conv_rows_kernel", "conv_patch_kernel", "conv_gemm_kernel"};
+const char* const kFormKernels[] = {"conv_few_kernel", "conv_wide_kernel", "conv_split_kernel", "conv_block_kernel", "conv_rows_kernel", "conv_patch_kernel", "conv_gemm_kernel"};
 
 const char* gather_tile_name(const ConvGeom& g, const Tuning& tune, bool bytes) {
     ConvGeom gt = g.fold ? folded_view(g) : g;
@@ -512,7 +516,7 @@ sparq_status plan_text(const sparq_conv_desc* desc, const sparq_mode* mode, char
     const bool trims = mode->window_bits != 8;
     const ConvPlan pl = make_plan(g, tune, forms, false, trims);
     const PlanForm form = plan_form(g, pl, false);
-    const char* copy = pl.pad_bytes ? " padded_copy" : "";
+    const char* copy = pl.pad_bytes && form != kFormFew ? " padded_copy" : "";
     char u8[64] = "";
     if (u8_too) {
         const ConvPlan p8 = make_plan(g, tune, forms, true, trims);
@@ -522,6 +526,7 @@ sparq_status plan_text(const sparq_conv_desc* desc, const sparq_mode* mode, char
     }
     char line[160];
     switch (form) {
+        case kFormFew: snprintf(line, sizeof(line), "conv_patch_kernel few_channels tile=%dx%d", pl.few.tm, kFewTN); break;
         case kFormSplit: snprintf(line, sizeof(line), "conv_patch_kernel split_reduction tile=%s patch_pixels=%d", pl.split->name, pl.npix); break;
         case kFormBlock: snprintf(line, sizeof(line), "conv_patch_kernel small_workgroups tile=256x64 patch_pixels=%d", pl.npix); break;
         case kFormWide: snprintf(line, sizeof(line), "conv_gemm_kernel tile=%s eight_wavefronts", pl.wide->name); break;
@@ -589,6 +594,30 @@ sparq_status conv_launch(const uint8_t* x, const void* packed_w, const sparq_con
     TrimKind kind = trim_kind(mode);
     size_t x_bytes = g.x_bytes;
     if (g.fold) {
+        if (pl.few.steps) {                     // (the workspace is asked for all the same: which form a call takes is not its caller's business)
+            if ((size_t)g.B * g.H * g.W * 4 >= kInvalidOffset) return SPARQ_EUNSUPPORTED;
+            FewParams q{};
+            q.x = x;
+            q.wpk = static_cast<const uint8_t*>(packed_w) + g.w_off;
+            q.colsum = static_cast<const int32_t*>(packed_w);
+            q.acc = acc; q.scale = scale; q.out = out; q.out_u8 = y;
+            q.x_bytes = (uint32_t)g.x_bytes;
+            q.w_bytes = (uint32_t)((size_t)g.Kp * g.Np);
+            q.M = (int)g.M; q.N = g.N; q.Np = g.Np;
+            q.B = g.B; q.H = g.H; q.W = g.W; q.Wo = g.Wo; q.Ho = g.Ho; q.KH = g.KH; q.sh = g.sh; q.sw = g.sw; q.ph = g.ph;
+            q.Hv = g.H + 2 * g.ph;
+            q.tm = pl.few.tm; q.tiles = (int)((g.M + q.tm - 1) / q.tm); q.patch_bytes = pl.few.patch_bytes;
+            q.taps_row = pl.few.taps_row; q.taps_pitch = g.fold_kw; q.group0 = g.fold_kw_min; q.steps = pl.few.steps;
+            q.kind = kind;
+            q.div_wo = make_fastdiv((uint32_t)g.Wo);
+            q.div_ho = make_fastdiv((uint32_t)g.Ho);
+            q.div_hv = make_fastdiv((uint32_t)q.Hv);
+            q.luts = make_luts(mode->window_bits, mode->shift_mask);
+            static constexpr sparq_status (*kLaunch[])(const FewParams&, hipStream_t) = {launch_few_c1, launch_few_c2, launch_few_c3, launch_few_c4};
+            const sparq_status st = kLaunch[g.C - 1](q, s);
+            if (st != SPARQ_OK || !trim_y) return st;
+            return sparq_trim(y, y, g.M, g.N, out_mode, stream);
+        }
         // A first-layer shape (C <= 4): trim into a copy with 4 channels per pixel, then contract the
         // pixel-folded problem (16-channel super-pixels, fold_p * N output channels) with trimming off.
         const ConvGeom f = folded_view(g);

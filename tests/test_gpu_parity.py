@@ -294,6 +294,37 @@ def test_conv_shapes(sq, oracle, layer, mode, path):
     check_layer(sq, oracle, layer, mode, seed_cfg=8)
 
 
+# The kernel of layers with at most four channels: every channel count, row stride and filter height it is compiled for (and
+# one in between), filters that need one or two groups of four pixels a row, an odd number of rows beside a half-empty last
+# step, tiles of several images, of several rows and of a part of one row, output channels that fill no 64, ragged last tiles.
+FEW_SHAPES = [
+    S.ConvLayer("f_7x7_s2_c3_n64", 3, 40, 36, 3, 64, 7, 7, (2, 2), (3, 3)),
+    S.ConvLayer("f_7x7_s2_c3_w224", 1, 30, 224, 3, 64, 7, 7, (2, 2), (3, 3)),
+    S.ConvLayer("f_3x3_s1_c3_n48", 2, 9, 16, 3, 48, 3, 3, (1, 1), (1, 1)),
+    S.ConvLayer("f_3x3_s1_c3_w1200", 1, 3, 1200, 3, 32, 3, 3, (1, 1), (1, 1)),
+    S.ConvLayer("f_5x5_s1_c1_n16", 2, 11, 20, 1, 16, 5, 5, (1, 1), (2, 2)),
+    S.ConvLayer("f_5x5_s2_c4_n80", 5, 7, 24, 4, 80, 5, 5, (2, 2), (2, 2)),
+    S.ConvLayer("f_6x6_s2_c2_n130", 2, 10, 40, 2, 130, 6, 6, (2, 2), (2, 2)),
+    S.ConvLayer("f_4x4_s4_c3_n96", 2, 16, 32, 3, 96, 4, 4, (4, 4), (0, 0)),
+    S.ConvLayer("f_7x4_s4_c4_n16", 1, 30, 16, 4, 16, 7, 4, (4, 4), (3, 0)),
+    S.ConvLayer("f_2x2_s2_c1_n17", 40, 2, 8, 1, 17, 2, 2, (2, 2), (0, 0)),
+    S.ConvLayer("f_8x7_s1_c3_n33", 1, 16, 12, 3, 33, 8, 7, (1, 1), (3, 3)),
+    S.ConvLayer("f_1x3_s1_c2_n64_m8", 1, 1, 8, 2, 64, 1, 3, (1, 1), (0, 1)),
+]
+
+
+@pytest.mark.parametrize("layer", FEW_SHAPES, ids=lambda l: l.name)
+@pytest.mark.parametrize("mode", [S.Mode(4, S.OPT5, 1, 1), S.Mode(4, S.OPT5, 1, 0), S.Mode(4, S.OPT3, 0, 1), S.Mode(4, S.OPT3, 0, 0),
+                                  S.Mode(3, S.OPT6_3B, 1, 0), S.Mode(2, S.OPT7_2B, 1, 1), S.Mode(2, S.OPT7_2B, 0, 1), S.PLAIN8],
+                         ids=lambda m: m.label)
+def test_conv_few_channels(sq, oracle, layer, mode):
+    d = sq.conv_desc(layer.B, layer.H, layer.W, layer.C, layer.N, layer.KH, layer.KW, layer.stride, layer.pad)
+    text = sq.sparq_conv_plan(d, sq.mode(*mode.astuple()))
+    assert " kernel=conv_few_kernel" in text and ("u8_kernel=conv_few_kernel" in text) == (layer.N % 16 == 0), text
+    check_layer(sq, oracle, layer, mode, seed_cfg=8)
+    check_layer_u8(sq, oracle, layer, mode, seed_cfg=8, out_mode=mode if layer.N == 64 else None)
+
+
 # The split-reduction form (small layers): its three tiles; fewer reduction steps than wavefronts, shares of unequal
 # length, ragged tiles, padded channels, images that share a tile, a patch that fills most of LDS.
 SPLIT_SHAPES = [
