@@ -704,6 +704,9 @@ sparq_status conv_launch(const uint8_t* x, const void* packed_w, const sparq_con
         q.div_steps_tap = make_fastdiv((uint32_t)q.steps_tap);
         q.div_kw = make_fastdiv((uint32_t)g.KW);
         q.g = pl.pg;
+        q.div_wo = make_fastdiv((uint32_t)q.g.Wo);
+        q.div_ho = make_fastdiv((uint32_t)q.g.Ho);
+        q.div_hv = make_fastdiv((uint32_t)q.g.Hv);
         return finish(pl.split->fn(okind, q, pl.npix, s), q.trim_out != 0);
     }
 

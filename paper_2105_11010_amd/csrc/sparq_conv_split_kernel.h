@@ -7,9 +7,13 @@
 // 32-index reduction steps, each reads its own weights straight from L2 (requested before the patch is staged;
 // every weight byte enters a workgroup once), and the eight partial tiles are added up through LDS.  The sums leave LDS
 // four channels at a time, so every output form is a vector store.
-// Bound by latency: launch, patch from memory, one barrier, the steps, the sum, the stores (5.2 us with nothing to reduce,
-// of which a launch that does nothing takes about 3).  Back to back on one stream, before -> now: 56 x 56 x 64 -> 64 3x3,
-// one image, 7.3 -> 5.5 us; 14 x 14 x 256 -> 256 9.1 -> 5.9; 7 x 7 x 512 -> 512 13.6 -> 6.8 (32 images 15.4 -> 12.9).
+// Bound by latency: launch, patch from memory, one barrier, the steps, the sum, the stores (a launch that does nothing takes about
+// 3 us), so what counts is how many instructions stand before the first request and between two matrix instructions: the
+// tile's geometry is integer arithmetic in scalar registers, a wavefront asks for whole pieces of a patch row, the fragments'
+// offset is carried along, and every wait for weights is for the oldest request only.  Back to back on one stream, us, tile kernels ->
+// first form (pixels numbered through with float divisions, a loop that could end half way) -> now: 56 x 56 x 64 -> 64 3x3, one
+// image, 7.3 -> 6.1 -> 4.8; 14 x 14 x 256 -> 256 9.1 -> 6.5 -> 5.4; 7 x 7 x 512 -> 512 13.6 -> 7.4 -> 6.3 (32 images 15.4 -> 14.8 ->
+// 12.6).  156 drawn layers 1.21 x on the first form.  Twice the weights requested ahead: 0.6 us slower (the longer code is fetched once per launch).
 #pragma once
 #include "sparq_conv_patch_kernel.h"
 #include "sparq_fastdiv.h"
@@ -33,7 +37,7 @@ struct SplitParams {
     int steps;               // 32-index reduction steps
     int steps_tap;           // ... per filter tap
     int tiles_n;
-    FastDiv div_planes, div_steps_tap, div_kw;
+    FastDiv div_planes, div_steps_tap, div_kw, div_wo, div_ho, div_hv, div_tiles_n;
     PatchGeom g;             // tm = the tile's output pixels
     TrimLuts luts;
 };
@@ -52,33 +56,61 @@ struct SplitCfg {
 
 inline int split_plane_stride(int npix_max) { return (int)round_up((int64_t)npix_max * kChunk, 256) + kChunk; }
 
-template <class Cfg, int KIND>
+// REMAP: a strided 1x1 layer (PatchGeom::rm_wo).
+template <class Cfg, int KIND, bool REMAP>
 __global__ __launch_bounds__(kSplitThreads, 2) void conv_split_kernel(const SplitParams p) {
     constexpr int FM = Cfg::kFM, FN = Cfg::kFN, D = Cfg::kAhead, TM = Cfg::kTM, TN = Cfg::kTN;
     constexpr int CH = 4;                                    // patch chunks in flight per lane
+    typedef float v4f __attribute__((ext_vector_type(4)));
     extern __shared__ __attribute__((aligned(16))) uint8_t lds[];
     const int tid = threadIdx.x, lane = tid & 63, l32 = lane & 31, lhi = lane >> 5;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const PatchGeom& g = p.g;
-    const int tile_m = (int)blockIdx.x / p.tiles_n, tile_n = (int)blockIdx.x - tile_m * p.tiles_n;
+    const int tile_m = (int)fastdiv(blockIdx.x, p.div_tiles_n), tile_n = (int)blockIdx.x - tile_m * p.tiles_n;
     const int m0 = tile_m * TM, n0 = tile_n * TN;
     const __amdgpu_buffer_rsrc_t xrsrc =
         __builtin_amdgcn_make_buffer_rsrc(const_cast<uint8_t*>(p.x), 0, (int)p.x_bytes, 0x00020000);
     const __amdgpu_buffer_rsrc_t wrsrc =
         __builtin_amdgcn_make_buffer_rsrc(const_cast<uint8_t*>(p.wpk), 0, (int)p.w_bytes, 0x00020000);
 
-    const TilePatch t = tile_patch(g, m0);
-    const int chunks = t.npix * p.planes;
-    v4u a_reg[CH];
-    auto load_chunk = [&](int i, int e) __attribute__((always_inline)) {
-        const int pix = (int)fastdiv((uint32_t)e, p.div_planes);
-        const int ch = (e - pix * p.planes) * kChunk;
-        uint32_t off = patch_pixel_offset_u32(g, t, pix, p.C, kPatchInvalidOffset);
-        off = ch < p.C ? off : kPatchInvalidOffset;          // a tap's channel padding reads as zero
-        off += off != kPatchInvalidOffset ? (uint32_t)ch : 0u;
-        a_reg[i] = __builtin_amdgcn_raw_buffer_load_b128(xrsrc, (int)off, 0, 0);
+    // ---- the tile's patch (as tile_patch; in integers, so that it stays in scalar registers) ----
+    const auto origin = [&](int m, int* row, int* x) __attribute__((always_inline)) {
+        const int r = (int)fastdiv((uint32_t)m, p.div_wo), b = (int)fastdiv((uint32_t)r, p.div_ho);
+        *row = r;
+        *x = (m - r * g.Wo) * g.sw - g.pw;
+        return b * g.Hv + (r - b * g.Ho) * g.sh;             // virtual row
     };
-    auto stage_chunk = [&](int i, int e) __attribute__((always_inline)) {
+    int row0, row1, x0, x1;
+    const int v0 = origin(m0, &row0, &x0), v1 = origin(m0 + TM < g.M ? m0 + TM - 1 : g.M - 1, &row1, &x1);
+    const int xlo = row0 == row1 ? x0 : -g.pw;
+    const int pwt = row0 == row1 ? x1 - x0 + g.KW : (g.Wo - 1) * g.sw + g.KW;
+    const int nrows = v1 - v0 + g.KH;
+
+    // ---- the patch: the chunks of a row lie next to each other in memory; a wavefront takes 64 of them at a time, every eighth
+    //      such piece.  A piece's row is uniform, so a lane's address is one division by a launch constant and a few adds: the
+    //      first request leaves after 60 instructions (250 and 100 for each further one while pixels were numbered through) ----
+    const int pieces = (pwt * p.planes + 63) >> 6;           // per row
+    int l_row = 0, l_piece = wave;                           // the piece requested next
+    auto next_piece = [&]() __attribute__((always_inline)) {
+        while (l_piece >= pieces) { l_piece -= pieces; ++l_row; }
+    };
+    next_piece();
+    v4u a_reg[CH];
+    int a_at[CH];                                            // where the chunk goes in LDS, -1: nowhere
+    auto load_chunk = [&](int i) __attribute__((always_inline)) {
+        const int vr = v0 + l_row, b = (int)fastdiv((uint32_t)vr, p.div_hv), iy = vr - b * g.Hv - g.ph;
+        const bool row_ok = (b < g.B) & ((unsigned)iy < (unsigned)g.H);
+        const uint32_t j = (uint32_t)(l_piece * 64 + lane);
+        const int px = (int)fastdiv(j, p.div_planes), plane = (int)j - px * p.planes, ix = xlo + px;
+        const bool ok = row_ok & (px < pwt) & ((unsigned)ix < (unsigned)g.W) & (plane * kChunk < p.C);      // a tap's channel padding reads as zero
+        int pix = (b * g.H + iy) * g.W + ix;
+        if constexpr (REMAP) pix = remap_pixel(g, ok ? ix : 0);
+        a_reg[i] = __builtin_amdgcn_raw_buffer_load_b128(xrsrc, ok ? pix * p.C + plane * kChunk : (int)kPatchInvalidOffset, 0, 0);
+        a_at[i] = px < pwt ? plane * p.plane_stride + (l_row * pwt + px) * kChunk : -1;
+        l_piece += kSplitWaves;
+        next_piece();
+    };
+    auto stage_chunk = [&](int i) __attribute__((always_inline)) {
         v4u v = a_reg[i];
         if (KIND != kTrimNone && p.trim_in) {
 #pragma unroll
@@ -86,77 +118,82 @@ __global__ __launch_bounds__(kSplitThreads, 2) void conv_split_kernel(const Spli
         }
 #pragma unroll
         for (int j = 0; j < 4; ++j) v[j] ^= 0x80808080u;
-        const int pix = (int)fastdiv((uint32_t)e, p.div_planes);
-        if (e < chunks) *reinterpret_cast<v4u*>(lds + (e - pix * p.planes) * p.plane_stride + pix * kChunk) = v;
+        if (a_at[i] >= 0) *reinterpret_cast<v4u*>(lds + a_at[i]) = v;
     };
-    // first patch chunks, then the first weights: the patch waits for its own requests only
+    // first patch chunks, then the first weights: the patch waits for its own requests only.  (Requests under a uniform
+    // condition: `left` counts the pieces of this wavefront.)
+    const int total = nrows * pieces;
+    int left = total > wave ? (total - wave + kSplitWaves - 1) / kSplitWaves : 0;
 #pragma unroll
-    for (int i = 0; i < CH; ++i) load_chunk(i, tid + i * kSplitThreads);
+    for (int i = 0; i < CH; ++i)
+        if (i < left) load_chunk(i);
 
     // ---- this wavefront's share of the reduction steps ----
     const int h0 = p.steps * wave / kSplitWaves, h1 = p.steps * (wave + 1) / kSplitWaves;
     const int wlane = (lhi * p.Np + n0 + l32) * kChunk;
     v4i b_reg[D][FN];
-    auto load_b = [&](v4i (&b)[FN], int h) __attribute__((always_inline)) {
+    const int w_step = 2 * p.Np * kChunk, w_last = (h1 - 1) * w_step;
+    int w_off = h0 * w_step;                                 // the step requested next
+#pragma unroll
+    for (int k = 0; k < D; ++k) {
         // past the share: outside the buffer (by the lane's part of the offset), not fetched
-        const int voff = h < h1 ? wlane : (int)kPatchInvalidOffset, soff = h < h1 ? h * 2 * p.Np * kChunk : 0;
+        const int voff = h0 + k < h1 ? wlane : (int)kPatchInvalidOffset, soff = h0 + k < h1 ? w_off : 0;
 #pragma unroll
         for (int j = 0; j < FN; ++j)
-            b[j] = __builtin_bit_cast(v4i, __builtin_amdgcn_raw_buffer_load_b128(wrsrc, voff + j * 32 * kChunk, soff, 0));
-    };
+            b_reg[k][j] = __builtin_bit_cast(v4i, __builtin_amdgcn_raw_buffer_load_b128(wrsrc, voff + j * 32 * kChunk, soff, 0));
+        w_off += w_step;
+    }
+    auto load_b = [&](v4i (&b)[FN]) __attribute__((always_inline)) {
+        const int soff = w_off < w_last ? w_off : w_last;    // past the share: the last step's once more, from L1
 #pragma unroll
-    for (int k = 0; k < D; ++k) load_b(b_reg[k], h0 + k);
+        for (int j = 0; j < FN; ++j)
+            b[j] = __builtin_bit_cast(v4i, __builtin_amdgcn_raw_buffer_load_b128(wrsrc, wlane + j * 32 * kChunk, soff, 0));
+        w_off += w_step;
+    };
 
     // per-channel constants of the epilogue: group q of this lane is channels n0 + 4 * (q % (TN / 4)) .. + 3 for every q
     static_assert(kSplitThreads % (TN / 4) == 0, "a lane's groups share their channels");
     const int en = n0 + 4 * (tid % (TN / 4));
-    int32_t corr[4];
-    float sc[4];
-    const float* scale_or_dummy = (p.out || p.out_u8) ? p.scale : reinterpret_cast<const float*>(p.colsum);
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-        const int nc = en + e < p.N ? en + e : 0;
-        corr[e] = p.colsum[nc] * 128;
-        sc[e] = scale_or_dummy[nc];
-    }
+    const bool scaled = p.out || p.out_u8;
+    const __amdgpu_buffer_rsrc_t frsrc =
+        __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(p.scale), 0, scaled ? p.N * 4 : 0, 0x00020000);     // (past N: 0)
+    const v4i colsum4 = *reinterpret_cast<const v4i*>(p.colsum + en);        // Np entries
+    const v4u scale4 = __builtin_amdgcn_raw_buffer_load_b128(frsrc, en * 4, 0, 0);
     __builtin_amdgcn_sched_barrier(0);
 
-    // ---- the whole patch into LDS ----
-    for (int e0 = 0; e0 < chunks; e0 += CH * kSplitThreads) {
-#pragma unroll
-        for (int i = 0; i < CH; ++i)
-            if (e0 + i * kSplitThreads + wave * 64 < chunks) {       // uniform
-                stage_chunk(i, e0 + tid + i * kSplitThreads);
-                const int next = e0 + (CH + i) * kSplitThreads;
-                if (next + wave * 64 < chunks) load_chunk(i, next + tid);
-            }
-    }
-    __syncthreads();
-
-    // ---- multiply ----
+    // where the fragments of the first step lie: worked out while the requests are on their way
     int32_t fbase[FM];
 #pragma unroll
     for (int i = 0; i < FM; ++i) {
-        int m = m0 + i * 32 + l32;
+        int m = m0 + i * 32 + l32, row, x;
         m = m < g.M ? m : g.M - 1;
-        fbase[i] = patch_pixel_of_output(g, t, m) * kChunk + lhi * p.plane_stride;
+        const int v = origin(m, &row, &x);
+        fbase[i] = ((v - v0) * pwt + (x - xlo)) * kChunk + lhi * p.plane_stride;
     }
     const int tap0 = (int)fastdiv((uint32_t)h0, p.div_steps_tap);
-    int f_c = h0 - tap0 * p.steps_tap;
-    int f_kh = (int)fastdiv((uint32_t)tap0, p.div_kw);
-    int f_kw = tap0 - f_kh * g.KW;
-    auto frag_offset = [&]() __attribute__((always_inline)) {
-        return f_c * 2 * p.plane_stride + (f_kh * t.pwt + f_kw) * kChunk;
-    };
-    auto advance = [&]() __attribute__((always_inline)) {
-        if (++f_c == p.steps_tap) {
-            f_c = 0;
-            if (++f_kw == g.KW) {
-                f_kw = 0;
-                if (++f_kh == g.KH) f_kh = 0;                // past the last step: any place inside the patch
+    const int kh0 = (int)fastdiv((uint32_t)tap0, p.div_kw), kw0 = tap0 - kh0 * g.KW, c0 = h0 - tap0 * p.steps_tap;
+    // patch offset of the step whose fragments are read next, steps left in its tap and taps left in its row.  (One step past the last
+    // the offset is a row further: other planes of the patch, not used.)
+    const int c_step = 2 * p.plane_stride, tap_step = kChunk - p.steps_tap * c_step, row_step = (pwt - g.KW) * kChunk;
+    int f_off = c0 * c_step + (kh0 * pwt + kw0) * kChunk, f_c = p.steps_tap - c0, f_kw = g.KW - kw0;
+#pragma unroll
+    for (int i = 0; i < FM; ++i) asm volatile("" : "+v"(fbase[i]));
+
+    // ---- the whole patch into LDS (the first round apart: in the loop a wait could not tell the patch from the weights) ----
+    auto stage_round = [&]() __attribute__((always_inline)) {
+#pragma unroll
+        for (int i = 0; i < CH; ++i)
+            if (i < left) {                                  // uniform
+                stage_chunk(i);
+                if (i + CH < left) load_chunk(i);
             }
-        }
+        left -= CH;
     };
+    stage_round();
+    while (left > 0) stage_round();
+    __syncthreads();
+
+    // ---- multiply ----
     v16i c[FM][FN];
 #pragma unroll
     for (int i = 0; i < FM; ++i)
@@ -166,26 +203,43 @@ __global__ __launch_bounds__(kSplitThreads, 2) void conv_split_kernel(const Spli
             for (int v = 0; v < 16; ++v) c[i][j][v] = 0;
     v4i af[2][FM];
     auto load_frags = [&](v4i (&a)[FM]) __attribute__((always_inline)) {
-        const int off = frag_offset();
 #pragma unroll
-        for (int i = 0; i < FM; ++i) a[i] = *reinterpret_cast<const v4i*>(lds + fbase[i] + off);
-        advance();
+        for (int i = 0; i < FM; ++i) a[i] = *reinterpret_cast<const v4i*>(lds + fbase[i] + f_off);
+        f_off += c_step;
+        if (--f_c == 0) {
+            f_c = p.steps_tap;
+            f_off += tap_step;
+            if (--f_kw == 0) {
+                f_kw = g.KW;
+                f_off += row_step;
+            }
+        }
     };
     load_frags(af[0]);
     static_assert(D % 2 == 0, "fragment slots alternate");
-    for (int h = h0; h < h1; h += D) {
+    // weights as the row operand: a lane ends up with channels 8 * (v / 4) + 4 * lhi + v % 4 of pixel l32
+    auto multiply = [&](int k) __attribute__((always_inline)) {
+        load_frags(af[(k + 1) & 1]);
+#pragma unroll
+        for (int i = 0; i < FM; ++i)
+#pragma unroll
+            for (int j = 0; j < FN; ++j) c[i][j] = __builtin_amdgcn_mfma_i32_32x32x32_i8(b_reg[k][j], af[k & 1][i], c[i][j], 0, 0, 0);
+    };
+    // whole rounds of D steps, then the rest apart: a round left half way would meet the loop's start with its requests in
+    // another order, and the compiler would wait there for all of them
+    int h = h0;
+    for (; h + D <= h1; h += D) {
 #pragma unroll
         for (int k = 0; k < D; ++k) {
-            if (k && h + k >= h1) break;                     // uniform
-            load_frags(af[(k + 1) & 1]);
-            // weights as the row operand: a lane ends up with channels 8 * (v / 4) + 4 * lhi + v % 4 of pixel l32
-#pragma unroll
-            for (int i = 0; i < FM; ++i)
-#pragma unroll
-                for (int j = 0; j < FN; ++j)
-                    c[i][j] = __builtin_amdgcn_mfma_i32_32x32x32_i8(b_reg[k][j], af[k & 1][i], c[i][j], 0, 0, 0);
-            load_b(b_reg[k], h + k + D);
+            multiply(k);
+            load_b(b_reg[k]);
         }
+    }
+    const int rest = h1 - h;
+#pragma unroll
+    for (int k = 0; k < D - 1; ++k) {
+        if (k >= rest) break;                                // uniform
+        multiply(k);
     }
     __syncthreads();                                         // the patch is not read any more
 
@@ -211,12 +265,13 @@ __global__ __launch_bounds__(kSplitThreads, 2) void conv_split_kernel(const Spli
 #pragma unroll
         for (int w = 1; w < kSplitWaves; ++w) r += *reinterpret_cast<const v4i*>(src + w * Cfg::kPartialBytes);
 #pragma unroll
-        for (int e = 0; e < 4; ++e) r[e] += corr[e];
+        for (int e = 0; e < 4; ++e) r[e] += colsum4[e] * 128;
         const int m = m0 + row;
         if (m >= g.M || en >= p.N) continue;
         const size_t at = (size_t)m * p.N + en;
         const bool whole = (p.N & 3) == 0;                   // then the four channels are inside N together and aligned
         if (p.out_u8) {
+            const auto sc = __builtin_bit_cast(v4f, scale4);
             uint32_t w = requant_u8(r[0], sc[0]) | (requant_u8(r[1], sc[1]) << 8) | (requant_u8(r[2], sc[2]) << 16) |
                          (requant_u8(r[3], sc[3]) << 24);
             if (whole) {
@@ -239,7 +294,7 @@ __global__ __launch_bounds__(kSplitThreads, 2) void conv_split_kernel(const Spli
             }
         }
         if (p.out) {
-            typedef float v4f __attribute__((ext_vector_type(4)));
+            const auto sc = __builtin_bit_cast(v4f, scale4);
             v4f f;
 #pragma unroll
             for (int e = 0; e < 4; ++e) f[e] = __fmul_rn((float)r[e], sc[e]);
@@ -263,16 +318,17 @@ int split_lds_bytes(int npix_max, int planes) {
 }
 
 // `p` carries everything except plane_stride and tiles_n; npix_max bounds TilePatch::npix.
-template <class Cfg, int KIND>
-sparq_status launch_split_cfg(const SplitParams& p, int npix_max, hipStream_t s) {
+template <class Cfg, int KIND, bool REMAP>
+sparq_status launch_split_remap(const SplitParams& p, int npix_max, hipStream_t s) {
     SplitParams q = p;
     q.plane_stride = split_plane_stride(npix_max);
     const int lds_bytes = split_lds_bytes<Cfg>(npix_max, p.planes);
     if (lds_bytes < 0 || p.g.tm != Cfg::kTM) return SPARQ_EUNSUPPORTED;
     q.tiles_n = (p.N + Cfg::kTN - 1) / Cfg::kTN;
+    q.div_tiles_n = make_fastdiv((uint32_t)q.tiles_n);
     const int64_t tiles = (int64_t)((p.g.M + Cfg::kTM - 1) / Cfg::kTM) * q.tiles_n;
     if (tiles > 0x7FFFFFFF) return SPARQ_EUNSUPPORTED;
-    auto kern = conv_split_kernel<Cfg, KIND>;
+    auto kern = conv_split_kernel<Cfg, KIND, REMAP>;
     // largest dynamic LDS size enabled so far, per device (relaxed atomics: concurrent callers at worst repeat the call)
     static std::atomic<int> lds_set_dev[kMaxDevices];
     const int slot = current_device_slot();
@@ -284,6 +340,11 @@ sparq_status launch_split_cfg(const SplitParams& p, int npix_max, hipStream_t s)
     }
     kern<<<(unsigned)tiles, kSplitThreads, lds_bytes, s>>>(q);
     return launch_status();
+}
+
+template <class Cfg, int KIND>
+sparq_status launch_split_cfg(const SplitParams& p, int npix_max, hipStream_t s) {
+    return p.g.rm_wo ? launch_split_remap<Cfg, KIND, true>(p, npix_max, s) : launch_split_remap<Cfg, KIND, false>(p, npix_max, s);
 }
 
 template <class Cfg>

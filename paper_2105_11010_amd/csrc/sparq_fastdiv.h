@@ -19,11 +19,11 @@ namespace sparq {
 
 struct FastDiv {
     uint32_t mul, shift;
-    uint32_t one;            // the divisor is 1: the quotient is the dividend
+    uint32_t one;            // all ones if the divisor is 1 (then mul is 0 and the quotient is the dividend)
 };
 
 inline FastDiv make_fastdiv(uint32_t d) {
-    FastDiv f{0u, 0u, 1u};
+    FastDiv f{0u, 0u, 0xFFFFFFFFu};
     if (d <= 1) return f;
     uint32_t s = 0;
     while ((1ull << (s + 1)) < d) ++s;                       // 2^s < d <= 2^(s+1)
@@ -40,7 +40,7 @@ SPARQ_FD uint32_t fastdiv(uint32_t n, const FastDiv& f) {
 #else
     const uint32_t hi = (uint32_t)(((uint64_t)n * f.mul) >> 32);
 #endif
-    return f.one ? n : hi >> f.shift;
+    return (hi >> f.shift) | (n & f.one);
 }
 
 }  // namespace sparq

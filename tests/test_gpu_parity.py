@@ -335,6 +335,8 @@ SPLIT_SHAPES = [
     ("32x32", S.ConvLayer("s_3x3_3x3_c80", 9, 3, 3, 80, 50, 3, 3, (1, 1), (1, 1))),
     ("32x32", S.ConvLayer("s_1x1_c4608", 1, 40, 1, 4608, 40)),
     ("32x32", S.ConvLayer("s_2x2_c72", 2, 10, 10, 72, 16, 2, 2, (1, 1), (0, 0))),
+    ("32x32", S.ConvLayer("s_1x1_s2_c320", 3, 9, 9, 320, 40, 1, 1, (2, 2), (0, 0))),       # pixels of a strided 1x1 layer
+    ("32x32", S.ConvLayer("s_3x3_s2_8x8_c96", 2, 8, 8, 96, 48, 3, 3, (2, 2), (1, 1))),     # many short patch rows
     ("32x64", S.ConvLayer("s_3x3_28_c64_n130", 3, 28, 28, 64, 130, 3, 3, (1, 1), (1, 1))),
     ("64x64", S.ConvLayer("s_3x3_56_c64", 4, 56, 56, 64, 64, 3, 3, (1, 1), (1, 1))),
     ("64x64", S.ConvLayer("s_3x3_s2_c96_n70", 6, 60, 60, 96, 70, 3, 3, (2, 2), (1, 1))),
