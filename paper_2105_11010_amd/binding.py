@@ -1,4 +1,5 @@
-"""ctypes binding of libsparq.so -- argument marshalling only.
+"""Binding of libsparq.so -- argument marshalling only: ctypes here, and _sparq_native.so (csrc/binding/sparq_native.cpp) for the
+calls a program makes per layer.
 
 Function names and arguments mirror include/sparq.h.  Tensors are torch CUDA
 (ROCm) tensors used purely as device buffers; every step of the computation
@@ -92,6 +93,29 @@ def _load() -> ctypes.CDLL:
 lib = _load()
 
 
+def _load_native():
+    """The per-layer entry points, on the library loaded above."""
+    try:
+        from . import _sparq_native as n
+    except ImportError as e:
+        raise ImportError(f"_sparq_native.so not built; run `python -c 'import __graft_entry__ as g; g.build()'` ({e})") from e
+    names = ("trim", "conv_gemm", "conv_gemm_u8", "conv_gemm_packed", "conv_gemm_sparse24", "dequant", "requant", "pack_act", "unpack_act")
+    n.bind(tuple(ctypes.cast(getattr(lib, "sparq_" + k), ctypes.c_void_p).value for k in names), SparqMode, SparqConvDesc, SparqError)
+    return n
+
+
+_native = _load_native()
+sparq_trim = _native.sparq_trim
+sparq_conv_gemm = _native.sparq_conv_gemm
+sparq_conv_gemm_u8 = _native.sparq_conv_gemm_u8
+sparq_conv_gemm_packed = _native.sparq_conv_gemm_packed
+sparq_conv_gemm_sparse24 = _native.sparq_conv_gemm_sparse24
+sparq_dequant = _native.sparq_dequant
+sparq_requant = _native.sparq_requant
+sparq_pack_act = _native.sparq_pack_act
+sparq_unpack_act = _native.sparq_unpack_act
+
+
 def strerror(status: int) -> str:
     return lib.sparq_strerror(int(status)).decode()
 
@@ -134,16 +158,6 @@ def _check(status: int, what: str) -> None:
         raise SparqError(status, what)
 
 
-def sparq_trim(x: torch.Tensor, y: torch.Tensor, m: SparqMode) -> None:
-    """y = vSPARQ/bSPARQ-trimmed x along the last axis (uint8 device tensors; y may be x)."""
-    C = x.shape[-1]
-    rows = x.numel() // C if C else 0
-    if y.shape != x.shape:
-        raise ValueError("x and y must have the same shape")
-    _check(lib.sparq_trim(_dev(x, torch.uint8, "x"), _dev(y, torch.uint8, "y"), rows, C, ctypes.byref(m), _stream()),
-           "sparq_trim")
-
-
 def sparq_packed_bytes(d: SparqConvDesc) -> int:
     return int(lib.sparq_packed_bytes(ctypes.byref(d)))
 
@@ -174,24 +188,6 @@ def sparq_pack_weights(w: torch.Tensor, d: SparqConvDesc, packed: torch.Tensor) 
                                   packed.numel(), _stream()), "sparq_pack_weights")
 
 
-def sparq_conv_gemm(x: torch.Tensor, packed: torch.Tensor, d: SparqConvDesc, m: SparqMode,
-                    acc: Optional[torch.Tensor] = None, scale: Optional[torch.Tensor] = None,
-                    out: Optional[torch.Tensor] = None, workspace: Optional[torch.Tensor] = None) -> None:
-    if x.numel() != d.B * d.H * d.W * d.C:
-        raise ValueError("activation size does not match the descriptor")
-    M = out_rows(d)
-    for t, nm in ((acc, "acc"), (out, "out")):
-        if t is not None and t.numel() != M * d.N:
-            raise ValueError(f"{nm} must hold M*N = {M * d.N} elements")
-    if scale is not None and scale.numel() != d.N:
-        raise ValueError("scale must hold N elements")
-    ws_ptr = _dev(workspace, torch.uint8, "workspace")
-    ws_bytes = workspace.numel() if workspace is not None else 0
-    _check(lib.sparq_conv_gemm(_dev(x, torch.uint8, "x"), _dev(packed, torch.uint8, "packed"), ctypes.byref(d),
-                               ctypes.byref(m), _dev(acc, torch.int32, "acc"), _dev(scale, torch.float32, "scale"),
-                               _dev(out, torch.float32, "out"), ws_ptr, ws_bytes, _stream()), "sparq_conv_gemm")
-
-
 def sparq_conv_gemm_static_ws(x: torch.Tensor, packed: torch.Tensor, d: SparqConvDesc, m: SparqMode,
                               acc: Optional[torch.Tensor] = None, scale: Optional[torch.Tensor] = None,
                               out: Optional[torch.Tensor] = None) -> None:
@@ -210,80 +206,13 @@ def sparq_conv_gemm_static_ws(x: torch.Tensor, packed: torch.Tensor, d: SparqCon
            "sparq_conv_gemm_static_ws")
 
 
-def sparq_dequant(acc: torch.Tensor, scale: torch.Tensor, out: torch.Tensor) -> None:
-    M, N = acc.shape
-    if out.shape != acc.shape or scale.numel() != N:
-        raise ValueError("shape mismatch")
-    _check(lib.sparq_dequant(_dev(acc, torch.int32, "acc"), _dev(scale, torch.float32, "scale"),
-                             _dev(out, torch.float32, "out"), M, N, _stream()), "sparq_dequant")
-
-
-def sparq_conv_gemm_u8(x: torch.Tensor, packed: torch.Tensor, d: SparqConvDesc, m: SparqMode, factor: torch.Tensor,
-                       y: torch.Tensor, workspace: Optional[torch.Tensor] = None,
-                       out_mode: Optional[SparqMode] = None) -> None:
-    """The convolution with its result requantised to uint8 (y holds M*N bytes: the next layer's NHWC input),
-    optionally trimmed with out_mode as the next layer would trim it on loading."""
-    if x.numel() != d.B * d.H * d.W * d.C:
-        raise ValueError("activation size does not match the descriptor")
-    if y.numel() != out_rows(d) * d.N:
-        raise ValueError(f"y must hold M*N = {out_rows(d) * d.N} elements")
-    if factor.numel() != d.N:
-        raise ValueError("factor must hold N elements")
-    ws_ptr = _dev(workspace, torch.uint8, "workspace")
-    ws_bytes = workspace.numel() if workspace is not None else 0
-    _check(lib.sparq_conv_gemm_u8(_dev(x, torch.uint8, "x"), _dev(packed, torch.uint8, "packed"), ctypes.byref(d),
-                                  ctypes.byref(m), _dev(factor, torch.float32, "factor"), _dev(y, torch.uint8, "y"),
-                                  ctypes.byref(out_mode) if out_mode is not None else None,
-                                  ws_ptr, ws_bytes, _stream()), "sparq_conv_gemm_u8")
-
-
-def sparq_requant(acc: torch.Tensor, factor: torch.Tensor, y: torch.Tensor) -> None:
-    M, N = acc.shape
-    if y.shape != acc.shape or factor.numel() != N:
-        raise ValueError("shape mismatch")
-    _check(lib.sparq_requant(_dev(acc, torch.int32, "acc"), _dev(factor, torch.float32, "factor"),
-                             _dev(y, torch.uint8, "y"), M, N, _stream()), "sparq_requant")
-
-
 def sparq_packed_act_bytes(rows: int, C: int, m: SparqMode, group: int = 1) -> int:
     """Bytes of the packed form of [rows][C] activations (0: this mode / group has none)."""
     return int(lib.sparq_packed_act_bytes(int(rows), int(C), ctypes.byref(m), int(group)))
 
 
-def sparq_pack_act(x: torch.Tensor, packed: torch.Tensor, m: SparqMode, group: int = 1) -> None:
-    """packed (uint8 device buffer) = the n-bit data + ShiftCtrl + MuxCtrl records of the trimmed x (last axis = channels)."""
-    C = x.shape[-1]
-    _check(lib.sparq_pack_act(_dev(x, torch.uint8, "x"), _dev(packed, torch.uint8, "packed"), packed.numel(),
-                              x.numel() // C, C, ctypes.byref(m), int(group), _stream()), "sparq_pack_act")
-
-
-def sparq_unpack_act(packed: torch.Tensor, y: torch.Tensor, m: SparqMode, group: int = 1) -> None:
-    """y (uint8, last axis = channels) = the values the records encode."""
-    C = y.shape[-1]
-    _check(lib.sparq_unpack_act(_dev(packed, torch.uint8, "packed"), packed.numel(), _dev(y, torch.uint8, "y"),
-                                y.numel() // C, C, ctypes.byref(m), int(group), _stream()), "sparq_unpack_act")
-
-
 def sparq_conv_packed_workspace_bytes(d: SparqConvDesc, m: SparqMode) -> int:
     return int(lib.sparq_conv_packed_workspace_bytes(ctypes.byref(d), ctypes.byref(m)))
-
-
-def sparq_conv_gemm_packed(packed_x: torch.Tensor, group: int, packed_w: torch.Tensor, d: SparqConvDesc, m: SparqMode,
-                           acc: Optional[torch.Tensor] = None, scale: Optional[torch.Tensor] = None,
-                           out: Optional[torch.Tensor] = None, workspace: Optional[torch.Tensor] = None) -> None:
-    """sparq_conv_gemm on an input held in packed storage (written by sparq_pack_act with the same mode and group)."""
-    M = out_rows(d)
-    for t, nm in ((acc, "acc"), (out, "out")):
-        if t is not None and t.numel() != M * d.N:
-            raise ValueError(f"{nm} must hold M*N = {M * d.N} elements")
-    if scale is not None and scale.numel() != d.N:
-        raise ValueError("scale must hold N elements")
-    ws_ptr = _dev(workspace, torch.uint8, "workspace")
-    ws_bytes = workspace.numel() if workspace is not None else 0
-    _check(lib.sparq_conv_gemm_packed(_dev(packed_x, torch.uint8, "packed_x"), packed_x.numel(), int(group),
-                                      _dev(packed_w, torch.uint8, "packed_w"), ctypes.byref(d), ctypes.byref(m),
-                                      _dev(acc, torch.int32, "acc"), _dev(scale, torch.float32, "scale"),
-                                      _dev(out, torch.float32, "out"), ws_ptr, ws_bytes, _stream()), "sparq_conv_gemm_packed")
 
 
 def sparq_sparse24_packed_bytes(d: SparqConvDesc, m: SparqMode) -> int:
@@ -302,23 +231,6 @@ def sparq_pack_weights_sparse24(w_vals: torch.Tensor, w_idx: torch.Tensor, d: Sp
     _check(lib.sparq_pack_weights_sparse24(_dev(w_vals, torch.int8, "w_vals"), _dev(w_idx, torch.uint8, "w_idx"),
                                            ctypes.byref(d), ctypes.byref(m), _dev(packed, torch.uint8, "packed"),
                                            packed.numel(), _stream()), "sparq_pack_weights_sparse24")
-
-
-def sparq_conv_gemm_sparse24(x: torch.Tensor, packed: torch.Tensor, d: SparqConvDesc, m: SparqMode,
-                             acc: Optional[torch.Tensor] = None, scale: Optional[torch.Tensor] = None,
-                             out: Optional[torch.Tensor] = None, workspace: Optional[torch.Tensor] = None) -> None:
-    """The convolution with 2:4 pruned weights: activations picked by the weights' coordinates, then paired."""
-    if x.numel() != d.B * d.H * d.W * d.C:
-        raise ValueError("activation size does not match the descriptor")
-    M = out_rows(d)
-    for t, nm in ((acc, "acc"), (out, "out")):
-        if t is not None and t.numel() != M * d.N:
-            raise ValueError(f"{nm} must hold M*N = {M * d.N} elements")
-    ws_ptr = _dev(workspace, torch.uint8, "workspace")
-    ws_bytes = workspace.numel() if workspace is not None else 0
-    _check(lib.sparq_conv_gemm_sparse24(_dev(x, torch.uint8, "x"), _dev(packed, torch.uint8, "packed"), ctypes.byref(d),
-                                        ctypes.byref(m), _dev(acc, torch.int32, "acc"), _dev(scale, torch.float32, "scale"),
-                                        _dev(out, torch.float32, "out"), ws_ptr, ws_bytes, _stream()), "sparq_conv_gemm_sparse24")
 
 
 def sparq_set_tuning(spec: Optional[str] = None) -> None:
