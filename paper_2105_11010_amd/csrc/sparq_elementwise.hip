@@ -3,6 +3,8 @@
 // and the trimmed, channel-padded copy used for channel counts that are not a
 // multiple of 16.  All of them are bound by HBM traffic, so each lane moves
 // 128-bit words and the grid is sized to a few workgroups per compute unit.
+#include <type_traits>
+
 #include "sparq_common.h"
 #include "sparq_fastdiv.h"
 
@@ -20,6 +22,16 @@ static int ew_grid(int64_t work_items, int per_block) {
     if (blocks > cap) blocks = cap;
     if (blocks < 1) blocks = 1;
     return (int)blocks;
+}
+
+// Kernels that only stream: one word per lane and as many workgroups as that takes, so that the accesses of the moment lie close
+// together (65536 x 4608 trimmed, 604 MB moved, 105 us with 4096 workgroups striding through the tensor, 122 with four words ahead per
+// lane, 96 this way).  What has much to do per word or to set up per lane is better off with fewer workgroups (ew_grid).
+// (2^19 workgroups move 2 GiB; larger tensors go round again.)
+constexpr int kMaxStreamGrid = 1 << 19;
+static int stream_grid(int64_t words) {
+    const int64_t blocks = (words + kEwThreads - 1) / kEwThreads;
+    return (int)(blocks < 1 ? 1 : blocks > kMaxStreamGrid ? kMaxStreamGrid : blocks);
 }
 
 // ---- standalone trim ---------------------------------------------------------
@@ -77,20 +89,22 @@ __global__ __launch_bounds__(kEwThreads) void trim_pair_kernel(const uint8_t* x,
 // memory and its arithmetic about equally (35 vector instructions per four activations).  156800 x 289: 49.8 -> 20.4 us
 // (4.4 TB/s; one lane per pair, byte accesses and a 64-bit division before).
 // col_step: channel by which a wavefront's position in its row moves per round.
-template <int KIND>
+template <int KIND, bool NT>
 __global__ __launch_bounds__(kEwThreads) void trim_odd_rows_kernel(const uint8_t* __restrict__ x, uint8_t* __restrict__ y,
                                                                    int64_t bytes, uint32_t C, FastDiv divC, uint32_t col_step,
                                                                    TrimLuts L) {
     const int lane = threadIdx.x & 63;
     const int64_t stride = (int64_t)gridDim.x * kEwThreads;
     int64_t w0 = (int64_t)blockIdx.x * kEwThreads + (threadIdx.x & ~63);         // the wavefront's first word
-    uint32_t wave_col = (uint32_t)((w0 * 16) % C);
+    uint32_t wave_col = (uint32_t)w0 * 16;                   // (the first round's words: below 2^25)
+    wave_col -= fastdiv(wave_col, divC) * C;
     for (; w0 * 16 < bytes; w0 += stride) {
         const int64_t at = (w0 + lane) * 16;
         const int valid = bytes - at >= 16 ? 16 : bytes > at ? (int)(bytes - at) : 0;
         uint32_t w[4] = {0, 0, 0, 0}, nz[4], pm[4];
         if (valid == 16) {
-            const v4u v = *reinterpret_cast<const v4u*>(x + at);
+            const v4u* src = reinterpret_cast<const v4u*>(x + at);
+            const v4u v = NT ? __builtin_nontemporal_load(src) : *src;
 #pragma unroll
             for (int k = 0; k < 4; ++k) w[k] = v[k];
         } else {
@@ -111,7 +125,9 @@ __global__ __launch_bounds__(kEwThreads) void trim_odd_rows_kernel(const uint8_t
 #pragma unroll
         for (int k = 0; k < 4; ++k) w[k] = trim4_kind_beside<KIND>(w[k], pm[k], L);
         if (valid == 16) {
-            *reinterpret_cast<v4u*>(y + at) = v4u{w[0], w[1], w[2], w[3]};
+            const v4u v = {w[0], w[1], w[2], w[3]};
+            if (NT) __builtin_nontemporal_store(v, reinterpret_cast<v4u*>(y + at));
+            else *reinterpret_cast<v4u*>(y + at) = v;
         } else {
 #pragma unroll
             for (int k = 0; k < 16; ++k)
@@ -130,10 +146,10 @@ static void launch_trim_kind(const uint8_t* x, uint8_t* y, int64_t rows, int C, 
     if (aligned16 && bytes >= 16 && (C % 2 == 0 || !trim_kind_pairs(KIND))) {
         const int64_t n_vec = bytes / 16;
         if (x != y && 2 * bytes >= kStreamedBytes)
-            trim_vec_kernel<KIND, true><<<ew_grid(n_vec, kEwThreads * 4), kEwThreads, 0, s>>>(
+            trim_vec_kernel<KIND, true><<<stream_grid(n_vec), kEwThreads, 0, s>>>(
                 reinterpret_cast<const uint4*>(x), reinterpret_cast<uint4*>(y), n_vec, (int)(bytes % 16), L);
         else
-            trim_vec_kernel<KIND, false><<<ew_grid(n_vec, kEwThreads * 4), kEwThreads, 0, s>>>(
+            trim_vec_kernel<KIND, false><<<stream_grid(n_vec), kEwThreads, 0, s>>>(
                 reinterpret_cast<const uint4*>(x), reinterpret_cast<uint4*>(y), n_vec, (int)(bytes % 16), L);
         return;
     }
@@ -141,8 +157,9 @@ static void launch_trim_kind(const uint8_t* x, uint8_t* y, int64_t rows, int C, 
         if (aligned16 && x != y && C >= 16 && C < (1 << 30)) {
             const int64_t words = (bytes + 15) / 16;
             const int grid = ew_grid(words, kEwThreads);
-            trim_odd_rows_kernel<KIND><<<grid, kEwThreads, 0, s>>>(x, y, bytes, (uint32_t)C, make_fastdiv((uint32_t)C),
-                                                                   (uint32_t)((int64_t)grid * kEwThreads * 16 % C), L);
+            const auto kernel = 2 * bytes >= kStreamedBytes ? trim_odd_rows_kernel<KIND, true> : trim_odd_rows_kernel<KIND, false>;
+            kernel<<<grid, kEwThreads, 0, s>>>(x, y, bytes, (uint32_t)C, make_fastdiv((uint32_t)C),
+                                               (uint32_t)((int64_t)grid * kEwThreads * 16 % C), L);
             return;
         }
     }
@@ -249,57 +266,118 @@ sparq_status launch_trim_pad(const uint8_t* x, uint8_t* xp, int64_t pixels, int 
     return launch_status();
 }
 
-// ---- dequantisation ----------------------------------------------------------
-template <bool NT>
-__global__ __launch_bounds__(kEwThreads) void dequant_vec_kernel(const int4* __restrict__ acc, const float* __restrict__ scale,
-                                                                 float4* __restrict__ out, int64_t n_vec, int N) {
-    // N % 4 == 0: a 16-byte word never straddles a row
-    const int64_t stride = (int64_t)gridDim.x * kEwThreads;
-    for (int64_t i = (int64_t)blockIdx.x * kEwThreads + threadIdx.x; i < n_vec; i += stride) {
-        const int n = (int)((i * 4) % N);
-        const v4s* src = reinterpret_cast<const v4s*>(acc) + i;
-        const v4s a = NT ? __builtin_nontemporal_load(src) : *src;
-        const float4 s = *reinterpret_cast<const float4*>(scale + n);
+// ---- dequantisation, and requantisation to the next layer's unsigned 8-bit activations ----
+// out = (float)acc * scale[n];  y = clamp(round_to_nearest_even(acc * factor[n]), 0, 255), the product and the rounding in fp32
+// (requant_u8 and the packing conversion instruction, which rounds and saturates the same way).
+// The accumulators are one stream of words of four, whatever N is.  N a multiple of four: a word's factors are one aligned word.
+// Bound by memory; the streamed form's workgroups do one word per lane (200704 x 512 dequantised 150 -> 130 us), smaller calls stride.
+template <bool U8, bool NT>
+__device__ __forceinline__ void per_channel_word(v4s a, v4f f, void* out, int64_t i) {
+    if constexpr (U8) {
+        uint32_t w = 0;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) w = __builtin_amdgcn_cvt_pk_u8_f32(__fmul_rn((float)a[k], f[k]), k, w);
+        static_cast<uint32_t*>(out)[i] = w;
+    } else {
         v4f o;
-        o.x = __fmul_rn((float)a.x, s.x);
-        o.y = __fmul_rn((float)a.y, s.y);
-        o.z = __fmul_rn((float)a.z, s.z);
-        o.w = __fmul_rn((float)a.w, s.w);
-        if (NT) __builtin_nontemporal_store(o, reinterpret_cast<v4f*>(out) + i);
-        else reinterpret_cast<v4f*>(out)[i] = o;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) o[k] = __fmul_rn((float)a[k], f[k]);
+        if (NT) __builtin_nontemporal_store(o, static_cast<v4f*>(out) + i);
+        else static_cast<v4f*>(out)[i] = o;
     }
 }
-
-__global__ __launch_bounds__(kEwThreads) void dequant_scalar_kernel(const int32_t* __restrict__ acc, const float* __restrict__ scale,
-                                                                    float* __restrict__ out, int64_t total, int N) {
-    const int64_t stride = (int64_t)gridDim.x * kEwThreads;
-    for (int64_t i = (int64_t)blockIdx.x * kEwThreads + threadIdx.x; i < total; i += stride)
-        out[i] = __fmul_rn((float)acc[i], scale[i % N]);
-}
-
-// ---- requantisation to the next layer's unsigned 8-bit activations ------------
-// y = clamp(round_to_nearest_even(acc * factor[n]), 0, 255), the product and the rounding in fp32
-// (requant_u8 and the packing conversion instruction, which rounds and saturates the same way)
-__global__ __launch_bounds__(kEwThreads) void requant_vec_kernel(const int4* __restrict__ acc, const float* __restrict__ factor,
-                                                                 uint32_t* __restrict__ y, int64_t n_vec, int N) {
-    // N % 4 == 0: a word of four results never straddles a row
+template <bool U8, bool NT>
+__global__ __launch_bounds__(kEwThreads) void per_channel_vec_kernel(const v4s* __restrict__ acc, const float* __restrict__ factor,
+                                                                     void* __restrict__ out, int64_t n_vec, int N) {
     const int64_t stride = (int64_t)gridDim.x * kEwThreads;
     for (int64_t i = (int64_t)blockIdx.x * kEwThreads + threadIdx.x; i < n_vec; i += stride) {
-        const int n = (int)((i * 4) % N);
-        const int4 a = acc[i];
-        const float4 f = *reinterpret_cast<const float4*>(factor + n);
-        uint32_t w = __builtin_amdgcn_cvt_pk_u8_f32(__fmul_rn((float)a.x, f.x), 0, 0);
-        w = __builtin_amdgcn_cvt_pk_u8_f32(__fmul_rn((float)a.y, f.y), 1, w);
-        w = __builtin_amdgcn_cvt_pk_u8_f32(__fmul_rn((float)a.z, f.z), 2, w);
-        y[i] = __builtin_amdgcn_cvt_pk_u8_f32(__fmul_rn((float)a.w, f.w), 3, w);
+        const v4s a = NT ? __builtin_nontemporal_load(acc + i) : acc[i];
+        per_channel_word<U8, NT>(a, *reinterpret_cast<const v4f*>(factor + (i * 4) % N), out, i);
+    }
+}
+// Any N the table holds: the factors come from LDS, where the first three are repeated after the last, so that a word that ends a
+// row and begins the next reads four in a row as well.  A workgroup does UNROLL neighbouring groups of words: two, or with more than 1024
+// channels eight, for its table's sake.  Before (results one at a time, a 64-bit division each) -> now, us: 36992 x 161 dequantised
+// 10.1 -> 9.2, requantised 9.0 -> 7.2; 200000 x 161 60 -> 46, 47 -> 30; 200704 x 511 189 -> 132, 146 -> 89.
+constexpr int kMaxTable = 2 * 1024;
+template <bool U8, bool NT, int UNROLL>
+__global__ __launch_bounds__(kEwThreads) void per_channel_table_kernel(const v4s* __restrict__ acc, const float* __restrict__ factor,
+                                                                       void* __restrict__ out, int64_t n_vec, int tail, uint32_t N,
+                                                                       FastDiv divN) {
+    extern __shared__ float table[];
+    int64_t i = (int64_t)blockIdx.x * UNROLL * kEwThreads + threadIdx.x;
+    v4s a[UNROLL];
+    auto request = [&]() __attribute__((always_inline)) {
+#pragma unroll
+        for (int u = 0; u < UNROLL; ++u)
+            if (i + u * kEwThreads < n_vec) a[u] = NT ? __builtin_nontemporal_load(acc + i + u * kEwThreads) : acc[i + u * kEwThreads];
+    };
+    request();
+    for (uint32_t n = threadIdx.x; n < N + 3; n += kEwThreads) table[n] = factor[n < N ? n : (n - N) % N];
+    __syncthreads();
+    for (;;) {
+#pragma unroll
+        for (int u = 0; u < UNROLL; ++u) {
+            const int64_t at = i + u * kEwThreads;
+            if (at >= n_vec) break;
+            uint32_t col = (uint32_t)at * 4;
+            if (n_vec <= (1 << 29)) col -= fastdiv(col, divN) * N;           // uniform
+            else col = (uint32_t)(at * 4 % N);
+            v4f f;
+#pragma unroll
+            for (int k = 0; k < 4; ++k) f[k] = table[col + k];
+            per_channel_word<U8, NT>(a[u], f, out, at);
+        }
+        i += (int64_t)gridDim.x * UNROLL * kEwThreads;
+        if (i >= n_vec) break;
+        request();
+    }
+    if (blockIdx.x == 0 && (int)threadIdx.x < tail) {        // results past the last whole word
+        const int64_t at = n_vec * 4 + threadIdx.x;
+        const float f = factor[at % N];
+        const int32_t v = reinterpret_cast<const int32_t*>(acc)[at];
+        if constexpr (U8) static_cast<uint8_t*>(out)[at] = (uint8_t)requant_u8(v, f);
+        else static_cast<float*>(out)[at] = __fmul_rn((float)v, f);
     }
 }
 
-__global__ __launch_bounds__(kEwThreads) void requant_scalar_kernel(const int32_t* __restrict__ acc, const float* __restrict__ factor,
-                                                                    uint8_t* __restrict__ y, int64_t total, int N) {
+// Pointers off their words' alignment, or channels beyond what the table is for.
+template <bool U8>
+__global__ __launch_bounds__(kEwThreads) void per_channel_scalar_kernel(const int32_t* __restrict__ acc, const float* __restrict__ factor,
+                                                                        void* __restrict__ out, int64_t total, int N) {
     const int64_t stride = (int64_t)gridDim.x * kEwThreads;
-    for (int64_t i = (int64_t)blockIdx.x * kEwThreads + threadIdx.x; i < total; i += stride)
-        y[i] = (uint8_t)requant_u8(acc[i], factor[i % N]);
+    for (int64_t i = (int64_t)blockIdx.x * kEwThreads + threadIdx.x; i < total; i += stride) {
+        if constexpr (U8) static_cast<uint8_t*>(out)[i] = (uint8_t)requant_u8(acc[i], factor[i % N]);
+        else static_cast<float*>(out)[i] = __fmul_rn((float)acc[i], factor[i % N]);
+    }
+}
+
+template <bool U8>
+static sparq_status launch_per_channel(const int32_t* acc, const float* factor, void* out, int64_t total, int N, hipStream_t s) {
+    const bool words = aligned(acc, 16) && aligned(out, U8 ? 4 : 16), nt = !U8 && 8 * total >= kStreamedBytes;
+    const int64_t n_vec = total / 4;
+    const v4s* acc4 = reinterpret_cast<const v4s*>(acc);
+    if (words && N % 4 == 0 && aligned(factor, 16)) {
+        if (nt) per_channel_vec_kernel<U8, true><<<stream_grid(n_vec), kEwThreads, 0, s>>>(acc4, factor, out, n_vec, N);
+        else per_channel_vec_kernel<U8, false><<<ew_grid(n_vec, kEwThreads * 4), kEwThreads, 0, s>>>(acc4, factor, out, n_vec, N);
+        return launch_status();
+    }
+    // (a table of more than 1024 factors is for large calls: 200 x 2001 3.5 us without, 5.4 with it, 20000 x 2001 76 and 60)
+    if (words && N <= kMaxTable && (N <= 1024 || total >= (4 << 20))) {
+        const int tail = (int)(total % 4);
+        const FastDiv div = make_fastdiv((uint32_t)N);
+        const size_t lds = (size_t)(N + 3) * sizeof(float);
+        const auto launch = [&](auto nt_, auto unroll_) {
+            constexpr int U = decltype(unroll_)::value;
+            per_channel_table_kernel<U8, decltype(nt_)::value, U><<<stream_grid((n_vec + U - 1) / U), kEwThreads, lds, s>>>(
+                acc4, factor, out, n_vec, tail, (uint32_t)N, div);
+        };
+        if (N <= 1024) nt ? launch(std::true_type{}, std::integral_constant<int, 2>{}) : launch(std::false_type{}, std::integral_constant<int, 2>{});
+        else nt ? launch(std::true_type{}, std::integral_constant<int, 8>{}) : launch(std::false_type{}, std::integral_constant<int, 8>{});
+        return launch_status();
+    }
+    per_channel_scalar_kernel<U8><<<ew_grid(total, kEwThreads * 4), kEwThreads, 0, s>>>(acc, factor, out, total, N);
+    return launch_status();
 }
 
 // ---- weight packing ----------------------------------------------------------
@@ -395,20 +473,7 @@ extern "C" sparq_status sparq_dequant(const int32_t* acc, const float* scale, fl
     if (M == 0) return SPARQ_OK;
     if (!acc || !scale || !out) return SPARQ_EINVAL;
     if (M > (INT64_MAX / 8) / N) return SPARQ_EINVAL;
-    hipStream_t s = static_cast<hipStream_t>(stream);
-    const int64_t total = M * N;
-    if (N % 4 == 0 && aligned(acc, 16) && aligned(out, 16) && aligned(scale, 16)) {
-        const int64_t n_vec = total / 4;
-        if (8 * total >= kStreamedBytes)
-            dequant_vec_kernel<true><<<ew_grid(n_vec, kEwThreads * 4), kEwThreads, 0, s>>>(
-                reinterpret_cast<const int4*>(acc), scale, reinterpret_cast<float4*>(out), n_vec, N);
-        else
-            dequant_vec_kernel<false><<<ew_grid(n_vec, kEwThreads * 4), kEwThreads, 0, s>>>(
-                reinterpret_cast<const int4*>(acc), scale, reinterpret_cast<float4*>(out), n_vec, N);
-    } else {
-        dequant_scalar_kernel<<<ew_grid(total, kEwThreads * 4), kEwThreads, 0, s>>>(acc, scale, out, total, N);
-    }
-    return launch_status();
+    return launch_per_channel<false>(acc, scale, out, M * N, N, static_cast<hipStream_t>(stream));
 }
 
 extern "C" sparq_status sparq_requant(const int32_t* acc, const float* factor, uint8_t* y, int64_t M, int32_t N,
@@ -417,16 +482,7 @@ extern "C" sparq_status sparq_requant(const int32_t* acc, const float* factor, u
     if (M == 0) return SPARQ_OK;
     if (!acc || !factor || !y) return SPARQ_EINVAL;
     if (M > (INT64_MAX / 8) / N) return SPARQ_EINVAL;
-    hipStream_t s = static_cast<hipStream_t>(stream);
-    const int64_t total = M * N;
-    if (N % 4 == 0 && aligned(acc, 16) && aligned(y, 4) && aligned(factor, 16)) {
-        const int64_t n_vec = total / 4;
-        requant_vec_kernel<<<ew_grid(n_vec, kEwThreads * 4), kEwThreads, 0, s>>>(
-            reinterpret_cast<const int4*>(acc), factor, reinterpret_cast<uint32_t*>(y), n_vec, N);
-    } else {
-        requant_scalar_kernel<<<ew_grid(total, kEwThreads * 4), kEwThreads, 0, s>>>(acc, factor, y, total, N);
-    }
-    return launch_status();
+    return launch_per_channel<true>(acc, factor, y, M * N, N, static_cast<hipStream_t>(stream));
 }
 
 extern "C" size_t sparq_packed_bytes(const sparq_conv_desc* desc) {

@@ -190,6 +190,24 @@ def test_requant(sq, oracle, M, N):
     assert np.array_equal(y.cpu().numpy(), oracle.requant(acc, f))
 
 
+# Widths that are no multiple of four and factors off 16 bytes: words that end a row and begin the next, results past the last
+# word, the table's smallest and largest widths (and one past them), calls of less than and more than one workgroup.
+@pytest.mark.parametrize("M,N,skew", [(3, 1, 0), (1031, 2, 0), (5, 3, 0), (4099, 5, 0), (37, 161, 0), (2051, 161, 0), (513, 64, 1),
+                                      (33, 1023, 0), (2050, 2047, 0), (2048, 2049, 0), (2050, 2048, 1), (524289, 65, 0)])
+def test_per_channel_any_width(sq, oracle, M, N, skew):
+    rng = S.rng_for(8, 500 + N)
+    acc = np.resize(rng.integers(-60000, 200000, size=min(M * N, 1 << 18), dtype=np.int64).astype(np.int32), (M, N))
+    f = np.concatenate([np.zeros(skew), rng.uniform(5e-4, 3e-3, size=N)]).astype(np.float32)
+    accd, fd = dev(acc), dev(f)[skew:]
+    y = torch.full((M, N), 7, dtype=torch.uint8, device="cuda:0")
+    out = torch.full((M, N), -7.0, dtype=torch.float32, device="cuda:0")
+    sq.sparq_requant(accd, fd, y)
+    sq.sparq_dequant(accd, fd, out)
+    torch.cuda.synchronize()
+    assert np.array_equal(y.cpu().numpy(), oracle.requant(acc, f[skew:]))
+    assert np.array_equal(out.cpu().numpy(), acc.astype(np.float32) * f[skew:])      # two roundings to nearest, as defined
+
+
 def run_conv_u8(sq, x, w, f, layer, mode, out_mode=None):
     d = sq.conv_desc(layer.B, layer.H, layer.W, layer.C, layer.N, layer.KH, layer.KW, layer.stride, layer.pad)
     m = sq.mode(*mode.astuple())
