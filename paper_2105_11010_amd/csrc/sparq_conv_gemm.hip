@@ -433,6 +433,27 @@ bool sparse_plan(const ConvPlan& pl, TrimKind kind) {
     return pl.patch && pl.ws && pl.variant->fn_sp && single;
 }
 
+// The plan of a layer with 2:4 pruned weights.  Where the rules of dense layers pick a form made for the layer's shape, the decompressed
+// weights run there (`*dense`): the tile kernel's sparse instruction halves the matrix instructions, which is not what those layers
+// wait for.  With vSPARQ off (the layer itself) that is every form, small workgroups only where the layer would otherwise go to the
+// gather kernel (224 -> 64 3x3, 538103 pixels 287 -> 163 us; where the sparse instruction applies they are behind: 64 -> 96 3x3, 1280448
+// pixels 154 against 163): 512 -> 45 3x3, 600 pixels 16.0 -> 6.8, 496 -> 129 3x3/2, 512 pixels 28 -> 10.  With vSPARQ on (g is the expanded layer,
+// taps x channels of the layer itself: k) it costs the expansion an extra launch, and is the split form from k = 2048 on (512 -> 420
+// 1x7, 361 pixels 44 -> 13 us; 384 -> 229 3x3, 250 pixels 39 -> 13; shorter reductions gain 1.1-1.9 x too, but stay where the expansion
+// is made while staging, as that kernel's tests ask for) and small workgroups in place of the gather kernel.  1x1 layers keep to
+// the tile kernels (192 -> 96, 699328 pixels 304 against 308 with their activations in registers).
+ConvPlan make_sparse_plan(const ConvGeom& g, const Tuning& tune, bool expanded, int64_t k, TrimKind kind, bool trims, bool* dense) {
+    *dense = g.fold || g.Cq % kStepK != 0;                   // taps that are not step-aligned: no operands for the sparse instruction
+    if (*dense) return make_plan(g, tune, true, false, trims);
+    const ConvPlan base = make_plan(g, tune, false, false, trims);
+    if (tune.form || tune.set()) return base;
+    const ConvPlan pl = make_plan(g, tune, true, false, trims);
+    const bool sparse = sparse_plan(base, kind);
+    if (expanded) *dense = pl.split ? k >= 2048 : pl.block && !base.patch;
+    else *dense = pl.split || pl.wide || (pl.block ? !sparse : pl.rows && rows_launchable(*pl.rows, g, false));
+    return *dense ? pl : base;
+}
+
 }  // namespace
 
 extern "C" sparq_status sparq_set_tuning(const char* spec) {
@@ -507,19 +528,19 @@ const char* gather_tile_name(const ConvGeom& g, const Tuning& tune, bool bytes) 
     return "?";
 }
 
-// The line starts with the kernel family and the form, then names the kernel itself; `forms`: not the 2:4 layers, which keep to
-// the tile kernels and have no byte results.
-sparq_status plan_text(const sparq_conv_desc* desc, const sparq_mode* mode, char* text, size_t text_bytes, bool forms, bool u8_too) {
+// The line starts with the kernel family and the form, then names the kernel itself; `plan`: of a 2:4 layer (which has no byte
+// results), else the rules'.
+sparq_status plan_text(const sparq_conv_desc* desc, const sparq_mode* mode, char* text, size_t text_bytes, const ConvPlan* plan, bool u8_too) {
     ConvGeom g;
     if (!text || text_bytes == 0 || !conv_geom(desc, &g) || !mode_valid(mode)) return SPARQ_EINVAL;
     const Tuning tune = current_tuning();
     const bool trims = mode->window_bits != 8;
-    const ConvPlan pl = make_plan(g, tune, forms, false, trims);
+    const ConvPlan pl = plan ? *plan : make_plan(g, tune, true, false, trims);
     const PlanForm form = plan_form(g, pl, false);
     const char* copy = pl.pad_bytes && form != kFormFew ? " padded_copy" : "";
     char u8[64] = "";
     if (u8_too) {
-        const ConvPlan p8 = make_plan(g, tune, forms, true, trims);
+        const ConvPlan p8 = make_plan(g, tune, true, true, trims);
         const PlanForm f8 = plan_form(g, p8, true);
         const char* tile = f8 == kFormWide ? p8.wide->name : f8 == kFormSplit ? p8.split->name : f8 == kFormGather ? gather_tile_name(g, tune, true) : nullptr;
         snprintf(u8, sizeof(u8), " u8_kernel=%s%s%s", kFormKernels[f8], tile ? ":" : "", tile ? tile : "");
@@ -543,7 +564,7 @@ sparq_status plan_text(const sparq_conv_desc* desc, const sparq_mode* mode, char
 }  // namespace
 
 extern "C" sparq_status sparq_conv_plan(const sparq_conv_desc* desc, const sparq_mode* mode, char* text, size_t text_bytes) {
-    return plan_text(desc, mode, text, text_bytes, true, true);
+    return plan_text(desc, mode, text, text_bytes, nullptr, true);
 }
 
 namespace {
@@ -562,7 +583,8 @@ void set_row_division(GemmParams& p) {
 // the wave-specialised input-patch kernel, ignored otherwise.
 // expand_mode: desc is the expanded layer (blocked order) but x is the tensor itself, with x_channels channels; the
 // sparse kernel expands it under that mode.  Where that kernel does not apply the call returns SPARQ_EUNSUPPORTED.
-struct SparseOperand { const uint8_t* vals; const uint32_t* pos; const sparq_mode* expand_mode = nullptr; int x_channels = 0; };
+// plan: the layer's (make_sparse_plan); vals null: the plan is a dense kernel's, the operands are not looked at.
+struct SparseOperand { const uint8_t* vals; const uint32_t* pos; const ConvPlan* plan = nullptr; const sparq_mode* expand_mode = nullptr; int x_channels = 0; };
 sparq_status conv_launch(const uint8_t* x, const void* packed_w, const sparq_conv_desc* desc, const sparq_mode* mode,
                          int32_t* acc, const float* scale, float* out, uint8_t* y, const sparq_mode* out_mode,
                          void* workspace, size_t workspace_bytes, void* stream, const SparseOperand* sp = nullptr) {
@@ -583,7 +605,8 @@ sparq_status conv_launch(const uint8_t* x, const void* packed_w, const sparq_con
         return SPARQ_EINVAL;
     hipStream_t s = static_cast<hipStream_t>(stream);
     const Tuning tune = current_tuning();
-    const ConvPlan pl = make_plan(g, tune, sp == nullptr, y != nullptr, mode->window_bits != 8);
+    const ConvPlan pl = sp ? *sp->plan : make_plan(g, tune, true, y != nullptr, mode->window_bits != 8);
+    if (sp && !sp->vals) sp = nullptr;
     const size_t need = pl.pad_bytes;
     if (need) {
         if (!workspace || !aligned(workspace, 256)) return SPARQ_EINVAL;
@@ -916,6 +939,8 @@ bool sparse24_geometry(const sparq_conv_desc* desc, const sparq_mode* mode, spar
     return conv_geom(eff, &g);
 }
 const sparq_mode kNoPairPlain = {8, 1, 0, 0};
+// The trim the contracting kernel does itself: a padded copy is trimmed by its pre-pass.
+TrimKind sparse24_kind(const ConvGeom& g, const sparq_mode* mode) { return g.fold || g.Cp != g.C ? kTrimNone : trim_kind(mode); }
 
 // The staging wavefronts expand what they load where a tile's patch is small beside its taps: each patch pixel is then
 // trimmed three times per 64 channels and channel tile, which the matrix instructions of its taps have to cover (3x3 on 32 x
@@ -986,19 +1011,23 @@ extern "C" sparq_status sparq_conv_gemm_sparse24(const uint8_t* x, const void* p
     if (!x || !packed || (!acc && !out) || !sparse24_geometry(desc, mode, &eff, &expand)) return SPARQ_EINVAL;
     const Sparse24Layout L = sparse24_layout(eff);
     const uint8_t* sp_vals = static_cast<const uint8_t*>(packed) + L.tiles + L.dense;
+    ConvGeom ge;
+    conv_geom(&eff, &ge);
+    const sparq_mode* emode = expand ? &kNoPairPlain : mode;
+    bool dense;
+    const ConvPlan plan = make_sparse_plan(ge, current_tuning(), expand, (int64_t)desc->KH * desc->KW * desc->C,
+                                           sparse24_kind(ge, emode), emode->window_bits != 8, &dense);
     SparseOperand sp_op;
-    sp_op.vals = sp_vals;
+    sp_op.vals = L.sparse && !dense ? sp_vals : nullptr;
     sp_op.pos = reinterpret_cast<const uint32_t*>(sp_vals + L.vals);
-    const SparseOperand* sp = L.sparse ? &sp_op : nullptr;
+    sp_op.plan = &plan;
     if (!expand)      // nothing depends on the partner: the decompressed weights, the ordinary path
-        return conv_launch(x, packed, desc, mode, acc, scale, out, nullptr, nullptr, workspace, workspace_bytes, stream, sp);
+        return conv_launch(x, packed, desc, mode, acc, scale, out, nullptr, nullptr, workspace, workspace_bytes, stream, &sp_op);
     if (!aligned(x, 4) || !workspace || !aligned(workspace, 256)) return SPARQ_EINVAL;
     if (workspace_bytes < sparq_sparse24_workspace_bytes(desc, mode)) return SPARQ_EWORKSPACE;
     const int64_t pixels = (int64_t)desc->B * desc->H * desc->W;
     if (pixels * desc->C * 4 >= (int64_t)kInvalidOffset) return SPARQ_EUNSUPPORTED;
-    ConvGeom ge;
-    conv_geom(&eff, &ge);
-    if (sp && aligned(x, 16) && expands_while_staging(*desc, make_plan(ge, current_tuning(), false))) {
+    if (sp_op.vals && aligned(x, 16) && expands_while_staging(*desc, plan)) {
         SparseOperand fused = sp_op;
         fused.expand_mode = mode;
         fused.x_channels = desc->C;
@@ -1011,7 +1040,7 @@ extern "C" sparq_status sparq_conv_gemm_sparse24(const uint8_t* x, const void* p
     const sparq_status st = launch_sparse24_expand_act(x, xe, pixels, desc->C, eff.C, mode, static_cast<hipStream_t>(stream));
     if (st != SPARQ_OK) return st;
     return conv_launch(xe, packed, &eff, &kNoPairPlain, acc, scale, out, nullptr, nullptr, xe + x_room,
-                       workspace_bytes - x_room, stream, sp);
+                       workspace_bytes - x_room, stream, &sp_op);
 }
 
 extern "C" sparq_status sparq_sparse24_plan(const sparq_conv_desc* desc, const sparq_mode* mode, char* text, size_t text_bytes) {
@@ -1019,14 +1048,15 @@ extern "C" sparq_status sparq_sparse24_plan(const sparq_conv_desc* desc, const s
     bool expand;
     if (!text || text_bytes == 0 || !sparse24_geometry(desc, mode, &eff, &expand)) return SPARQ_EINVAL;
     const sparq_mode* m = expand ? &kNoPairPlain : mode;
-    char line[200];
-    const sparq_status st = plan_text(&eff, m, line, sizeof(line), !sparse24_layout(eff).sparse, false);
-    if (st != SPARQ_OK) return st;
     ConvGeom g;
     conv_geom(&eff, &g);
-    const ConvPlan pl = make_plan(g, current_tuning(), false);
-    const TrimKind kind = (g.fold || g.Cp != g.C) ? kTrimNone : trim_kind(m);     // a padded copy is trimmed by its pre-pass
-    const bool smfmac = sparse24_layout(eff).sparse && sparse_plan(pl, kind);
+    const TrimKind kind = sparse24_kind(g, m);
+    bool dense;
+    const ConvPlan pl = make_sparse_plan(g, current_tuning(), expand, (int64_t)desc->KH * desc->KW * desc->C, kind, m->window_bits != 8, &dense);
+    char line[200];
+    const sparq_status st = plan_text(&eff, m, line, sizeof(line), &pl, false);
+    if (st != SPARQ_OK) return st;
+    const bool smfmac = !dense && sparse24_layout(eff).sparse && sparse_plan(pl, kind);
     snprintf(text, text_bytes, "%s%s%s%s", line, expand ? " expanded_x4" : "",
              expand && smfmac && expands_while_staging(*desc, pl) ? " expanded_while_staging" : "", smfmac ? " sparse_mfma" : " dense_mfma");
     return SPARQ_OK;
