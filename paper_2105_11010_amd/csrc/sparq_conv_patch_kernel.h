@@ -600,16 +600,22 @@ __global__ __launch_bounds__(Cfg::kThreads, Cfg::kWgPerCu * Cfg::kThreads / 256)
                     asm volatile("" : "+v"(le));
                     uint8_t* xr = lds + 2 * buf_bytes + kChunk + wave * (32 * kSparseRowPitch);
                     uint8_t* xw = xr + (le & 31) * kSparseRowPitch + 16 * (le >> 5);
-                    const uint8_t* xrd = xr + (le >> 4) * kSparseRowPitch + (le & 15) * 16;
-                    const int nrun = n0 + wn * Cfg::kWTN + (le & 15) * 4;            // first channel of this lane's 16 bytes
-                    const uint32_t run_off = (uint32_t)((wm * Cfg::kWTM + (le >> 4)) * pitch + nrun * 4);
-                    // the lane's four channels' constants: requested here, ahead of every store, and not at the
+                    // N % 4 == 0: a lane stores 16 bytes, four of a row's channels, which are inside N together or not at all.
+                    // Otherwise one result, its lane's channel of one row after the other, so that a store instruction still
+                    // writes 256 bytes in a row (as four single results per lane, 16 bytes from the next lane's, 750 outputs took
+                    // four times what 748 do: 128 -> 750 3x3, 78400 pixels 399 against 98 us).
+                    constexpr int kRun = kVec ? 4 : 1, kLanes = kVec ? 16 : 64, kRows = 64 / kLanes;       // channels of a lane, lanes and rows of a store
+                    const int row_of = kVec ? le >> 4 : 0, col_of = le & (kLanes - 1);
+                    const uint8_t* xrd = xr + row_of * kSparseRowPitch + col_of * (4 * kRun);
+                    const int nrun = n0 + wn * Cfg::kWTN + col_of * kRun;            // the lane's first channel
+                    const uint32_t run_off = (uint32_t)((wm * Cfg::kWTM + row_of) * pitch + nrun * 4);
+                    // the lane's channels' constants: requested here, ahead of every store, and not at the
                     // tile's start (the step loop has no registers to spare for them)
                     static_assert(!SP || Cfg::kWTN == 64, "64 channels per wavefront");
-                    int32_t corr4[4];
-                    float sc4[4];
+                    int32_t corr4[kRun];
+                    float sc4[kRun];
 #pragma unroll
-                    for (int e = 0; e < 4; ++e) {
+                    for (int e = 0; e < kRun; ++e) {
                         const int nc = nrun + e < p.N ? nrun + e : 0;
                         corr4[e] = p.colsum[nc] * 128;
                         sc4[e] = scale_or_dummy[nc];
@@ -625,26 +631,23 @@ __global__ __launch_bounds__(Cfg::kThreads, Cfg::kWgPerCu * Cfg::kThreads / 256)
                             }
                         wavefront_lds_fence();
 #pragma unroll
-                        for (int k = 0; k < 8; ++k) {
-                            v4i r = *reinterpret_cast<const v4i*>(xrd + 4 * k * kSparseRowPitch);
-                            v4i f;
+                        for (int k = 0; k < 32 / kRows; ++k) {
+                            const int o = (int)(nrun < p.N ? run_off + (uint32_t)((i * 32 + kRows * k) * pitch) : 0x80000000u);
+                            if constexpr (kVec) {
+                                v4i r = *reinterpret_cast<const v4i*>(xrd + kRows * k * kSparseRowPitch);
+                                v4i f;
 #pragma unroll
-                            for (int e = 0; e < 4; ++e) {
-                                r[e] += corr4[e];
-                                f[e] = __builtin_bit_cast(int, __fmul_rn((float)r[e], sc4[e]));
-                            }
-                            const uint32_t off = run_off + (uint32_t)((i * 32 + 4 * k) * pitch);
-                            if constexpr (kVec) {      // N % 4 == 0: the four channels are inside N together or not at all
-                                const int o = (int)(nrun < p.N ? off : 0x80000000u);
+                                for (int e = 0; e < 4; ++e) {
+                                    r[e] += corr4[e];
+                                    f[e] = __builtin_bit_cast(int, __fmul_rn((float)r[e], sc4[e]));
+                                }
                                 if constexpr (kAcc) __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(v4u, r), arsrc, o, 0, kResultStorePolicy);
                                 if constexpr (kOut) __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(v4u, f), orsrc, o, 0, kResultStorePolicy);
                             } else {
-#pragma unroll
-                                for (int e = 0; e < 4; ++e) {
-                                    const int o = (int)(nrun + e < p.N ? off + 4u * e : 0x80000000u);
-                                    if constexpr (kAcc) __builtin_amdgcn_raw_buffer_store_b32(r[e], arsrc, o, 0, kResultStorePolicy);
-                                    if constexpr (kOut) __builtin_amdgcn_raw_buffer_store_b32(f[e], orsrc, o, 0, kResultStorePolicy);
-                                }
+                                const int32_t r = *reinterpret_cast<const int32_t*>(xrd + kRows * k * kSparseRowPitch) + corr4[0];
+                                if constexpr (kAcc) __builtin_amdgcn_raw_buffer_store_b32(r, arsrc, o, 0, kResultStorePolicy);
+                                if constexpr (kOut)
+                                    __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(int, __fmul_rn((float)r, sc4[0])), orsrc, o, 0, kResultStorePolicy);
                             }
                         }
                         wavefront_lds_fence();
