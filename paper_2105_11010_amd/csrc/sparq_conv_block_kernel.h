@@ -16,7 +16,7 @@
 namespace sparq {
 
 struct BlockParams {
-    const uint8_t* x;        // activations, NHWC, C a multiple of 16
+    const uint8_t* x;        // activations, NHWC, C a multiple of 4
     const uint8_t* wpk;      // packed weight tiles
     const int32_t* colsum;   // sum_k w[n][k], Np entries
     int32_t* acc;            // [M][N] or null

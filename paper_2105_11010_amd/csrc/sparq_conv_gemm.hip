@@ -1,5 +1,5 @@
 // Host entry point of the fused SPARQ convolution: validation, the channel-padding
-// pre-pass for channel counts that are not a multiple of 16, and the choice of tile shape.
+// pre-pass for channel counts that are not a multiple of four, and the choice of tile shape.
 #include "sparq_conv_gemm_kernel.h"
 #include "sparq_conv_block_kernel.h"
 #include "sparq_conv_few_kernel.h"
@@ -382,15 +382,17 @@ struct ConvPlan {
     PatchGeom pg{};
     int npix = 0, ac = 0, cbs = 0;
     bool ws = false;            // wave-specialised form of the patch kernel
-    size_t pad_bytes = 0;       // channel-padded copy of x (channel counts that are not a multiple of 16)
+    bool copy = false;          // the kernel reads a channel-padded, trimmed copy of x
+    size_t pad_bytes = 0;       // room for that copy (channel counts that are not a multiple of 16: asked for whether or not it is made)
 };
 
 // forms: the forms other than the two tile kernels may be taken (never for 2:4 pruned weights; where the tuning hook asks for
 // a tile kernel, no rule takes them; where it asks for one of them, that one wherever the layer fits it).
 // bytes: requantised results.  trims: the layer's mode trims (its size queries and descriptors without one do not care).
-ConvPlan make_plan(const ConvGeom& g, const Tuning& tune, bool forms = true, bool bytes = false, bool trims = true) {
+// copy: the channel-padded copy is made (channel counts that are not a multiple of 16).
+ConvPlan make_plan_of(const ConvGeom& g, const Tuning& tune, bool forms, bool bytes, bool trims, bool copy) {
     ConvPlan pl;
-    const bool plain = !trims || g.Cp != g.C;                    // the kernel itself does not trim (a padded copy is trimmed already)
+    const bool plain = !trims || copy;                           // the kernel itself does not trim (the copy is trimmed already)
     if (g.fold) {               // at most 4 channels: their own kernel, or 4-channel padded copy, pixel-folded, gather kernel
         pl.pad_bytes = (size_t)round_up((int64_t)g.B * g.H * g.W * 4, 256);
         if (forms && !tune.form && !tune.set()) pl.few = few_geom(g, bytes, device_cu_count());
@@ -399,7 +401,8 @@ ConvPlan make_plan(const ConvGeom& g, const Tuning& tune, bool forms = true, boo
     if (g.Cp != g.C) pl.pad_bytes = (size_t)round_up((int64_t)g.B * g.H * g.W * g.Cp, 256);
     const bool force_gather = tune.path == 1, force_patch = tune.path == 2;
     ConvGeom gk = g;
-    gk.C = gk.Cp;                                                // what the kernel sees after the padding pre-pass
+    pl.copy = copy;
+    if (copy) gk.C = g.Cp;                                       // what the kernel sees
     const bool rules = forms && !tune.form && !tune.set();
     if (forms && tune.form) {
         if (tune.form == kTunedRows && (pl.rows = fit_rows(gk, bytes)) != nullptr && !rows_launchable(*pl.rows, gk, bytes)) pl.rows = nullptr;
@@ -425,6 +428,37 @@ ConvPlan make_plan(const ConvGeom& g, const Tuning& tune, bool forms = true, boo
     return pl;
 }
 
+// Channel counts that are no multiple of four are contracted from a channel-padded copy, trimmed as it is written.  The others are
+// read where they are: a pixel's 16-byte words then start on any four-byte border, which is all a load asks for; the last one runs
+// into the next pixel (or past the tensor, where it reads 0) and meets weights that are 0 there; pairs stay inside the pixel.
+// 670 drawn layers 1.28 x faster than from the copy (38851 x 188 -> 96 13 -> 6 us; 65536 x 516 -> 256 38 -> 28; 244 -> 256 3x3, 50176
+// pixels 45 -> 39), but for the few whose kernel would trim the same bytes over and over, which keep the copy: several taps in the
+// gather kernel (5x5 on 69 x 69 x 264 52 against 97 us), 128-pixel tiles of long 1x1 reductions for less than half the CUs
+// (2978 x 4312 -> 304 29 against 39), and, the trims with the most arithmetic (windows of two or three bits with rounding, 25
+// instructions for four bytes), tile kernels that stage more than five bytes for one of x (35 x 35 x 908 -> 736 3x3/2 45 against 66),
+// five column tiles of the eight-wavefront form (9167 x 1276 -> 1216 32 against 38) and long reductions of the split form, which
+// stages all of its patch before the first product (154 x 3364 -> 656 10.6 against 12.4).
+ConvPlan make_plan(const ConvGeom& g, const Tuning& tune, bool forms = true, bool bytes = false, TrimKind kind = kTrimFloor) {
+    const bool pads = !g.fold && g.Cp != g.C, trims = kind != kTrimNone;
+    if (!pads || g.C % 4 == 0) {
+        const ConvPlan pl = make_plan_of(g, tune, forms, bytes, trims, false);
+        if (!pads || !trims) return pl;
+        const bool gather = !pl.wide && !pl.split && !pl.block && !pl.rows && !pl.patch;
+        const int64_t tiles_m = (g.M + 127) / 128;
+        const bool costly = kind == kTrimRound || kind == kTrimRoundPairWide;
+        bool once = gather && g.KH * g.KW > 1;
+        if (pl.split && !tune.form) once = costly ? g.K >= 1800 : kind == kTrimRoundPair4 && g.K >= 8000;
+        if (pl.wide && !tune.form) once = tiles_m * ((g.N + 255) / 256) * 2 < device_cu_count();
+        if (costly) {
+            if (pl.wide && !tune.form) once = once || (g.N + pl.wide->tn - 1) / pl.wide->tn >= 5;
+            else if (pl.patch && !pl.split && !pl.block && !pl.rows)
+                once = tiles_m * ((g.N + pl.variant->tn - 1) / pl.variant->tn) * pl.npix > (int64_t)5 * g.B * g.H * g.W;
+        }
+        if (!once) return pl;
+    }
+    return make_plan_of(g, tune, forms, bytes, trims, true);
+}
+
 // 2:4 pruned weights run on the sparse matrix instruction when the layer's plan is the wave-specialised
 // input-patch kernel and the trim looks at one activation at a time (with pairing on, the problem is the expanded
 // one and `kind` is the plain one; with it off the staging wavefronts trim as in the dense form).
@@ -442,12 +476,12 @@ bool sparse_plan(const ConvPlan& pl, TrimKind kind) {
 // 1x7, 361 pixels 44 -> 13 us; 384 -> 229 3x3, 250 pixels 39 -> 13; shorter reductions gain 1.1-1.9 x too, but stay where the expansion
 // is made while staging, as that kernel's tests ask for) and small workgroups in place of the gather kernel.  1x1 layers keep to
 // the tile kernels (192 -> 96, 699328 pixels 304 against 308 with their activations in registers).
-ConvPlan make_sparse_plan(const ConvGeom& g, const Tuning& tune, bool expanded, int64_t k, TrimKind kind, bool trims, bool* dense) {
+ConvPlan make_sparse_plan(const ConvGeom& g, const Tuning& tune, bool expanded, int64_t k, TrimKind kind, bool* dense) {
     *dense = g.fold || g.Cq % kStepK != 0;                   // taps that are not step-aligned: no operands for the sparse instruction
-    if (*dense) return make_plan(g, tune, true, false, trims);
-    const ConvPlan base = make_plan(g, tune, false, false, trims);
+    if (*dense) return make_plan(g, tune, true, false, kind);
+    const ConvPlan base = make_plan(g, tune, false, false, kind);
     if (tune.form || tune.set()) return base;
-    const ConvPlan pl = make_plan(g, tune, true, false, trims);
+    const ConvPlan pl = make_plan(g, tune, true, false, kind);
     const bool sparse = sparse_plan(base, kind);
     if (expanded) *dense = pl.split ? k >= 2048 : pl.block && !base.patch;
     else *dense = pl.split || pl.wide || (pl.block ? !sparse : pl.rows && rows_launchable(*pl.rows, g, false));
@@ -534,13 +568,13 @@ sparq_status plan_text(const sparq_conv_desc* desc, const sparq_mode* mode, char
     ConvGeom g;
     if (!text || text_bytes == 0 || !conv_geom(desc, &g) || !mode_valid(mode)) return SPARQ_EINVAL;
     const Tuning tune = current_tuning();
-    const bool trims = mode->window_bits != 8;
-    const ConvPlan pl = plan ? *plan : make_plan(g, tune, true, false, trims);
+    const TrimKind kind = trim_kind(mode);
+    const ConvPlan pl = plan ? *plan : make_plan(g, tune, true, false, kind);
     const PlanForm form = plan_form(g, pl, false);
-    const char* copy = pl.pad_bytes && form != kFormFew ? " padded_copy" : "";
+    const char* copy = pl.pad_bytes && form != kFormFew && (g.fold || pl.copy) ? " padded_copy" : "";
     char u8[64] = "";
     if (u8_too) {
-        const ConvPlan p8 = make_plan(g, tune, true, true, trims);
+        const ConvPlan p8 = make_plan(g, tune, true, true, kind);
         const PlanForm f8 = plan_form(g, p8, true);
         const char* tile = f8 == kFormWide ? p8.wide->name : f8 == kFormSplit ? p8.split->name : f8 == kFormGather ? gather_tile_name(g, tune, true) : nullptr;
         snprintf(u8, sizeof(u8), " u8_kernel=%s%s%s", kFormKernels[f8], tile ? ":" : "", tile ? tile : "");
@@ -605,7 +639,7 @@ sparq_status conv_launch(const uint8_t* x, const void* packed_w, const sparq_con
         return SPARQ_EINVAL;
     hipStream_t s = static_cast<hipStream_t>(stream);
     const Tuning tune = current_tuning();
-    const ConvPlan pl = sp ? *sp->plan : make_plan(g, tune, true, y != nullptr, mode->window_bits != 8);
+    const ConvPlan pl = sp ? *sp->plan : make_plan(g, tune, true, y != nullptr, trim_kind(mode));
     if (sp && !sp->vals) sp = nullptr;
     const size_t need = pl.pad_bytes;
     if (need) {
@@ -667,12 +701,12 @@ sparq_status conv_launch(const uint8_t* x, const void* packed_w, const sparq_con
         if (stf != SPARQ_OK || !trim_y) return stf;
         return sparq_trim(y, y, g.M, g.N, out_mode, stream);
     }
-    if (g.Cp != g.C) {
-        // Channel counts that are not a multiple of 16: trim into a channel-padded copy
+    if (g.Cp != g.C && (size_t)g.B * g.H * g.W * g.Cp >= kInvalidOffset) return SPARQ_EUNSUPPORTED;
+    if (pl.copy) {
+        // Trim into a channel-padded copy
         // first (pairs stay inside the row; padded channels are zeros with zero weights),
         // then contract the copy without further trimming.
         x_bytes = (size_t)g.B * g.H * g.W * g.Cp;
-        if (x_bytes >= kInvalidOffset) return SPARQ_EUNSUPPORTED;
         const sparq_status st = launch_trim_pad(x, static_cast<uint8_t*>(workspace), (int64_t)g.B * g.H * g.W, g.C,
                                                 g.Cp, mode, s);
         if (st != SPARQ_OK) return st;
@@ -680,6 +714,7 @@ sparq_status conv_launch(const uint8_t* x, const void* packed_w, const sparq_con
         kind = kTrimNone;
         fused_trim = false;                     // the kernel runs with trimming off
     }
+    const int xc = pl.copy ? g.Cp : g.C;         // bytes from pixel to pixel
     if (x_bytes >= kInvalidOffset) return SPARQ_EUNSUPPORTED;
     const auto finish = [&](sparq_status st, bool fused) {
         if (st != SPARQ_OK || !trim_y || fused) return st;
@@ -688,7 +723,7 @@ sparq_status conv_launch(const uint8_t* x, const void* packed_w, const sparq_con
 
     // An input that arrives trimmed (plain 8 bits) with an output to be trimmed for the next layer: the variants of the
     // OUTPUT mode, told not to trim their input, do it in their epilogue (the two forms below; the third says why not always).
-    const bool out_only = trim_y && !fused_trim && kind == kTrimNone && mode->window_bits == 8 && g.N % 4 == 0 && g.Cp == g.C;
+    const bool out_only = trim_y && !fused_trim && kind == kTrimNone && mode->window_bits == 8 && g.N % 4 == 0 && !pl.copy;
     const sparq_mode* kmode = out_only ? out_mode : mode;
     const auto fill = [&](auto& q) {
         q.x = xin;
@@ -697,7 +732,7 @@ sparq_status conv_launch(const uint8_t* x, const void* packed_w, const sparq_con
         q.acc = acc; q.scale = scale; q.out = out; q.out_u8 = y;
         q.x_bytes = (uint32_t)x_bytes;
         q.w_bytes = (uint32_t)((size_t)g.Kp * g.Np);
-        q.N = g.N; q.Np = g.Np; q.C = g.Cp;
+        q.N = g.N; q.Np = g.Np; q.C = xc;
         q.luts = make_luts(kmode->window_bits, kmode->shift_mask);
         q.trim_in = out_only ? 0 : 1;
         q.trim_out = fused_trim || out_only ? 1 : 0;
@@ -762,7 +797,7 @@ sparq_status conv_launch(const uint8_t* x, const void* packed_w, const sparq_con
         q.acc = acc; q.scale = scale; q.out = out; q.out_u8 = y; q.trim_out = fused_trim ? 1 : 0;
         q.x_bytes = (uint32_t)x_bytes;
         q.w_bytes = (uint32_t)((size_t)g.Kp * g.Np);
-        q.N = g.N; q.Np = g.Np; q.C = g.Cp;
+        q.N = g.N; q.Np = g.Np; q.C = xc;
         q.ksteps_tap = g.Cq / kStepK;
         q.ncb = q.ksteps_tap / pl.cbs;
         q.nsteps = g.KH * g.KW * pl.cbs;
@@ -777,7 +812,7 @@ sparq_status conv_launch(const uint8_t* x, const void* packed_w, const sparq_con
         // the separate trim pass over y it avoids costs more.)
         bool use_ws = pl.ws;
         if (trim_y && !fused_trim && kind == kTrimNone && mode->window_bits == 8 && g.N % 4 == 0 &&
-            g.Cp == g.C && pl.variant->fn_ws) {
+            !pl.copy && pl.variant->fn_ws) {
             use_ws = true;
             pkind = trim_kind(out_mode);
             q.luts = make_luts(out_mode->window_bits, out_mode->shift_mask);
@@ -820,7 +855,7 @@ sparq_status conv_launch(const uint8_t* x, const void* packed_w, const sparq_con
     p.M = g.M;
     p.x_bytes = (uint32_t)x_bytes;
     p.N = g.N; p.Np = g.Np; p.Kk = g.Kk; p.nkb = g.Kp / kStepK; p.scale_n = g.N;
-    p.H = g.H; p.W = g.W; p.C = g.Cp; p.Cq = g.Cq; p.Ho = g.Ho; p.Wo = g.Wo; p.KH = g.KH; p.KW = g.KW;
+    p.H = g.H; p.W = g.W; p.C = xc; p.Cq = g.Cq; p.Ho = g.Ho; p.Wo = g.Wo; p.KH = g.KH; p.KW = g.KW;
     p.sh = g.sh; p.sw = g.sw; p.ph = g.ph; p.pw = g.pw;
     p.rcp_c = 1.0f / (float)g.Cq;
     p.rcp_kw = 1.0f / (float)g.KW;
@@ -939,8 +974,8 @@ bool sparse24_geometry(const sparq_conv_desc* desc, const sparq_mode* mode, spar
     return conv_geom(eff, &g);
 }
 const sparq_mode kNoPairPlain = {8, 1, 0, 0};
-// The trim the contracting kernel does itself: a padded copy is trimmed by its pre-pass.
-TrimKind sparse24_kind(const ConvGeom& g, const sparq_mode* mode) { return g.fold || g.Cp != g.C ? kTrimNone : trim_kind(mode); }
+// The trim of the contracted layer (a padded copy's pre-pass does it where there is one; single activations either way).
+TrimKind sparse24_kind(const ConvGeom& g, const sparq_mode* mode) { return g.fold ? kTrimNone : trim_kind(mode); }
 
 // The staging wavefronts expand what they load where a tile's patch is small beside its taps: each patch pixel is then
 // trimmed three times per 64 channels and channel tile, which the matrix instructions of its taps have to cover (3x3 on 32 x
@@ -1016,7 +1051,7 @@ extern "C" sparq_status sparq_conv_gemm_sparse24(const uint8_t* x, const void* p
     const sparq_mode* emode = expand ? &kNoPairPlain : mode;
     bool dense;
     const ConvPlan plan = make_sparse_plan(ge, current_tuning(), expand, (int64_t)desc->KH * desc->KW * desc->C,
-                                           sparse24_kind(ge, emode), emode->window_bits != 8, &dense);
+                                           sparse24_kind(ge, emode), &dense);
     SparseOperand sp_op;
     sp_op.vals = L.sparse && !dense ? sp_vals : nullptr;
     sp_op.pos = reinterpret_cast<const uint32_t*>(sp_vals + L.vals);
@@ -1052,7 +1087,7 @@ extern "C" sparq_status sparq_sparse24_plan(const sparq_conv_desc* desc, const s
     conv_geom(&eff, &g);
     const TrimKind kind = sparse24_kind(g, m);
     bool dense;
-    const ConvPlan pl = make_sparse_plan(g, current_tuning(), expand, (int64_t)desc->KH * desc->KW * desc->C, kind, m->window_bits != 8, &dense);
+    const ConvPlan pl = make_sparse_plan(g, current_tuning(), expand, (int64_t)desc->KH * desc->KW * desc->C, kind, &dense);
     char line[200];
     const sparq_status st = plan_text(&eff, m, line, sizeof(line), &pl, false);
     if (st != SPARQ_OK) return st;

@@ -37,7 +37,7 @@ typedef int v16i __attribute__((ext_vector_type(16)));
 typedef unsigned int v4u __attribute__((ext_vector_type(4)));
 
 struct PatchParams {
-    const uint8_t* x;        // activations, NHWC, C a multiple of 16
+    const uint8_t* x;        // activations, NHWC, C a multiple of 4
     const uint8_t* wpk;      // packed weight tiles (taps padded to 64 channels); sparse form: the kept weights
     const int32_t* colsum;   // sum_k w[n][k], Np entries
     int32_t* acc;            // [M][N] or null

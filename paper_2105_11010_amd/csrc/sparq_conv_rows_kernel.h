@@ -24,7 +24,7 @@ namespace sparq {
 typedef float v4f_rows __attribute__((ext_vector_type(4)));
 
 struct RowsParams {
-    const uint8_t* x;        // activations, NHWC, C a multiple of 16
+    const uint8_t* x;        // activations, NHWC, C a multiple of 4
     const uint8_t* wpk;      // packed weight tiles
     const int32_t* colsum;   // sum_k w[n][k], Np entries
     int32_t* acc;            // [M][N] or null

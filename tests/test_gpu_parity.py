@@ -433,6 +433,31 @@ def test_conv_small_workgroups(sq, oracle, layer, mode):
     check_layer_u8(sq, oracle, layer, mode, seed_cfg=8, out_mode=S.Mode(4, S.OPT5, 1, 1))
 
 
+# Channel counts that are a multiple of four and not of 16, read where they are: words that start off a 16-byte border, run into
+# the next pixel and past the tensor's end, in every form; and the layers that keep the channel-padded copy (`copy`).
+@pytest.mark.parametrize("kernel,copy,layer", [
+    ("split", False, S.ConvLayer("a_split_3x3_c36", 2, 9, 11, 36, 48, 3, 3, (1, 1), (1, 1))), ("split", False, S.ConvLayer("a_split_1x1_c364", 1, 97, 1, 364, 80)),
+    ("rows", False, S.ConvLayer("a_rows_c60", 1, 71, 1, 60, 64)), ("rows", False, S.ConvLayer("a_rows_c188_s2", 3, 15, 13, 188, 96, 1, 1, (2, 2), (0, 0))),
+    ("rows", False, S.ConvLayer("a_rows_c492", 1, 6003, 1, 492, 144)), ("wide", False, S.ConvLayer("a_wide_c516", 1, 20011, 1, 516, 256)),
+    ("wide", False, S.ConvLayer("a_wide_c1004", 1, 32801, 1, 1004, 320)), ("block", False, S.ConvLayer("a_block_3x3_c52", 25, 56, 56, 52, 64, 3, 3, (1, 1), (1, 1))),
+    ("patch", False, S.ConvLayer("a_patch_3x3_c100", 21, 35, 35, 100, 96, 3, 3, (1, 1), (1, 1))), ("patch", False, S.ConvLayer("a_patch_1x7_c132", 33, 17, 17, 132, 272, 1, 7, (1, 1), (0, 3))),
+    ("gemm", False, S.ConvLayer("a_gather_1x1_c20", 3, 13, 11, 20, 48)), ("gemm", False, S.ConvLayer("a_gather_1x1_c4", 2, 9, 7, 4, 33)),
+    ("gemm", True, S.ConvLayer("a_gather_3x3_c28", 2, 13, 11, 28, 48, 3, 3, (1, 1), (1, 1))), ("wide", True, S.ConvLayer("a_few_tiles_c4108", 1, 2978, 1, 4108, 304)),
+], ids=lambda v: v.name if hasattr(v, "name") else str(v))
+@pytest.mark.parametrize("mode", [S.Mode(4, S.OPT5, 1, 1), S.Mode(4, S.OPT3, 0, 0), S.Mode(2, S.OPT7_2B, 1, 1), S.PLAIN8], ids=lambda m: m.label)
+def test_conv_channels_in_words(sq, oracle, kernel, copy, layer, mode):
+    d = sq.conv_desc(layer.B, layer.H, layer.W, layer.C, layer.N, layer.KH, layer.KW, layer.stride, layer.pad)
+    m = sq.mode(*mode.astuple())
+    text = sq.sparq_conv_plan(d, m)
+    assert sq.sparq_workspace_bytes(d, m) > 0                    # (asked for whether or not the copy is made)
+    assert ("padded_copy" in text) == (copy and mode.window_bits != 8), text
+    if not copy:
+        assert f" kernel=conv_{kernel}_kernel" in text, text
+    check_layer(sq, oracle, layer, mode, seed_cfg=8)
+    check_layer_u8(sq, oracle, layer, mode, seed_cfg=8)
+    check_layer_u8(sq, oracle, layer, mode, seed_cfg=8, out_mode=mode if layer.N % 16 == 0 else S.Mode(4, S.OPT5, 1, 1))
+
+
 # Each of these forms, forced by the tuning hook, in every trim variant it is built for and every form of its results: int32
 # alone, fp32 alone, both, bytes, bytes trimmed with the layer's own mode, and bytes trimmed where the input already is.
 FORM_SHAPES = [
