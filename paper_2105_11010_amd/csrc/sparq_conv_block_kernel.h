@@ -5,7 +5,9 @@
 // long epilogues alone.  Here a workgroup does one tile in plain phases -- stage 64 channels of the patch, multiply all taps,
 // next 64 channels, results out -- and four of them share a CU, so that one stages while another multiplies and a third
 // stores.  A tile is 256 pixels x 64 channels: of a 56-pixel-wide 3x3 layer 256 pixels need 1.6 patch pixels each, 128 need
-// 2.6, and the trim of the patch is the largest item of such a layer.  A patch pixel's address is worked out once per tile, into
+// 2.6, and the trim of the patch is the largest item of such a layer.  128 pixels x 128 channels trim a patch once per 128 outputs
+// instead: ahead beyond 64 of them, except where rows are wide (35 x 35 x 64 -> 96 3x3, batch 128, bytes 21.1 -> 19.1 us; the tile
+// kernel 23.5).  A patch pixel's address is worked out once per tile, into
 // LDS.  Requantised results: weights as the row operand (see sparq_conv_rows_kernel.h), rows leave through LDS.
 // Bound by vector issue (60 % of the cycles by the counters, the matrix pipeline 30) and the phases' waits (40 % of a wavefront's
 // life): 56 x 56 x 64 -> 64 3x3, batch 256, bytes: 78 -> 58 us (memory alone 21, the
@@ -34,17 +36,20 @@ struct BlockParams {
     TrimLuts luts;
 };
 
-// Four wavefronts along the pixels, each 32 FM pixels x 32 FN channels.
+// WM x WN = 4 wavefronts, each 32 FM pixels x 32 FN channels.
+template <int WM, int WN>
 struct BlockCfg {
-    static constexpr int kFM = 2, kFN = 2, kOcc = 4;         // four workgroups per CU: 128 registers
-    static constexpr int kThreads = 256, kTM = 128 * kFM, kTN = 32 * kFN;
+    static constexpr int kWM = WM, kWN = WN, kFM = 2, kFN = 2, kOcc = 4;         // four workgroups per CU: 128 registers
+    static constexpr int kThreads = 256, kTM = 32 * kFM * WM, kTN = 32 * kFN * WN;
     static constexpr int kRowPitch = kTN + 16;               // LDS row of a pixel's result bytes
     static constexpr int kAhead = 2;                         // weight steps requested ahead
+    static_assert(WM * WN == 4, "one wavefront per SIMD and workgroup");
 };
+typedef BlockCfg<4, 1> Block256x64;
+typedef BlockCfg<2, 2> Block128x128;
 
-template <int KIND, bool U8>
-__global__ __launch_bounds__(BlockCfg::kThreads, BlockCfg::kOcc) void conv_block_kernel(const BlockParams p) {
-    typedef BlockCfg Cfg;
+template <class Cfg, int KIND, bool U8>
+__global__ __launch_bounds__(Cfg::kThreads, Cfg::kOcc) void conv_block_kernel(const BlockParams p) {
     constexpr int FM = Cfg::kFM, FN = Cfg::kFN, TM = Cfg::kTM, TN = Cfg::kTN, NT = Cfg::kThreads, D = Cfg::kAhead;
     constexpr int CH = 4;                                    // patch chunks in flight per lane
     extern __shared__ __attribute__((aligned(16))) uint8_t lds[];            // [patch | pixel offsets], then result rows
@@ -52,10 +57,10 @@ __global__ __launch_bounds__(BlockCfg::kThreads, BlockCfg::kOcc) void conv_block
     const int tile = ((int)blockIdx.x & 7) * p.tiles_xcd + ((int)blockIdx.x >> 3);
     if (tile >= p.tiles) return;
     const int tid = threadIdx.x, lane = tid & 63, l32 = lane & 31, lhi = lane >> 5;
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), wm = wave % Cfg::kWM, wn = wave / Cfg::kWM;
     const PatchGeom& g = p.g;
     const int tile_m = tile / p.tiles_n, tile_n = tile - tile_m * p.tiles_n;
-    const int m0 = tile_m * TM, n0 = tile_n * TN;
+    const int m0 = tile_m * TM, n0t = tile_n * TN, n0 = n0t + wn * 32 * FN;      // the wavefront's channels
     const __amdgpu_buffer_rsrc_t xrsrc =
         __builtin_amdgcn_make_buffer_rsrc(const_cast<uint8_t*>(p.x), 0, (int)p.x_bytes, 0x00020000);
     const __amdgpu_buffer_rsrc_t wrsrc =
@@ -93,7 +98,7 @@ __global__ __launch_bounds__(BlockCfg::kThreads, BlockCfg::kOcc) void conv_block
     int32_t fbase[FM];
 #pragma unroll
     for (int i = 0; i < FM; ++i) {
-        int m = m0 + (wave * FM + i) * 32 + l32;
+        int m = m0 + (wm * FM + i) * 32 + l32;
         m = m < g.M ? m : g.M - 1;
         fbase[i] = patch_pixel_of_output(g, t, m) * kChunk + lhi * p.plane_stride;
     }
@@ -208,7 +213,7 @@ __global__ __launch_bounds__(BlockCfg::kThreads, BlockCfg::kOcc) void conv_block
                 }
                 const auto s02 = __builtin_amdgcn_permlane32_swap(w[0], w[2], false, false);
                 const auto s13 = __builtin_amdgcn_permlane32_swap(w[1], w[3], false, false);
-                *reinterpret_cast<v4u*>(lds + ((wave * FM + i) * 32 + l32) * Cfg::kRowPitch + j * 32 + 16 * lhi) =
+                *reinterpret_cast<v4u*>(lds + ((wm * FM + i) * 32 + l32) * Cfg::kRowPitch + (wn * FN + j) * 32 + 16 * lhi) =
                     v4u{s02[0], s02[1], s13[0], s13[1]};
             }
         }
@@ -216,7 +221,7 @@ __global__ __launch_bounds__(BlockCfg::kThreads, BlockCfg::kOcc) void conv_block
         const __amdgpu_buffer_rsrc_t orsrc =
             __builtin_amdgcn_make_buffer_rsrc((void*)(p.out_u8 + base), 0, rows * p.N, 0x00020000);
         constexpr int LPR = TN / 16, RPR = NT / LPR;         // lanes per row, rows per round
-        const int col = n0 + 16 * (tid % LPR);
+        const int col = n0t + 16 * (tid % LPR);
 #pragma unroll
         for (int r = 0; r < TM / RPR; ++r) {
             const int row = r * RPR + tid / LPR;
@@ -237,7 +242,7 @@ __global__ __launch_bounds__(BlockCfg::kThreads, BlockCfg::kOcc) void conv_block
 #pragma unroll
                     for (int j = 0; j < FN; ++j) {
                         const int n = n0 + 32 * j + l32;
-                        const int row = (wave * FM + i) * 32 + 8 * (v / 4) + 4 * lhi + v % 4;
+                        const int row = (wm * FM + i) * 32 + 8 * (v / 4) + 4 * lhi + v % 4;
                         const int off = n < p.N ? row * pitch + n * 4 : (int)kPatchInvalidOffset;
                         const int32_t r = c[i][j][v] + corr[j];
                         if constexpr (decltype(acc_)::value) __builtin_amdgcn_raw_buffer_store_b32(r, arsrc, off, 0, kResultStorePolicy);
@@ -252,37 +257,59 @@ __global__ __launch_bounds__(BlockCfg::kThreads, BlockCfg::kOcc) void conv_block
 }
 
 // LDS of a launch: the patch and its pixel offsets, or the result rows in the same place.
-inline int block_lds_bytes(int npix_max) {
-    const int64_t patch = 4ll * patch_plane_stride(npix_max, 4) + round_up(4ll * npix_max, 16), rows = (int64_t)BlockCfg::kTM * BlockCfg::kRowPitch;
+template <class Cfg>
+int block_lds_bytes(int npix_max) {
+    const int64_t patch = 4ll * patch_plane_stride(npix_max, 4) + round_up(4ll * npix_max, 16), rows = (int64_t)Cfg::kTM * Cfg::kRowPitch;
     const int64_t need = patch > rows ? patch : rows;
     return need > kLdsPerCu ? -1 : (int)need;
 }
 
-inline int64_t block_tiles(int64_t M, int64_t N) {
-    return (M + BlockCfg::kTM - 1) / BlockCfg::kTM * ((N + BlockCfg::kTN - 1) / BlockCfg::kTN);
+template <class Cfg>
+int64_t block_tiles(int64_t M, int64_t N) {
+    return (M + Cfg::kTM - 1) / Cfg::kTM * ((N + Cfg::kTN - 1) / Cfg::kTN);
 }
 // What the kernel can be launched for: LDS (64 KB: what a launch may use without asking), 32-bit offsets inside a tile of
 // results, tile numbers.  The rule that picks this form asks the same, so that other layers go on to the other kernels.
-inline bool block_launchable(int64_t M, int64_t N, int npix_max) {
-    const int lds_bytes = block_lds_bytes(npix_max);
-    return lds_bytes >= 0 && lds_bytes <= 64 * 1024 && N * 4 * BlockCfg::kTM < 0x7FFFFFFF && block_tiles(M, N) <= 0x0FFFFFFF;
+template <class Cfg>
+bool block_launchable(int64_t M, int64_t N, int npix_max) {
+    const int lds_bytes = block_lds_bytes<Cfg>(npix_max);
+    return lds_bytes >= 0 && lds_bytes <= 64 * 1024 && N * 4 * Cfg::kTM < 0x7FFFFFFF && block_tiles<Cfg>(M, N) <= 0x0FFFFFFF;
 }
 
 // `p` carries everything except plane_stride and the tile counts; npix_max bounds TilePatch::npix.
-template <int KIND, bool U8>
+template <class Cfg, int KIND, bool U8>
 sparq_status launch_block_cfg(const BlockParams& p, int npix_max, hipStream_t s) {
-    typedef BlockCfg Cfg;
     BlockParams q = p;
     q.plane_stride = patch_plane_stride(npix_max, 4);
-    const int lds_bytes = block_lds_bytes(npix_max);
-    if (p.g.tm != Cfg::kTM || p.g.rm_wo || !block_launchable(p.g.M, p.N, npix_max)) return SPARQ_EUNSUPPORTED;
+    const int lds_bytes = block_lds_bytes<Cfg>(npix_max);
     q.tiles_n = (p.N + Cfg::kTN - 1) / Cfg::kTN;
-    q.tiles = (int)block_tiles(p.g.M, p.N);
+    if (p.g.tm != Cfg::kTM || p.g.rm_wo || q.tiles_n * Cfg::kTN > p.Np || !block_launchable<Cfg>(p.g.M, p.N, npix_max)) return SPARQ_EUNSUPPORTED;
+    q.tiles = (int)block_tiles<Cfg>(p.g.M, p.N);
     q.tiles_xcd = (q.tiles + 7) / 8;
-    conv_block_kernel<KIND, U8><<<(unsigned)(8 * q.tiles_xcd), Cfg::kThreads, lds_bytes, s>>>(q);
+    conv_block_kernel<Cfg, KIND, U8><<<(unsigned)(8 * q.tiles_xcd), Cfg::kThreads, lds_bytes, s>>>(q);
     return launch_status();
 }
 
-sparq_status launch_block(TrimKind kind, const BlockParams& p, int npix_max, hipStream_t s);
+template <class Cfg>
+sparq_status launch_block_tile(TrimKind kind, const BlockParams& p, int npix_max, hipStream_t s) {
+    const auto go = [&](auto kind_) {
+        constexpr int K = decltype(kind_)::value;
+        return p.out_u8 ? launch_block_cfg<Cfg, K, true>(p, npix_max, s) : launch_block_cfg<Cfg, K, false>(p, npix_max, s);
+    };
+    switch (kind) {
+        case kTrimNone: return go(int_c<kTrimNone>{});
+        case kTrimFloor: return go(int_c<kTrimFloor>{});
+        case kTrimFloorPair: return go(int_c<kTrimFloorPair>{});
+        case kTrimFloorPairWide: return go(int_c<kTrimFloorPairWide>{});
+        case kTrimRound: return go(int_c<kTrimRound>{});
+        case kTrimRound4: return go(int_c<kTrimRound4>{});
+        case kTrimRoundPairWide: return go(int_c<kTrimRoundPairWide>{});
+        case kTrimRoundPair4: return go(int_c<kTrimRoundPair4>{});
+        default: return SPARQ_EUNSUPPORTED;
+    }
+}
+typedef sparq_status (*BlockLauncher)(TrimKind, const BlockParams&, int npix_max, hipStream_t);
+sparq_status launch_block_256x64(TrimKind kind, const BlockParams& p, int npix_max, hipStream_t s);
+sparq_status launch_block_128x128(TrimKind kind, const BlockParams& p, int npix_max, hipStream_t s);
 
 }  // namespace sparq

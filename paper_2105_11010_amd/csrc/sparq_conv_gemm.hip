@@ -321,13 +321,18 @@ const WideVariant* pick_wide(const ConvGeom& g, bool bytes, bool plain, bool for
 }
 
 // ---- multi-tap layers as many small workgroups -----------------------------------------------
-bool fit_block(const ConvGeom& g, bool bytes, PatchGeom* pg, int* npix) {
+struct BlockVariant { const char* name; int tm, tn; bool (*launchable)(int64_t, int64_t, int); BlockLauncher fn; };
+const BlockVariant kBlockVariants[] = {
+    {"256x64", 256, 64, block_launchable<Block256x64>, launch_block_256x64},
+    {"128x128", 128, 128, block_launchable<Block128x128>, launch_block_128x128},
+};
+const BlockVariant* fit_block(const ConvGeom& g, bool bytes, const BlockVariant& v, PatchGeom* pg, int* npix) {
     PatchGeom q;
     int n;
-    if (g.KH * g.KW == 1 || (bytes && g.N % 16) || !patch_geom_for(g, BlockCfg::kTM, &q, &n) || !block_launchable(g.M, g.N, n)) return false;
+    if (g.KH * g.KW == 1 || (bytes && g.N % 16) || !patch_geom_for(g, v.tm, &q, &n) || !v.launchable(g.M, g.N, n)) return nullptr;
     *pg = q;
     *npix = n;
-    return true;
+    return &v;
 }
 
 // Small workgroups: multi-tap layers with tiles for every CU (300 and more: from 250 to 310 tiles of 56 x 56 x 64 it is within
@@ -350,24 +355,56 @@ bool fit_block(const ConvGeom& g, bool bytes, PatchGeom* pg, int* npix) {
 // 10.4 against 12.7; bytes beyond 128 outputs 12 x 12 x 48 -> 192 7x1 81 against 95) and with 113 to 128 channels beyond 64 outputs (35 x 35 x 128 -> 256
 // bytes 55 against 61; 14 x 14 x 128 -> 96 14 against 16; up to 128 outputs on rows of 28 pixels and more it stays 1.02-1.15 x ahead).  With
 // these lines 58 of 3002 timed layers are more than 6 % slower than on the tile kernels, before 217.
-bool pick_block(const ConvGeom& g, bool bytes, bool plain, bool gather, PatchGeom* pg, int* npix) {
+const BlockVariant* pick_block(const ConvGeom& g, bool bytes, bool plain, bool gather, PatchGeom* pg, int* npix) {
     const int taps = g.KH * g.KW;
-    if (taps == 1 || block_tiles(g.M, g.N) < 300) return false;
+    if (taps == 1 || block_tiles<Block256x64>(g.M, g.N) < 300) return nullptr;
     gather = gather && (g.Cq == 64 || g.N <= 64 || taps >= 15) && g.Cq <= 256;
     if (gather && g.N > 64 && g.N <= 128 && taps < 15) {
         const bool column = g.KW == 1, aligned = g.N % 16 == 0;
         if (bytes ? plain && column && taps >= 5 : plain ? (aligned ? column : g.N >= 72 && g.N < 96) : aligned && column && g.M <= 128 * 1024)
-            return false;
+            return nullptr;
     }
     if (!gather) {
-        if (g.Cq > 128) return false;
-        if (!bytes && (g.N <= 64 ? taps < 7 : taps < 9 || g.N % 16 || (!plain && g.Wo <= 8))) return false;
-        if (bytes && !plain && (g.Cq == 64 ? g.N > 128 && g.Wo <= 14 : g.N > 128 || (g.N > 64 && (g.Wo < 28 || taps < 9)))) return false;
+        if (g.Cq > 128) return nullptr;
+        if (!bytes && (g.N <= 64 ? taps < 7 : taps < 9 || g.N % 16 || (!plain && g.Wo <= 8))) return nullptr;
+        if (bytes && !plain && (g.Cq == 64 ? g.N > 128 && g.Wo <= 14 : g.N > 128 || (g.N > 64 && (g.Wo < 28 || taps < 9)))) return nullptr;
     }
     // patch pixels of a tile that starts and ends anywhere in its rows (the largest one may cross two images)
-    const bool small = ((int64_t)BlockCfg::kTM + (int64_t)g.KH * g.Wo) * ((int64_t)(g.Wo - 1) * g.sw + g.KW) < 450ll * g.Wo;
-    if (!gather && !(g.Cq == 64 ? g.N <= 64 || small : small && bytes && g.C > 112)) return false;
-    return fit_block(g, bytes, pg, npix);
+    const bool small = ((int64_t)Block256x64::kTM + (int64_t)g.KH * g.Wo) * ((int64_t)(g.Wo - 1) * g.sw + g.KW) < 450ll * g.Wo;
+    if (!gather && !(g.Cq == 64 ? g.N <= 64 || small : small && bytes && g.C > 112)) return nullptr;
+    return fit_block(g, bytes, kBlockVariants[0], pg, npix);
+}
+
+// The 128 x 128 tile: layers of more than 64 outputs whose patch it trims half as often as the 256 x 64 tile does, where that is ahead of
+// the kernel the layer would take (picked: 256 x 64; tn: the tile kernel's output channels per tile, 0 the gather kernel).  1347
+// timed layers of several taps, fp32 and bytes; tiles of 128 x 128 for more than one round of CUs:
+//   64 channels, tiles 128 wide: bytes 1.05-1.4 x faster; fp32 1.06-1.16 x where rows start on 64 bytes (N = 292 and 101 0.85 and
+//   0.71 x), for seven taps and more, and not where 256 x 64 was ahead on several columns already (0.90-1.02 x);
+//   64 channels, tiles 256 wide: up to one and a third rounds of those 1.08-1.25 x, beyond 0.8-1.1 x (images of 8 pixels a row: 0.85 x);
+//   65 to 128 channels: bytes of more than 128 outputs, tiles 128 wide, 1.04-1.21 x; up to 192 in the first third of a second
+//   round of 256-wide tiles 1.08-1.18 x (17 x 17 x 192 1x7, batch 128: 289 tiles, 23.2 against 21.2 us);
+//   the gather kernel's layers, trimmed once per tap there: nine taps and more, up to 128 channels, 65 to 384 outputs 1.02-1.55 x
+//   in up to 1200 tiles (35 x 35 x 96 3x3/2 23.2 against 19.9 us; more tiles 0.88-1.4 x, more outputs 0.8-1.1 x), and 15 taps and
+//   more whose patch for 256 pixels does not fit (78 x 78 x 128 -> 48 5x5 125 against 76).
+const BlockVariant* pick_block_square(const ConvGeom& g, bool bytes, bool plain, const BlockVariant* picked, int tn, PatchGeom* pg, int* npix) {
+    const int taps = g.KH * g.KW;
+    const int64_t cus = device_cu_count(), t128 = block_tiles<Block128x128>(g.M, g.N);
+    if (taps == 1 || t128 <= cus || g.Cq > 192) return picked;
+    bool square = false;
+    if (tn == 0) {
+        if (plain || picked || g.Cq > 128) return picked;
+        PatchGeom q;
+        int n;
+        square = (taps >= 9 && g.N > 64 && g.N <= 384 && t128 <= 1200) || (taps >= 15 && g.N <= 384 && !fit_block(g, bytes, kBlockVariants[0], &q, &n));
+    } else if (g.N > 64 && tn >= 128 && (bytes || taps >= 7)) {
+        const int64_t t256 = (g.M + 127) / 128 * ((g.N + 255) / 256);
+        const bool third = t256 * 3 <= cus * 4;
+        if (tn == 256) square = third && (g.Cq == 64 ? plain || g.Wo > 8 : t256 > cus);
+        else if (g.Cq == 64) square = bytes || (g.N % 16 == 0 && (!picked || g.N <= 128));
+        else square = g.Cq == 128 && bytes && g.N > 128;
+    }
+    const BlockVariant* v = square ? fit_block(g, bytes, kBlockVariants[1], pg, npix) : nullptr;
+    return v ? v : picked;
 }
 
 // Everything the entry points decide before launching.
@@ -375,7 +412,7 @@ struct ConvPlan {
     const SplitVariant* split = nullptr;   // split-reduction form (then pg and npix are its own)
     const RowsVariant* rows = nullptr;     // activations in registers; what follows is for calls it does not take
     const WideVariant* wide = nullptr;     // eight wavefronts per tile; what follows is for calls it does not take
-    bool block = false;                    // small workgroups (then pg and npix are its own)
+    const BlockVariant* block = nullptr;   // small workgroups (then pg and npix are its own)
     FewGeom few{};                         // at most four channels (steps != 0)
     bool patch = false;
     const PatchVariant* variant = nullptr;
@@ -423,8 +460,13 @@ ConvPlan make_plan_of(const ConvGeom& g, const Tuning& tune, bool forms, bool by
         pl.variant = pick_patch(g, tune, pl.ac, pl.cbs, pl.npix, force_patch, &pl.ws);
         pl.patch = pl.variant != nullptr;
     }
-    if (rules) pl.block = pick_block(gk, bytes, plain, !pl.patch, &pl.pg, &pl.npix);
-    else if (forms && tune.form == kTunedBlock) pl.block = fit_block(gk, bytes, &pl.pg, &pl.npix);
+    if (rules) {
+        pl.block = pick_block(gk, bytes, plain, !pl.patch, &pl.pg, &pl.npix);
+        pl.block = pick_block_square(gk, bytes, plain, pl.block, pl.patch ? pl.variant->tn : 0, &pl.pg, &pl.npix);
+    }
+    else if (forms && tune.form == kTunedBlock)
+        for (const BlockVariant& v : kBlockVariants)
+            if ((pl.block = fit_block(gk, bytes, v, &pl.pg, &pl.npix)) != nullptr) break;
     return pl;
 }
 
@@ -583,7 +625,7 @@ sparq_status plan_text(const sparq_conv_desc* desc, const sparq_mode* mode, char
     switch (form) {
         case kFormFew: snprintf(line, sizeof(line), "conv_patch_kernel few_channels tile=%dx%d", pl.few.tm, kFewTN); break;
         case kFormSplit: snprintf(line, sizeof(line), "conv_patch_kernel split_reduction tile=%s patch_pixels=%d", pl.split->name, pl.npix); break;
-        case kFormBlock: snprintf(line, sizeof(line), "conv_patch_kernel small_workgroups tile=256x64 patch_pixels=%d", pl.npix); break;
+        case kFormBlock: snprintf(line, sizeof(line), "conv_patch_kernel small_workgroups tile=%s patch_pixels=%d", pl.block->name, pl.npix); break;
         case kFormWide: snprintf(line, sizeof(line), "conv_gemm_kernel tile=%s eight_wavefronts", pl.wide->name); break;
         case kFormRows: snprintf(line, sizeof(line), "conv_patch_kernel in_registers channels=%s", pl.rows->name); break;
         case kFormPatch:
@@ -774,7 +816,7 @@ sparq_status conv_launch(const uint8_t* x, const void* packed_w, const sparq_con
         fill(q);
         q.ncb = g.Cq / kStepK;
         q.g = pl.pg;
-        return finish(launch_block(okind, q, pl.npix, s), q.trim_out != 0);
+        return finish(pl.block->fn(okind, q, pl.npix, s), q.trim_out != 0);
     }
 
     // 1x1 layers with a short reduction: activations in registers.

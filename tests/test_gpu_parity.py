@@ -458,6 +458,31 @@ def test_conv_channels_in_words(sq, oracle, kernel, copy, layer, mode):
     check_layer_u8(sq, oracle, layer, mode, seed_cfg=8, out_mode=mode if layer.N % 16 == 0 else S.Mode(4, S.OPT5, 1, 1))
 
 
+FORM_MODES = [S.Mode(4, S.OPT5, 1, 1), S.Mode(4, S.OPT5, 1, 0), S.Mode(4, S.OPT3, 0, 1), S.Mode(4, S.OPT3, 0, 0),
+              S.Mode(3, S.OPT6_3B, 1, 0), S.Mode(2, S.OPT7_2B, 1, 1), S.Mode(2, S.OPT7_2B, 0, 1), S.PLAIN8]
+
+
+# The 128 x 128 tile of the small workgroups: outputs that fill no 128 (and no wavefront's 64), ragged pixels, several 64-channel
+# blocks, images that share a tile, the layers of the gather kernel it takes; `takes`: for four-byte results, for bytes.
+SQUARE_SHAPES = [
+    ((True, True), S.ConvLayer("q_3x3_c64_n80", 27, 35, 35, 64, 80, 3, 3, (1, 1), (1, 1))), ((True, True), S.ConvLayer("q_3x3_c52_n144", 150, 11, 10, 52, 144, 3, 3, (1, 1), (1, 1))),
+    ((True, True), S.ConvLayer("q_1x7_c160_n176", 115, 17, 17, 160, 176, 1, 7, (1, 1), (0, 3))), ((False, True), S.ConvLayer("q_3x3_c128_n272", 61, 17, 17, 128, 272, 3, 3, (1, 1), (1, 1))),
+    ((True, True), S.ConvLayer("q_3x3_s2_c96_n112", 115, 35, 35, 96, 112, 3, 3, (2, 2))), ((True, True), S.ConvLayer("q_5x5_c112_n48", 6, 78, 77, 112, 48, 5, 5, (1, 1), (2, 2))),
+]
+
+
+@pytest.mark.parametrize("takes,layer", SQUARE_SHAPES, ids=lambda v: v.name if hasattr(v, "name") else "")
+@pytest.mark.parametrize("mode", FORM_MODES, ids=lambda m: m.label)
+def test_conv_square_tiles(sq, oracle, takes, layer, mode):
+    d = sq.conv_desc(layer.B, layer.H, layer.W, layer.C, layer.N, layer.KH, layer.KW, layer.stride, layer.pad)
+    text = sq.sparq_conv_plan(d, sq.mode(*mode.astuple()))
+    gather = layer.stride != (1, 1) or layer.KH == 5                # (what is not trimmed stays with the gather kernel)
+    assert ("small_workgroups tile=128x128" in text) == (takes[0] and not (gather and mode.window_bits == 8)), text
+    assert ("u8_kernel=conv_block_kernel" in text) == (takes[1] and not (gather and mode.window_bits == 8)), text
+    check_layer(sq, oracle, layer, mode, seed_cfg=8)
+    check_layer_u8(sq, oracle, layer, mode, seed_cfg=8, out_mode=mode)
+
+
 # Each of these forms, forced by the tuning hook, in every trim variant it is built for and every form of its results: int32
 # alone, fp32 alone, both, bytes, bytes trimmed with the layer's own mode, and bytes trimmed where the input already is.
 FORM_SHAPES = [
@@ -471,8 +496,6 @@ FORM_SHAPES = [
     ("wide", S.ConvLayer("f_c528_n320", 1, 16500, 1, 528, 320)),          # the 512-wide tile
     ("block", S.ConvLayer("f_3x3_c80_n80", 2, 13, 11, 80, 80, 3, 3, (1, 1), (1, 1))), ("block", S.ConvLayer("f_5x5_c144_n48", 1, 20, 20, 144, 48, 5, 5, (1, 1), (2, 2))),
 ]
-FORM_MODES = [S.Mode(4, S.OPT5, 1, 1), S.Mode(4, S.OPT5, 1, 0), S.Mode(4, S.OPT3, 0, 1), S.Mode(4, S.OPT3, 0, 0),
-              S.Mode(3, S.OPT6_3B, 1, 0), S.Mode(2, S.OPT7_2B, 1, 1), S.Mode(2, S.OPT7_2B, 0, 1), S.PLAIN8]
 
 
 @pytest.mark.parametrize("form,layer", FORM_SHAPES, ids=lambda v: v if isinstance(v, str) else v.name)
