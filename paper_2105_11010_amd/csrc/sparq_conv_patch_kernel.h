@@ -243,8 +243,24 @@ __global__ __launch_bounds__(Cfg::kThreads, Cfg::kWgPerCu * Cfg::kThreads / 256)
     };
 
     // fragment cursor: which (kh, kw, 64-channel sub-block) the next fragment read is for
+    // (kLean: one sub-block, counted down; f_kh is then the unit's steps that are left.  The sparse form's step is half as many matrix
+    // instructions, and 40 scalar ones of cursor arithmetic stood beside its eight: 15 here.  125 drawn 2:4 layers 1.015 x, 40 x 40 x
+    // 144 -> 464 5x5 16.3 -> 14.7 us, 512 -> 288 3x3 on 39 x 39 52 -> 50; where staging is the bound, as on 32 x 32 x 512 -> 512, nothing)
+    constexpr bool kLean = SP && CBS == 1;
     int f_j = 0, f_kw = 0, f_kh = 0, f_off = 0;
+    auto reset_frag_cursor = [&]() __attribute__((always_inline)) {
+        f_j = f_off = 0;
+        f_kw = kLean ? g.KW : 0;
+        f_kh = kLean ? p.nsteps : 0;
+    };
     auto advance_frag_cursor = [&]() __attribute__((always_inline)) {
+        if constexpr (kLean) {
+            const bool wk = --f_kw == 0;
+            f_off += wk ? c_pwt16 - (g.KW - 1) * kChunk : kChunk;
+            f_kw = wk ? g.KW : f_kw;
+            f_off = --f_kh == 0 ? 0 : f_off;       // past the unit's last step (the read is not used)
+            return;
+        }
         const int sub = 4 * p.plane_stride;
         ++f_j;
         f_off += sub;
@@ -281,7 +297,28 @@ __global__ __launch_bounds__(Cfg::kThreads, Cfg::kWgPerCu * Cfg::kThreads / 256)
     const int w_half = (SP ? 1 : 2) * p.Np * kChunk;   // bytes between the two 32-index halves of a step
     const int grid_n = grid % p.tiles_n;
     int b_s = 0, b_cb = 0, b_tn = (int)blockIdx.x % p.tiles_n;
+    // kLean: runs of steps with a fixed distance (a unit's taps, or of a 1x1 layer the tile's channel blocks) of at least three
+    // steps, so that the cursor is never more than one run ahead and a run's start is worked out at the unit boundaries.
+    const int b_run = p.nsteps > 1 ? p.nsteps : p.ncb, b_runs = p.nsteps > 1 ? p.ncb : 1;
+    const int b_dist = (p.nsteps > 1 ? p.ksteps_tap : 1) * 2 * w_half;
+    int b_left = b_run, b_off = b_tn * TN * kChunk, b_start = 0;
+    auto next_b_run = [&]() __attribute__((always_inline)) {
+        ++b_cb;
+        const bool wc = b_cb == b_runs;
+        b_cb = wc ? 0 : b_cb;
+        b_tn += wc ? grid_n : 0;
+        b_tn -= b_tn >= p.tiles_n ? p.tiles_n : 0;
+        b_start = b_tn * TN * kChunk + b_cb * 2 * w_half;
+    };
+    if constexpr (kLean) next_b_run();
     auto next_b_offset = [&]() __attribute__((always_inline)) -> int {
+        if constexpr (kLean) {
+            const bool wr = b_left == 0;
+            const int at = wr ? b_start : b_off;
+            b_left = (wr ? b_run : b_left) - 1;
+            b_off = at + b_dist;
+            return at;
+        }
         const int kidx = (b_s / CBS) * p.ksteps_tap + b_cb * CBS + (b_s % CBS);
         const int off = b_tn * TN * kChunk + kidx * 2 * w_half;
         ++b_s;
@@ -465,7 +502,7 @@ __global__ __launch_bounds__(Cfg::kThreads, Cfg::kWgPerCu * Cfg::kThreads / 256)
 #pragma unroll
         for (int k = 0; k < NMF; ++k) {
             __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);                    // one matrix instruction
-            __builtin_amdgcn_sched_group_barrier(0x004, (40 + NMF - 1) / NMF, 0); // a slice of the scalar work
+            __builtin_amdgcn_sched_group_barrier(0x004, ((kLean ? 16 : 40) + NMF - 1) / NMF, 0); // a slice of the scalar work
         }
         __builtin_amdgcn_sched_barrier(0);
     };
@@ -478,7 +515,7 @@ __global__ __launch_bounds__(Cfg::kThreads, Cfg::kWgPerCu * Cfg::kThreads / 256)
     constexpr int U0 = Cfg::kUnrolled;
     auto run_unit = [&](auto P_, const uint8_t* rbuf, uint8_t* sbuf) __attribute__((always_inline)) {
         constexpr int P = decltype(P_)::value;
-        f_j = f_kw = f_kh = f_off = 0;
+        reset_frag_cursor();
         load_frags(a_frag[P], rbuf);
         advance_frag_cursor();
         auto head = [&](auto self, auto s_) __attribute__((always_inline)) {
@@ -501,6 +538,9 @@ __global__ __launch_bounds__(Cfg::kThreads, Cfg::kWgPerCu * Cfg::kThreads / 256)
     auto boundary = [&]() __attribute__((always_inline)) {
         ubuf ^= 1;
         const bool tile_done = c_cb == p.ncb - 1;
+        if constexpr (kLean) {
+            if (p.nsteps > 1 || tile_done) next_b_run();
+        }
         if (tile_done) {
             // ---- epilogue: undo the -128 offset, store int32 and/or dequantised fp32 ----
             // Register v of fragment (i, j) is pixel 8*(v/4) + 4*lhi + v%4, channel l32: each store
@@ -706,6 +746,7 @@ sparq_status launch_patch_cfg(const PatchParams& p, int npix_max, hipStream_t s)
     if (Cfg::kSparse != (p.widx != nullptr) || (Cfg::kSparse && p.out_u8)) return SPARQ_EUNSUPPORTED;
     if (!p.trim_in && !Cfg::kWaveSpecialised && KIND != kTrimNone) return SPARQ_EUNSUPPORTED;
     if ((int64_t)p.N * 4 * kPatchTM >= 0x7FFFFFFF) return SPARQ_EUNSUPPORTED;   // 32-bit offsets inside a tile of results
+    if (Cfg::kSparse && (int64_t)p.nsteps * p.ncb < (Cfg::kCBS == 1 ? 3 : 1)) return SPARQ_EUNSUPPORTED;     // (the weight cursor runs three steps ahead)
     if (npix_max > Cfg::kMaxPix || lds_bytes > kLdsPerCu || q.nsteps < Cfg::kUnrolled ||
         ((q.nsteps - Cfg::kUnrolled) & 1))
         return SPARQ_EUNSUPPORTED;
