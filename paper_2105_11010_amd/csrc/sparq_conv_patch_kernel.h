@@ -362,7 +362,69 @@ __global__ __launch_bounds__(Cfg::kThreads, Cfg::kWgPerCu * Cfg::kThreads / 256)
 
     // ---- staging wavefronts (wave-specialised form): a loop of their own, so that their registers
     //      and those of the matrix wavefronts do not add up; both loops pass the same barriers ----
-    if constexpr (WS) {
+    if constexpr (EXPAND && CBS == 1) {
+        // The three expanded blocks of a channel block are staged one after the other from one request: what does not depend on
+        // the partner -- the byte's trim beside a non-zero partner (`full`) and beside a zero one (left in a_reg) -- is worked out
+        // with the first, each block then chooses between the two by its own partners (a byte is zero where `full` is): 6
+        // vector instructions per word and block beside 17 for the three, where a whole trim for each was 22.  The next
+        // channel block is requested when the third has been written.  us: 32 x 32 x 512 -> 512 3x3,
+        // batch 64 235 -> 229 (two-bit windows 237 -> 227), 48 x 48 x 224 -> 133 1x7 24.5 -> 18.6.  That layer is bound by power: no staging at
+        // all 203, weights of one address 203, no fragment reads 203, none of the three 171.
+        if (producer) {
+            v4u full[AC];
+            int s_cb = 0, s_order = 0;                // the unit staged next
+            auto stage_unit = [&](uint8_t* buf) __attribute__((always_inline)) {
+                const uint32_t order = sparse24_pair_order(s_order), partner = sparse24_partner_flags(s_order);
+#pragma unroll
+                for (int i = 0; i < AC; ++i) {
+                    if (i * (NT / PL) < stage_npix) {             // uniform
+                        if (s_order == 0) {
+#pragma unroll
+                            for (int j = 0; j < 4; ++j) {
+                                full[i][j] = trim4_kind_beside<KIND>(a_reg[i][j], 0xFFFFFFFFu, p.luts);
+                                a_reg[i][j] = trim4_kind_beside<KIND>(a_reg[i][j], 0u, p.luts);
+                            }
+                        }
+                        v4u v;
+#pragma unroll
+                        for (int j = 0; j < 4; ++j) v[j] = sparse24_choose(full[i][j], a_reg[i][j], partner, order) ^ 0x80808080u;
+                        const int pix = my_pix + i * (NT / PL);
+                        uint8_t* dst = (pix < stage_npix) ? buf + my_loff + i * (NT / PL) * kChunk : lds + dummy_off;
+                        *reinterpret_cast<v4u*>(dst) = v;
+                    }
+                }
+                const bool tile_end = ++s_cb == p.ncb;
+                s_order = tile_end || s_order == 2 ? 0 : s_order + 1;
+                s_cb = tile_end ? 0 : s_cb;
+                if (s_order == 0) {
+                    l_cb += 3;
+                    if (tile_end) {
+                        l_cb = 0;
+                        l_tile += grid;
+                        load_tile_patch();
+                    }
+#pragma unroll
+                    for (int i = 0; i < AC; ++i) load_chunk(i);
+                    stage_npix = lt.npix;
+                }
+            };
+            load_tile_patch();
+#pragma unroll
+            for (int i = 0; i < AC; ++i) load_chunk(i);
+            stage_npix = lt.npix;
+            stage_unit(lds);
+            __syncthreads();
+            int p_tile = (int)blockIdx.x, p_cb = 0, p_buf = 0;     // the unit the matrix wavefronts are on
+            while (true) {
+                stage_unit(lds + (p_buf ^ 1) * buf_bytes);
+                p_buf ^= 1;
+                __syncthreads();
+                if (p_cb == p.ncb - 1) { p_cb = 0; p_tile += grid; } else { ++p_cb; }
+                if (p_tile >= ntiles) break;
+            }
+            return;
+        }
+    } else if constexpr (WS) {
         if (producer) {
             int s_cb = 0;                             // channel block of the unit staged next
             auto set_pair_order = [&]() __attribute__((always_inline)) {

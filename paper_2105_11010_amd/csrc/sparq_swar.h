@@ -135,6 +135,10 @@ SPARQ_HD uint32_t lerp(uint32_t a, uint32_t b, uint32_t c) {
 // partition j: j = 0: 01|23, 1: 02|13, 2: 03|12.
 SPARQ_HD uint32_t sparse24_pair_order(int j) { return j == 0 ? 0x03020100u : j == 1 ? 0x03010200u : 0x02010300u; }
 
+// Selector (for perm(f << 8, f, .), f with a flag in bit 7 of every byte) that puts the flag of each byte's partner in partition j
+// over the byte.
+SPARQ_HD uint32_t sparse24_partner_flags(int j) { return j == 0 ? 0x0B090A08u : j == 1 ? 0x080A090Bu : 0x0A080B09u; }
+
 SPARQ_HD uint32_t bfi(uint32_t mask, uint32_t a, uint32_t b) { return (mask & a) | (~mask & b); }
 
 // 0xFF in every byte whose bit 7 is set in f
@@ -143,6 +147,13 @@ SPARQ_HD uint32_t expand_bit7(uint32_t f) { return perm(f << 8, f, 0x090B080Au);
 SPARQ_HD uint32_t expand_bit7_swapped(uint32_t f) { return perm(f << 8, f, 0x0B090A08u); }
 // bit 7 of each byte = (byte != 0); other bits unspecified
 SPARQ_HD uint32_t nonzero_flag(uint32_t v) { return lerp(v, 0xFFFFFFFFu, 0u); }
+
+// The trim of four channels in partition j, in its byte order, from their trims beside non-zero partners (`full`: zero exactly where the
+// channel is, since every window holds the leading one) and beside zero ones (`alone`).
+SPARQ_HD uint32_t sparse24_choose(uint32_t full, uint32_t alone, uint32_t partner, uint32_t order) {
+    const uint32_t f = nonzero_flag(full);
+    return perm(0, bfi(perm(f << 8, f, partner), full, alone), order);
+}
 
 SPARQ_HD uint32_t low_mask(uint32_t selA, uint32_t selB, uint32_t a_hi, uint32_t a_lo, uint32_t b_hi,
                            uint32_t b_lo) {

@@ -13,3 +13,22 @@ extern "C" void swar_all_pairs(int n, unsigned S, int round_nearest, int pair, u
             for (int i = 0; i < 4; ++i) out[4 * (a * 256 + b) + i] = (unsigned char)(y >> (8 * i));
         }
 }
+
+// 2:4 groups of four: words[k] trimmed in partition j, in its byte order; out[0][j][k] from one pair of trims, out[1][j][k] by
+// a trim of the reordered word.
+extern "C" void swar_partitions(int n, unsigned S, int round_nearest, const uint32_t* words, int count, uint32_t* out) {
+    using namespace sparq;
+    const TrimLuts L = make_luts(n, S);
+    for (int k = 0; k < count; ++k) {
+        const uint32_t x = words[k];
+        const auto beside = [&](uint32_t pm) {
+            if (n == 4) return round_nearest ? trim4_round_n4_beside<true>(x, pm, L) : trim4_beside<false, true, false>(x, pm, L);
+            return round_nearest ? trim4_beside<true, true, true>(x, pm, L) : trim4_beside<false, true, true>(x, pm, L);
+        };
+        const uint32_t full = beside(0xFFFFFFFFu), alone = beside(0u);
+        for (int j = 0; j < 3; ++j) {
+            out[j * count + k] = sparse24_choose(full, alone, sparse24_partner_flags(j), sparse24_pair_order(j));
+            out[(3 + j) * count + k] = trim4_any(perm(0, x, sparse24_pair_order(j)), L, round_nearest != 0, true);
+        }
+    }
+}

@@ -34,3 +34,17 @@ def test_packed_trim_equals_oracle_on_all_pairs(oracle, swar, n, mask, rnd, pair
     x = np.stack([a, b, b, a], axis=-1).reshape(-1, 4)
     exp = oracle.trim(x, n, mask, rnd, pairing).reshape(256, 256, 4)
     assert np.array_equal(out, exp)
+
+
+@pytest.mark.parametrize("n,mask", MODES)
+@pytest.mark.parametrize("rnd", [0, 1])
+def test_partitions_of_four_from_one_pair_of_trims(oracle, swar, n, mask, rnd):
+    """Every value beside every value and zero, in each of the four places and three partitions of a 2:4 group."""
+    if oracle.mode_check(n, mask, rnd, 1):
+        pytest.skip("mode not valid with pairing")
+    a, b = np.meshgrid(np.arange(256, dtype=np.uint32), np.arange(256, dtype=np.uint32), indexing="ij")
+    words = np.concatenate([(a | b << 8 | (a ^ 255) << 16 | b << 24).ravel(), (a | b << 16).ravel(), (a << 8 | b << 24).ravel(),
+                            (a << 24 | b).ravel(), (a << 8 | b << 16).ravel()]).astype(np.uint32)
+    out = np.empty((2, 3, words.size), dtype=np.uint32)
+    swar.swar_partitions(n, mask, rnd, words.ctypes.data_as(ctypes.c_void_p), ctypes.c_int(words.size), out.ctypes.data_as(ctypes.c_void_p))
+    assert np.array_equal(out[0], out[1])
