@@ -1021,12 +1021,15 @@ const sparq_mode kNoPairPlain = {8, 1, 0, 0};
 // The trim of the contracted layer (a padded copy's pre-pass does it where there is one; single activations either way).
 TrimKind sparse24_kind(const ConvGeom& g, const sparq_mode* mode) { return g.fold ? kTrimNone : trim_kind(mode); }
 
-// The staging wavefronts expand what they load where a tile's patch is small beside its taps: each patch pixel is then
-// trimmed three times per 64 channels and channel tile, which the matrix instructions of its taps have to cover (3x3 on 32 x
-// 32 pixels, 204 patch pixels: 357 -> 241 us; strided 1x7 on 12 x 12 54 -> 108).  Elsewhere the expanded tensor is written first.
+// The staging wavefronts expand what they load where a tile's patch is small beside its taps (each patch pixel is then worked out
+// once per channel tile, which the matrix instructions of its taps have to cover) or where there are tiles for every CU, so that the
+// expanded tensor would be written to memory and read back.  Elsewhere it is written first.  Of 200 drawn layers of more than 32
+// patch pixels per tap: up to 50 of them in units of 64 channels 1.24 x faster than written (59, one slower, 0.94 x; 39 x 39 x 192 ->
+// 608 1x7 75 -> 58 us); beyond, from 8192 pixels on 1.36 x (45, none slower; 51 x 51 x 272 -> 128 7x1, 7803 pixels 36 against 39, and
+// fewer pixels down to 0.59 x: a strided 7x1 on 196 pixels 37 against 63); 1x1 layers in wider units 1.6 x from there on, 0.6-1.2 x below.
 // `pl`: the plan of the expanded layer.
 bool expands_while_staging(const sparq_conv_desc& desc, const ConvPlan& pl) {
-    return sparse24_blocked(desc.C) && sparse_plan(pl, kTrimNone) && pl.npix <= 32 * desc.KH * desc.KW;
+    return sparse24_blocked(desc.C) && sparse_plan(pl, kTrimNone) && (pl.npix <= (pl.cbs == 1 ? 50 : 32) * desc.KH * desc.KW || pl.pg.M >= 8192);
 }
 
 // Layout of the buffer sparq_pack_weights_sparse24 fills: the dense packed tiles of the contracted problem, room

@@ -149,6 +149,15 @@ STAGING_LAYERS = [
     (256, S.ConvLayer("blk_1x1_576_40", 1, 3, 9, 576, 40, 1, 1, (1, 1), (0, 0), 0.5, M45)),         # 27 blocks and one of zeros
     (256, S.ConvLayer("blk_1x1_512_64_floor", 1, 31, 1, 512, 64, 1, 1, (1, 1), (0, 0), 0.4, S.Mode(4, S.OPT2, 0, 1))),
 ]
+# ... and the larger patches that are expanded while staging: up to 50 pixels per tap, any from 8192 pixels on (units of one, two and
+# four blocks, tiles of several images, a last tile that is partly empty).
+LARGE_STAGING_LAYERS = [
+    (64, S.ConvLayer("blk_1x7_56_192_40", 2, 15, 17, 192, 40, 1, 7, (1, 1), (0, 3), 0.5, M45)),
+    (64, S.ConvLayer("blk_3x3s2_112_65_2bit", 29, 35, 33, 112, 65, 3, 3, (2, 2), (1, 1), 0.6, S.Mode(2, S.OPT7_2B, 1, 1))),
+    (64, S.ConvLayer("blk_7x1_64_72_floor", 32, 17, 17, 64, 72, 7, 1, (1, 1), (3, 0), 0.5, S.Mode(4, S.OPT3, 0, 1))),
+    (128, S.ConvLayer("blk_1x1_128_70_many", 1, 8201, 1, 128, 70, 1, 1, (1, 1), (0, 0), 0.5, S.Mode(3, S.OPT6_3B, 1, 1))),
+    (256, S.ConvLayer("blk_1x1s2_256_136_many", 9, 61, 63, 256, 136, 1, 1, (2, 2), (0, 0), 0.5, M45)),
+]
 WRITTEN_LAYERS = [
     S.ConvLayer("blk_1x1_576_70", 1, 9, 11, 576, 70, 1, 1, (1, 1), (0, 0), 0.5, M45),           # 27 blocks and one of zeros
     S.ConvLayer("blk_1x1_176_136", 2, 15, 15, 176, 136, 1, 1, (1, 1), (0, 0), 0.5, S.Mode(4, S.OPT3, 0, 1)),
@@ -176,6 +185,21 @@ def check_blocked_layer(sq, oracle, layer, stream, staging, unit=None):
             assert np.all(np.abs(out.astype(np.float64) - ref_out) <= 1e-6 * np.abs(ref_out)), plan
     finally:
         sq.sparq_set_tuning(None)
+
+
+@pytest.mark.parametrize("unit,layer", LARGE_STAGING_LAYERS, ids=lambda v: v.name if isinstance(v, S.ConvLayer) else f"unit{v}")
+def test_sparse24_large_patches_expanded_while_staging(sq, oracle, unit, layer):
+    d = sq.conv_desc(layer.B, layer.H, layer.W, layer.C, layer.N, layer.KH, layer.KW, layer.stride, layer.pad)
+    plan = sq.sparq_sparse24_plan(d, sq.mode(*layer.mode.astuple()))
+    assert "expanded_while_staging" in plan and f"unit_channels={unit} " in plan, plan
+    rng = S.rng_for(10, 400 + [l for _, l in LARGE_STAGING_LAYERS].index(layer))
+    x = S.gen_activations(layer.x_shape(), layer.zf, rng)
+    wv, wi = S.gen_sparse24_weights(layer.w_shape(), rng)
+    sc = S.gen_scales(layer.N, rng)
+    ref_acc, ref_out = oracle.conv_gemm_sparse24(x, wv, wi, layer.stride, layer.pad, scale=sc, **layer.mode.kwargs())
+    acc, out = run_sparse(sq, layer, x, wv, wi, sc)
+    assert np.array_equal(acc, ref_acc), plan
+    assert np.all(np.abs(out.astype(np.float64) - ref_out) <= 1e-6 * np.abs(ref_out)), plan
 
 
 @pytest.mark.parametrize("unit,layer", STAGING_LAYERS, ids=lambda v: v.name if isinstance(v, S.ConvLayer) else f"unit{v}")
