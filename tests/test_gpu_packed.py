@@ -125,6 +125,21 @@ def test_convolution_on_packed_input(sq, oracle, layer, group):
         assert torch.equal(acc, acc2)
 
 
+# Channel counts that are no multiple of four unpack into the channel-padded tensor: one and several records a row, a last record
+# of one channel and of all but one, counts below a 16-channel word, every form of the contraction, and a folded first layer.
+@pytest.mark.parametrize("layer,group", [
+    (S.ConvLayer("p_1x1_315_224", 3, 19, 19, 315, 224, 1, 1, (1, 1), (0, 0), 0.5, S.Mode(4, S.OPT3, 0, 1)), 1),
+    (S.ConvLayer("p_1x1s2_549_33", 1, 97, 33, 549, 33, 1, 1, (2, 2), (0, 0), 0.5, S.Mode(4, S.OPT5, 1, 0)), 8),
+    (S.ConvLayer("p_3x3_33_40", 2, 11, 9, 33, 40, 3, 3, (1, 1), (1, 1), 0.5, S.Mode(2, S.OPT7_2B, 1, 1)), 1),
+    (S.ConvLayer("p_3x3_63_96", 25, 35, 35, 63, 96, 3, 3, (1, 1), (1, 1), 0.5, S.Mode(4, S.OPT5, 1, 1)), 1),
+    (S.ConvLayer("p_5x5_17_20", 2, 13, 12, 17, 20, 5, 5, (1, 1), (2, 2), 0.5, S.Mode(3, S.OPT6_3B, 0, 0)), 32),
+    (S.ConvLayer("p_3x3_6_12", 2, 9, 7, 6, 12, 3, 3, (1, 1), (1, 1), 0.5, S.Mode(4, S.OPT3, 0, 1)), 1),
+    (S.ConvLayer("p_1x1_3_8", 2, 9, 7, 3, 8, 1, 1, (1, 1), (0, 0), 0.5, S.Mode(4, S.OPT5, 1, 1)), 1),
+    (S.ConvLayer("p_7x7s2_3_64", 1, 28, 28, 3, 64, 7, 7, (2, 2), (3, 3), 0.5, S.Mode(4, S.OPT5, 1, 1)), 1)], ids=lambda v: getattr(v, "name", v))
+def test_convolution_on_packed_input_of_any_width(sq, oracle, layer, group):
+    test_convolution_on_packed_input(sq, oracle, layer, group)
+
+
 @pytest.mark.parametrize("mode,group", [((4, S.OPT5, 1, 1), 1), ((4, S.OPT3, 0, 1), 1), ((4, S.OPT5, 1, 0), 8)], ids=str)
 def test_calls_larger_than_the_last_level_cache(sq, mode, group):
     """More than 256 MiB moved: unpacking goes through LDS; the last wavefront holds fewer than 64 records."""
