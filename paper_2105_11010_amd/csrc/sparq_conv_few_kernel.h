@@ -320,6 +320,10 @@ inline int64_t few_patch_bytes(const ConvGeom& g, int taps_row, int tm) {
     return rows * (d > 0 ? full : single < full ? single : full) * kChunk;
 }
 
+// A tile's results are addressed in 32 bits, and kPatchInvalidOffset has to lie beyond them for a column past N to be dropped (as it
+// has to lie beyond the weights for a row past the filter's last to read zeros).
+inline bool few_addressable(int N, bool bytes, int tm) { return (int64_t)tm * N * (bytes ? 1 : 4) < 0x7FFFFFFF; }
+
 inline FewGeom few_geom(const ConvGeom& g, bool bytes, int cus) {
     FewGeom f{};
     if (!g.fold || (bytes && g.N % 16)) return f;
@@ -327,7 +331,7 @@ inline FewGeom few_geom(const ConvGeom& g, bool bytes, int cus) {
     f.taps_row = (words + 3) / 4;
     const int steps = (g.KH * f.taps_row + 1) / 2;
     if (f.taps_row > 2 || steps > 8) return f;
-    if (g.M > (1 << 30) || ((int64_t)g.B * g.H + 2 * (int64_t)g.B * g.ph) > (1 << 30) || g.N > (1 << 20)) return f;
+    if (g.M > (1 << 30) || ((int64_t)g.B * g.H + 2 * (int64_t)g.B * g.ph) > (1 << 30) || g.N > (1 << 20) || (size_t)g.Kp * g.Np >= kPatchInvalidOffset) return f;
     // Four-byte results of many outputs beside a short reduction are bound by their stores, which the gather kernel's wider tiles make
     // in longer runs (3x3, 1.6 M pixels -> 192 / 256 / 384: 246 against 239 us, 316 against 295, 478 against 442; -> 128 167 against 173),
     // and up to 32 of them leave half of a 64-column tile empty (5x5, 262144 pixels -> 32: 15.1 against 13.4).
@@ -338,6 +342,7 @@ inline FewGeom few_geom(const ConvGeom& g, bool bytes, int cus) {
     // 10), or, for four-byte results, whose stores want many tiles in flight, 12 (401408 pixels 22 / 22 / 25 / 24; 3.2 M 175 / 167 / 159 / 144).
     for (int tm = 1024; tm >= 128; tm /= 2) {
         const int64_t patch_bytes = few_patch_bytes(g, f.taps_row, tm);
+        if (!few_addressable(g.N, bytes, tm)) continue;
         if (2 * patch_bytes + (bytes ? kFewTurnBytes : 0) > kFewLds) continue;
         f.tm = tm;
         f.patch_bytes = (int)patch_bytes;
@@ -349,6 +354,7 @@ inline FewGeom few_geom(const ConvGeom& g, bool bytes, int cus) {
 
 template <int STEPS, int C, bool U8, bool EVEN>
 sparq_status launch_few_cfg(const FewParams& p, hipStream_t s) {
+    if (!few_addressable(p.N, U8, p.tm) || p.w_bytes >= kPatchInvalidOffset) return SPARQ_EUNSUPPORTED;
     const int columns = (p.N + kFewTN - 1) / kFewTN, slots = 2 * device_cu_count() / columns;
     const dim3 grid((unsigned)(p.tiles < slots ? p.tiles : slots > 0 ? slots : 1), (unsigned)columns);
     const int lds_bytes = (U8 ? kFewTurnBytes : 0) + 2 * p.patch_bytes;

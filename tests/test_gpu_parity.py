@@ -343,6 +343,32 @@ def test_conv_few_channels(sq, oracle, layer, mode):
     check_layer_u8(sq, oracle, layer, mode, seed_cfg=8, out_mode=mode if layer.N == 64 else None)
 
 
+def test_few_channels_beside_half_a_million_outputs(sq, oracle):
+    """The widest results: 1024 of these rows are 2^31 bytes and more, so tiles of 1024 pixels would store what is past N inside the
+    tensor.  Every int32 and fp32 result against exact sums in double precision of the oracle's trimmed input."""
+    layer, mode = S.ConvLayer("f_5x3_c2_n524304", 1, 32, 32, 2, 524304, 5, 3, (1, 1), (2, 1)), S.Mode(4, S.OPT5, 1, 1)
+    d = sq.conv_desc(layer.B, layer.H, layer.W, layer.C, layer.N, layer.KH, layer.KW, layer.stride, layer.pad)
+    m = sq.mode(*mode.astuple())
+    text = sq.sparq_conv_plan(d, m)
+    assert "few_channels tile=512x64" in text, text
+    x, w, sc = S.gen_layer(8, layer)
+    wd, sd = dev(w), dev(sc)
+    packed = torch.empty(sq.sparq_packed_bytes(d), dtype=torch.uint8, device="cuda:0")
+    sq.sparq_pack_weights(wd, d, packed)
+    ws = torch.empty(sq.sparq_workspace_bytes(d, m), dtype=torch.uint8, device="cuda:0")
+    acc = torch.full((layer.M, layer.N), -7, dtype=torch.int32, device="cuda:0")
+    out = torch.full((layer.M, layer.N), -7.0, dtype=torch.float32, device="cuda:0")
+    sq.sparq_conv_gemm(dev(x), packed, d, m, acc=acc, scale=sd, out=out, workspace=ws)
+    torch.cuda.synchronize()
+    rows = torch.nn.functional.unfold(dev(oracle.trim(x, **mode.kwargs())).double().permute(0, 3, 1, 2), (5, 3), padding=(2, 1))[0].T.contiguous()
+    cols = wd.double().permute(0, 3, 1, 2).reshape(layer.N, -1)
+    for n in range(0, layer.N, 1 << 16):
+        at = slice(n, n + (1 << 16))
+        ref = (rows @ cols[at].T.contiguous()).to(torch.int32)
+        assert torch.equal(acc[:, at], ref), n
+        assert torch.equal(out[:, at], ref.float() * sd[at]), n          # two roundings to nearest, as defined
+
+
 # The split-reduction form (small layers): its three tiles; fewer reduction steps than wavefronts, shares of unequal
 # length, ragged tiles, padded channels, images that share a tile, a patch that fills most of LDS.
 SPLIT_SHAPES = [

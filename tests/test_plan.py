@@ -207,6 +207,17 @@ def test_small_workgroups_only_where_they_can_be_launched(lib):
             assert ("small_workgroups" in text) == small, text
 
 
+def test_few_channel_tiles_stay_inside_32_bit_offsets(lib):
+    """Layers of at most four channels: a tile's four-byte results are addressed in 32 bits, with 2^31 as the offset of what is to be
+    dropped, so wider layers get lower tiles.  So are the packed weights: 2 GiB of them are for the gather kernel."""
+    for n, height in ((262144, 1024), (524287, 1024), (524288, 512), (524304, 512), (600016, 512), (1048575, 512), (1 << 20, 256)):
+        text, _, packed = plan(lib, S.ConvLayer("few", 1, 32, 32, 3, n, 5, 5, (1, 1), (2, 2)), S.Mode(4, S.OPT5, 1, 1))
+        assert f"few_channels tile={height}x64" in text and packed - 16 * n < 1 << 31, text
+    for n, few in (((1 << 20) - 64, True), (1 << 20, False)):        # 15 rows of two taps of 16 bytes for each of 4 n columns
+        text, _, packed = plan(lib, S.ConvLayer("tall", 1, 32, 32, 4, n, 15, 1, (1, 1), (7, 2)), S.Mode(4, S.OPT5, 1, 1))
+        assert (packed - 16 * n < 1 << 31) == few and words(text, "kernel=") == ["conv_few_kernel" if few else "conv_gemm_kernel"], text
+
+
 def test_layers_in_turn_do_not_walk_their_tiles_again(lib):
     """The largest patch of a layer comes from a walk over its tile positions (193 us for 147 x 147 pixels) and is kept per
     geometry.  These two geometries share the low nine bits of the cache's hash: called in turn, neither pushes the other out."""
