@@ -336,6 +336,16 @@ inline FewGeom few_geom(const ConvGeom& g, bool bytes, int cus) {
     // in longer runs (3x3, 1.6 M pixels -> 192 / 256 / 384: 246 against 239 us, 316 against 295, 478 against 442; -> 128 167 against 173),
     // and up to 32 of them leave half of a 64-column tile empty (5x5, 262144 pixels -> 32: 15.1 against 13.4).
     if (!bytes && ((g.N > 128 && steps <= 3 && g.M * g.N * 4 >= kStreamedBytes) || (g.N <= 32 && steps > 3 && g.M > 64 * 1024))) return f;
+    // Its folded rows of fold_p * N results are also whole 64-byte lines where the layer's own rows are not (`whole`), which counts for
+    // more than its copy from 32 to 128 MiB of results on; where neither are, its longer runs do from 128 MiB on; and of few outputs it works out
+    // four pixels' side by side where this kernel leaves nearly all of its columns empty.  1160 timed layers of 1 to 384 outputs, 20000 to 3 M
+    // pixels: 248 of them go back to it by these lines, on which this kernel took 1.28 x its time (7x7, 259000 pixels -> 300 181 against
+    // 76 us; 5x3, 752928 -> 108 203 against 86; 1x7, 631120 -> 5 28.6 against 17.0; 3x3, 196800 -> 14 even).
+    if (!bytes && g.sw == 1 && g.M > 176 * 1024 && g.N <= (g.N % 4 ? 16 : 32)) return f;
+    if (!bytes && g.N % 16 != 0 && g.sw < 4) {
+        const bool whole = g.fold_p * g.N % 16 == 0;
+        if ((whole || g.N > 64) && g.M * g.N * 4 >= ((int64_t)(!whole || g.N <= 64 ? 128 : g.sw == 1 ? 32 : 48) << 20)) return f;
+    }
     const int64_t columns = (g.N + kFewTN - 1) / kFewTN;
     // The larger the tile, the fewer of its input rows belong to two tiles; smaller ones only while there are not 1.5 of them per CU
     // (three channels, 7x7, bytes: 3.2 M pixels 129 / 96 / 80 / 76 us at 128 / 256 / 512 / 1024 pixels, 12544 pixels 5.0 / 5.7 / 7.0 /

@@ -210,12 +210,29 @@ def test_small_workgroups_only_where_they_can_be_launched(lib):
 def test_few_channel_tiles_stay_inside_32_bit_offsets(lib):
     """Layers of at most four channels: a tile's four-byte results are addressed in 32 bits, with 2^31 as the offset of what is to be
     dropped, so wider layers get lower tiles.  So are the packed weights: 2 GiB of them are for the gather kernel."""
-    for n, height in ((262144, 1024), (524287, 1024), (524288, 512), (524304, 512), (600016, 512), (1048575, 512), (1 << 20, 256)):
+    for n, height in ((262144, 1024), (524272, 1024), (524288, 512), (524304, 512), (600016, 512), (1048560, 512), (1 << 20, 256)):
         text, _, packed = plan(lib, S.ConvLayer("few", 1, 32, 32, 3, n, 5, 5, (1, 1), (2, 2)), S.Mode(4, S.OPT5, 1, 1))
         assert f"few_channels tile={height}x64" in text and packed - 16 * n < 1 << 31, text
     for n, few in (((1 << 20) - 64, True), (1 << 20, False)):        # 15 rows of two taps of 16 bytes for each of 4 n columns
         text, _, packed = plan(lib, S.ConvLayer("tall", 1, 32, 32, 4, n, 15, 1, (1, 1), (7, 2)), S.Mode(4, S.OPT5, 1, 1))
         assert (packed - 16 * n < 1 << 31) == few and words(text, "kernel=") == ["conv_few_kernel" if few else "conv_gemm_kernel"], text
+
+
+@pytest.mark.parametrize("b,h,w,c,n,k,stride,pad,takes", [
+    # few outputs of many pixels: the gather kernel works out four pixels' side by side
+    (14, 230, 196, 4, 5, (1, 7), 1, (0, 3), False), (2, 230, 196, 4, 5, (1, 7), 1, (0, 3), True), (9, 150, 148, 2, 14, (3, 3), 1, (1, 1), False),
+    (9, 150, 148, 2, 16, (3, 3), 1, (1, 1), False), (9, 150, 148, 2, 17, (3, 3), 1, (1, 1), True), (9, 150, 148, 2, 32, (3, 3), 1, (1, 1), False),
+    (9, 150, 148, 2, 36, (3, 3), 1, (1, 1), True), (36, 150, 148, 2, 5, (3, 1), 2, (1, 0), True),
+    # rows off a 64-byte border: stored by whole lines as the folded rows of the gather kernel
+    (16, 128, 128, 1, 300, (3, 3), 1, (1, 1), False), (2, 128, 128, 1, 300, (7, 7), 1, (3, 3), False), (1, 128, 128, 1, 300, (7, 7), 1, (3, 3), True),
+    (16, 128, 128, 1, 304, (7, 7), 1, (3, 3), True), (16, 128, 128, 1, 60, (3, 3), 1, (1, 1), True), (40, 128, 128, 1, 60, (3, 3), 1, (1, 1), False),
+    (16, 256, 256, 3, 120, (7, 7), 2, (3, 3), False), (4, 256, 256, 3, 120, (7, 7), 2, (3, 3), True), (32, 128, 128, 1, 65, (3, 3), 1, (1, 1), False),
+    (16, 128, 128, 1, 65, (3, 3), 1, (1, 1), True), (40, 128, 128, 1, 61, (3, 3), 1, (1, 1), True), (16, 256, 256, 3, 200, (4, 4), 4, (0, 0), True)], ids=str)
+def test_few_channel_layers_the_gather_kernel_is_ahead_on(lib, b, h, w, c, n, k, stride, pad, takes):
+    """Both sides of the lines at which four-byte results go to the folded gather kernel; bytes stay."""
+    text = plan(lib, S.ConvLayer("few", b, h, w, c, n, *k, (stride, stride), pad), S.Mode(4, S.OPT5, 1, 1))[0]
+    assert words(text, "kernel=") == ["conv_few_kernel" if takes else "conv_gemm_kernel"], text
+    assert n % 16 or words(text, "u8_kernel=") == ["conv_few_kernel"], text
 
 
 def test_layers_in_turn_do_not_walk_their_tiles_again(lib):
