@@ -472,16 +472,28 @@ ConvPlan make_plan_of(const ConvGeom& g, const Tuning& tune, bool forms, bool by
     return pl;
 }
 
+// What trimming while staging adds to a tile kernel, against the copy: the trim's instructions for the patch beyond those that the taps'
+// matrix instructions cover, tile after tile on the busiest CU, and a launch and the tensor written and read once more (1/32 ns and
+// 2 us + 0.25 ns per KB).  Of 950 timed layers with up to 2500 channels none is left more than 5 % behind the better of the two; where all
+// were trimmed in place 119 of the first 500 were, by up to 2.3 x (15 x 15 x 1396 -> 96 1x7/2, seven images, three-bit windows, 38 against
+// 86 us; 7 x 7 x 2148 -> 349 1x7/2, sixteen, 57 against 112: few tiles, each a patch of its own, leave the trim to a few CUs).
+bool staging_outlasts_copy(const ConvGeom& g, const ConvPlan& pl, TrimKind kind) {
+    static const int instructions[kTrimKinds] = {0, 40, 48, 64, 80, 128, 68, 84};          // for 16 bytes (the first by its timings: it has 32)
+    const int64_t tn = pl.variant->tn, tiles = (g.M + kPatchTM - 1) / kPatchTM * ((g.N + tn - 1) / tn), cus = device_cu_count();
+    const int64_t beyond = (int64_t)pl.npix * instructions[kind] - (int64_t)34 * g.KH * g.KW * (tn < 128 ? tn : 128);
+    return (tiles + cus - 1) / cus * (g.Cq / kStepK) * beyond > 64000 + (int64_t)g.x_bytes / 125;
+}
+
 // Channel counts that are no multiple of four are contracted from a channel-padded copy, trimmed as it is written.  The others are
 // read where they are: a pixel's 16-byte words then start on any four-byte border, which is all a load asks for; the last one runs
 // into the next pixel (or past the tensor, where it reads 0) and meets weights that are 0 there; pairs stay inside the pixel.
 // 670 drawn layers 1.28 x faster than from the copy (38851 x 188 -> 96 13 -> 6 us; 65536 x 516 -> 256 38 -> 28; 244 -> 256 3x3, 50176
 // pixels 45 -> 39), but for the few whose kernel would trim the same bytes over and over, which keep the copy: several taps in the
 // gather kernel (5x5 on 69 x 69 x 264 52 against 97 us), 128-pixel tiles of long 1x1 reductions for less than half the CUs
-// (2978 x 4312 -> 304 29 against 39), and, the trims with the most arithmetic (windows of two or three bits with rounding, 25
-// instructions for four bytes), tile kernels that stage more than five bytes for one of x (35 x 35 x 908 -> 736 3x3/2 45 against 66),
-// five column tiles of the eight-wavefront form (9167 x 1276 -> 1216 32 against 38) and long reductions of the split form, which
-// stages all of its patch before the first product (154 x 3364 -> 656 10.6 against 12.4).
+// (2978 x 4312 -> 304 29 against 39), tile kernels whose staging is the longer side (above), and, the trims with the most arithmetic
+// (windows of two or three bits with rounding, 20 and 32 instructions for four bytes), tile kernels that stage more than five bytes for
+// one of x (35 x 35 x 908 -> 736 3x3/2 45 against 66), five column tiles of the eight-wavefront form (9167 x 1276 -> 1216 32 against 38)
+// and long reductions of the split form, which stages all of its patch before the first product (154 x 3364 -> 656 10.6 against 12.4).
 ConvPlan make_plan(const ConvGeom& g, const Tuning& tune, bool forms = true, bool bytes = false, TrimKind kind = kTrimFloor) {
     const bool pads = !g.fold && g.Cp != g.C, trims = kind != kTrimNone;
     if (!pads || g.C % 4 == 0) {
@@ -493,10 +505,10 @@ ConvPlan make_plan(const ConvGeom& g, const Tuning& tune, bool forms = true, boo
         bool once = gather && g.KH * g.KW > 1;
         if (pl.split && !tune.form) once = costly ? g.K >= 1800 : kind == kTrimRoundPair4 && g.K >= 8000;
         if (pl.wide && !tune.form) once = tiles_m * ((g.N + 255) / 256) * 2 < device_cu_count();
-        if (costly) {
-            if (pl.wide && !tune.form) once = once || (g.N + pl.wide->tn - 1) / pl.wide->tn >= 5;
-            else if (pl.patch && !pl.split && !pl.block && !pl.rows)
-                once = tiles_m * ((g.N + pl.variant->tn - 1) / pl.variant->tn) * pl.npix > (int64_t)5 * g.B * g.H * g.W;
+        if (costly && pl.wide && !tune.form) once = once || (g.N + pl.wide->tn - 1) / pl.wide->tn >= 5;
+        if (pl.patch && !pl.wide && !pl.split && !pl.block && !pl.rows) {
+            const int64_t staged = tiles_m * ((g.N + pl.variant->tn - 1) / pl.variant->tn) * pl.npix;
+            once = (costly && staged > (int64_t)5 * g.B * g.H * g.W) || staging_outlasts_copy(g, pl, kind);
         }
         if (!once) return pl;
     }

@@ -484,6 +484,18 @@ def test_conv_channels_in_words(sq, oracle, kernel, copy, layer, mode):
     check_layer_u8(sq, oracle, layer, mode, seed_cfg=8, out_mode=mode if layer.N % 16 == 0 else S.Mode(4, S.OPT5, 1, 1))
 
 
+# The tile kernels' layers of that kind which keep the copy because their staging would be the longer side.
+@pytest.mark.parametrize("layer", [S.ConvLayer("a_copy_1x7_c1396", 3, 15, 15, 1396, 96, 1, 7, (2, 2), (0, 3)), S.ConvLayer("a_copy_3x3_c1016", 2, 31, 5, 1016, 18, 3, 3, (2, 2))],
+                         ids=lambda l: l.name)
+@pytest.mark.parametrize("mode", [S.Mode(4, S.OPT5, 1, 1), S.Mode(2, S.OPT7_2B, 1, 1)], ids=lambda m: m.label)
+def test_conv_channels_in_words_copied(sq, oracle, layer, mode):
+    d = sq.conv_desc(layer.B, layer.H, layer.W, layer.C, layer.N, layer.KH, layer.KW, layer.stride, layer.pad)
+    text = sq.sparq_conv_plan(d, sq.mode(*mode.astuple()))
+    assert "padded_copy" in text and " kernel=conv_patch_kernel" in text, text
+    check_layer(sq, oracle, layer, mode, seed_cfg=8)
+    check_layer_u8(sq, oracle, layer, mode, seed_cfg=8, out_mode=mode)
+
+
 FORM_MODES = [S.Mode(4, S.OPT5, 1, 1), S.Mode(4, S.OPT5, 1, 0), S.Mode(4, S.OPT3, 0, 1), S.Mode(4, S.OPT3, 0, 0),
               S.Mode(3, S.OPT6_3B, 1, 0), S.Mode(2, S.OPT7_2B, 1, 1), S.Mode(2, S.OPT7_2B, 0, 1), S.PLAIN8]
 

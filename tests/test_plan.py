@@ -235,6 +235,21 @@ def test_few_channel_layers_the_gather_kernel_is_ahead_on(lib, b, h, w, c, n, k,
     assert n % 16 or words(text, "u8_kernel=") == ["conv_few_kernel"], text
 
 
+@pytest.mark.parametrize("shape,k,stride,pad,mode,copy", [
+    # few tiles, each with a patch of its own beside few taps' products: the trim of many channels would be left to a few CUs
+    ((7, 15, 15, 1396, 96), (1, 7), 2, (0, 3), S.Mode(3, S.OPT6_3B, 1, 1), True), ((16, 7, 7, 2148, 349), (1, 7), 2, (0, 3), S.Mode(4, S.OPT5, 1, 1), True),
+    ((10, 5, 63, 836, 320), (1, 7), 2, (0, 0), S.Mode(4, S.OPT5, 1, 1), True), ((6, 7, 17, 980, 32), (7, 1), 3, (0, 0), S.Mode(4, S.OPT3, 0, 1), True),
+    ((6, 8, 8, 892, 320), (7, 1), 3, (3, 0), S.Mode(4, S.OPT5, 0, 0), True), ((5, 31, 5, 1016, 18), (3, 3), 2, (0, 0), S.Mode(2, S.OPT7_2B, 1, 1), True),
+    # ... against short reductions, patches that the taps reuse, tiles for every CU, nothing to trim
+    ((128, 15, 15, 60, 96), (1, 7), 2, (0, 3), S.Mode(4, S.OPT5, 1, 1), False), ((16, 14, 14, 1396, 96), (3, 3), 1, (1, 1), S.Mode(4, S.OPT5, 1, 1), False),
+    ((64, 28, 28, 244, 256), (3, 3), 1, (1, 1), S.Mode(4, S.OPT5, 1, 1), False), ((16, 7, 7, 2148, 349), (1, 7), 2, (0, 3), S.PLAIN8, False),
+    ((64, 12, 12, 1000, 96), (3, 3), 1, (1, 1), S.Mode(4, S.OPT5, 0, 0), False)], ids=str)
+def test_tile_kernels_that_would_trim_longer_than_a_copy_takes(lib, shape, k, stride, pad, mode, copy):
+    """Channel counts in whole words are read where they are, except by a tile kernel whose staging is the longer side then."""
+    text = plan(lib, S.ConvLayer("words", *shape, *k, (stride, stride), pad), mode)[0]
+    assert words(text, "kernel=") == ["conv_patch_kernel"] and ("padded_copy" in text) == copy, text
+
+
 def test_layers_in_turn_do_not_walk_their_tiles_again(lib):
     """The largest patch of a layer comes from a walk over its tile positions (193 us for 147 x 147 pixels) and is kept per
     geometry.  These two geometries share the low nine bits of the cache's hash: called in turn, neither pushes the other out."""
