@@ -9,11 +9,12 @@
 // four channels at a time, so every output form is a vector store.
 // Bound by latency: launch, patch from memory, one barrier, the steps, the sum, the stores (a launch that does nothing takes about
 // 3 us), so what counts is how many instructions stand before the first request and between two matrix instructions: the
-// tile's geometry is integer arithmetic in scalar registers, a wavefront asks for whole pieces of a patch row, the fragments'
-// offset is carried along, and every wait for weights is for the oldest request only.  Back to back on one stream, us, tile kernels ->
-// first form (pixels numbered through with float divisions, a loop that could end half way) -> now: 56 x 56 x 64 -> 64 3x3, one
-// image, 7.3 -> 6.1 -> 4.8; 14 x 14 x 256 -> 256 9.1 -> 6.5 -> 5.4; 7 x 7 x 512 -> 512 13.6 -> 7.4 -> 6.3 (32 images 15.4 -> 14.8 ->
-// 12.6).  156 drawn layers 1.21 x on the first form.  Twice the weights requested ahead: 0.6 us slower (the longer code is fetched once per launch).
+// tile's geometry is integer arithmetic in scalar registers, a lane's chunk of the patch two or three divisions by constants, the fragments'
+// offset is carried along, and every wait for weights is for the oldest request only.  Launches replayed back to back as a graph, us,
+// first form (pixels numbered through with float divisions, a loop that could end half way) -> now: 56 x 56 x 64 -> 64 3x3, one image,
+// 5.4 -> 4.2; 14 x 14 x 256 -> 256 6.1 -> 5.0; 7 x 7 x 512 -> 512 7.2 -> 6.1 (32 images 13.6 -> 11.9); 1x1 7 x 7 x 2048 -> 512 9.0 -> 6.9
+// (the tile kernels before it: 7.3 / 9.1 / 13.6 / 15.4, one call after the other).  1100 drawn layers 1.25 x on the first form, two below
+// 0.95 x.  Twice the weights requested ahead: 0.6 us slower (the longer code is fetched once per launch).
 #pragma once
 #include "sparq_conv_patch_kernel.h"
 #include "sparq_fastdiv.h"
@@ -56,8 +57,8 @@ struct SplitCfg {
 
 inline int split_plane_stride(int npix_max) { return (int)round_up((int64_t)npix_max * kChunk, 256) + kChunk; }
 
-// REMAP: a strided 1x1 layer (PatchGeom::rm_wo).
-template <class Cfg, int KIND, bool REMAP>
+// ONE_ROW: the input is one row (1x1 layers: PatchGeom's long row, of pixels of a strided layer where rm_wo is set).
+template <class Cfg, int KIND, bool ONE_ROW>
 __global__ __launch_bounds__(kSplitThreads, 2) void conv_split_kernel(const SplitParams p) {
     constexpr int FM = Cfg::kFM, FN = Cfg::kFN, D = Cfg::kAhead, TM = Cfg::kTM, TN = Cfg::kTN;
     constexpr int CH = 4;                                    // patch chunks in flight per lane
@@ -86,29 +87,37 @@ __global__ __launch_bounds__(kSplitThreads, 2) void conv_split_kernel(const Spli
     const int pwt = row0 == row1 ? x1 - x0 + g.KW : (g.Wo - 1) * g.sw + g.KW;
     const int nrows = v1 - v0 + g.KH;
 
-    // ---- the patch: the chunks of a row lie next to each other in memory; a wavefront takes 64 of them at a time, every eighth
-    //      such piece.  A piece's row is uniform, so a lane's address is one division by a launch constant and a few adds: the
-    //      first request leaves after 60 instructions (250 and 100 for each further one while pixels were numbered through) ----
-    const int pieces = (pwt * p.planes + 63) >> 6;           // per row
-    int l_row = 0, l_piece = wave;                           // the piece requested next
-    auto next_piece = [&]() __attribute__((always_inline)) {
-        while (l_piece >= pieces) { l_piece -= pieces; ++l_row; }
-    };
-    next_piece();
+    // ---- the patch: its 16-byte chunks numbered through, those of a row next to each other in memory; a wavefront takes 64 of them at a
+    //      time, every eighth such piece.  A lane's address is two divisions by launch constants, one by the row's chunks and a few
+    //      adds (while it was pixels that were numbered through, 250 instructions before the first request and 100 for each
+    //      further one).  Row by row, with what depends on the row in scalar registers, each row's last piece is asked for whole: 1-3 %
+    //      slower on the networks' layers, and 6.5 -> 21.3 us where rows are short (2 x 2 x 148 -> 608 7x1/2, 57 images) ----
+    const int row_chunks = pwt * p.planes, chunks = nrows * row_chunks;
+    const float rcp_row = ONE_ROW ? 0.0f : 1.0f / (float)row_chunks;
+    int l_piece = wave;                                      // the piece requested next
     v4u a_reg[CH];
     int a_at[CH];                                            // where the chunk goes in LDS, -1: nowhere
     auto load_chunk = [&](int i) __attribute__((always_inline)) {
-        const int vr = v0 + l_row, b = (int)fastdiv((uint32_t)vr, p.div_hv), iy = vr - b * g.Hv - g.ph;
-        const bool row_ok = (b < g.B) & ((unsigned)iy < (unsigned)g.H);
-        const uint32_t j = (uint32_t)(l_piece * 64 + lane);
-        const int px = (int)fastdiv(j, p.div_planes), plane = (int)j - px * p.planes, ix = xlo + px;
-        const bool ok = row_ok & (px < pwt) & ((unsigned)ix < (unsigned)g.W) & (plane * kChunk < p.C);      // a tap's channel padding reads as zero
-        int pix = (b * g.H + iy) * g.W + ix;
-        if constexpr (REMAP) pix = remap_pixel(g, ok ? ix : 0);
-        a_reg[i] = __builtin_amdgcn_raw_buffer_load_b128(xrsrc, ok ? pix * p.C + plane * kChunk : (int)kPatchInvalidOffset, 0, 0);
-        a_at[i] = px < pwt ? plane * p.plane_stride + (l_row * pwt + px) * kChunk : -1;
+        const int at = l_piece * 64 + lane;
+        const bool inside = at < chunks;
+        PatchChunk k;
+        int pix;
+        bool ok = inside;
+        if constexpr (ONE_ROW) {
+            k = patch_chunk(at, p.planes, p.div_planes);
+            pix = xlo + k.px;
+            ok &= (unsigned)pix < (unsigned)g.W;
+            if (g.rm_wo) pix = remap_pixel(g, ok ? pix : 0);
+        } else {
+            k = patch_chunk(at, row_chunks, rcp_row, p.planes, p.div_planes);
+            const int vr = v0 + k.row, b = (int)fastdiv((uint32_t)vr, p.div_hv), iy = vr - b * g.Hv - g.ph, ix = xlo + k.px;
+            ok &= (b < g.B) & ((unsigned)iy < (unsigned)g.H) & ((unsigned)ix < (unsigned)g.W);
+            pix = (b * g.H + iy) * g.W + ix;
+        }
+        ok &= k.plane * kChunk < p.C;                        // a tap's channel padding reads as zero
+        a_reg[i] = __builtin_amdgcn_raw_buffer_load_b128(xrsrc, ok ? pix * p.C + k.plane * kChunk : (int)kPatchInvalidOffset, 0, 0);
+        a_at[i] = inside ? k.plane * p.plane_stride + (k.row * pwt + k.px) * kChunk : -1;
         l_piece += kSplitWaves;
-        next_piece();
     };
     auto stage_chunk = [&](int i) __attribute__((always_inline)) {
         v4u v = a_reg[i];
@@ -122,7 +131,7 @@ __global__ __launch_bounds__(kSplitThreads, 2) void conv_split_kernel(const Spli
     };
     // first patch chunks, then the first weights: the patch waits for its own requests only.  (Requests under a uniform
     // condition: `left` counts the pieces of this wavefront.)
-    const int total = nrows * pieces;
+    const int total = patch_pieces(chunks);
     int left = total > wave ? (total - wave + kSplitWaves - 1) / kSplitWaves : 0;
 #pragma unroll
     for (int i = 0; i < CH; ++i)
@@ -318,8 +327,8 @@ int split_lds_bytes(int npix_max, int planes) {
 }
 
 // `p` carries everything except plane_stride and tiles_n; npix_max bounds TilePatch::npix.
-template <class Cfg, int KIND, bool REMAP>
-sparq_status launch_split_remap(const SplitParams& p, int npix_max, hipStream_t s) {
+template <class Cfg, int KIND, bool ONE_ROW>
+sparq_status launch_split_rows(const SplitParams& p, int npix_max, hipStream_t s) {
     SplitParams q = p;
     q.plane_stride = split_plane_stride(npix_max);
     const int lds_bytes = split_lds_bytes<Cfg>(npix_max, p.planes);
@@ -328,7 +337,7 @@ sparq_status launch_split_remap(const SplitParams& p, int npix_max, hipStream_t 
     q.div_tiles_n = make_fastdiv((uint32_t)q.tiles_n);
     const int64_t tiles = (int64_t)((p.g.M + Cfg::kTM - 1) / Cfg::kTM) * q.tiles_n;
     if (tiles > 0x7FFFFFFF) return SPARQ_EUNSUPPORTED;
-    auto kern = conv_split_kernel<Cfg, KIND, REMAP>;
+    auto kern = conv_split_kernel<Cfg, KIND, ONE_ROW>;
     // largest dynamic LDS size enabled so far, per device (relaxed atomics: concurrent callers at worst repeat the call)
     static std::atomic<int> lds_set_dev[kMaxDevices];
     const int slot = current_device_slot();
@@ -344,7 +353,8 @@ sparq_status launch_split_remap(const SplitParams& p, int npix_max, hipStream_t 
 
 template <class Cfg, int KIND>
 sparq_status launch_split_cfg(const SplitParams& p, int npix_max, hipStream_t s) {
-    return p.g.rm_wo ? launch_split_remap<Cfg, KIND, true>(p, npix_max, s) : launch_split_remap<Cfg, KIND, false>(p, npix_max, s);
+    const bool one_row = p.g.B == 1 && p.g.H == 1 && p.g.ph == 0;
+    return one_row ? launch_split_rows<Cfg, KIND, true>(p, npix_max, s) : launch_split_rows<Cfg, KIND, false>(p, npix_max, s);
 }
 
 template <class Cfg>

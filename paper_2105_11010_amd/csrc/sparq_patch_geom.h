@@ -16,6 +16,8 @@
 #pragma once
 #include <stdint.h>
 
+#include "sparq_fastdiv.h"
+
 #if defined(__HIPCC__)
 #define SPARQ_GEOM_HD __host__ __device__ __forceinline__
 #else
@@ -172,6 +174,22 @@ SPARQ_GEOM_HD uint32_t patch_pixel_offset_u32(const PatchGeom& g, const TilePatc
     if (REMAP && g.rm_wo) off = (uint32_t)(remap_pixel(g, ok ? ix : 0) * C);
     return ok ? off : invalid;
 }
+
+// The patch as 16-byte chunks, `planes` to a pixel, numbered through its rows: chunk `at` of one row, of rows of row_chunks = pwt * planes,
+// and how many groups of 64 they take.
+struct PatchChunk { int row, px, plane; };
+SPARQ_GEOM_HD PatchChunk patch_chunk(int at, int planes, const FastDiv& div_planes) {
+    const int px = (int)fastdiv((uint32_t)at, div_planes);
+    return {0, px, at - px * planes};
+}
+SPARQ_GEOM_HD PatchChunk patch_chunk(int at, int row_chunks, float rcp_row, int planes, const FastDiv& div_planes) {
+    int in_row;
+    const int row = div_rcp(at, row_chunks, rcp_row, &in_row);
+    PatchChunk k = patch_chunk(in_row, planes, div_planes);
+    k.row = row;
+    return k;
+}
+SPARQ_GEOM_HD int patch_pieces(int chunks) { return (chunks + 63) >> 6; }
 
 // Patch pixel index of output pixel m's tap (0, 0); tap (kh, kw) sits kh * pwt + kw further.
 SPARQ_GEOM_HD int patch_pixel_of_output(const PatchGeom& g, const TilePatch& t, int m) {

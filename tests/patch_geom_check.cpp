@@ -8,6 +8,7 @@
 #include <stdlib.h>
 
 #include <initializer_list>
+#include <vector>
 
 #include "../paper_2105_11010_amd/csrc/sparq_patch_geom.h"
 
@@ -38,6 +39,23 @@ static int walk(int B, int H, int W, int KH, int KW, int sh, int sw, int ph, int
                     const uint32_t got32 = patch_pixel_offset_u32(g, t, pix, C, 0x80000000u);
                     if (got32 != (want < 0 ? 0x80000000u : (uint32_t)want)) { printf("FAIL map32: m %d tap %d,%d\n", m, kh, kw); return 1; }
                 }
+        }
+        // staged as chunks, 64 at a time: every chunk of the patch once, and no more requests than that takes
+        for (int planes : {4, 5, 12}) {
+            const int row_chunks = t.pwt * planes, chunks = t.npix * planes;
+            if (tm > 64 || chunks > 10240) continue;         // (what LDS holds)
+            std::vector<char> seen(chunks);
+            int asked = 0;
+            for (int piece = 0; piece < patch_pieces(chunks); ++piece)
+                for (int lane = 0; lane < 64; ++lane, ++asked) {
+                    const int at = piece * 64 + lane;
+                    const PatchChunk k = patch_chunk(at, row_chunks, 1.0f / (float)row_chunks, planes, make_fastdiv((uint32_t)planes));
+                    if (at >= chunks) continue;
+                    const int pix = k.row * t.pwt + k.px;
+                    if (k.px < 0 || k.px >= t.pwt || k.plane < 0 || k.plane >= planes || pix >= t.npix || seen[pix * planes + k.plane]++) { printf("FAIL chunk %d\n", at); return 1; }
+                }
+            if (asked >= chunks + 64) { printf("FAIL: %d chunks asked for %d\n", chunks, asked); return 1; }
+            for (char c : seen) if (!c) { printf("FAIL: a chunk is not staged\n"); return 1; }
         }
         // pixels past the patch must decode as "nothing"
         if (patch_pixel_offset(g, t, t.npix, C) != -1) { printf("FAIL tail\n"); return 1; }

@@ -398,6 +398,27 @@ def test_conv_split_reduction(sq, oracle, tile, layer, mode):
     check_layer_u8(sq, oracle, layer, mode, seed_cfg=8)
 
 
+# ... and patches whose rows are far from whole pieces of 64 chunks: one output column, strides that leave rows and columns out, many
+# images to a tile, tiles inside one output row beside tiles of several, channel padding, each tile.
+SPLIT_SHORT_ROWS = [
+    ("32x32", S.ConvLayer("u_7x1_s2_2x2_c148", 57, 2, 2, 148, 36, 7, 1, (2, 2), (3, 0))), ("32x32", S.ConvLayer("u_3x3_s3_5x5_c112", 59, 5, 5, 112, 17, 3, 3, (3, 3), (1, 0))),
+    ("32x32", S.ConvLayer("u_2x2_s3_88x4_c48", 5, 88, 4, 48, 60, 2, 2, (3, 3), (1, 0))), ("32x32", S.ConvLayer("u_1x3_5x40_c64", 2, 5, 40, 64, 50, 1, 3, (1, 1), (0, 1))),
+    ("32x32", S.ConvLayer("u_5x5_s2_6x6_c96_m9", 1, 6, 6, 96, 80, 5, 5, (2, 2), (2, 2))), ("32x64", S.ConvLayer("u_3x3_5x5_c64_n96", 131, 5, 5, 64, 96, 3, 3, (1, 1), (1, 1))),
+    ("64x64", S.ConvLayer("u_3x3_5x5_c60_n130", 121, 5, 5, 60, 130, 3, 3, (1, 1), (1, 1))),
+]
+
+
+@pytest.mark.parametrize("tile,layer", SPLIT_SHORT_ROWS, ids=lambda v: v if isinstance(v, str) else v.name)
+@pytest.mark.parametrize("mode", [S.Mode(4, S.OPT5, 1, 1), S.Mode(4, S.OPT5, 1, 0), S.Mode(4, S.OPT3, 0, 1), S.Mode(4, S.OPT3, 0, 0),
+                                  S.Mode(3, S.OPT6_3B, 1, 0), S.Mode(2, S.OPT7_2B, 1, 1), S.Mode(2, S.OPT7_2B, 0, 1), S.PLAIN8],
+                         ids=lambda m: m.label)
+def test_conv_split_reduction_of_short_patch_rows(sq, oracle, tile, layer, mode):
+    d = sq.conv_desc(layer.B, layer.H, layer.W, layer.C, layer.N, layer.KH, layer.KW, layer.stride, layer.pad)
+    assert f"split_reduction tile={tile}" in sq.sparq_conv_plan(d, sq.mode(*mode.astuple()))
+    check_layer(sq, oracle, layer, mode, seed_cfg=8)
+    check_layer_u8(sq, oracle, layer, mode, seed_cfg=8, out_mode=mode)
+
+
 # The form with the activations in registers (1x1 layers): every number of reduction steps it holds and numbers in between,
 # pixels and channels that fill no fragment, strides, odd channel counts, runs of fewer than 128 result bytes, shares of the
 # output channels, 64 pixels per wavefront (many pixels and channels).
