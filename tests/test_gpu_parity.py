@@ -343,6 +343,68 @@ def test_conv_few_channels(sq, oracle, layer, mode):
     check_layer_u8(sq, oracle, layer, mode, seed_cfg=8, out_mode=mode if layer.N == 64 else None)
 
 
+def exact_sums(oracle, x, w, layer, mode):
+    """int32 sums of the trimmed input on the GPU, in double precision (every product and sum exact), a few images at a time."""
+    xt, wd = dev(oracle.trim(x, **mode.kwargs())), dev(w).double().permute(0, 3, 1, 2).reshape(layer.N, -1).T.contiguous()
+    step = max(1, (1 << 19) * layer.B // layer.M)
+    for b in range(0, layer.B, step):
+        rows = torch.nn.functional.unfold(xt[b:b + step].double().permute(0, 3, 1, 2), (layer.KH, layer.KW), padding=layer.pad, stride=layer.stride)
+        yield rows.transpose(1, 2).reshape(-1, layer.K).contiguous().mm(wd).to(torch.int32)
+
+
+# Workgroups that do several tiles one after the other -- their two patches in turn, the next tile's input on its way -- at every tile
+# height (tm: of the results named) and row stride, with one, two and four channels, several column blocks and ragged last tiles.
+FEW_MANY_TILES = [
+    (128, "fp32", S.ConvLayer("f_many_3x3_c2_n96", 5, 111, 112, 2, 96, 3, 3, (1, 1), (1, 1))),
+    (256, "fp32", S.ConvLayer("f_many_7x7_c4_n96", 31, 121, 116, 4, 96, 7, 7, (1, 1), (3, 3))),
+    (512, "fp32", S.ConvLayer("f_many_7x7s2_c3_n80", 67, 219, 224, 3, 80, 7, 7, (2, 2), (3, 3))),
+    (1024, "fp32", S.ConvLayer("f_many_3x1s2_c1_n18", 259, 223, 224, 1, 18, 3, 1, (2, 2), (1, 0))),
+    (256, "bytes", S.ConvLayer("f_many_4x4s4_c2_n272", 9, 232, 240, 2, 272, 4, 4, (4, 4), (0, 0))),
+    (512, "bytes", S.ConvLayer("f_many_5x7s2_c1_n144", 9, 213, 216, 1, 144, 5, 7, (2, 2), (2, 3))),
+    (1024, "bytes", S.ConvLayer("f_many_3x3_c4_n48", 341, 40, 40, 4, 48, 3, 3, (1, 1), (1, 1))),
+]
+
+
+@pytest.mark.parametrize("tm,results,layer", FEW_MANY_TILES, ids=lambda v: v.name if isinstance(v, S.ConvLayer) else str(v))
+@pytest.mark.parametrize("mode", [S.Mode(4, S.OPT5, 1, 1), S.Mode(2, S.OPT7_2B, 0, 1), S.PLAIN8], ids=lambda m: m.label)
+def test_few_channels_many_tiles(sq, oracle, tm, results, layer, mode):
+    d = sq.conv_desc(layer.B, layer.H, layer.W, layer.C, layer.N, layer.KH, layer.KW, layer.stride, layer.pad)
+    m = sq.mode(*mode.astuple())
+    text, columns = sq.sparq_conv_plan(d, m), (layer.N + 63) // 64
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    slots = 2 * cus // columns
+    assert layer.M > slots * tm and layer.M % tm != 0                # more tiles than workgroups, a ragged one at the end
+    if results == "fp32":
+        assert f"few_channels tile={tm}x64" in text, text
+    else:                                                            # (the text names four-byte tiles: three tiles for two CUs decide for bytes)
+        assert "u8_kernel=conv_few_kernel" in text, text
+        assert (tm == 1024 or -(-layer.M // (2 * tm)) * columns * 2 < 3 * cus) and -(-layer.M // tm) * columns * 2 >= 3 * cus
+    x, w, sc = S.gen_layer(8, layer)
+    wd, sd = dev(w), dev(sc if results == "fp32" else S.rng_for(8, 900).uniform(2e-4, 4e-4, size=layer.N).astype(np.float32))
+    packed = torch.empty(sq.sparq_packed_bytes(d), dtype=torch.uint8, device="cuda:0")
+    sq.sparq_pack_weights(wd, d, packed)
+    ws = torch.empty(sq.sparq_workspace_bytes(d, m), dtype=torch.uint8, device="cuda:0")
+    acc = out = y = None
+    if results == "fp32":
+        acc = torch.full((layer.M, layer.N), -7, dtype=torch.int32, device="cuda:0")
+        out = torch.full((layer.M, layer.N), -7.0, dtype=torch.float32, device="cuda:0")
+        sq.sparq_conv_gemm(dev(x), packed, d, m, acc=acc, scale=sd, out=out, workspace=ws)
+    else:
+        y = torch.full((layer.M, layer.N), 7, dtype=torch.uint8, device="cuda:0")
+        sq.sparq_conv_gemm_u8(dev(x), packed, d, m, sd, y, workspace=ws)
+    torch.cuda.synchronize()
+    at = 0
+    for ref in exact_sums(oracle, x, w, layer, mode):
+        here = slice(at, at + ref.shape[0])
+        if results == "fp32":
+            assert torch.equal(acc[here], ref), at
+            assert torch.equal(out[here], ref.float() * sd), at      # two roundings to nearest, as defined
+        else:
+            assert torch.equal(y[here], (ref.float() * sd).round().clamp(0, 255).to(torch.uint8)), at
+        at += ref.shape[0]
+    assert at == layer.M
+
+
 def test_few_channels_beside_half_a_million_outputs(sq, oracle):
     """The widest results: 1024 of these rows are 2^31 bytes and more, so tiles of 1024 pixels would store what is past N inside the
     tensor.  Every int32 and fp32 result against exact sums in double precision of the oracle's trimmed input."""
@@ -360,13 +422,9 @@ def test_few_channels_beside_half_a_million_outputs(sq, oracle):
     out = torch.full((layer.M, layer.N), -7.0, dtype=torch.float32, device="cuda:0")
     sq.sparq_conv_gemm(dev(x), packed, d, m, acc=acc, scale=sd, out=out, workspace=ws)
     torch.cuda.synchronize()
-    rows = torch.nn.functional.unfold(dev(oracle.trim(x, **mode.kwargs())).double().permute(0, 3, 1, 2), (5, 3), padding=(2, 1))[0].T.contiguous()
-    cols = wd.double().permute(0, 3, 1, 2).reshape(layer.N, -1)
-    for n in range(0, layer.N, 1 << 16):
-        at = slice(n, n + (1 << 16))
-        ref = (rows @ cols[at].T.contiguous()).to(torch.int32)
-        assert torch.equal(acc[:, at], ref), n
-        assert torch.equal(out[:, at], ref.float() * sd[at]), n          # two roundings to nearest, as defined
+    (ref,) = exact_sums(oracle, x, w, layer, mode)
+    assert torch.equal(acc, ref)
+    assert torch.equal(out, ref.float() * sd)                            # two roundings to nearest, as defined
 
 
 # The split-reduction form (small layers): its three tiles; fewer reduction steps than wavefronts, shares of unequal
