@@ -202,6 +202,33 @@ def test_sparse24_large_patches_expanded_while_staging(sq, oracle, unit, layer):
     assert np.all(np.abs(out.astype(np.float64) - ref_out) <= 1e-6 * np.abs(ref_out)), plan
 
 
+# The decompressed weights on the kernels made for a layer's shape.  Expanded first: long reductions of few pixels, and layers the gather
+# kernel would take (an even number of taps); with vSPARQ off every form, channel counts in whole words among them.
+DENSE_FORM_LAYERS = [
+    ("split", S.ConvLayer("df_3x3_240_33", 1, 9, 9, 240, 33, 3, 3, (1, 1), (1, 1), 0.5, M45)), ("split", S.ConvLayer("df_7x1_304_70_2bit", 2, 9, 9, 304, 70, 7, 1, (1, 1), (3, 0), 0.5, S.Mode(2, S.OPT7_2B, 0, 1))),
+    ("block", S.ConvLayer("df_2x2_64_20", 26, 56, 56, 64, 20, 2, 2, (1, 1), (0, 0), 0.5, M45)), ("block", S.ConvLayer("df_2x2_16_36_3bit", 26, 56, 56, 16, 36, 2, 2, (1, 1), (1, 1), 0.5, S.Mode(3, S.OPT6_3B, 1, 1))),
+    ("split", S.ConvLayer("df_3x3_64_33_novS", 2, 9, 9, 64, 33, 3, 3, (1, 1), (1, 1), 0.5, S.Mode(4, S.OPT5, 1, 0))), ("split", S.ConvLayer("df_3x3s2_512_44_plain8", 1, 21, 21, 512, 44, 3, 3, (2, 2), (1, 1), 0.5, S.PLAIN8)),
+    ("rows", S.ConvLayer("df_1x1_128_40_novS", 1, 5003, 1, 128, 40, 1, 1, (1, 1), (0, 0), 0.5, S.Mode(4, S.OPT5, 1, 0))), ("rows", S.ConvLayer("df_1x1_188_40_novS", 1, 5003, 1, 188, 40, 1, 1, (1, 1), (0, 0), 0.5, S.Mode(4, S.OPT3, 0, 0))),
+    ("wide", S.ConvLayer("df_1x1_528_256_novS", 1, 16411, 1, 528, 256, 1, 1, (1, 1), (0, 0), 0.5, S.Mode(4, S.OPT5, 1, 0))), ("block", S.ConvLayer("df_2x2_52_24_novS", 26, 56, 56, 52, 24, 2, 2, (1, 1), (0, 0), 0.5, S.Mode(4, S.OPT3, 0, 0))),
+    ("block", S.ConvLayer("df_5x4_36_72_novS", 6, 78, 77, 36, 72, 5, 4, (1, 1), (2, 2), 0.5, S.Mode(4, S.OPT5, 1, 0))),
+]
+
+
+@pytest.mark.parametrize("kernel,layer", DENSE_FORM_LAYERS, ids=lambda v: v.name if isinstance(v, S.ConvLayer) else v)
+def test_sparse24_on_the_forms_of_dense_layers(sq, oracle, kernel, layer):
+    d = sq.conv_desc(layer.B, layer.H, layer.W, layer.C, layer.N, layer.KH, layer.KW, layer.stride, layer.pad)
+    plan = sq.sparq_sparse24_plan(d, sq.mode(*layer.mode.astuple()))
+    assert f" kernel=conv_{kernel}_kernel" in plan and plan.endswith("dense_mfma") and ("expanded_x4" in plan) == bool(layer.mode.pair), plan
+    rng = S.rng_for(10, 500 + [l for _, l in DENSE_FORM_LAYERS].index(layer))
+    x = S.gen_activations(layer.x_shape(), layer.zf, rng)
+    wv, wi = S.gen_sparse24_weights(layer.w_shape(), rng)
+    sc = S.gen_scales(layer.N, rng)
+    ref_acc, ref_out = oracle.conv_gemm_sparse24(x, wv, wi, layer.stride, layer.pad, scale=sc, **layer.mode.kwargs())
+    acc, out = run_sparse(sq, layer, x, wv, wi, sc)
+    assert np.array_equal(acc, ref_acc), plan
+    assert np.all(np.abs(out.astype(np.float64) - ref_out) <= 1e-6 * np.abs(ref_out)), plan
+
+
 @pytest.mark.parametrize("unit,layer", STAGING_LAYERS, ids=lambda v: v.name if isinstance(v, S.ConvLayer) else f"unit{v}")
 def test_sparse24_expanded_while_staging(sq, oracle, unit, layer):
     check_blocked_layer(sq, oracle, layer, 300 + [l for _, l in STAGING_LAYERS].index(layer), True, unit)
