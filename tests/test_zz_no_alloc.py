@@ -50,14 +50,16 @@ def _both(sq, layer, seed):
 
 def test_two_calls_in_a_row_the_second_smaller(sq, oracle):
     m5 = S.Mode(4, S.OPT5, 1, 1)
-    # first: a first-layer shape (3 channels: trimmed 4-channel copy in the scratch, pixel-folded), 6.4 MB of scratch;
-    # second: a smaller layer with an odd channel count (channel-padded copy in the same scratch);
+    # first: a layer with an odd channel count (trimmed, channel-padded copy in the scratch), 6.4 MB of scratch;
+    # second: a smaller such layer (in the same scratch, among what the first left there);
     # third: a layer that needs no scratch at all
-    layers = [S.ConvLayer("first_7x7s2", 8, 224, 224, 3, 64, 7, 7, (2, 2), (3, 3), 0.3, m5),
+    layers = [S.ConvLayer("first_3x3_63", 2, 223, 223, 63, 64, 3, 3, (2, 2), (1, 1), 0.3, m5),
               S.ConvLayer("odd_3x3_65", 2, 17, 17, 65, 48, 3, 3, (1, 1), (1, 1), 0.5, S.Mode(4, S.OPT3, 0, 1)),
               S.ConvLayer("plain_1x1_128", 2, 14, 14, 128, 96, 1, 1, (1, 1), (0, 0), 0.5, m5)]
     used = []
     for i, layer in enumerate(layers):
+        d = sq.conv_desc(layer.B, layer.H, layer.W, layer.C, layer.N, layer.KH, layer.KW, layer.stride, layer.pad)
+        assert ("padded_copy" in sq.sparq_conv_plan(d, sq.mode(*layer.mode.astuple()))) == (i < 2)      # (written, not only asked for)
         wsb, (x, w, sc), acc0, out0, acc1, out1 = _both(sq, layer, i)
         used.append(wsb)
         assert torch.equal(acc0, acc1), f"{layer.name}: int32 results differ from sparq_conv_gemm"
