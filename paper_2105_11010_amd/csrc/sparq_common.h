@@ -91,7 +91,7 @@ struct ConvGeom {
     int B, H, W, C, N, KH, KW, sh, sw, ph, pw;
     int Ho, Wo;
     int64_t M;
-    int Cp;          // channels padded to a multiple of 16 (what the kernel loads)
+    int Cp;          // channels padded to a multiple of 16 (what a padded copy holds)
     int Cq;          // one filter tap's extent in the packed weights: C padded to 64 (to 16 when C <= 32)
     int K;           // KH*KW*C   (the method's dot-product length)
     int Kk;          // KH*KW*Cq  (what the kernel contracts over; with C > 32 every 64-byte step lies inside one tap)

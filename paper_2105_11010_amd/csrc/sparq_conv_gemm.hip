@@ -87,7 +87,7 @@ const PatchVariant kPatchVariants[] = {
 // are cached because the same layers are launched over and over.
 int patch_npix_max(const PatchGeom& g) {
     struct Key { int v[13]; int npix; };
-    // 128 sets of four geometries (a layer table asks for up to two tile heights per layer).  Four ways, because two layers that
+    // 128 sets of four geometries (a layer's rules ask for up to four tile heights).  Four ways, because two layers that
     // push each other out pay the walk on every call: 12 us at 35 x 35 pixels, 193 at 147 x 147, against 0.1 for a look-up.
     struct Set { Key way[4]; unsigned next; };
     static Set cache[128];
@@ -214,7 +214,7 @@ const SplitVariant kSplitVariants[] = {
 };
 
 // The split form is taken by layers whose tiles, at one of its sizes, do not outnumber the CUs: the smallest such tile,
-// and only if the reduction is long enough for the sharing to pay.  Measured over 235 small layers of the three tables
+// and only if the reduction is long enough for the sharing to pay.  Measured, with its first form, over 235 small layers of the three tables
 // (batch 1 to 128): 2.81 ms in the other kernels, 2.07 with this rule, 2.07 with the best choice layer by layer (7 x 7 x 512
 // 3x3, one image: 13.6 -> 6.8 us; 56 x 56 x 64: 7.3 -> 5.5; 1x1 over 64 channels: 4.7 -> 5.2, hence the lower limits).
 // With more tiles than CUs every tile's patch and its sum cost more than the shorter chain gains (four images of
@@ -424,8 +424,8 @@ struct ConvPlan {
     size_t pad_bytes = 0;       // room for that copy (channel counts that are not a multiple of 16: asked for whether or not it is made)
 };
 
-// forms: the forms other than the two tile kernels may be taken (never for 2:4 pruned weights; where the tuning hook asks for
-// a tile kernel, no rule takes them; where it asks for one of them, that one wherever the layer fits it).
+// forms: the forms other than the two tile kernels may be taken (where the tuning hook asks for a tile kernel, no rule takes them; where
+// it asks for one of them, that one wherever the layer fits it).  Layers with 2:4 pruned weights are planned both ways (make_sparse_plan).
 // bytes: requantised results.  trims: the layer's mode trims (its size queries and descriptors without one do not care).
 // copy: the channel-padded copy is made (channel counts that are not a multiple of 16).
 ConvPlan make_plan_of(const ConvGeom& g, const Tuning& tune, bool forms, bool bytes, bool trims, bool copy) {

@@ -367,9 +367,10 @@ __global__ __launch_bounds__(Cfg::kThreads, Cfg::kWgPerCu * Cfg::kThreads / 256)
         // the partner -- the byte's trim beside a non-zero partner (`full`) and beside a zero one (left in a_reg) -- is worked out
         // with the first, each block then chooses between the two by its own partners (a byte is zero where `full` is): 6
         // vector instructions per word and block beside 17 for the three, where a whole trim for each was 22.  The next
-        // channel block is requested when the third has been written.  us: 32 x 32 x 512 -> 512 3x3,
-        // batch 64 235 -> 229 (two-bit windows 237 -> 227), 48 x 48 x 224 -> 133 1x7 24.5 -> 18.6.  That layer is bound by power: no staging at
-        // all 203, weights of one address 203, no fragment reads 203, none of the three 171.
+        // channel block is requested when the third has been written.  us, whole trims -> now, in turn in one process: 32 x 32 x 512 ->
+        // 512 3x3, batch 64 236.0 -> 233.5 (two-bit windows 238.6 -> 234.6); 7 x 7 x 512 -> 512 35.4 -> 30.9; 48 x 48 x 224 -> 133 1x7, eight
+        // images 38.4 -> 34.9; 84 x 84 x 288 -> 749 3x3, three 104 -> 90.  The first is bound by power: no staging at all 203, weights of one
+        // address 203, no fragment reads 203, none of the three 171.
         if (producer) {
             v4u full[AC];
             int s_cb = 0, s_order = 0;                // the unit staged next

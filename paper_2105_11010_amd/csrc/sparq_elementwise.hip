@@ -1,8 +1,9 @@
 // Streaming kernels of libsparq: the standalone trim (Sections 3.1-3.2), the
 // per-output-channel dequantisation (Section 5), the one-time weight packing
 // and the trimmed, channel-padded copy used for channel counts that are not a
-// multiple of 16.  All of them are bound by HBM traffic, so each lane moves
-// 128-bit words and the grid is sized to a few workgroups per compute unit.
+// multiple of four and where trimming while staging would take longer.  Nearly all are
+// bound by memory: each lane moves 128-bit words, and the grid is sized by how much
+// there is to do per word (ew_grid, stream_grid).
 #include <type_traits>
 
 #include "sparq_common.h"
