@@ -8,8 +8,8 @@
 // Weights: output class 0 of the pixel-folded layout (ConvGeom::fold), whose super-pixel taps 0 and 1 are exactly
 // those eight words.
 // Workgroups are persistent, two per CU: while a tile is multiplied the next one's pixels are on their way.
-// Bound by memory (four-byte results: 5.3 TB/s) or, for bytes, by vector issue (three instructions per result beside 14 matrix
-// instructions per 32 pixels) and the staging.  7x7/2, 224 x 224 x 3 -> 64, us, pixel-folded gather kernel with its padded copy -> now:
+// Bound by memory (four-byte results: 5.3 TB/s) or, for bytes, by vector issue (55 % of the cycles by the counters, matrix pipeline 31;
+// three instructions per result beside 14 matrix instructions per 32 pixels) and the staging (38 % of a wavefront's life in waits).  7x7/2, 224 x 224 x 3 -> 64, us, pixel-folded gather kernel with its padded copy -> now:
 // 256 images, bytes 182 -> 79 (memory alone 49), fp32 204 -> 156; 32 images 30 -> 17, fp32 30 -> 23; one image 9.0 -> 5.0.
 // 64 shapes of 32 to 384 outputs: 1.59 x.  Tried: one tile per workgroup (124, and 85 at best with its largest tile: the weights and
 // constants are 120 registers to fill); three workgroups per CU (spills, 94); fragments of a strided layer as one 16-byte LDS read at
