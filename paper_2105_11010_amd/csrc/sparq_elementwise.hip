@@ -346,7 +346,7 @@ __global__ __launch_bounds__(kEwThreads) void per_channel_table_kernel(const v4s
     }
 }
 
-// Pointers off their words' alignment, or channels beyond what the table is for.
+// Pointers off their words' alignment, or calls the table is not for.
 template <bool U8>
 __global__ __launch_bounds__(kEwThreads) void per_channel_scalar_kernel(const int32_t* __restrict__ acc, const float* __restrict__ factor,
                                                                         void* __restrict__ out, int64_t total, int N) {
@@ -368,8 +368,12 @@ static sparq_status launch_per_channel(const int32_t* acc, const float* factor, 
         else per_channel_vec_kernel<U8, false><<<ew_grid(n_vec, kEwThreads * 4), kEwThreads, 0, s>>>(acc4, factor, out, n_vec, (uint32_t)N, div);
         return launch_status();
     }
-    // (a table of more than 1024 factors is for large calls: 200 x 2001 3.5 us without, 5.4 with it, 20000 x 2001 76 and 60)
-    if (words && N <= kMaxTable && (N <= 1024 || total >= (4 << 20))) {
+    // A workgroup fills its table before its first result, so calls with fewer rows than three quarters of their channels, or of less than
+    // two workgroups' words, are ahead without (us, without -> with, replayed as a graph, requantised: 1 x 255 1.90 -> 2.19, 31 x 511 2.31 ->
+    // 2.49, 62 x 1023 2.46 -> 2.71, 391 x 1023 2.59 -> 2.75; even at 250 x 511, 782 x 767, 899 x 1001; 1955 x 1023 3.74 -> 3.30), and those
+    // of more than 1024 factors are for large calls (200 x 2001 3.5 us without, 5.4 with it, 20000 x 2001 76 and 60).
+    const bool table = N <= 1024 ? total >= 2048 && 4 * (total / N) >= 3ll * N : N <= kMaxTable && total >= (4 << 20);
+    if (words && table) {
         const int tail = (int)(total % 4);
         const FastDiv div = make_fastdiv((uint32_t)N);
         const size_t lds = (size_t)(N + 3) * sizeof(float);

@@ -193,7 +193,10 @@ def test_requant(sq, oracle, M, N):
 # Widths that are no multiple of four and factors off 16 bytes: words that end a row and begin the next, results past the last
 # word, the table's smallest and largest widths (and one past them), calls of less than and more than one workgroup.
 @pytest.mark.parametrize("M,N,skew", [(3, 1, 0), (1031, 2, 0), (5, 3, 0), (4099, 5, 0), (37, 161, 0), (2051, 161, 0), (513, 64, 1),
-                                      (33, 1023, 0), (2050, 2047, 0), (2048, 2049, 0), (2050, 2048, 1), (524289, 65, 0)])
+                                      (33, 1023, 0), (2050, 2047, 0), (2048, 2049, 0), (2050, 2048, 1), (524289, 65, 0),
+                                      # ... and the line below which there is no table, by results and by rows
+                                      (2047, 1, 0), (2050, 1, 0), (682, 3, 0), (683, 3, 0), (120, 161, 0), (121, 161, 0), (767, 1023, 0),
+                                      (768, 1023, 0), (767, 1024, 1), (769, 1024, 1)])
 def test_per_channel_any_width(sq, oracle, M, N, skew):
     rng = S.rng_for(8, 500 + N)
     acc = np.resize(rng.integers(-60000, 200000, size=min(M * N, 1 << 18), dtype=np.int64).astype(np.int32), (M, N))
