@@ -419,7 +419,6 @@ struct ConvPlan {
     PatchGeom pg{};
     int npix = 0, ac = 0, cbs = 0;
     bool ws = false;            // wave-specialised form of the patch kernel
-    bool sparse_steps = false;  // three reduction steps and more, which the sparse form's weight cursor runs ahead (or units of several)
     bool copy = false;          // the kernel reads a channel-padded, trimmed copy of x
     size_t pad_bytes = 0;       // room for that copy (channel counts that are not a multiple of 16: asked for whether or not it is made)
 };
@@ -460,7 +459,6 @@ ConvPlan make_plan_of(const ConvGeom& g, const Tuning& tune, bool forms, bool by
     if (!force_gather && (force_patch || !prefer_gather(g)) && plan_patch(gk, max_unit, &pl.pg, &pl.npix, &pl.ac, &pl.cbs)) {
         pl.variant = pick_patch(g, tune, pl.ac, pl.cbs, pl.npix, force_patch, &pl.ws);
         pl.patch = pl.variant != nullptr;
-        pl.sparse_steps = pl.cbs > 1 || g.Kk >= 3 * kStepK;
     }
     if (rules) {
         pl.block = pick_block(gk, bytes, plain, !pl.patch, &pl.pg, &pl.npix);
@@ -520,7 +518,7 @@ ConvPlan make_plan(const ConvGeom& g, const Tuning& tune, bool forms = true, boo
 // one and `kind` is the plain one; with it off the staging wavefronts trim as in the dense form).
 bool sparse_plan(const ConvPlan& pl, TrimKind kind) {
     const bool single = kind == kTrimNone || kind == kTrimFloor || kind == kTrimRound || kind == kTrimRound4;
-    return pl.patch && pl.ws && pl.variant->fn_sp && single && pl.sparse_steps;
+    return pl.patch && pl.ws && pl.variant->fn_sp && single;
 }
 
 // The plan of a layer with 2:4 pruned weights.  Where the rules of dense layers pick a form made for the layer's shape, the decompressed

@@ -297,8 +297,9 @@ __global__ __launch_bounds__(Cfg::kThreads, Cfg::kWgPerCu * Cfg::kThreads / 256)
     const int w_half = (SP ? 1 : 2) * p.Np * kChunk;   // bytes between the two 32-index halves of a step
     const int grid_n = grid % p.tiles_n;
     int b_s = 0, b_cb = 0, b_tn = (int)blockIdx.x % p.tiles_n;
-    // kLean: runs of steps with a fixed distance (a unit's taps, or of a 1x1 layer the tile's channel blocks) of at least three
-    // steps, so that the cursor is never more than one run ahead and a run's start is worked out at the unit boundaries.
+    // kLean: runs of steps with a fixed distance (a unit's taps, or of a 1x1 layer the tile's channel blocks).  The cursor enters a run once
+    // per run that the matrix instructions finish, so the start of the run after it is worked out at the unit boundaries; runs entered by
+    // the three steps of the prologue (of one or two steps) are followed by that at once.
     const int b_run = p.nsteps > 1 ? p.nsteps : p.ncb, b_runs = p.nsteps > 1 ? p.ncb : 1;
     const int b_dist = (p.nsteps > 1 ? p.ksteps_tap : 1) * 2 * w_half;
     int b_left = b_run, b_off = b_tn * TN * kChunk, b_start = 0;
@@ -477,13 +478,19 @@ __global__ __launch_bounds__(Cfg::kThreads, Cfg::kWgPerCu * Cfg::kThreads / 256)
         for (int i = 0; i < AC; ++i) load_chunk(i);
     }
     {
-        const int w0 = next_b_offset();
+        auto first_b_offset = [&]() __attribute__((always_inline)) -> int {
+            const bool enters = kLean && b_left == 0;
+            const int off = next_b_offset();
+            if (enters) next_b_run();
+            return off;
+        };
+        const int w0 = first_b_offset();
         load_b(b_reg[0][0], b_idx[0][0], w0, 0);
         load_b(b_reg[0][1], b_idx[0][1], w0, 1);
-        const int w1 = next_b_offset();
+        const int w1 = first_b_offset();
         load_b(b_reg[1][0], b_idx[1][0], w1, 0);
         load_b(b_reg[1][1], b_idx[1][1], w1, 1);
-        w_next = next_b_offset();
+        w_next = first_b_offset();
     }
     if constexpr (!WS) {
         stage_npix = lt.npix;
@@ -809,7 +816,6 @@ sparq_status launch_patch_cfg(const PatchParams& p, int npix_max, hipStream_t s)
     if (Cfg::kSparse != (p.widx != nullptr) || (Cfg::kSparse && p.out_u8)) return SPARQ_EUNSUPPORTED;
     if (!p.trim_in && !Cfg::kWaveSpecialised && KIND != kTrimNone) return SPARQ_EUNSUPPORTED;
     if ((int64_t)p.N * 4 * kPatchTM >= 0x7FFFFFFF) return SPARQ_EUNSUPPORTED;   // 32-bit offsets inside a tile of results
-    if (Cfg::kSparse && (int64_t)p.nsteps * p.ncb < (Cfg::kCBS == 1 ? 3 : 1)) return SPARQ_EUNSUPPORTED;     // (the weight cursor runs three steps ahead)
     if (npix_max > Cfg::kMaxPix || lds_bytes > kLdsPerCu || q.nsteps < Cfg::kUnrolled ||
         ((q.nsteps - Cfg::kUnrolled) & 1))
         return SPARQ_EUNSUPPORTED;

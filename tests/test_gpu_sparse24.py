@@ -40,6 +40,10 @@ SPARSE_MFMA_LAYERS = [
     S.ConvLayer("spm_1x1_256_260_novS_round3", 2, 15, 15, 256, 260, 1, 1, (1, 1), (0, 0), 0.5, S.Mode(3, S.OPT6_3B, 1, 0)),
     S.ConvLayer("spm_1x7_64_64_novS_floor2", 2, 17, 17, 64, 64, 1, 7, (1, 1), (0, 3), 0.5, S.Mode(2, S.OPT7_2B, 0, 0)),
     S.ConvLayer("spm_1x1_192_100_plain8", 2, 19, 19, 192, 100, 1, 1, (1, 1), (0, 0), 0.5, S.PLAIN8),
+    # one reduction step to a tile, over more tiles than workgroups and over several columns of them
+    S.ConvLayer("spm_1x1_48_60_novS", 1, 70001, 1, 48, 60, 1, 1, (1, 1), (0, 0), 0.5, S.Mode(4, S.OPT3, 0, 0)),
+    S.ConvLayer("spm_1x1_64_520_plain8", 1, 16500, 1, 64, 520, 1, 1, (1, 1), (0, 0), 0.5, S.PLAIN8),
+    S.ConvLayer("spm_1x1s2_36_200_novS", 3, 41, 43, 36, 200, 1, 1, (2, 2), (0, 0), 0.5, S.Mode(4, S.OPT5, 1, 0)),
 ]
 FORMS = [None, "path=gather", "path=patch,patch_ws=1", "path=patch,patch_ws=1,patch_tn=64", "path=patch,patch_ws=1,patch_tn=128",
          "path=patch,patch_ws=1,patch_tn=256"]

@@ -283,6 +283,14 @@ def sparse_plan(lib, d, m):
     return buf.value.decode()
 
 
+def test_sparse24_layers_of_one_step_keep_the_sparse_instruction(lib):
+    """1x1 layers of at most 64 channels, vSPARQ off, whose results are too many for the activations-in-registers form."""
+    for c, n in ((48, 60), (36, 61), (64, 250)):
+        for m in (Mode(4, 0x15, 0, 0), Mode(8, 1, 0, 0)):
+            text = sparse_plan(lib, Desc(171, 62, 62, c, n, 1, 1, 1, 1, 0, 0), m)
+            assert " kernel=conv_patch_kernel" in text and text.endswith("sparse_mfma"), text
+
+
 def test_sparse24_plan_names_the_matrix_instruction(lib):
     """2:4 pruned weights: the sparse matrix instruction wherever the (expanded) layer takes the wave-specialised
     input-patch kernel, for every mode; the dense kernels where it does not; and the packed buffer holds both forms."""
