@@ -470,15 +470,20 @@ ConvPlan make_plan_of(const ConvGeom& g, const Tuning& tune, bool forms, bool by
     return pl;
 }
 
+// Vector instructions that trim 16 bytes (kTrimFloor by its timings: it has 32).
+int trim_instructions(TrimKind kind) {
+    static const int instructions[kTrimKinds] = {0, 40, 48, 64, 80, 128, 68, 84};
+    return instructions[kind];
+}
+
 // What trimming while staging adds to a tile kernel, against the copy: the trim's instructions for the patch beyond those that the taps'
 // matrix instructions cover, tile after tile on the busiest CU, and a launch and the tensor written and read once more (1/32 ns and
 // 2 us + 0.25 ns per KB).  Of 950 timed layers with up to 2500 channels none is left more than 5 % behind the better of the two; where all
 // were trimmed in place 119 of the first 500 were, by up to 2.3 x (15 x 15 x 1396 -> 96 1x7/2, seven images, three-bit windows, 38 against
 // 86 us; 7 x 7 x 2148 -> 349 1x7/2, sixteen, 57 against 112: few tiles, each a patch of its own, leave the trim to a few CUs).
 bool staging_outlasts_copy(const ConvGeom& g, const ConvPlan& pl, TrimKind kind) {
-    static const int instructions[kTrimKinds] = {0, 40, 48, 64, 80, 128, 68, 84};          // for 16 bytes (the first by its timings: it has 32)
     const int64_t tn = pl.variant->tn, tiles = (g.M + kPatchTM - 1) / kPatchTM * ((g.N + tn - 1) / tn), cus = device_cu_count();
-    const int64_t beyond = (int64_t)pl.npix * instructions[kind] - (int64_t)34 * g.KH * g.KW * (tn < 128 ? tn : 128);
+    const int64_t beyond = (int64_t)pl.npix * trim_instructions(kind) - (int64_t)34 * g.KH * g.KW * (tn < 128 ? tn : 128);
     return (tiles + cus - 1) / cus * (g.Cq / kStepK) * beyond > 64000 + (int64_t)g.x_bytes / 125;
 }
 
@@ -492,6 +497,9 @@ bool staging_outlasts_copy(const ConvGeom& g, const ConvPlan& pl, TrimKind kind)
 // (windows of two or three bits with rounding, 20 and 32 instructions for four bytes), tile kernels that stage more than five bytes for
 // one of x (35 x 35 x 908 -> 736 3x3/2 45 against 66), five column tiles of the eight-wavefront form (9167 x 1276 -> 1216 32 against 38)
 // and long reductions of the split form, which stages all of its patch before the first product (154 x 3364 -> 656 10.6 against 12.4).
+// 1x1 layers trim x once per column tile, which the products of that tile hide in part (`beyond`).  3200 timed layers of 768 to 4600 channels and
+// 2 to 8 columns of 256, in place against the copy, by (instructions - 32) x columns: bytes on the gather kernel 0.95-1.1 x up to 128, 0.92 x at
+// 156, 0.7-0.8 x from 192 on (9739 x 3828 -> 1595, two-bit windows, 105 us against 162); eight wavefronts 1.0-1.4 x up to 255, 0.88-1.0 x beyond.
 ConvPlan make_plan(const ConvGeom& g, const Tuning& tune, bool forms = true, bool bytes = false, TrimKind kind = kTrimFloor) {
     const bool pads = !g.fold && g.Cp != g.C, trims = kind != kTrimNone;
     if (!pads || g.C % 4 == 0) {
@@ -500,10 +508,14 @@ ConvPlan make_plan(const ConvGeom& g, const Tuning& tune, bool forms = true, boo
         const bool gather = !pl.wide && !pl.split && !pl.block && !pl.rows && !pl.patch;
         const int64_t tiles_m = (g.M + 127) / 128;
         const bool costly = kind == kTrimRound || kind == kTrimRoundPairWide;
-        bool once = gather && g.KH * g.KW > 1;
+        const int beyond = trim_instructions(kind) - 32;         // what the products of one column tile leave uncovered
+        bool once = gather && (g.KH * g.KW > 1 || beyond * ((g.N + 255) / 256) > 128);
         if (pl.split && !tune.form) once = costly ? g.K >= 1800 : kind == kTrimRoundPair4 && g.K >= 8000;
         if (pl.wide && !tune.form) once = tiles_m * ((g.N + 255) / 256) * 2 < device_cu_count();
-        if (costly && pl.wide && !tune.form) once = once || (g.N + pl.wide->tn - 1) / pl.wide->tn >= 5;
+        if (pl.wide && !tune.form) {
+            const int columns = (g.N + pl.wide->tn - 1) / pl.wide->tn;
+            once = once || (costly && columns >= 5) || beyond * columns > 255;
+        }
         if (pl.patch && !pl.wide && !pl.split && !pl.block && !pl.rows) {
             const int64_t staged = tiles_m * ((g.N + pl.variant->tn - 1) / pl.variant->tn) * pl.npix;
             once = (costly && staged > (int64_t)5 * g.B * g.H * g.W) || staging_outlasts_copy(g, pl, kind);

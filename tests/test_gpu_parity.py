@@ -578,6 +578,16 @@ def test_conv_channels_in_words_copied(sq, oracle, layer, mode):
     check_layer_u8(sq, oracle, layer, mode, seed_cfg=8, out_mode=mode)
 
 
+# 1x1 layers of several column tiles: bytes of the gather kernel, and the eight-wavefront form, in place and from the copy by their trims.
+@pytest.mark.parametrize("layer", [S.ConvLayer("a_columns_c772_n1001", 1, 20003, 1, 772, 1001)], ids=lambda l: l.name)
+@pytest.mark.parametrize("mode", [S.Mode(4, S.OPT5, 1, 1), S.Mode(4, S.OPT3, 0, 1), S.Mode(2, S.OPT7_2B, 1, 1), S.Mode(3, S.OPT6_3B, 1, 0)], ids=lambda m: m.label)
+def test_conv_channels_in_words_over_column_tiles(sq, oracle, layer, mode):
+    d = sq.conv_desc(layer.B, layer.H, layer.W, layer.C, layer.N, layer.KH, layer.KW, layer.stride, layer.pad)
+    assert " u8_kernel=conv_gemm_kernel" in sq.sparq_conv_plan(d, sq.mode(*mode.astuple()))
+    check_layer(sq, oracle, layer, mode, seed_cfg=8)
+    check_layer_u8(sq, oracle, layer, mode, seed_cfg=8, out_mode=mode)
+
+
 FORM_MODES = [S.Mode(4, S.OPT5, 1, 1), S.Mode(4, S.OPT5, 1, 0), S.Mode(4, S.OPT3, 0, 1), S.Mode(4, S.OPT3, 0, 0),
               S.Mode(3, S.OPT6_3B, 1, 0), S.Mode(2, S.OPT7_2B, 1, 1), S.Mode(2, S.OPT7_2B, 0, 1), S.PLAIN8]
 

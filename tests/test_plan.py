@@ -250,6 +250,15 @@ def test_tile_kernels_that_would_trim_longer_than_a_copy_takes(lib, shape, k, st
     assert words(text, "kernel=") == ["conv_patch_kernel"] and ("padded_copy" in text) == copy, text
 
 
+@pytest.mark.parametrize("n,mode,copy", [
+    (566, S.Mode(3, S.OPT6_3B, 1, 1), True), (512, S.Mode(3, S.OPT6_3B, 1, 1), False), (566, S.Mode(4, S.OPT5, 1, 1), False), (1100, S.Mode(4, S.OPT5, 1, 1), True),
+    (1100, S.Mode(4, S.OPT5, 1, 0), False), (1700, S.Mode(4, S.OPT5, 1, 0), False), (1700, S.Mode(4, S.OPT3, 0, 1), False), (1700, S.PLAIN8, False)], ids=str)
+def test_1x1_layers_that_would_trim_once_per_column_tile(lib, n, mode, copy):
+    """Read where they are while the columns of tiles and the trim's instructions are few enough for the products to cover."""
+    text = plan(lib, S.ConvLayer("columns", 1, 11669, 1, 3444, n), mode)[0]
+    assert (copy or words(text, "kernel=") == ["conv_wide_kernel"]) and ("padded_copy" in text) == copy, text
+
+
 def test_layers_in_turn_do_not_walk_their_tiles_again(lib):
     """The largest patch of a layer comes from a walk over its tile positions (193 us for 147 x 147 pixels) and is kept per
     geometry.  These two geometries share the low nine bits of the cache's hash: called in turn, neither pushes the other out."""
