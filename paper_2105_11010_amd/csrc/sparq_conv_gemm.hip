@@ -384,8 +384,10 @@ const BlockVariant* pick_block(const ConvGeom& g, bool bytes, bool plain, bool g
 //   65 to 128 channels: bytes of more than 128 outputs, tiles 128 wide, 1.04-1.21 x; up to 192 in the first third of a second
 //   round of 256-wide tiles 1.08-1.18 x (17 x 17 x 192 1x7, batch 128: 289 tiles, 23.2 against 21.2 us);
 //   the gather kernel's layers, trimmed once per tap there: nine taps and more, up to 128 channels, 65 to 384 outputs 1.02-1.55 x
-//   in up to 1200 tiles (35 x 35 x 96 3x3/2 23.2 against 19.9 us; more tiles 0.88-1.4 x, more outputs 0.8-1.1 x), and 15 taps and
-//   more whose patch for 256 pixels does not fit (78 x 78 x 128 -> 48 5x5 125 against 76).
+//   in up to 1200 tiles (35 x 35 x 96 3x3/2 23.2 against 19.9 us; more tiles 0.88-1.4 x, more outputs 0.8-1.1 x), of 65 to 128 channels and up
+//   to 14 taps while three workgroups share a CU (beyond 803 patch pixels 280 layers of 3x3/2 0.93 x, 93 x 93 x 112 -> 320, twelve images, 30.2 against
+//   45.3; 700 to 803 of them 1.04 x, and 64 channels 1.05 x), and 15 taps and more whose patch for 256 pixels does not fit (78 x 78 x 128 -> 48
+//   5x5 125 against 76).
 const BlockVariant* pick_block_square(const ConvGeom& g, bool bytes, bool plain, const BlockVariant* picked, int tn, PatchGeom* pg, int* npix) {
     const int taps = g.KH * g.KW;
     const int64_t cus = device_cu_count(), t128 = block_tiles<Block128x128>(g.M, g.N);
@@ -395,7 +397,8 @@ const BlockVariant* pick_block_square(const ConvGeom& g, bool bytes, bool plain,
         if (plain || picked || g.Cq > 128) return picked;
         PatchGeom q;
         int n;
-        square = (taps >= 9 && g.N > 64 && g.N <= 384 && t128 <= 1200) || (taps >= 15 && g.N <= 384 && !fit_block(g, bytes, kBlockVariants[0], &q, &n));
+        const bool shared = g.Cq == 64 || taps >= 15 || (fit_block(g, bytes, kBlockVariants[1], &q, &n) && 3 * block_lds_bytes<Block128x128>(n) <= kLdsPerCu);
+        square = (taps >= 9 && g.N > 64 && g.N <= 384 && t128 <= 1200 && shared) || (taps >= 15 && g.N <= 384 && !fit_block(g, bytes, kBlockVariants[0], &q, &n));
     } else if (g.N > 64 && tn >= 128 && (bytes || taps >= 7)) {
         const int64_t t256 = (g.M + 127) / 128 * ((g.N + 255) / 256);
         const bool third = t256 * 3 <= cus * 4;

@@ -250,6 +250,13 @@ def test_tile_kernels_that_would_trim_longer_than_a_copy_takes(lib, shape, k, st
     assert words(text, "kernel=") == ["conv_patch_kernel"] and ("padded_copy" in text) == copy, text
 
 
+@pytest.mark.parametrize("b,hw,c,n,square", [(12, 93, 112, 320, False), (52, 69, 128, 160, False), (64, 65, 112, 80, False), (57, 45, 96, 160, True), (52, 69, 64, 160, True)])
+def test_square_tile_while_three_workgroups_share_a_cu(lib, b, hw, c, n, square):
+    """Strided layers of 65 to 128 channels that the 256 x 64 tile leaves to the gather kernel: the 128 x 128 tile up to 803 patch pixels."""
+    text = plan(lib, S.ConvLayer("strided", b, hw, hw, c, n, 3, 3, (2, 2), (1, 1)), S.Mode(4, S.OPT5, 1, 1))[0]
+    assert ("small_workgroups tile=128x128" in text) == square and words(text, "u8_kernel=") == ["conv_block_kernel" if square else "conv_gemm_kernel:128x%d" % (256 if n > 128 else 128)], text
+
+
 @pytest.mark.parametrize("n,mode,copy", [
     (566, S.Mode(3, S.OPT6_3B, 1, 1), True), (512, S.Mode(3, S.OPT6_3B, 1, 1), False), (566, S.Mode(4, S.OPT5, 1, 1), False), (1100, S.Mode(4, S.OPT5, 1, 1), True),
     (1100, S.Mode(4, S.OPT5, 1, 0), False), (1700, S.Mode(4, S.OPT5, 1, 0), False), (1700, S.Mode(4, S.OPT3, 0, 1), False), (1700, S.PLAIN8, False)], ids=str)
