@@ -106,6 +106,9 @@ inline TrimLuts make_luts(int n, uint32_t S) {
 #if defined(__HIP_DEVICE_COMPILE__)
 SPARQ_HD uint32_t perm(uint32_t hi, uint32_t lo, uint32_t sel) { return __builtin_amdgcn_perm(hi, lo, sel); }
 SPARQ_HD uint32_t lerp(uint32_t a, uint32_t b, uint32_t c) { return __builtin_amdgcn_lerp(a, b, c); }
+// Any bitwise function of three words in one instruction: bit 4a + 2b + c of TABLE is the result for bits a, b, c.
+template <uint32_t TABLE>
+SPARQ_HD uint32_t bitop3(uint32_t a, uint32_t b, uint32_t c) { return __builtin_amdgcn_bitop3_b32(a, b, c, TABLE); }
 #else
 SPARQ_HD uint32_t perm(uint32_t hi, uint32_t lo, uint32_t sel) {
     const uint64_t pool = ((uint64_t)hi << 32) | lo;
@@ -127,6 +130,13 @@ SPARQ_HD uint32_t lerp(uint32_t a, uint32_t b, uint32_t c) {
         const uint32_t s = ((a >> (8 * i)) & 0xFF) + ((b >> (8 * i)) & 0xFF) + ((c >> (8 * i)) & 1);
         r |= ((s >> 1) & 0xFF) << (8 * i);
     }
+    return r;
+}
+template <uint32_t TABLE>
+SPARQ_HD uint32_t bitop3(uint32_t a, uint32_t b, uint32_t c) {
+    uint32_t r = 0;
+    for (uint32_t i = 0; i < 8; ++i)
+        if ((TABLE >> i) & 1u) r |= (i & 4u ? a : ~a) & (i & 2u ? b : ~b) & (i & 1u ? c : ~c);
     return r;
 }
 #endif
@@ -170,27 +180,22 @@ SPARQ_HD uint32_t trim4_beside(uint32_t x, uint32_t pm, const TrimLuts& L) {
     const uint32_t selB = (x >> 2) & 0x07070707u;
     const uint32_t low_n = low_mask(selA, selB, L.a_hi, L.a_lo, L.b_hi, L.b_lo);
     uint32_t low = low_n;
-    uint32_t wtop = 0;          // all bits up to the window top, per byte (only needed for ROUND)
-    if (PAIR) {
-        if (WIDE) {
-            const uint32_t low_w = low_mask(selA, selB, L.wa_hi, L.wa_lo, L.wb_hi, L.wb_lo);
-            low = bfi(pm, low_n, low_w);
-            if (ROUND) wtop = bfi(pm, (low_n << L.n) | L.ones_n, (low_w << L.n2) | L.ones_w);
-        } else {
-            low = low_n & pm;
-            if (ROUND) wtop = (low << L.n) | L.ones_n;
-        }
-    } else if (ROUND) {
-        wtop = (low << L.n) | L.ones_n;
+    uint32_t above = 0;         // the bits above the window, per byte (only needed for ROUND)
+    if (PAIR && WIDE) {
+        const uint32_t low_w = low_mask(selA, selB, L.wa_hi, L.wa_lo, L.wb_hi, L.wb_lo);
+        low = bitop3<0xCA>(pm, low_n, low_w);                                  // pm ? low_n : low_w
+        if (ROUND) above = bitop3<0x35>(pm, (low_n << L.n) | L.ones_n, (low_w << L.n2) | L.ones_w);    // ~(pm ? . : .)
+    } else {
+        if (PAIR) low &= pm;
+        if (ROUND) above = ~((low << L.n) | L.ones_n);
     }
-    const uint32_t fl = x & ~low;
-    if (!ROUND) return fl;
-    const uint32_t below_half = low & (low >> 1);      // residual bits under the rounding bit
-    const uint32_t half = low ^ below_half;            // 2^(s-1), or 0 when s == 0
-    const uint32_t zeros = ~x & (wtop ^ below_half);   // zero bits of x among window + rounding bit
-    const uint32_t may_round = expand_bit7(nonzero_flag(zeros));   // 0 => window full and rounding bit set
-    const uint32_t r = x & half & may_round;
-    return fl + (r << 1);
+    if (!ROUND) return x & ~low;
+    // The window and the rounding bit are all ones where the bits under the rounding bit, filled up, complete x to the window's top.
+    // Elsewhere x + 2^(s-1) stays below the bits above the window.
+    const uint32_t filled = bitop3<0xF8>(x, low, low >> 1);                    // x | (low & (low >> 1))
+    const uint32_t sat = expand_bit7(lerp(filled, above, 0x01010101u));        // filled + above + 1 >= 256
+    const uint32_t half = bitop3<0x10>(low, low >> 1, sat);                    // low & ~(low >> 1) & ~sat: 2^(s-1), or 0
+    return (x + half) & ~low;
 }
 template <bool ROUND, bool PAIR, bool WIDE>
 SPARQ_HD uint32_t trim4(uint32_t x, const TrimLuts& L) {
@@ -204,11 +209,11 @@ template <bool PAIR>
 SPARQ_HD uint32_t trim4_round_n4_beside(uint32_t x, uint32_t pm, const TrimLuts& L) {
     const uint32_t selA = (x >> 5) & 0x07070707u;
     const uint32_t selB = (x >> 2) & 0x07070707u;
-    uint32_t low = low_mask(selA, selB, L.a_hi, L.a_lo, L.b_hi, L.b_lo);
-    if (PAIR) low &= pm;
-    const uint32_t half = low & ~(low >> 1);
+    const uint32_t low_a = perm(L.a_hi, L.a_lo, selA), low_b = perm(L.b_hi, L.b_lo, selB);
+    const uint32_t low = PAIR ? bitop3<0xA8>(low_a, low_b, pm) : low_a | low_b;        // (a | b) & pm
     const uint32_t sat = expand_bit7(lerp(x, perm(L.ncap_hi, L.ncap_lo, selA), 0u));   // x + (256 - cap) >= 256
-    return (x + (half & ~sat)) & ~low;
+    const uint32_t half = bitop3<0x10>(low, low >> 1, sat);                            // low & ~(low >> 1) & ~sat
+    return (x + half) & ~low;
 }
 template <bool PAIR>
 SPARQ_HD uint32_t trim4_round_n4(uint32_t x, const TrimLuts& L) {
