@@ -12,10 +12,9 @@
 // which transpose lane quads); they leave through a wavefront's own LDS rows, 128 bytes of a pixel at a time (as 32-byte
 // pieces straight from the registers 64 -> 256 channels took 118 us, this way 58).  int32 / fp32 results: the activations
 // are the row operand and a store writes whole runs.
-// Up to 128 channels bound by memory (64 -> 256, 802816 pixels, bytes: 106 -> 58 us, 4.4 TB/s; 128 -> 512, 200704 pixels:
-// 60 -> 35); from 256 channels on by the trim's vector instructions and the weights from L2 (256 -> 64, 802816 pixels:
-// 80 -> 69, 56 without a trim; 256 -> 1024, 50176 pixels: 42 -> 29; 512 -> 1024: 69 -> 47).  Counters, bytes: with 64 channels 55 % of
-// a wavefront's life in waits, with 256 25 % and vector issue at 45 to 53 % of the cycles.
+// Many pixels and few enough weights: one workgroup per CU holds all of them in LDS, and memory is what bounds the layer (launch_rows_held,
+// where the figures are).  Otherwise the weights come from L2, and with 256 channels and more they and the trim's vector instructions do
+// (256 -> 1024, 50176 pixels: 42 -> 29 us; 512 -> 1024: 69 -> 47; vector issue 45 to 53 % of the cycles, waits 25 % of a wavefront's life).
 #pragma once
 #include "sparq_conv_patch_kernel.h"
 
@@ -44,48 +43,50 @@ struct RowsParams {
 };
 
 constexpr int kRowsThreads = 256;
-constexpr int kRowsPitch = 128 + 16;               // LDS row of 128 result bytes, padded against bank conflicts
 
 // KS 32-index steps of activations in registers, FM fragments of 32 pixels per wavefront, PF: the next pixels are requested
 // while the current ones are multiplied, OCC wavefronts per SIMD.
-template <int KS, int FM, bool PF, int OCC>
+template <int KS, int FM, bool PF, int OCC, bool WL = false, int RUN = 128>
 struct RowsCfg {
-    static constexpr int kKS = KS, kFM = FM, kOcc = OCC, kRM = 32 * FM;
-    static constexpr bool kPF = PF;
-    static constexpr int kRing = KS % 8 == 0 ? 8 : KS % 6 == 0 ? 6 : KS % 5 == 0 ? 5 : KS;     // weight steps requested ahead; divides KS
+    static constexpr int kKS = KS, kFM = FM, kOcc = OCC, kRM = 32 * FM, kRun = RUN, kPitch = RUN + 16;
+    static constexpr bool kPF = PF, kWL = WL;
+    static constexpr int kThreads = WL ? 256 * OCC : kRowsThreads;
+    // weight steps requested ahead; divides KS
+    static constexpr int kRing = WL ? (KS % 4 == 0 ? 4 : KS % 5 == 0 ? 5 : KS % 3 == 0 ? 3 : KS) : KS % 8 == 0 ? 8 : KS % 6 == 0 ? 6 : KS % 5 == 0 ? 5 : KS;
     static_assert(KS % kRing == 0, "ring slots are fixed per step");
 };
 
 template <class Cfg, int KIND, bool U8>
-__global__ __launch_bounds__(kRowsThreads, Cfg::kOcc) void conv_rows_kernel(const RowsParams p) {
+__global__ __launch_bounds__(Cfg::kThreads, Cfg::kOcc) void conv_rows_kernel(const RowsParams p) {
     constexpr int KS = Cfg::kKS, FM = Cfg::kFM, RM = Cfg::kRM, D = Cfg::kRing;
-    constexpr bool PF = Cfg::kPF;
+    constexpr bool PF = Cfg::kPF, WL = Cfg::kWL;
+    constexpr int NT = Cfg::kThreads, PITCH = Cfg::kPitch, LPR = Cfg::kRun / 16, RPR = 64 / LPR;       // lanes per row, rows per store
     // U8: a wavefront's bytes on their way out, then [corr | factor] of all channels
     extern __shared__ __attribute__((aligned(16))) uint8_t lds[];
     const int lane = threadIdx.x & 63, l32 = lane & 31, lhi = lane >> 5;
     const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
     const int nr = (p.N + 31) & ~31;
-    int32_t* lcorr = reinterpret_cast<int32_t*>(lds + (kRowsThreads / 64) * RM * kRowsPitch);
+    int32_t* lcorr = reinterpret_cast<int32_t*>(lds + (NT / 64) * RM * PITCH);
     float* lfac = reinterpret_cast<float*>(lcorr) + nr;
     // turned through LDS (the wavefront's own area, no barrier): a lane writes 16 bytes of its pixel per block and reads
     // 16 bytes of the row its group of eight lanes stores
-    uint8_t* const turn = lds + wave * RM * kRowsPitch;
-    uint8_t* const turn_w = turn + l32 * kRowsPitch + 16 * lhi;
-    const uint8_t* const turn_r = turn + (lane >> 3) * kRowsPitch + 16 * (lane & 7);
+    uint8_t* const turn = lds + wave * RM * PITCH;
+    uint8_t* const turn_w = turn + l32 * PITCH + 16 * lhi;
+    const uint8_t* const turn_r = turn + lane / LPR * PITCH + 16 * (lane % LPR);
     if constexpr (U8) {
-        for (int n = threadIdx.x; n < nr; n += kRowsThreads) {
+        for (int n = threadIdx.x; n < nr; n += NT) {
             const int nc = n < p.N ? n : 0;
             lcorr[n] = p.colsum[nc] * 128;
             lfac[n] = p.scale[nc];
         }
-        __syncthreads();
+        if constexpr (!WL) __syncthreads();
     }
     const __amdgpu_buffer_rsrc_t xrsrc =
         __builtin_amdgcn_make_buffer_rsrc(const_cast<uint8_t*>(p.x), 0, (int)p.x_bytes, 0x00020000);
     const __amdgpu_buffer_rsrc_t wrsrc =
         __builtin_amdgcn_make_buffer_rsrc(const_cast<uint8_t*>(p.wpk), 0, (int)p.w_bytes, 0x00020000);
     // items go round by wavefront slot first, so that what is left over spreads over all workgroups
-    const int stride = (int)gridDim.x * (kRowsThreads / 64);
+    const int stride = (int)gridDim.x * (NT / 64);
     int item = wave * (int)gridDim.x + (int)blockIdx.x;
 
     v4u raw[FM][KS];
@@ -105,7 +106,14 @@ __global__ __launch_bounds__(kRowsThreads, Cfg::kOcc) void conv_rows_kernel(cons
     };
     const int wlane = (lhi * p.Np + l32) * kChunk;
     v4i b[D];
+    // WL: the weights as 32-channel blocks of [step][half][channel][16 bytes]
+    uint8_t* const lw = U8 ? reinterpret_cast<uint8_t*>(lfac + nr) : lds;
+    const uint8_t* const lw_lane = lw + (lhi * 32 + l32) * kChunk;
     auto load_b = [&](v4i& dst, int n0, int h) __attribute__((always_inline)) {
+        if constexpr (WL) {
+            dst = *reinterpret_cast<const v4i*>(lw_lane + n0 * KS * 32 + h * 1024);
+            return;
+        }
         const bool live = h < p.steps;                       // uniform; KS can exceed the layer's steps
         const int voff = live ? wlane : (int)kPatchInvalidOffset, soff = live ? (h * 2 * p.Np + n0) * kChunk : 0;
         dst = __builtin_bit_cast(v4i, __builtin_amdgcn_raw_buffer_load_b128(wrsrc, voff, soff, 0));
@@ -113,6 +121,14 @@ __global__ __launch_bounds__(kRowsThreads, Cfg::kOcc) void conv_rows_kernel(cons
     const float* scale_or_dummy = p.out ? p.scale : reinterpret_cast<const float*>(p.colsum);
 
     load_rows(item);
+    if constexpr (WL) {
+        for (int q = threadIdx.x; q < nr * KS * 2; q += NT) {
+            const int blk = q / (KS * 64), k16 = q % (KS * 64) / 32, n = blk * 32 + q % 32;
+            const int off = k16 < 2 * p.steps ? (k16 * p.Np + n) * kChunk : (int)kPatchInvalidOffset;          // (past the last step: 0)
+            *reinterpret_cast<v4u*>(lw + q * kChunk) = __builtin_amdgcn_raw_buffer_load_b128(wrsrc, off, 0, 0);
+        }
+        __syncthreads();
+    }
     for (; item < p.items; item += stride) {
         const int rg = item / p.items_n;
         const int n_begin = (item - rg * p.items_n) * p.item_blocks * 32;
@@ -121,7 +137,7 @@ __global__ __launch_bounds__(kRowsThreads, Cfg::kOcc) void conv_rows_kernel(cons
         // workgroups of an XCD (every eighth) start their walk at different channels: all at the same one keep asking the
         // same few L2 channels for the same weights
         const int runs = (n_end - n_begin + 127) >> 7;
-        const int n_first = n_begin + ((int)(blockIdx.x >> 3) % runs) * 128;
+        const int n_first = WL ? n_begin : n_begin + ((int)(blockIdx.x >> 3) % runs) * 128;
 #pragma unroll
         for (int h = 0; h < D; ++h) load_b(b[h], n_first, h);
         v4i a[FM][KS];
@@ -176,9 +192,12 @@ __global__ __launch_bounds__(kRowsThreads, Cfg::kOcc) void conv_rows_kernel(cons
                               : __builtin_amdgcn_mfma_i32_32x32x32_i8(a[i][h], b[h % D], c[i], 0, 0, 0);
                 if (h + D < KS) load_b(b[h % D], n0, h + D);
                 else load_b(b[h % D], n_next, h + D - KS);
+                // (left to itself the compiler puts some variants' requests right in front of their use: 320 -> 512, 132278 pixels, bytes
+                // 64 us, so 49)
+                __builtin_amdgcn_sched_barrier(0x0006);      // vector and scalar arithmetic may cross
             }
             if constexpr (U8) {
-                const int part = ((n0 - n_begin) >> 5) & 3;          // which 32 bytes of a run
+                const int part = (n0 - n_begin) / 32 % (Cfg::kRun / 32);     // which 32 bytes of a run
 #pragma unroll
                 for (int i = 0; i < FM; ++i) {
                     uint32_t w[4];
@@ -197,18 +216,18 @@ __global__ __launch_bounds__(kRowsThreads, Cfg::kOcc) void conv_rows_kernel(cons
                     // channels 0..15 of its pixels and the high half 16..31
                     const auto s02 = __builtin_amdgcn_permlane32_swap(w[0], w[2], false, false);
                     const auto s13 = __builtin_amdgcn_permlane32_swap(w[1], w[3], false, false);
-                    *reinterpret_cast<v4u*>(turn_w + i * 32 * kRowsPitch + 32 * part) = v4u{s02[0], s02[1], s13[0], s13[1]};
+                    *reinterpret_cast<v4u*>(turn_w + i * 32 * PITCH + 32 * part) = v4u{s02[0], s02[1], s13[0], s13[1]};
                 }
-                if (part == 3 || n0 + 32 >= n_end) {                 // uniform: 128 channels gathered, or the last ones
+                if (part == Cfg::kRun / 32 - 1 || n0 + 32 >= n_end) {        // uniform: a run gathered, or the last channels
                     wavefront_lds_fence();
                     const __amdgpu_buffer_rsrc_t orsrc =
                         __builtin_amdgcn_make_buffer_rsrc((void*)(p.out_u8 + base), 0, rows * p.N, 0x00020000);
-                    const int no = n0 - 32 * part + 16 * (lane & 7);
-                    const int lane_off = ((lane & 7) < 2 * (part + 1) && no < p.N) ? (lane >> 3) * p.N + no : (int)kPatchInvalidOffset;
+                    const int no = n0 - 32 * part + 16 * (lane % LPR);
+                    const int lane_off = (lane % LPR < 2 * (part + 1) && no < p.N) ? lane / LPR * p.N + no : (int)kPatchInvalidOffset;
 #pragma unroll
-                    for (int r = 0; r < RM / 8; ++r) {
-                        const v4u o = *reinterpret_cast<const v4u*>(turn_r + 8 * r * kRowsPitch);
-                        __builtin_amdgcn_raw_buffer_store_b128(o, orsrc, lane_off + 8 * r * p.N, 0, 0);
+                    for (int r = 0; r < RM / RPR; ++r) {
+                        const v4u o = *reinterpret_cast<const v4u*>(turn_r + RPR * r * PITCH);
+                        __builtin_amdgcn_raw_buffer_store_b128(o, orsrc, lane_off + RPR * r * p.N, 0, 0);
                     }
                     wavefront_lds_fence();
                 }
@@ -244,7 +263,13 @@ __global__ __launch_bounds__(kRowsThreads, Cfg::kOcc) void conv_rows_kernel(cons
 
 // Dynamic LDS of a launch with rm pixels per wavefront.
 inline int64_t rows_lds_bytes(int rm, int64_t N, bool bytes) {
-    return bytes ? (kRowsThreads / 64) * rm * kRowsPitch + (N + 31) / 32 * 32 * 8 : 0;
+    return bytes ? (kRowsThreads / 64) * rm * (128 + 16) + (N + 31) / 32 * 32 * 8 : 0;
+}
+// ... with the weights in LDS.
+template <class Cfg>
+int64_t rows_held_lds_bytes(int64_t N, bool bytes) {
+    const int64_t nr = (N + 31) / 32 * 32;
+    return (bytes ? Cfg::kThreads / 64 * Cfg::kRM * Cfg::kPitch + nr * 8 : 0) + nr * Cfg::kKS * 32;
 }
 
 // `p` carries everything except the item counts.
@@ -284,11 +309,67 @@ sparq_status launch_rows_cfg(const RowsParams& p, hipStream_t s) {
     return launch_status();
 }
 
+// The same with the weights in LDS, one workgroup per CU.
+template <class Cfg, int KIND, bool U8>
+sparq_status launch_rows_held_cfg(const RowsParams& p, hipStream_t s) {
+    RowsParams q = p;
+    q.item_blocks = (p.N + 31) / 32;
+    q.items_n = 1;
+    q.items = (int)(((int64_t)p.M + Cfg::kRM - 1) / Cfg::kRM);
+    const int64_t lds_bytes = rows_held_lds_bytes<Cfg>(p.N, U8);
+    if (lds_bytes > kLdsPerCu || (int64_t)p.N * 4 * Cfg::kRM >= 0x7FFFFFFF || p.steps > Cfg::kKS) return SPARQ_EUNSUPPORTED;
+    auto kern = conv_rows_kernel<Cfg, KIND, U8>;
+    static std::atomic<bool> lds_set_dev[kMaxDevices];       // (concurrent callers at worst repeat the call, with the same value)
+    std::atomic<bool>& lds_set = lds_set_dev[current_device_slot()];
+    if (!lds_set.load(std::memory_order_relaxed) || current_device_slot() == kMaxDevices - 1) {
+        if (hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, kLdsPerCu) != hipSuccess)
+            return SPARQ_ELAUNCH;
+        lds_set.store(true, std::memory_order_relaxed);
+    }
+    const int64_t wgs = ((int64_t)q.items + Cfg::kThreads / 64 - 1) / (Cfg::kThreads / 64), cus = device_cu_count();
+    kern<<<(unsigned)(wgs < cus ? wgs : cus), Cfg::kThreads, (size_t)lds_bytes, s>>>(q);
+    return launch_status();
+}
+
+// KS steps: wavefronts per SIMD are what the registers allow (bytes: what the result rows leave LDS for, too); 512 channels without the
+// next pixels requested ahead, 512 -> 128 channels, 200704 pixels, bytes: 39.2 us (41.1 with, and two wavefronts per SIMD).
+template <int KS, bool U8>
+struct RowsHeld {
+    typedef RowsCfg<KS, 1, KS <= 12, U8 ? (KS == 2 ? 4 : 3) : KS <= 8 ? 4 : 3, true> Main;
+    typedef RowsCfg<KS, 1, true, 2, true, 64> Large;         // bytes: fewer result rows, half as long, and room for more weights
+};
+
+// Weights in LDS where they fit and every wavefront slot has pixels of its own.  A wavefront otherwise asks L1 for all weights once per 32
+// pixels, 64 bytes a cycle for the whole CU and at the latency of L2 (13 to 23 % of such layers when the requests were left out).  Measured
+// cold, us before -> after: bytes, 256 -> 128, 802816 pixels 98 -> 69; 256 -> 64 76 -> 59; 64 -> 256 72 -> 57; 512 -> 128, 200704 pixels
+// 48 -> 41; fp32, 288 -> 48, 156800 pixels 25.8 -> 20.9, 192 -> 48 17.5 -> 13.2.  Warm, 2321 drawn layers with pixels for every slot:
+// bytes 1.08 x (7 of 1403 below 0.95, the lowest 0.91; 0.94 x with half the pixels).  Four-byte results up to 64 outputs 1.05 x, but with more
+// than 256 channels 0.96 x up to 1.3 rounds (lowest 0.86, the second round nearly empty); up to 128 from two rounds on 1.04, up to 96 of more than
+// 256 channels from 1.5 on as much faster as slower warm (0.85 to 1.05), cold 27.1 -> 21.8 (288 -> 96); wider ones are bound by their stores and
+// lose as much as they gain (0.78 to 1.1).  More weights than fit beside three wavefronts per SIMD, bytes, up to 128 KB: 1.13 x from three rounds of
+// two on, but 0.98 x with up to 256 channels.
+template <int KS, int KIND, bool U8>
+sparq_status launch_rows_held(const RowsParams& p, hipStream_t s) {
+    typedef typename RowsHeld<KS, U8>::Main Main;
+    const int64_t items = ((int64_t)p.M + 31) / 32, simds = (int64_t)device_cu_count() * 4, slots = simds * Main::kOcc;
+    if (rows_held_lds_bytes<Main>(p.N, U8) <= kLdsPerCu) {
+        constexpr bool SHORT = KS <= 8;
+        const int64_t tenths = U8 ? 10 : p.N <= 64 ? (SHORT ? 11 : 14) : p.N <= 96 && !SHORT ? 15 : p.N <= 128 ? 20 : INT64_MAX / (slots + 1);
+        if (items * 10 >= slots * tenths) return launch_rows_held_cfg<Main, KIND, U8>(p, s);
+    } else if constexpr (U8 && KS > 8) {
+        typedef typename RowsHeld<KS, U8>::Large Large;
+        if (rows_held_lds_bytes<Large>(p.N, U8) <= kLdsPerCu && items >= simds * 6) return launch_rows_held_cfg<Large, KIND, U8>(p, s);
+    }
+    return SPARQ_EUNSUPPORTED;
+}
+
 // Cfg1: 32 pixels per wavefront, Cfg2: 64.  Sixty-four halve the weight traffic and win once both sides of the product are
 // large (K 256, N 1024, M 200704: 75 against 83 us); otherwise the shorter items do (K 256, N 256, M 12544: 7.2 against 9.9).
 inline bool rows_large(int64_t M, int64_t N) { return N >= 512 && M >= 48 * 1024; }
 template <class Cfg1, class Cfg2, int KIND>
 sparq_status launch_rows_out(const RowsParams& p, hipStream_t s) {
+    const sparq_status st = p.out_u8 ? launch_rows_held<Cfg1::kKS, KIND, true>(p, s) : launch_rows_held<Cfg1::kKS, KIND, false>(p, s);
+    if (st != SPARQ_EUNSUPPORTED) return st;
     if (!std::is_same_v<Cfg1, Cfg2> && rows_large(p.M, p.N))
         return p.out_u8 ? launch_rows_cfg<Cfg2, KIND, true>(p, s) : launch_rows_cfg<Cfg2, KIND, false>(p, s);
     return p.out_u8 ? launch_rows_cfg<Cfg1, KIND, true>(p, s) : launch_rows_cfg<Cfg1, KIND, false>(p, s);

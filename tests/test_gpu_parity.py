@@ -502,6 +502,27 @@ def test_conv_activations_in_registers(sq, oracle, layer, mode):
     check_layer_u8(sq, oracle, layer, mode, seed_cfg=8, out_mode=S.Mode(4, S.OPT5, 1, 1))
 
 
+# The same with the weights in LDS (pixels for every wavefront slot of 256 CUs, 98304 or 131072, and 1.1 to 2 times that for four-byte
+# results): every number of steps held, steps past the layer's own, ragged pixels and channels, a stride, the most weights that fit beside 128
+# bytes of result rows and beside 64.
+ROWS_HELD_SHAPES = [
+    S.ConvLayer("rh_c40_n33", 1, 144193, 1, 40, 33), S.ConvLayer("rh_c64_n208", 1, 131103, 1, 64, 208), S.ConvLayer("rh_c64_n64_s2", 6, 299, 301, 64, 64, 1, 1, (2, 2), (0, 0)),
+    S.ConvLayer("rh_c96_n96", 1, 196641, 1, 96, 96), S.ConvLayer("rh_c160_n128", 1, 262175, 1, 160, 128), S.ConvLayer("rh_c256_n64", 1, 144224, 1, 256, 64),
+    S.ConvLayer("rh_c260_n16", 1, 147457, 1, 260, 16), S.ConvLayer("rh_c384_n224", 1, 98305, 1, 384, 224), S.ConvLayer("rh_c448_n48", 1, 98335, 1, 448, 48),
+    S.ConvLayer("rh_c512_n208", 1, 98304, 1, 512, 208), S.ConvLayer("rh_c512_n240", 1, 196609, 1, 512, 240),
+]
+
+
+@pytest.mark.parametrize("layer", ROWS_HELD_SHAPES, ids=lambda l: l.name)
+@pytest.mark.parametrize("mode", [S.Mode(4, S.OPT5, 1, 1), S.PLAIN8], ids=lambda m: m.label)
+def test_conv_activations_in_registers_weights_in_lds(sq, oracle, layer, mode):
+    d = sq.conv_desc(layer.B, layer.H, layer.W, layer.C, layer.N, layer.KH, layer.KW, layer.stride, layer.pad)
+    if layer.N % 16 == 0:
+        assert "u8_kernel=conv_rows_kernel" in sq.sparq_conv_plan(d, sq.mode(*mode.astuple()))
+        check_layer_u8(sq, oracle, layer, mode, seed_cfg=8, out_mode=S.Mode(4, S.OPT5, 1, 1))
+    check_layer(sq, oracle, layer, mode, seed_cfg=8)
+
+
 # Eight wavefronts per tile (1x1 layers with long reductions): steps that are padded to a multiple of four, an odd channel
 # count, strides, ragged pixels and channels, one tile, more tiles than CUs with two tiles of channels each.
 WIDE_SHAPES = [
