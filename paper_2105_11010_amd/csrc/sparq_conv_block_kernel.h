@@ -10,8 +10,11 @@
 // kernel 23.5).  A patch pixel's address is worked out once per tile, into
 // LDS.  Requantised results: weights as the row operand (see sparq_conv_rows_kernel.h), rows leave through LDS.
 // Bound by vector issue (60 % of the cycles by the counters, the matrix pipeline 30) and the phases' waits (40 % of a wavefront's
-// life): 56 x 56 x 64 -> 64 3x3, batch 256, bytes: 78 -> 58 us (memory alone 21, the
-// matrix instructions 18); three workgroups per CU with twice the weights requested ahead: 63; 128 pixels per tile: 77.
+// life): 56 x 56 x 64 -> 64 3x3, batch 256, bytes: 78 -> 52 us (memory alone 21, the
+// matrix instructions 18); three workgroups per CU with twice the weights requested ahead: 63; 128 pixels per tile: 77.  Waits that count
+// exactly -- no request under a condition, none of the staging's left when the taps begin, fragments and weights asked for where it is
+// written -- are 8 to 15 % of that (before 57; 35 x 35 x 96 3x3/2, batch 128, fp32 23.9 -> 20.3, 17 x 17 x 192 7x1 25.5 -> 23.5); the first
+// requests ahead of the accumulators' constants, which keeps the weights' registers through the staging: 4 % slower.
 #pragma once
 #include "sparq_conv_patch_kernel.h"
 
@@ -51,7 +54,7 @@ typedef BlockCfg<2, 2> Block128x128;
 template <class Cfg, int KIND, bool U8>
 __global__ __launch_bounds__(Cfg::kThreads, Cfg::kOcc) void conv_block_kernel(const BlockParams p) {
     constexpr int FM = Cfg::kFM, FN = Cfg::kFN, TM = Cfg::kTM, TN = Cfg::kTN, NT = Cfg::kThreads, D = Cfg::kAhead;
-    constexpr int CH = 4;                                    // patch chunks in flight per lane
+    constexpr int CH = 3;                                    // patch chunks in flight per lane (4: 1 % slower)
     extern __shared__ __attribute__((aligned(16))) uint8_t lds[];            // [patch | pixel offsets], then result rows
     // every eighth workgroup runs on the same XCD: neighbouring tiles, which share patch rows and weights, go to one
     const int tile = ((int)blockIdx.x & 7) * p.tiles_xcd + ((int)blockIdx.x >> 3);
@@ -123,10 +126,13 @@ __global__ __launch_bounds__(Cfg::kThreads, Cfg::kOcc) void conv_block_kernel(co
             b_half ^= 1;
             if (2 * b_tap == steps) b_tap = 0;               // past the last: a read that is not used
         };
+        // A request past the patch reads 0 without touching memory: under a condition it would cost the exact wait counts, and every chunk
+        // a full latency.
+        const uint32_t ch = (uint32_t)(cb * 64 + plane * kChunk);
+        const bool live = (int)ch < p.C;
         auto load_chunk = [&](int i, int e) __attribute__((always_inline)) {
-            const uint32_t ch = (uint32_t)(cb * 64 + plane * kChunk);
-            const uint32_t off = e < chunks && (int)ch < p.C ? loff[e >> 2] + ch : kPatchInvalidOffset;
-            a_reg[i] = __builtin_amdgcn_raw_buffer_load_b128(xrsrc, (int)off, 0, 0);
+            const uint32_t off = loff[e < chunks ? e >> 2 : 0] + ch;
+            a_reg[i] = __builtin_amdgcn_raw_buffer_load_b128(xrsrc, e < chunks && live ? (int)off : (int)kPatchInvalidOffset, 0, 0);
         };
 #pragma unroll
         for (int i = 0; i < CH; ++i) load_chunk(i, tid + i * NT);
@@ -146,10 +152,13 @@ __global__ __launch_bounds__(Cfg::kThreads, Cfg::kOcc) void conv_block_kernel(co
 #pragma unroll
                     for (int j = 0; j < 4; ++j) v[j] ^= 0x80808080u;
                     if (e < chunks) *reinterpret_cast<v4u*>(lds + plane * p.plane_stride + (e >> 2) * kChunk) = v;
-                    if (e0 + (CH + i) * NT + wave * 64 < chunks) load_chunk(i, e + CH * NT);
                 }
+                load_chunk(i, e + CH * NT);
             }
         }
+        // the last requests (past the patch) end here: their registers serve the loop below, which would wait for its weights with them
+#pragma unroll
+        for (int i = 0; i < CH; ++i) asm volatile("" ::"v"(a_reg[i]));
         __syncthreads();
 
         // ---- all taps ----
@@ -167,17 +176,18 @@ __global__ __launch_bounds__(Cfg::kThreads, Cfg::kOcc) void conv_block_kernel(co
             }
         };
         load_frags(af[0]);
-        for (int h = 0; h < steps; h += D) {
+        for (int h = 0; h < steps; h += D) {                 // (two steps a tap)
 #pragma unroll
             for (int k = 0; k < D; ++k) {
-                if (k && h + k >= steps) break;              // uniform
                 load_frags(af[(k + 1) & 1]);
+                __builtin_amdgcn_sched_barrier(0);           // (the compiler puts reads and requests right in front of their use)
 #pragma unroll
                 for (int i = 0; i < FM; ++i)
 #pragma unroll
                     for (int j = 0; j < FN; ++j)
                         c[i][j] = U8 ? __builtin_amdgcn_mfma_i32_32x32x32_i8(b[k][j], af[k & 1][i], c[i][j], 0, 0, 0)
                                      : __builtin_amdgcn_mfma_i32_32x32x32_i8(af[k & 1][i], b[k][j], c[i][j], 0, 0, 0);
+                __builtin_amdgcn_sched_barrier(0);
                 load_b(b[k]);
             }
         }
