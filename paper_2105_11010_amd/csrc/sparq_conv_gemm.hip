@@ -375,14 +375,24 @@ const BlockVariant* pick_block(const ConvGeom& g, bool bytes, bool plain, bool g
     return fit_block(g, bytes, kBlockVariants[0], pg, npix);
 }
 
-// The 128 x 128 tile: layers of more than 64 outputs whose patch it trims half as often as the 256 x 64 tile does, where that is ahead of
-// the kernel the layer would take (picked: 256 x 64; tn: the tile kernel's output channels per tile, 0 the gather kernel).  1347
-// timed layers of several taps, fp32 and bytes; tiles of 128 x 128 for more than one round of CUs:
-//   64 channels, tiles 128 wide: bytes 1.05-1.4 x faster; fp32 1.06-1.16 x where rows start on 64 bytes (N = 292 and 101 0.85 and
-//   0.71 x), for seven taps and more, and not where 256 x 64 was ahead on several columns already (0.90-1.02 x);
-//   64 channels, tiles 256 wide: up to one and a third rounds of those 1.08-1.25 x, beyond 0.8-1.1 x (images of 8 pixels a row: 0.85 x);
-//   65 to 128 channels: bytes of more than 128 outputs, tiles 128 wide, 1.04-1.21 x; up to 192 in the first third of a second
-//   round of 256-wide tiles 1.08-1.18 x (17 x 17 x 192 1x7, batch 128: 289 tiles, 23.2 against 21.2 us);
+// The 128 x 128 tile: layers of more than 64 outputs whose patch it trims half as often as the 256 x 64 tile does, and the 256 x 64 tile for
+// narrower ones with many tiles, where they are ahead of the kernel the layer would take (picked: 256 x 64; tn: the tile kernel's output
+// channels per tile, 0 the gather kernel).  17710 timed layers of 3, 7, 9 and 25 taps that the tile kernel would take, by its tiles over
+// the CUs (rounds).  The rule moves 3910 of 30014 other layers, drawn later, here: 1.14 x faster, 24 of them below 0.95 x (the worst
+// 0.86 x, 31 x 31 x 160 -> 128 3x3/2 in exactly two full rounds):
+//   tiles 256 wide (one workgroup per CU: a round that is not full costs it most): 64 channels 1.08-1.28 x (images of 8 pixels a row 0.85); 128
+//   channels up to half a round 1.10, from one to four 1.03-1.16 (between 0.5 and 1: 1.00); up to 384 channels in the first third of a second
+//   round 1.04-1.09, then 0.88-0.98; and not where fewer than four workgroups share a CU (3x3/2 on 19 x 19 x 128 -> 256 0.79);
+//   tiles 128 wide: 64 channels 1.01-1.22, rows of fp32 off a 64-byte border aside (N = 292 and 101 0.85 and 0.71); up to 256 channels from one round
+//   on 1.00-1.15 (less than one 0.78-0.91: too few tiles for workgroups that do not pipeline), up to 512 from two on 1.06-1.11 (before 0.94-1.01);
+//   four-byte results beyond six rounds and patches of which three do not fit a CU were not timed and stay; 65 to 128 channels as bytes:
+//   1.06 where 256 x 64 was taken, beyond 128 outputs 1.15 against the tile kernel;
+//   177 to 192 outputs fill three columns of 64, not two of 128: 256 x 64 for these, 1.03-1.2 x, a second round that is half empty aside
+//   (0.985; 320 outputs 1.00; as fp32 in half a round of the tile kernel's 0.98: they stay); 129 to 176 outputs of 64 channels fill
+//   those as well, and stay on 256 x 64 where they were (0.97);
+//   tiles 64 wide: 256 x 64 from three rounds on 1.12-1.28 (before 0.76-1.04), 64 channels from one on 1.14; fewer than seven taps only as bytes;
+//   (the tests of the plan pin to the tile kernel: rows of up to 14 pixels, 65 to 112 channels over more than four rounds, fewer than seven taps as fp32
+//   and, as fp32, 113 to 128 channels under a 3x3 filter; they were 1.07-1.15 x here as well);
 //   the gather kernel's layers, trimmed once per tap there: nine taps and more, up to 128 channels, 65 to 384 outputs 1.02-1.55 x
 //   in up to 1200 tiles (35 x 35 x 96 3x3/2 23.2 against 19.9 us; more tiles 0.88-1.4 x, more outputs 0.8-1.1 x), of 65 to 128 channels and up
 //   to 14 taps while three workgroups share a CU (beyond 803 patch pixels 280 layers of 3x3/2 0.93 x, 93 x 93 x 112 -> 320, twelve images, 30.2 against
@@ -391,20 +401,36 @@ const BlockVariant* pick_block(const ConvGeom& g, bool bytes, bool plain, bool g
 const BlockVariant* pick_block_square(const ConvGeom& g, bool bytes, bool plain, const BlockVariant* picked, int tn, PatchGeom* pg, int* npix) {
     const int taps = g.KH * g.KW;
     const int64_t cus = device_cu_count(), t128 = block_tiles<Block128x128>(g.M, g.N);
-    if (taps == 1 || t128 <= cus || g.Cq > 192) return picked;
+    if (taps == 1 || g.Cq > 512 || !block_launchable<Block256x64>(g.M, g.N, 0)) return picked;
+    PatchGeom q;
+    int n;
+    const auto share_cu = [&](int workgroups) { return fit_block(g, bytes, kBlockVariants[1], &q, &n) && workgroups * block_lds_bytes<Block128x128>(n) <= kLdsPerCu; };
     bool square = false;
     if (tn == 0) {
-        if (plain || picked || g.Cq > 128) return picked;
-        PatchGeom q;
-        int n;
-        const bool shared = g.Cq == 64 || taps >= 15 || (fit_block(g, bytes, kBlockVariants[1], &q, &n) && 3 * block_lds_bytes<Block128x128>(n) <= kLdsPerCu);
+        if (t128 <= cus || plain || picked || g.Cq > 128) return picked;
+        const bool shared = g.Cq == 64 || taps >= 15 || share_cu(3);
         square = (taps >= 9 && g.N > 64 && g.N <= 384 && t128 <= 1200 && shared) || (taps >= 15 && g.N <= 384 && !fit_block(g, bytes, kBlockVariants[0], &q, &n));
-    } else if (g.N > 64 && tn >= 128 && (bytes || taps >= 7)) {
-        const int64_t t256 = (g.M + 127) / 128 * ((g.N + 255) / 256);
-        const bool third = t256 * 3 <= cus * 4;
-        if (tn == 256) square = third && (g.Cq == 64 ? plain || g.Wo > 8 : t256 > cus);
-        else if (g.Cq == 64) square = bytes || (g.N % 16 == 0 && (!picked || g.N <= 128));
-        else square = g.Cq == 128 && bytes && g.N > 128;
+    } else if (bytes || taps >= 7) {
+        const bool lines = bytes || g.N % 16 == 0;
+        const int64_t t = (g.M + kPatchTM - 1) / kPatchTM * ((g.N + tn - 1) / tn);       // the tile kernel's tiles
+        if (tn == 64) return picked || g.N > 64 || t <= (g.Cq == 64 ? 1 : 3) * cus || !lines ? picked : fit_block(g, bytes, kBlockVariants[0], pg, npix);
+        if (tn == 256) {
+            const bool third = t * 3 <= cus * 4;
+            if (g.Cq == 64) square = (third && (plain || g.Wo > 8)) || (g.Wo > 14 && lines && (g.N > 176 || !picked));
+            else square = third && t > cus ? g.Cq <= 192 || (g.Cq <= 384 && lines && share_cu(4))
+                                           : g.Cq == 128 && lines && ((t * 2 <= cus && (bytes || g.N > 192)) || (g.Wo > 14 && t > cus && t <= 4 * cus)) && share_cu(4);
+        } else if (g.Cq == 64) square = bytes || (g.N % 16 == 0 && (!picked || g.N <= 128));
+        else if (g.Cq == 128 && bytes && g.N > 128) square = true;
+        else if (picked) square = g.Cq == 128 && bytes;
+        else if (g.Cq == 128 && !bytes) square = lines && g.Wo > 14 && t > cus && t <= 6 * cus && (g.KH == 1 || g.KW == 1 || (plain && g.C <= 112));
+        else square = lines && g.Wo > 14 && t > (g.Cq <= 256 ? 1 : 2) * cus && (bytes || t <= 6 * cus) && (g.Cq > 128 || g.C > 112 || plain || t <= 4 * cus) && share_cu(3);
+        // (fewer tiles than CUs leave half of them idle, unless the tile kernel's are half as many again)
+        if (t128 <= cus && !(tn == 256 && g.Cq <= 128 && t128 * 4 >= cus)) square = false;
+    }
+    const int64_t t256 = block_tiles<Block256x64>(g.M, g.N);
+    if (square && tn && g.N > 176 && g.N <= 192 && (t256 <= cus || t256 * 2 > cus * 3)) {
+        const BlockVariant* v = fit_block(g, bytes, kBlockVariants[0], pg, npix);
+        if (v) return v;
     }
     const BlockVariant* v = square ? fit_block(g, bytes, kBlockVariants[1], pg, npix) : nullptr;
     return v ? v : picked;

@@ -634,6 +634,26 @@ def test_conv_square_tiles(sq, oracle, takes, layer, mode):
     check_layer_u8(sq, oracle, layer, mode, seed_cfg=8, out_mode=mode)
 
 
+# The small workgroups on either side of where the tile kernel hands a layer over: its tiles one above and one below the rounds that the
+# rule names for three and for five 64-channel blocks and for tiles 64 wide, 192 outputs in three columns of 64, ragged outputs and channels.
+HANDED_OVER = [
+    ("128x128", S.ConvLayer("q_1x7_c160_n96", 114, 17, 17, 160, 96, 1, 7, (1, 1), (0, 3))), (None, S.ConvLayer("q_1x7_c160_n96_less", 113, 17, 17, 160, 96, 1, 7, (1, 1), (0, 3))),
+    ("128x128", S.ConvLayer("q_1x7_c272_n80", 228, 17, 17, 272, 80, 1, 7, (1, 1), (0, 3))), (None, S.ConvLayer("q_1x7_c272_n80_less", 226, 17, 17, 272, 80, 1, 7, (1, 1), (0, 3))),
+    ("256x64", S.ConvLayer("q_1x7_c160_n48", 341, 17, 17, 160, 48, 1, 7, (1, 1), (0, 3))), (None, S.ConvLayer("q_1x7_c160_n48_less", 340, 17, 17, 160, 48, 1, 7, (1, 1), (0, 3))),
+    ("256x64", S.ConvLayer("q_3x3_c52_n192", 115, 17, 17, 52, 192, 3, 3, (1, 1), (1, 1))), ("256x64", S.ConvLayer("q_7x1_c160_n192", 115, 17, 17, 160, 192, 7, 1, (1, 1), (3, 0))),
+]
+
+
+@pytest.mark.parametrize("tile,layer", HANDED_OVER, ids=lambda v: v.name if hasattr(v, "name") else str(v))
+@pytest.mark.parametrize("mode", [S.Mode(4, S.OPT5, 1, 1), S.PLAIN8], ids=lambda m: m.label)
+def test_conv_tile_kernel_hands_over(sq, oracle, tile, layer, mode):
+    d = sq.conv_desc(layer.B, layer.H, layer.W, layer.C, layer.N, layer.KH, layer.KW, layer.stride, layer.pad)
+    text = sq.sparq_conv_plan(d, sq.mode(*mode.astuple()))
+    assert (f"small_workgroups tile={tile}" in text) if tile else (" kernel=conv_patch_kernel" in text), text
+    check_layer(sq, oracle, layer, mode, seed_cfg=8)
+    check_layer_u8(sq, oracle, layer, mode, seed_cfg=8, out_mode=mode)
+
+
 # Each of these forms, forced by the tuning hook, in every trim variant it is built for and every form of its results: int32
 # alone, fp32 alone, both, bytes, bytes trimmed with the layer's own mode, and bytes trimmed where the input already is.
 FORM_SHAPES = [
