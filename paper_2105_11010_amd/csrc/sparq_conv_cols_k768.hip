@@ -1,0 +1,6 @@
+// 1x1 SPARQ convolution with the weights in registers: up to 768 channels, every trim variant and output.
+#include "sparq_conv_cols_kernel.h"
+
+namespace sparq {
+SPARQ_DECLARE_ROWS(launch_cols_k768) { return launch_cols_kind<ColsCfg<24, 1, 1, 1, 2>>(kind, p, s); }
+}  // namespace sparq

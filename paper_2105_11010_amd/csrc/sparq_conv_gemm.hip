@@ -5,6 +5,7 @@
 #include "sparq_conv_few_kernel.h"
 #include "sparq_conv_patch_kernel.h"
 #include "sparq_conv_rows_kernel.h"
+#include "sparq_conv_cols_kernel.h"
 #include "sparq_conv_split_kernel.h"
 #include "sparq_conv_wide_kernel.h"
 
@@ -19,7 +20,7 @@ using namespace sparq;
 namespace {
 
 // ---- the one test / tuning hook (sparq_set_tuning): process-wide overrides of the kernel choice ----
-enum TunedForm { kTunedSplit = 1, kTunedRows, kTunedWide, kTunedBlock };
+enum TunedForm { kTunedSplit = 1, kTunedRows, kTunedCols, kTunedWide, kTunedBlock };
 struct Tuning {
     int path = 0;             // 0: rules decide, 1: gather kernel, 2: input-patch kernel
     char tile[16] = "";       // gather kernel tile "128x128" | "128x256" | "128x512"
@@ -279,6 +280,45 @@ const RowsVariant* pick_rows(const ConvGeom& g, bool bytes, bool plain) {
     return fit_rows(g, bytes);
 }
 
+// ---- 1x1 layers with the weights in registers ------------------------------------------------
+struct ColsVariant { int steps; const char* name; RowsLauncher fn; };
+const ColsVariant kColsVariants[] = {{8, "256", launch_cols_k256}, {12, "384", launch_cols_k384}, {16, "512", launch_cols_k512}, {24, "768", launch_cols_k768}};
+
+const ColsVariant* fit_cols(const ConvGeom& g, bool bytes) {
+    if (one_tap(g, bytes) && g.N * 4ll * 32 < 0x7FFFFFFF && (g.N + 255) / 256 <= device_cu_count() / 8)
+        for (const ColsVariant& v : kColsVariants)
+            if (g.Cq / 32 <= v.steps) return &v;
+    return nullptr;
+}
+
+// Weights in registers, against the forms above and below by 32808 timed layers of 129 to 768 channels.  `rounds`: 32-pixel fragments for
+// each workgroup of a share of the output channels; `full`: wavefronts that have channels.
+//   Up to 512 channels it walks 512 outputs per share: beyond 256 outputs, with the steps it is built for at least 7/8 filled, 256 channels 1.02-1.17 x
+//   from 1.3 rounds on (before 0.86-1.02), 384 as bytes 1.05-1.28 from 0.5 on, four-byte results 1.06-1.35 from four on (at three 0.97), 512
+//   as bytes 1.08-1.39 from 0.4 on, four-byte results 1.01-1.58 from 0.5 on; less filled (160 and 192, 320 channels) 1.04-1.13 from six rounds on but for
+//   bytes of the former (0.95-1.03).  320 and 640 outputs leave three wavefronts of eight idle (0.93-1.03), 768 as bytes two (from four rounds on 1.03-1.12,
+//   a fifth below 0.95).  Untrimmed four-byte results that the form above leaves to the tile kernels stay there.  Up to 256 outputs, where two
+//   wavefronts share their weights, from four rounds on: 384 and 512 channels as bytes 1.04-1.19 (1.0 for 160 outputs, a fifth of
+//   whose columns would be padding), 384 from 177 outputs on 1.05-1.08; 256 channels 0.83-1.03, 512 with four-byte results 0.6-0.88 (registers spill).
+//   Up to 768 channels it walks 256: 1.1-1.4 x between a half and two rounds, where the tiles of the eight-wavefront form fill their last round least
+//   (96 and 128 outputs 1.02-1.15, with a third below 0.95); beyond four 1.15-1.29 up to 256 outputs, four-byte results of more 1.05-1.17 (bytes
+//   0.97-1.16); between them 1.07-1.14 for 129 to 192 outputs, others 0.92-1.07.
+const ColsVariant* pick_cols(const ConvGeom& g, bool bytes, bool plain, bool rows) {
+    const ColsVariant* v = g.Cq > 128 && (bytes || rows || !plain || g.Cq > 512) ? fit_cols(g, bytes) : nullptr;
+    if (!v) return nullptr;
+    const bool two = v->steps <= 16, narrow = two && g.N <= 256;
+    const int64_t groups = (g.N + (two ? 63 : 31)) / (two ? 64 : 32), per = narrow ? 4 : 8, shares = (groups + per - 1) / per;
+    const int64_t tenths = (g.M + 31) / 32 * 10 / (device_cu_count() / (8 * shares) * 8);      // of a round
+    const bool filled = g.Cq * 8 >= v->steps * 32 * 7, full = groups * 10 >= shares * per * (bytes && v->steps < 16 && tenths >= 40 ? 8 : 7);
+    bool take;
+    if (narrow) take = filled && tenths >= 40 && v->steps > 8 && groups * 64 - g.N <= 16 && (bytes ? g.N > 96 : v->steps == 12 && g.N > 176);
+    else if (two && !filled) take = full && tenths >= 60 && (!bytes || v->steps == 12);
+    else if (two) take = full && tenths >= (v->steps == 8 ? 13 : v->steps == 12 ? (bytes ? 5 : 40) : bytes ? 4 : 5);
+    else if (tenths < 20) take = tenths >= 5 && (full || shares == 1) && g.N > 128;
+    else take = tenths < 40 ? g.N > 128 && g.N <= 192 : g.N > 64 && (g.N <= 256 || (!bytes && full));
+    return take ? v : nullptr;
+}
+
 // ---- 1x1 layers with a long reduction: eight wavefronts per tile ------------------------------
 struct WideVariant { const char* name; int tn; WideLauncher fn; };
 const WideVariant kWideVariants[] = {{"128x512", 512, launch_wide_512}, {"128x256", 256, launch_wide_256}};
@@ -440,6 +480,7 @@ const BlockVariant* pick_block_square(const ConvGeom& g, bool bytes, bool plain,
 struct ConvPlan {
     const SplitVariant* split = nullptr;   // split-reduction form (then pg and npix are its own)
     const RowsVariant* rows = nullptr;     // activations in registers; what follows is for calls it does not take
+    const ColsVariant* cols = nullptr;     // weights in registers; what follows is for calls it does not take
     const WideVariant* wide = nullptr;     // eight wavefronts per tile; what follows is for calls it does not take
     const BlockVariant* block = nullptr;   // small workgroups (then pg and npix are its own)
     FewGeom few{};                         // at most four channels (steps != 0)
@@ -473,6 +514,7 @@ ConvPlan make_plan_of(const ConvGeom& g, const Tuning& tune, bool forms, bool by
     if (forms && tune.form) {
         if (tune.form == kTunedRows && (pl.rows = fit_rows(gk, bytes)) != nullptr && !rows_launchable(*pl.rows, gk, bytes)) pl.rows = nullptr;
         if (tune.form == kTunedSplit && (pl.split = fit_split(gk, &pl.pg, &pl.npix)) != nullptr) return pl;
+        if (tune.form == kTunedCols) pl.cols = fit_cols(gk, bytes);
         if (tune.form == kTunedWide) pl.wide = pick_wide(gk, bytes, plain, true);
     }
     if (rules) {
@@ -480,6 +522,7 @@ ConvPlan make_plan_of(const ConvGeom& g, const Tuning& tune, bool forms, bool by
         // 256 -> 256, 784 pixels 5.3 against 5.7 us; 512 -> 256 7.9 against 6.0)
         pl.rows = pick_rows(gk, bytes, plain);
         if ((!pl.rows || g.K > 256) && (pl.split = pick_split(gk, &pl.pg, &pl.npix)) != nullptr) return pl;
+        pl.cols = pick_cols(gk, bytes, plain, pl.rows != nullptr);
         pl.wide = pick_wide(gk, bytes, plain);
     }
     // (units of four blocks and the sparse form's result rows leave LDS for one workgroup per CU, where narrow layers with more tiles
@@ -616,6 +659,7 @@ extern "C" sparq_status sparq_set_tuning(const char* spec) {
         } else if (!strcmp(key, "form")) {
             if (!strcmp(val, "split")) t.form = kTunedSplit;
             else if (!strcmp(val, "rows")) t.form = kTunedRows;
+            else if (!strcmp(val, "cols")) t.form = kTunedCols;
             else if (!strcmp(val, "wide")) t.form = kTunedWide;
             else if (!strcmp(val, "block")) t.form = kTunedBlock;
             else return SPARQ_EINVAL;
@@ -637,16 +681,17 @@ extern "C" size_t sparq_workspace_bytes(const sparq_conv_desc* desc, const sparq
 
 namespace {
 // Which of the plan's forms is launched, in the order conv_launch tries them.
-enum PlanForm { kFormFew, kFormWide, kFormSplit, kFormBlock, kFormRows, kFormPatch, kFormGather };
+enum PlanForm { kFormFew, kFormCols, kFormWide, kFormSplit, kFormBlock, kFormRows, kFormPatch, kFormGather };
 PlanForm plan_form(const ConvGeom& g, const ConvPlan& pl, bool bytes) {
     if (pl.few.steps) return kFormFew;
+    if (pl.cols) return kFormCols;
     if (pl.wide) return kFormWide;
     if (pl.split) return kFormSplit;
     if (pl.block) return kFormBlock;
     if (pl.rows && rows_launchable(*pl.rows, g, bytes)) return kFormRows;
     return pl.patch ? kFormPatch : kFormGather;
 }
-const char* const kFormKernels[] = {"conv_few_kernel", "conv_wide_kernel", "conv_split_kernel", "conv_block_kernel", "conv_rows_kernel", "conv_patch_kernel", "conv_gemm_kernel"};
+const char* const kFormKernels[] = {"conv_few_kernel", "conv_rows_kernel", "conv_wide_kernel", "conv_split_kernel", "conv_block_kernel", "conv_rows_kernel", "conv_patch_kernel", "conv_gemm_kernel"};
 
 const char* gather_tile_name(const ConvGeom& g, const Tuning& tune, bool bytes) {
     ConvGeom gt = g.fold ? folded_view(g) : g;
@@ -679,6 +724,7 @@ sparq_status plan_text(const sparq_conv_desc* desc, const sparq_mode* mode, char
         case kFormFew: snprintf(line, sizeof(line), "conv_patch_kernel few_channels tile=%dx%d", pl.few.tm, kFewTN); break;
         case kFormSplit: snprintf(line, sizeof(line), "conv_patch_kernel split_reduction tile=%s patch_pixels=%d", pl.split->name, pl.npix); break;
         case kFormBlock: snprintf(line, sizeof(line), "conv_patch_kernel small_workgroups tile=%s patch_pixels=%d", pl.block->name, pl.npix); break;
+        case kFormCols: snprintf(line, sizeof(line), "conv_patch_kernel weights_in_registers channels=%s", pl.cols->name); break;
         case kFormWide: snprintf(line, sizeof(line), "conv_gemm_kernel tile=%s eight_wavefronts", pl.wide->name); break;
         case kFormRows: snprintf(line, sizeof(line), "conv_patch_kernel in_registers channels=%s", pl.rows->name); break;
         case kFormPatch:
@@ -834,6 +880,20 @@ sparq_status conv_launch(const uint8_t* x, const void* packed_w, const sparq_con
     };
     const TrimKind okind = out_only ? trim_kind(out_mode) : kind;
 
+    // 1x1 layers with the weights in registers.
+    const auto fill_rows = [&](RowsParams& q) {
+        fill(q);
+        q.M = (int)g.M;
+        q.steps = g.Cq / 32;
+        q.g = make_patch_geom(g.B, g.H, g.W, 1, 1, g.sh, g.sw, 0, 0);
+    };
+    if (pl.cols) {
+        RowsParams q{};
+        fill_rows(q);
+        const sparq_status st = pl.cols->fn(okind, q, s);
+        if (st != SPARQ_EUNSUPPORTED) return finish(st, q.trim_out != 0);
+    }
+
     // 1x1 layers with a long reduction: eight wavefronts per tile.  (They always trim their input: a call
     // with only its output to be trimmed goes to the forms below.)
     if (pl.wide && !out_only) {
@@ -875,10 +935,7 @@ sparq_status conv_launch(const uint8_t* x, const void* packed_w, const sparq_con
     // 1x1 layers with a short reduction: activations in registers.
     if (pl.rows) {
         RowsParams q{};
-        fill(q);
-        q.M = (int)g.M;
-        q.steps = g.Cq / 32;
-        q.g = make_patch_geom(g.B, g.H, g.W, 1, 1, g.sh, g.sw, 0, 0);
+        fill_rows(q);
         const sparq_status st = pl.rows->fn(okind, q, s);
         if (st != SPARQ_EUNSUPPORTED) return finish(st, q.trim_out != 0);
     }

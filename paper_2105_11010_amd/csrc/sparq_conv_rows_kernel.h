@@ -14,7 +14,7 @@
 // are the row operand and a store writes whole runs.
 // Many pixels and few enough weights: one workgroup per CU holds all of them in LDS, and memory is what bounds the layer (launch_rows_held,
 // where the figures are).  Otherwise the weights come from L2, and with 256 channels and more they and the trim's vector instructions do
-// (256 -> 1024, 50176 pixels: 42 -> 29 us; 512 -> 1024: 69 -> 47; vector issue 45 to 53 % of the cycles, waits 25 % of a wavefront's life).
+// (192 -> 512: vector issue 45 to 53 % of the cycles, waits 25 % of a wavefront's life); wide layers of 256 channels and more hold the weights instead (sparq_conv_cols_kernel.h).
 #pragma once
 #include "sparq_conv_patch_kernel.h"
 

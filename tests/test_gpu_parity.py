@@ -690,6 +690,38 @@ def test_conv_every_variant_of_a_form(sq, oracle, tuning, form, layer, mode):
     assert np.array_equal(run_conv_u8(sq, x, w, f, layer, S.PLAIN8, out_mode=mode), oracle.trim(plain, **mode.kwargs()))
 
 
+# The weights in registers: every number of steps held, steps past the layer's own, shares of the output channels (with idle wavefronts in
+# the last), two wavefronts for the same channels, a stride, fewer pixels than a fragment and than workgroups, several tiles with an odd last one;
+# then where the rule takes it, at the fewest pixels up to 512 channels.
+COLS_SHAPES = [
+    (1, S.ConvLayer("k_c132_n272", 1, 1031, 1, 132, 272)), (1, S.ConvLayer("k_c256_n48", 1, 31, 1, 256, 48)), (1, S.ConvLayer("k_c256_n528_s2", 3, 29, 31, 256, 528, 1, 1, (2, 2), (0, 0))),
+    (1, S.ConvLayer("k_c200_n1040", 1, 7777, 1, 200, 1040)), (1, S.ConvLayer("k_c384_n272", 1, 9001, 1, 384, 272)), (1, S.ConvLayer("k_c330_n208", 1, 16421, 1, 330, 208)),
+    (1, S.ConvLayer("k_c512_n560_s2", 2, 99, 101, 512, 560, 1, 1, (2, 2), (0, 0))), (1, S.ConvLayer("k_c448_n240", 1, 24611, 1, 448, 240)), (1, S.ConvLayer("k_c512_n33", 1, 65, 1, 512, 33)),
+    (1, S.ConvLayer("k_c768_n288", 1, 8225, 1, 768, 288)), (1, S.ConvLayer("k_c580_n96", 1, 24577, 1, 580, 96)),
+    (0, S.ConvLayer("k_c256_n512", 1, 10656, 1, 256, 512)), (0, S.ConvLayer("k_c384_n512", 1, 32768, 1, 384, 512)), (0, S.ConvLayer("k_c512_n512", 1, 4096, 1, 512, 512)),
+    (0, S.ConvLayer("k_c768_n144", 1, 12321, 1, 768, 144)),
+]
+
+
+@pytest.mark.parametrize("forced,layer", COLS_SHAPES, ids=lambda v: v.name if hasattr(v, "name") else str(v))
+@pytest.mark.parametrize("mode", FORM_MODES, ids=lambda m: m.label)
+def test_conv_weights_in_registers(sq, oracle, tuning, forced, layer, mode):
+    if forced:
+        tuning("form=cols")
+    d = sq.conv_desc(layer.B, layer.H, layer.W, layer.C, layer.N, layer.KH, layer.KW, layer.stride, layer.pad)
+    assert "weights_in_registers" in sq.sparq_conv_plan(d, sq.mode(*mode.astuple()))
+    x, w, sc = S.gen_layer(8, layer)
+    ref_acc, ref_out = oracle.conv_gemm(x, w, layer.stride, layer.pad, scale=sc, **mode.kwargs())
+    for want_acc, want_out in ((True, False), (False, True), (True, True)):
+        acc, out = run_conv(sq, x, w, sc, layer, mode, want_acc, want_out)
+        assert acc is None or np.array_equal(acc, ref_acc)
+        assert out is None or np.all(np.abs(out.astype(np.float64) - ref_out) <= 1e-6 * np.abs(ref_out))
+    f = S.gen_requant(layer, S.rng_for(8, 900 + layer.index))
+    ref = oracle.requant(ref_acc, f)
+    assert np.array_equal(run_conv_u8(sq, x, w, f, layer, mode), ref)
+    assert np.array_equal(run_conv_u8(sq, x, w, f, layer, mode, out_mode=mode), oracle.trim(ref, **mode.kwargs()))
+
+
 # Shapes chosen for the input-patch kernel: tiles that span several image rows and several images,
 # one-row tiles, every staging variant (64/128/256-channel units), several output-channel tiles.
 PATCH_SHAPES = [
