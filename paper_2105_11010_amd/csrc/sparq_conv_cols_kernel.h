@@ -1,4 +1,4 @@
-// Fused SPARQ convolution for gfx950, 1x1 filters of up to 768 channels and more output channels: the weights stay in registers.
+// Fused SPARQ convolution for gfx950, 1x1 filters of up to 1024 channels and more output channels: the weights stay in registers.
 //
 // The form with the activations in registers asks L1 for all weights once per 32 pixels and wavefront, and where pixels are few it splits the
 // output channels over wavefronts that each load and trim the same pixels again.  Here a wavefront holds the weights of 64 (or 32) output channels
@@ -9,11 +9,12 @@
 // Up to 256 channels the requantisation's offsets and factors stay in registers, too (as the first matrix instruction's addend the offsets cost
 // nothing); beyond, they come from LDS.
 // The two wavefronts of a SIMD stage at opposite ends of a tile, so that one multiplies while the other trims or converts.
-// Cold, bytes, us before -> after: 256 -> 1024, 50176 pixels 28.5 -> 25.1; 256 -> 512/2, 200704 pixels 57.9 -> 44.8; 512 -> 256 56.2 -> 45.6;
-// 512 -> 1024/2, 50176 pixels 48.1 -> 35.6; 512 -> 2048, 12544 pixels 26.1 -> 22.5; fp32, 768 -> 192, 36992 pixels 22.5 -> 20.1.
+// Cold, bytes, us before -> after: 256 -> 1024, 50176 pixels 28.5 -> 25.1; 256 -> 512/2, 200704 pixels 57.9 -> 44.8; 512 -> 256 56.2 -> 44.7;
+// 512 -> 1024/2, 50176 pixels 48.1 -> 36.0; 512 -> 2048, 12544 pixels 26.1 -> 22.5; 1024 -> 256, 50176 pixels 30.0 -> 26.7; fp32, 768 -> 192, 36992
+// pixels 22.8 -> 18.4.
 // Bound by vector arithmetic and the stores: per pixel 256 -> 1024 takes 1.4 times as long as a copy of its bytes, and 7 us are the first
-// loads, weights and trim.  (Vector issue 52 % of the cycles, matrix pipeline 27 %.  Three tiles requested ahead instead of two, waits taken
-// at the start and 16 wavefronts' worth of outputs in two walks instead of two workgroups: within 3 % of this.)
+// loads, weights and trim.  (Vector issue 52 % of the cycles, matrix pipeline 27 %.  Two tiles requested ahead, with the tiles a round of requests
+// leaves empty: up to 7 % slower; 16 wavefronts' worth of outputs in two walks instead of two workgroups: within 3 % of this.)
 #pragma once
 #include "sparq_conv_rows_kernel.h"
 
@@ -22,10 +23,10 @@ namespace sparq {
 constexpr int kColsThreads = 512;
 
 // KS 32-index steps and 32 FN output channels of weights in a wavefront's registers; WM wavefronts hold the same ones, each with TI fragments
-// of 32 pixels per tile; D tiles are requested ahead.
-template <int KS, int FN, int WM, int TI, int D>
+// of 32 pixels per tile.
+template <int KS, int FN, int WM, int TI>
 struct ColsCfg {
-    static constexpr int kKS = KS, kFN = FN, kWM = WM, kTI = TI, kTF = WM * TI, kAhead = D;
+    static constexpr int kKS = KS, kFN = FN, kWM = WM, kTI = TI, kTF = WM * TI;
     static constexpr bool kTable = KS > 8;                   // bytes: what belongs to the channels stands in LDS, not in registers
     static constexpr int kTableBytes = kTable ? 8 / WM * 32 * FN * 8 : 0;
     static constexpr int kPlane = kTF * 32 * kChunk + 16;    // bytes between a buffer's 16-channel planes
@@ -46,7 +47,7 @@ struct ColsParams {
 template <class Cfg, int KIND, bool U8>
 __global__ __launch_bounds__(kColsThreads, 2) void conv_rows_kernel(const ColsParams cp) {
     const RowsParams& p = cp.r;
-    constexpr int KS = Cfg::kKS, FN = Cfg::kFN, WM = Cfg::kWM, TI = Cfg::kTI, TF = Cfg::kTF, CH = 2 * KS, NR = Cfg::kRequests, D = Cfg::kAhead, PITCH = Cfg::kPitch;
+    constexpr int KS = Cfg::kKS, FN = Cfg::kFN, WM = Cfg::kWM, TI = Cfg::kTI, TF = Cfg::kTF, CH = 2 * KS, NR = Cfg::kRequests, PITCH = Cfg::kPitch;
     constexpr bool LT = Cfg::kTable && U8;
     constexpr int LPR = 2 * FN, RPR = 64 / LPR;              // lanes per result row, rows per store
     extern __shared__ __attribute__((aligned(16))) uint8_t lds[];            // [buffers][U8: result rows per wavefront]
@@ -69,8 +70,8 @@ __global__ __launch_bounds__(kColsThreads, 2) void conv_rows_kernel(const ColsPa
         __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(p.scale), 0, p.scale ? p.N * 4 : 0, 0x00020000);
 
     // ---- activations: a tile's chunks go round over the lanes, a pixel's side by side ----
-    v4u raw[D][NR];
-    auto load_x = [&](v4u (&to)[NR], int t) __attribute__((always_inline)) {
+    v4u raw[NR];
+    auto load_x = [&](int t) __attribute__((always_inline)) {
 #pragma unroll
         for (int r = 0; r < NR; ++r) {
             const int q = tid + kColsThreads * r, ch = q % CH, m = (f0 + t * TF) * 32 + q / CH;
@@ -78,14 +79,14 @@ __global__ __launch_bounds__(kColsThreads, 2) void conv_rows_kernel(const ColsPa
             int pix = m;
             if (p.g.rm_wo) pix = remap_pixel(p.g, live ? m : 0);
             const uint32_t off = live ? (uint32_t)(pix * p.C + ch * kChunk) : kPatchInvalidOffset;
-            to[r] = __builtin_amdgcn_raw_buffer_load_b128(xrsrc, (int)off, 0, 0);
+            raw[r] = __builtin_amdgcn_raw_buffer_load_b128(xrsrc, (int)off, 0, 0);
         }
     };
-    auto stage = [&](const v4u (&from)[NR], int buf) __attribute__((always_inline)) {
+    auto stage = [&](int buf) __attribute__((always_inline)) {
 #pragma unroll
         for (int r = 0; r < NR; ++r) {
             const int q = tid + kColsThreads * r;
-            v4u v = from[r];
+            v4u v = raw[r];
             if (KIND != kTrimNone && p.trim_in) {
 #pragma unroll
                 for (int j = 0; j < 4; ++j) v[j] = trim4_kind<KIND>(v[j], p.luts);
@@ -253,8 +254,7 @@ __global__ __launch_bounds__(kColsThreads, 2) void conv_rows_kernel(const ColsPa
         }
     };
 
-#pragma unroll
-    for (int k = 0; k < D; ++k) load_x(raw[k], k);
+    load_x(0);
     load_b();
     if constexpr (LT)
         for (int i = tid; i < 8 / WM * 32 * FN; i += kColsThreads) {
@@ -262,32 +262,31 @@ __global__ __launch_bounds__(kColsThreads, 2) void conv_rows_kernel(const ColsPa
             tcorr[i] = (int)__builtin_amdgcn_raw_buffer_load_b32(krsrc, off, 0, 0) * 128;
             tfac[i] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(frsrc, off, 0, 0));
         }
-    stage(raw[0], 0);
+    stage(0);
     settle_b();
-    load_x(raw[0], D);
+    load_x(1);
     __syncthreads();
     // The two wavefronts of a SIMD stage at different ends of a tile: in step they would both multiply and then both convert.
-    // (tiles past the last one are empty)
     auto walk = [&](auto first_) __attribute__((always_inline)) {
         constexpr bool FIRST = decltype(first_)::value;
-        for (int t = 0; t < nt; t += D)
-#pragma unroll
-            for (int k = 0; k < D; ++k) {
-                if constexpr (FIRST) {
-                    stage(raw[(k + 1) % D], (t + k + 1) & 1);
-                    load_x(raw[(k + 1) % D], t + k + 1 + D);
-                }
-#pragma unroll
-                for (int i = 0; i < TI; ++i) fragment(t + k, (t + k) & 1, wm + i * WM);
-                if constexpr (!FIRST) {
-                    stage(raw[(k + 1) % D], (t + k + 1) & 1);
-                    load_x(raw[(k + 1) % D], t + k + 1 + D);
-                }
-                __syncthreads();
+        for (int t = 0; t < nt - 1; ++t) {
+            if constexpr (FIRST) {
+                stage((t + 1) & 1);
+                load_x(t + 2);
             }
+#pragma unroll
+            for (int i = 0; i < TI; ++i) fragment(t, t & 1, wm + i * WM);
+            if constexpr (!FIRST) {
+                stage((t + 1) & 1);
+                load_x(t + 2);
+            }
+            __syncthreads();
+        }
     };
     if (wave < 4) walk(std::false_type{});
     else walk(std::true_type{});
+#pragma unroll
+    for (int i = 0; i < TI; ++i) fragment(nt - 1, (nt - 1) & 1, wm + i * WM);
 }
 
 // `p` carries everything except what splits the launch.
@@ -349,5 +348,6 @@ SPARQ_DECLARE_ROWS(launch_cols_k256);
 SPARQ_DECLARE_ROWS(launch_cols_k384);
 SPARQ_DECLARE_ROWS(launch_cols_k512);
 SPARQ_DECLARE_ROWS(launch_cols_k768);
+SPARQ_DECLARE_ROWS(launch_cols_k1024);
 
 }  // namespace sparq

@@ -282,7 +282,7 @@ const RowsVariant* pick_rows(const ConvGeom& g, bool bytes, bool plain) {
 
 // ---- 1x1 layers with the weights in registers ------------------------------------------------
 struct ColsVariant { int steps; const char* name; RowsLauncher fn; };
-const ColsVariant kColsVariants[] = {{8, "256", launch_cols_k256}, {12, "384", launch_cols_k384}, {16, "512", launch_cols_k512}, {24, "768", launch_cols_k768}};
+const ColsVariant kColsVariants[] = {{8, "256", launch_cols_k256}, {12, "384", launch_cols_k384}, {16, "512", launch_cols_k512}, {24, "768", launch_cols_k768}, {32, "1024", launch_cols_k1024}};
 
 const ColsVariant* fit_cols(const ConvGeom& g, bool bytes) {
     if (one_tap(g, bytes) && g.N * 4ll * 32 < 0x7FFFFFFF && (g.N + 255) / 256 <= device_cu_count() / 8)
@@ -291,19 +291,23 @@ const ColsVariant* fit_cols(const ConvGeom& g, bool bytes) {
     return nullptr;
 }
 
-// Weights in registers, against the forms above and below by 32808 timed layers of 129 to 768 channels.  `rounds`: 32-pixel fragments for
+// Weights in registers, against the forms above and below by 32808 timed layers of 129 to 768 channels and 8749 of up to 1024.  `rounds`: 32-pixel fragments for
 // each workgroup of a share of the output channels; `full`: wavefronts that have channels.
 //   Up to 512 channels it walks 512 outputs per share: beyond 256 outputs, with the steps it is built for at least 7/8 filled, 256 channels 1.02-1.17 x
 //   from 1.3 rounds on (before 0.86-1.02), 384 as bytes 1.05-1.28 from 0.5 on, four-byte results 1.06-1.35 from four on (at three 0.97), 512
 //   as bytes 1.08-1.39 from 0.4 on, four-byte results 1.01-1.58 from 0.5 on; less filled (160 and 192, 320 channels) 1.04-1.13 from six rounds on but for
 //   bytes of the former (0.95-1.03).  320 and 640 outputs leave three wavefronts of eight idle (0.93-1.03), 768 as bytes two (from four rounds on 1.03-1.12,
-//   a fifth below 0.95).  Untrimmed four-byte results that the form above leaves to the tile kernels stay there.  Up to 256 outputs, where two
+//   a fifth below 0.95).  Untrimmed four-byte results that the form above leaves to the tile
+//   kernels stay there, as do up to one round of more than 768 channels that the form below leaves.  Up to 256 outputs, where two
 //   wavefronts share their weights, from four rounds on: 384 and 512 channels as bytes 1.04-1.19 (1.0 for 160 outputs, a fifth of
 //   whose columns would be padding), 384 from 177 outputs on 1.05-1.08; 256 channels 0.83-1.03, 512 with four-byte results 0.6-0.88 (registers spill).
-//   Up to 768 channels it walks 256: 1.1-1.4 x between a half and two rounds, where the tiles of the eight-wavefront form fill their last round least
+//   Up to 1024 channels it walks 256.  Beyond 768: bytes 1.16-1.44 x between a half and two rounds, four-byte results 1.09-1.25, both
+//   0.89-1.04 from there to four (bytes up to 160 outputs 1.08), then up to 256 outputs 1.1-1.3 (97 to 128 as four-byte results 1.02, a quarter below
+//   0.95), four-byte results of more 1.03-1.15 up to twenty rounds, bytes of more 0.92-1.07 (128 x 512 tiles).
+//   Up to 768: 1.1-1.4 x between a half and two rounds, where the tiles of the eight-wavefront form fill their last round least
 //   (96 and 128 outputs 1.02-1.15, with a third below 0.95); beyond four 1.15-1.29 up to 256 outputs, four-byte results of more 1.05-1.17 (bytes
 //   0.97-1.16); between them 1.07-1.14 for 129 to 192 outputs, others 0.92-1.07.
-const ColsVariant* pick_cols(const ConvGeom& g, bool bytes, bool plain, bool rows) {
+const ColsVariant* pick_cols(const ConvGeom& g, bool bytes, bool plain, bool rows, bool wide) {
     const ColsVariant* v = g.Cq > 128 && (bytes || rows || !plain || g.Cq > 512) ? fit_cols(g, bytes) : nullptr;
     if (!v) return nullptr;
     const bool two = v->steps <= 16, narrow = two && g.N <= 256;
@@ -314,8 +318,9 @@ const ColsVariant* pick_cols(const ConvGeom& g, bool bytes, bool plain, bool row
     if (narrow) take = filled && tenths >= 40 && v->steps > 8 && groups * 64 - g.N <= 16 && (bytes ? g.N > 96 : v->steps == 12 && g.N > 176);
     else if (two && !filled) take = full && tenths >= 60 && (!bytes || v->steps == 12);
     else if (two) take = full && tenths >= (v->steps == 8 ? 13 : v->steps == 12 ? (bytes ? 5 : 40) : bytes ? 4 : 5);
-    else if (tenths < 20) take = tenths >= 5 && (full || shares == 1) && g.N > 128;
-    else take = tenths < 40 ? g.N > 128 && g.N <= 192 : g.N > 64 && (g.N <= 256 || (!bytes && full));
+    else if (tenths < 20) take = tenths >= (v->steps == 24 || wide ? 5 : 10) && (full || shares == 1) && g.N > (bytes && v->steps == 32 ? 64 : 128);
+    else if (tenths < 40) take = v->steps == 24 ? g.N > 128 && g.N <= 192 : bytes && g.N > 64 && g.N <= 160;
+    else take = g.N <= 256 ? g.N > (!bytes && v->steps == 32 ? 128 : 64) : !bytes && full && (v->steps == 24 || tenths < 200);
     return take ? v : nullptr;
 }
 
@@ -522,8 +527,8 @@ ConvPlan make_plan_of(const ConvGeom& g, const Tuning& tune, bool forms, bool by
         // 256 -> 256, 784 pixels 5.3 against 5.7 us; 512 -> 256 7.9 against 6.0)
         pl.rows = pick_rows(gk, bytes, plain);
         if ((!pl.rows || g.K > 256) && (pl.split = pick_split(gk, &pl.pg, &pl.npix)) != nullptr) return pl;
-        pl.cols = pick_cols(gk, bytes, plain, pl.rows != nullptr);
         pl.wide = pick_wide(gk, bytes, plain);
+        pl.cols = pick_cols(gk, bytes, plain, pl.rows != nullptr, pl.wide != nullptr);
     }
     // (units of four blocks and the sparse form's result rows leave LDS for one workgroup per CU, where narrow layers with more tiles
     // than CUs want two: 72 -> 16, expanded to four blocks, 401408 pixels 63 against 54 us in units of two)

@@ -698,6 +698,7 @@ COLS_SHAPES = [
     (1, S.ConvLayer("k_c200_n1040", 1, 7777, 1, 200, 1040)), (1, S.ConvLayer("k_c384_n272", 1, 9001, 1, 384, 272)), (1, S.ConvLayer("k_c330_n208", 1, 16421, 1, 330, 208)),
     (1, S.ConvLayer("k_c512_n560_s2", 2, 99, 101, 512, 560, 1, 1, (2, 2), (0, 0))), (1, S.ConvLayer("k_c448_n240", 1, 24611, 1, 448, 240)), (1, S.ConvLayer("k_c512_n33", 1, 65, 1, 512, 33)),
     (1, S.ConvLayer("k_c768_n288", 1, 8225, 1, 768, 288)), (1, S.ConvLayer("k_c580_n96", 1, 24577, 1, 580, 96)),
+    (1, S.ConvLayer("k_c1024_n272", 1, 8225, 1, 1024, 272)), (1, S.ConvLayer("k_c780_n16", 1, 24577, 1, 780, 16)), (0, S.ConvLayer("k_c1024_n512", 1, 4099, 1, 1024, 512)),
     (0, S.ConvLayer("k_c256_n512", 1, 10656, 1, 256, 512)), (0, S.ConvLayer("k_c384_n512", 1, 32768, 1, 384, 512)), (0, S.ConvLayer("k_c512_n512", 1, 4096, 1, 512, 512)),
     (0, S.ConvLayer("k_c768_n144", 1, 12321, 1, 768, 144)),
 ]
