@@ -151,6 +151,13 @@ SPARQ_HD uint32_t sparse24_partner_flags(int j) { return j == 0 ? 0x0B090A08u : 
 
 SPARQ_HD uint32_t bfi(uint32_t mask, uint32_t a, uint32_t b) { return (mask & a) | (~mask & b); }
 
+// pm ? a : b (0xCA) or its complement (0x35).  A pm that the compiler knows goes past the instruction, which it does not see through.
+template <uint32_t TABLE>
+SPARQ_HD uint32_t pick(uint32_t pm, uint32_t a, uint32_t b) {
+    if (__builtin_constant_p(pm)) return TABLE == 0xCA ? bfi(pm, a, b) : ~bfi(pm, a, b);
+    return bitop3<TABLE>(pm, a, b);
+}
+
 // 0xFF in every byte whose bit 7 is set in f
 SPARQ_HD uint32_t expand_bit7(uint32_t f) { return perm(f << 8, f, 0x090B080Au); }
 // 0xFF in every byte whose PAIR PARTNER (byte ^ 1) has bit 7 set in f
@@ -183,8 +190,8 @@ SPARQ_HD uint32_t trim4_beside(uint32_t x, uint32_t pm, const TrimLuts& L) {
     uint32_t above = 0;         // the bits above the window, per byte (only needed for ROUND)
     if (PAIR && WIDE) {
         const uint32_t low_w = low_mask(selA, selB, L.wa_hi, L.wa_lo, L.wb_hi, L.wb_lo);
-        low = bitop3<0xCA>(pm, low_n, low_w);                                  // pm ? low_n : low_w
-        if (ROUND) above = bitop3<0x35>(pm, (low_n << L.n) | L.ones_n, (low_w << L.n2) | L.ones_w);    // ~(pm ? . : .)
+        low = pick<0xCA>(pm, low_n, low_w);                                    // pm ? low_n : low_w
+        if (ROUND) above = pick<0x35>(pm, (low_n << L.n) | L.ones_n, (low_w << L.n2) | L.ones_w);      // ~(pm ? . : .)
     } else {
         if (PAIR) low &= pm;
         if (ROUND) above = ~((low << L.n) | L.ones_n);
@@ -207,6 +214,7 @@ SPARQ_HD uint32_t trim4(uint32_t x, const TrimLuts& L) {
 // residual": x + 2^(s-1) cannot leave the byte unless the value saturates.
 template <bool PAIR>
 SPARQ_HD uint32_t trim4_round_n4_beside(uint32_t x, uint32_t pm, const TrimLuts& L) {
+    if (PAIR && __builtin_constant_p(pm) && pm == 0) return x;                 // (the whole byte is the window)
     const uint32_t selA = (x >> 5) & 0x07070707u;
     const uint32_t selB = (x >> 2) & 0x07070707u;
     const uint32_t low_a = perm(L.a_hi, L.a_lo, selA), low_b = perm(L.b_hi, L.b_lo, selB);
