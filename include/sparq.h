@@ -281,11 +281,11 @@ sparq_status sparq_sparse24_plan(const sparq_conv_desc *desc, const sparq_mode *
  *   patch_tn=64|128|256      input-patch kernel: output channels per tile
  *   patch_ws=0|1             input-patch kernel: plain / wave-specialised form
  *   form=split|rows|cols|wide|block   conv_split_kernel, conv_rows_kernel
- *                            (activations or weights in registers),
- *                            conv_wide_kernel or conv_block_kernel wherever the
- *                            layer fits it, the tile kernels elsewhere (2:4
- *                            layers that run on the sparse instruction's plan
- *                            keep to the tile kernels)
+ *                            (activations in registers), conv_cols_kernel
+ *                            (weights in registers), conv_wide_kernel or
+ *                            conv_block_kernel wherever the layer fits it, the
+ *                            tile kernels elsewhere (2:4 layers that run on the
+ *                            sparse instruction's plan keep to the tile kernels)
  * Any of the keys switches the rules of the other forms off.
  * Anything else returns SPARQ_EINVAL and leaves the override as it was.
  * Changing it while convolution calls are in flight on other threads makes

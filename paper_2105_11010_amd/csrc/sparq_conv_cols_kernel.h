@@ -45,7 +45,7 @@ struct ColsParams {
 };
 
 template <class Cfg, int KIND, bool U8>
-__global__ __launch_bounds__(kColsThreads, 2) void conv_rows_kernel(const ColsParams cp) {
+__global__ __launch_bounds__(kColsThreads, 2) void conv_cols_kernel(const ColsParams cp) {
     const RowsParams& p = cp.r;
     constexpr int KS = Cfg::kKS, FN = Cfg::kFN, WM = Cfg::kWM, TI = Cfg::kTI, TF = Cfg::kTF, CH = 2 * KS, NR = Cfg::kRequests, PITCH = Cfg::kPitch;
     constexpr bool LT = Cfg::kTable && U8;
@@ -155,7 +155,7 @@ __global__ __launch_bounds__(kColsThreads, 2) void conv_rows_kernel(const ColsPa
     float* const tfac = reinterpret_cast<float*>(tcorr) + 8 / WM * 32 * FN;
     const int tn = wn * 32 * FN + 4 * lhi;
     uint8_t* const turn = lds + 2 * Cfg::kBuf + wave * 32 * PITCH;
-    auto fragment = [&](int t, int buf, int i) __attribute__((always_inline)) {
+    auto fragment = [&](int t, int i) __attribute__((always_inline)) {
         const int f = f0 + t * TF + i;
         const bool live = f < f1 && n0 < p.N;                // uniform
         const int m0 = f * 32, rows = !live ? 0 : p.M - m0 < 32 ? p.M - m0 : 32;
@@ -275,7 +275,7 @@ __global__ __launch_bounds__(kColsThreads, 2) void conv_rows_kernel(const ColsPa
                 load_x(t + 2);
             }
 #pragma unroll
-            for (int i = 0; i < TI; ++i) fragment(t, t & 1, wm + i * WM);
+            for (int i = 0; i < TI; ++i) fragment(t, wm + i * WM);
             if constexpr (!FIRST) {
                 stage((t + 1) & 1);
                 load_x(t + 2);
@@ -286,7 +286,7 @@ __global__ __launch_bounds__(kColsThreads, 2) void conv_rows_kernel(const ColsPa
     if (wave < 4) walk(std::false_type{});
     else walk(std::true_type{});
 #pragma unroll
-    for (int i = 0; i < TI; ++i) fragment(nt - 1, (nt - 1) & 1, wm + i * WM);
+    for (int i = 0; i < TI; ++i) fragment(nt - 1, wm + i * WM);
 }
 
 // `p` carries everything except what splits the launch.
@@ -306,7 +306,7 @@ sparq_status launch_cols_cfg(const RowsParams& p, hipStream_t s) {
     q.one_more = (int)(fragments % wgs);
     constexpr int64_t lds_bytes = 2 * Cfg::kBuf + (U8 ? 8 * 32 * Cfg::kPitch + Cfg::kTableBytes : 0);
     static_assert(lds_bytes <= kLdsPerCu);
-    void (*const kern)(const ColsParams) = conv_rows_kernel<Cfg, KIND, U8>;
+    auto kern = conv_cols_kernel<Cfg, KIND, U8>;
     if constexpr (lds_bytes > 64 * 1024) {                   // (what a launch may use without asking)
         static std::atomic<bool> lds_set_dev[kMaxDevices];   // (concurrent callers at worst repeat the call, with the same value)
         std::atomic<bool>& lds_set = lds_set_dev[current_device_slot()];

@@ -697,7 +697,7 @@ PlanForm plan_form(const ConvGeom& g, const ConvPlan& pl, bool bytes) {
     if (pl.rows && rows_launchable(*pl.rows, g, bytes)) return kFormRows;
     return pl.patch ? kFormPatch : kFormGather;
 }
-const char* const kFormKernels[] = {"conv_few_kernel", "conv_rows_kernel", "conv_wide_kernel", "conv_split_kernel", "conv_block_kernel", "conv_rows_kernel", "conv_patch_kernel", "conv_gemm_kernel"};
+const char* const kFormKernels[] = {"conv_few_kernel", "conv_cols_kernel", "conv_wide_kernel", "conv_split_kernel", "conv_block_kernel", "conv_rows_kernel", "conv_patch_kernel", "conv_gemm_kernel"};
 
 const char* gather_tile_name(const ConvGeom& g, const Tuning& tune, bool bytes) {
     ConvGeom gt = g.fold ? folded_view(g) : g;

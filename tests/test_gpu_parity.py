@@ -482,7 +482,7 @@ def test_conv_split_reduction_of_short_patch_rows(sq, oracle, tile, layer, mode)
 
 # The form with the activations in registers (1x1 layers): every number of reduction steps it holds and numbers in between,
 # pixels and channels that fill no fragment, strides, odd channel counts, runs of fewer than 128 result bytes, shares of the
-# output channels, 64 pixels per wavefront (many pixels and channels).
+# output channels, 64 pixels per wavefront (many pixels and channels; asked for, since the rule holds the weights instead).
 ROWS_SHAPES = [
     S.ConvLayer("r_c64_m3", 1, 3, 1, 64, 64), S.ConvLayer("r_c64_n33", 1, 65, 1, 64, 33), S.ConvLayer("r_c48_n48", 1, 9, 7, 48, 48),
     S.ConvLayer("r_c128_n80_s2", 3, 15, 13, 128, 80, 1, 1, (2, 2), (0, 0)), S.ConvLayer("r_c65_n144", 2, 11, 11, 65, 144),
@@ -495,9 +495,12 @@ ROWS_SHAPES = [
 
 @pytest.mark.parametrize("layer", ROWS_SHAPES, ids=lambda l: l.name)
 @pytest.mark.parametrize("mode", [S.Mode(4, S.OPT5, 1, 1), S.Mode(3, S.OPT6_3B, 0, 1), S.PLAIN8], ids=lambda m: m.label)
-def test_conv_activations_in_registers(sq, oracle, layer, mode):
+def test_conv_activations_in_registers(sq, oracle, tuning, layer, mode):
+    if layer.name.endswith("_wide"):
+        tuning("form=rows")
     d = sq.conv_desc(layer.B, layer.H, layer.W, layer.C, layer.N, layer.KH, layer.KW, layer.stride, layer.pad)
-    assert "in_registers" in sq.sparq_conv_plan(d, sq.mode(*mode.astuple()))
+    words = sq.sparq_conv_plan(d, sq.mode(*mode.astuple())).split()
+    assert "kernel=conv_rows_kernel" in words and (layer.N % 16 or "u8_kernel=conv_rows_kernel" in words), words
     check_layer(sq, oracle, layer, mode, seed_cfg=8)
     check_layer_u8(sq, oracle, layer, mode, seed_cfg=8, out_mode=S.Mode(4, S.OPT5, 1, 1))
 
@@ -509,7 +512,7 @@ ROWS_HELD_SHAPES = [
     S.ConvLayer("rh_c40_n33", 1, 144193, 1, 40, 33), S.ConvLayer("rh_c64_n208", 1, 131103, 1, 64, 208), S.ConvLayer("rh_c64_n64_s2", 6, 299, 301, 64, 64, 1, 1, (2, 2), (0, 0)),
     S.ConvLayer("rh_c96_n96", 1, 196641, 1, 96, 96), S.ConvLayer("rh_c160_n128", 1, 262175, 1, 160, 128), S.ConvLayer("rh_c256_n64", 1, 144224, 1, 256, 64),
     S.ConvLayer("rh_c260_n16", 1, 147457, 1, 260, 16), S.ConvLayer("rh_c384_n224", 1, 98305, 1, 384, 224), S.ConvLayer("rh_c448_n48", 1, 98335, 1, 448, 48),
-    S.ConvLayer("rh_c512_n208", 1, 98304, 1, 512, 208), S.ConvLayer("rh_c512_n240", 1, 196609, 1, 512, 240),
+    S.ConvLayer("rh_c512_n208", 1, 98304, 1, 512, 208), S.ConvLayer("rh_c512_n224", 1, 196609, 1, 512, 224),
 ]
 
 
@@ -710,7 +713,8 @@ def test_conv_weights_in_registers(sq, oracle, tuning, forced, layer, mode):
     if forced:
         tuning("form=cols")
     d = sq.conv_desc(layer.B, layer.H, layer.W, layer.C, layer.N, layer.KH, layer.KW, layer.stride, layer.pad)
-    assert "weights_in_registers" in sq.sparq_conv_plan(d, sq.mode(*mode.astuple()))
+    words = sq.sparq_conv_plan(d, sq.mode(*mode.astuple())).split()
+    assert "kernel=conv_cols_kernel" in words and (layer.N % 16 or "u8_kernel=conv_cols_kernel" in words), words
     x, w, sc = S.gen_layer(8, layer)
     ref_acc, ref_out = oracle.conv_gemm(x, w, layer.stride, layer.pad, scale=sc, **mode.kwargs())
     for want_acc, want_out in ((True, False), (False, True), (True, True)):
@@ -721,6 +725,8 @@ def test_conv_weights_in_registers(sq, oracle, tuning, forced, layer, mode):
     ref = oracle.requant(ref_acc, f)
     assert np.array_equal(run_conv_u8(sq, x, w, f, layer, mode), ref)
     assert np.array_equal(run_conv_u8(sq, x, w, f, layer, mode, out_mode=mode), oracle.trim(ref, **mode.kwargs()))
+    plain = oracle.requant(oracle.conv_gemm(x, w, layer.stride, layer.pad, **S.PLAIN8.kwargs())[0], f)
+    assert np.array_equal(run_conv_u8(sq, x, w, f, layer, S.PLAIN8, out_mode=mode), oracle.trim(plain, **mode.kwargs()))
 
 
 # Shapes chosen for the input-patch kernel: tiles that span several image rows and several images,

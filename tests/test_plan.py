@@ -74,7 +74,7 @@ def words(text, key):
     ((64, 32, 32, 512, 512, 3, 1), "conv_patch_kernel", "conv_patch_kernel"),
     ((1, 65536, 1, 4608, 512, 1, 0), "conv_wide_kernel", "conv_wide_kernel:128x512"),
     ((256, 56, 56, 64, 256, 1, 0), "conv_patch_kernel", "conv_rows_kernel"),            # large four-byte rows / byte rows
-    ((256, 14, 14, 256, 1024, 1, 0), "conv_rows_kernel", "conv_rows_kernel"),
+    ((256, 14, 14, 256, 1024, 1, 0), "conv_cols_kernel", "conv_cols_kernel"),             # weights in registers
     ((256, 56, 56, 64, 64, 3, 1), "conv_block_kernel", "conv_block_kernel"),
     ((256, 28, 28, 128, 128, 3, 1), "conv_patch_kernel", "conv_block_kernel"),          # 113 to 128 channels: bytes only
     ((128, 35, 35, 96, 96, 3, 1), "conv_patch_kernel", "conv_patch_kernel"),
@@ -120,8 +120,9 @@ M45, PLAIN = S.Mode(4, S.OPT5, 1, 1), S.PLAIN8
     ("block", (206, 32, 32, 64, 72, 2, 1), PLAIN, (False, False)), ("block", (206, 32, 32, 64, 80, 2, 1), PLAIN, (True, True)),
     ("block", (51, 56, 56, 64, 100, (3, 1), (1, 0)), PLAIN, (True, False)), ("block", (33, 56, 56, 64, 100, (3, 1), (1, 0)), M45, (True, False)),
     # activations in registers: four-byte results of half the last-level cache and more beside little arithmetic
-    ("rows", (1, 144611, 1, 128, 448, 1, 0), M45, (False, True)), ("rows", (1, 144611, 1, 256, 448, 1, 0), M45, (True, True)),
-    ("rows", (1, 144611, 1, 256, 448, 1, 0), PLAIN, (False, True)), ("rows", (1, 70000, 1, 128, 448, 1, 0), M45, (True, True)),
+    # (from 129 channels on wide ones hold the weights there instead)
+    ("rows", (1, 144611, 1, 128, 448, 1, 0), M45, (False, True)), ("cols", (1, 144611, 1, 256, 448, 1, 0), M45, (True, True)),
+    ("cols", (1, 144611, 1, 256, 448, 1, 0), PLAIN, (False, True)), ("rows", (1, 70000, 1, 128, 448, 1, 0), M45, (True, True)),
     ("rows", (1, 802816, 1, 256, 64, 1, 0), M45, (True, True)), ("rows", (1, 802816, 1, 256, 128, 1, 0), M45, (False, True)),
 ], ids=str)
 def test_rules_leave_layers_to_the_tile_kernels(lib, form, shape, mode, takes):
@@ -165,6 +166,7 @@ def test_tuning_hook_forces_the_other_forms(lib):
     tiles = ("conv_patch_kernel", "conv_gemm_kernel")
     cases = {"split": ((taps, True, True), (one, True, True), (odd, True, True), (few, False, False)),
              "rows": ((one, True, True), (odd, True, False), (taps, False, False), (big, False, False)),
+             "cols": ((one, True, True), (odd, True, False), (taps, False, False), (S.ConvLayer("k", 1, 100, 1, 1030, 48), False, False)),
              "wide": ((one, True, True), (odd, True, False), (taps, False, False), (S.ConvLayer("k", 1, 100, 1, 256, 48), False, False)),
              "block": ((taps, True, True), (big, True, True), (one, False, False), (few, False, False))}
     base = [plan(lib, l, mode)[0] for l in (big, taps, one, odd, few)]

@@ -13,6 +13,7 @@ HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 
 KERNELS = {
     "rows": ("sparq_conv_rows_kernel.h", "conv_rows_kernel<RowsCfg<2, 1, true, 4>, kTrimNone, true>(const RowsParams)"),
+    "cols": ("sparq_conv_cols_kernel.h", "conv_cols_kernel<ColsCfg<8, 2, 1, 2>, kTrimNone, true>(const ColsParams)"),
     "wide": ("sparq_conv_wide_kernel.h", "conv_wide_kernel<Wide256, kTrimNone, true>(const WideParams)"),
     "sparse": ("sparq_conv_patch_kernel.h", "conv_patch_kernel<PatchCfg<64, 4, 1, 2, 1, 2, true, true>, kTrimNone>(const PatchParams)"),
     "codec": ("sparq_packed_act_kernel.h", "unpack_act_kernel<4, 3, 1, true, true>(const CodecParams)"),
