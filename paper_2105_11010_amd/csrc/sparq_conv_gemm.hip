@@ -307,6 +307,10 @@ const ColsVariant* fit_cols(const ConvGeom& g, bool bytes) {
 //   Up to 768: 1.1-1.4 x between a half and two rounds, where the tiles of the eight-wavefront form fill their last round least
 //   (96 and 128 outputs 1.02-1.15, with a third below 0.95); beyond four 1.15-1.29 up to 256 outputs, four-byte results of more 1.05-1.17 (bytes
 //   0.97-1.16); between them 1.07-1.14 for 129 to 192 outputs, others 0.92-1.07.
+//   Four-byte rows off a 64-byte border leave as pieces of lines, which only the caches put together again; the tile kernels write such rows
+//   whole.  19000 timed layers: up to 512 channels 1.0-1.3 x up to 24 MiB of results, beyond 0.43-1.0 (284 -> 1625, 46644 pixels 122 us against 222), and
+//   0.81-1.0 where the forms above or below stand; up to 768 channels 1.13-1.26 up to 80 MiB, beyond 1.07 with a fifth below 0.95, from 128 on 0.64-1.0;
+//   up to 1024 1.16-1.3 up to 128 MiB; rows on a 32-byte border 1.08-1.3 up to 160.
 const ColsVariant* pick_cols(const ConvGeom& g, bool bytes, bool plain, bool rows, bool wide) {
     const ColsVariant* v = g.Cq > 128 && (bytes || rows || !plain || g.Cq > 512) ? fit_cols(g, bytes) : nullptr;
     if (!v) return nullptr;
@@ -314,6 +318,10 @@ const ColsVariant* pick_cols(const ConvGeom& g, bool bytes, bool plain, bool row
     const int64_t groups = (g.N + (two ? 63 : 31)) / (two ? 64 : 32), per = narrow ? 4 : 8, shares = (groups + per - 1) / per;
     const int64_t tenths = (g.M + 31) / 32 * 10 / (device_cu_count() / (8 * shares) * 8);      // of a round
     const bool filled = g.Cq * 8 >= v->steps * 32 * 7, full = groups * 10 >= shares * per * (bytes && v->steps < 16 && tenths >= 40 ? 8 : 7);
+    if (!bytes && g.N % 16) {
+        const int64_t mib = g.M * g.N * 4 >> 20;
+        if (two ? rows || wide || mib >= 24 : mib >= (g.N % 8 == 0 ? 160 : v->steps == 24 ? 80 : 128)) return nullptr;
+    }
     bool take;
     if (narrow) take = filled && tenths >= 40 && v->steps > 8 && groups * 64 - g.N <= 16 && (bytes ? g.N > 96 : v->steps == 12 && g.N > 176);
     else if (two && !filled) take = full && tenths >= 60 && (!bytes || v->steps == 12);

@@ -135,6 +135,16 @@ def test_rules_leave_layers_to_the_tile_kernels(lib, form, shape, mode, takes):
         assert got == f"conv_{form}_kernel" if want else got in tiles, text
 
 
+@pytest.mark.parametrize("m,c,n,takes", [
+    (46644, 284, 1625, False), (46644, 320, 1632, True), (13900, 256, 450, True), (14100, 256, 450, False), (163072, 432, 493, False),
+    (726180, 352, 190, False), (4100, 512, 500, False), (4200, 512, 512, True), (57900, 768, 362, True), (58000, 768, 362, False),
+    (110000, 768, 376, True), (112000, 768, 376, False), (33500, 1024, 1001, True), (33600, 1024, 1001, False)])
+def test_weights_in_registers_leave_rows_off_a_line(lib, m, c, n, takes):
+    """Four-byte rows off a 64-byte border leave that kernel as pieces of lines: up to the results that the caches put together."""
+    text = plan(lib, S.ConvLayer("rows", 1, m, 1, c, n), S.Mode(4, S.OPT5, 1, 1))[0]
+    assert (words(text, "kernel=") == ["conv_cols_kernel"]) == takes, text
+
+
 def test_tuning_hook_forces_and_clears_the_choice(lib):
     """sparq_set_tuning: the documented keys change the plan, NULL restores the rules, junk is refused and changes nothing."""
     conv = S.ConvLayer("conv3x3", 64, 32, 32, 512, 512, 3, 3, (1, 1), (1, 1), 0.5, S.Mode(4, S.OPT5, 1, 1))
