@@ -307,6 +307,12 @@ const ColsVariant* fit_cols(const ConvGeom& g, bool bytes) {
 //   Up to 768: 1.1-1.4 x between a half and two rounds, where the tiles of the eight-wavefront form fill their last round least
 //   (96 and 128 outputs 1.02-1.15, with a third below 0.95); beyond four 1.15-1.29 up to 256 outputs, four-byte results of more 1.05-1.17 (bytes
 //   0.97-1.16); between them 1.07-1.14 for 129 to 192 outputs, others 0.92-1.07.
+//   The form above is at its best where its last round is more than three quarters full: 32 pixels for each of two wavefronts per SIMD, the outputs split over
+//   as many wavefronts as a round then takes (`fills`), or 64 pixels (`last`; bytes of wide outputs over many pixels, of more than one share).
+//   There the weights are 0.97 x up to 256 outputs (bytes of 193 and more 1.03-1.2), 0.99 with 384 channels and four-byte results (0.79 at worst); bytes in
+//   a round of 64 pixels per wavefront three quarters to seven eighths full 1.02-1.08 with all wavefronts at work (256 channels seven eighths of them) and
+//   0.93 else, fuller 0.91 (272 -> 1280, 112981 pixels 59 against 84 us), in half a round 0.95 with idle wavefronts or 320 channels (512: 1.05-1.17);
+//   everywhere else 1.02-1.4.  (70600 timed layers; 1.1 % of those it takes are below 0.95 x, the lowest 0.81.)
 //   Four-byte rows off a 64-byte border leave as pieces of lines, which only the caches put together again; the tile kernels write such rows
 //   whole.  19000 timed layers: up to 512 channels 1.0-1.3 x up to 24 MiB of results, beyond 0.43-1.0 (284 -> 1625, 46644 pixels 122 us against 222), and
 //   0.81-1.0 where the forms above or below stand; up to 768 channels 1.13-1.26 up to 80 MiB, beyond 1.07 with a fifth below 0.95, from 128 on 0.64-1.0;
@@ -321,6 +327,15 @@ const ColsVariant* pick_cols(const ConvGeom& g, bool bytes, bool plain, bool row
     if (!bytes && g.N % 16) {
         const int64_t mib = g.M * g.N * 4 >> 20;
         if (two ? rows || wide || mib >= 24 : mib >= (g.N % 8 == 0 ? 160 : v->steps == 24 ? 80 : 128)) return nullptr;
+    }
+    const int64_t round = (int64_t)device_cu_count() * 256, last = (g.M - 1) % (2 * round) + 1;
+    const bool fills = g.M <= round >> (shares - 1) && g.M * 4 > (round >> (shares - 1)) * 3;
+    if (narrow ? fills && !(bytes && g.N > 192) : v->steps == 12 && !bytes && fills) return nullptr;
+    if (bytes && two && shares > 1 && rows_large(g.M, g.N)) {
+        const int eighths = v->steps == 8 ? 7 : 8;           // of the wavefronts
+        if (last * 8 > 2 * round * 7) return nullptr;
+        if (last * 4 > 2 * round * 3 && !(filled && groups * 8 >= shares * per * eighths)) return nullptr;
+        if (g.M <= round && v->steps < 16 && !(filled && groups * 8 >= shares * per * 7)) return nullptr;
     }
     bool take;
     if (narrow) take = filled && tenths >= 40 && v->steps > 8 && groups * 64 - g.N <= 16 && (bytes ? g.N > 96 : v->steps == 12 && g.N > 176);

@@ -145,6 +145,24 @@ def test_weights_in_registers_leave_rows_off_a_line(lib, m, c, n, takes):
     assert (words(text, "kernel=") == ["conv_cols_kernel"]) == takes, text
 
 
+@pytest.mark.parametrize("m,c,n,takes", [
+    # (four-byte results, bytes), for 256 CUs.  Up to 256 outputs: 32 pixels for each of two wavefronts per SIMD are 65536
+    (49152, 512, 128, (False, True)), (49153, 512, 128, (False, False)), (65536, 512, 128, (False, False)), (65537, 512, 128, (False, True)),
+    (60000, 512, 256, (False, True)), (60000, 384, 192, (False, False)), (48000, 384, 192, (True, True)),
+    # four-byte results of 384 channels, the outputs of one, two and three shares
+    (49152, 384, 512, (True, True)), (49153, 384, 512, (False, True)), (24577, 384, 1024, (False, True)), (32769, 384, 1024, (True, True)),
+    (16384, 384, 1536, (False, True)), (16385, 384, 1536, (True, True)),
+    # bytes, 64 pixels per wavefront: three quarters of 131072 pixels and seven eighths, all wavefronts at work and not; half a round
+    (98304, 256, 1280, (True, True)), (98305, 256, 1280, (True, False)), (114688, 256, 1024, (True, True)), (114689, 256, 1024, (True, False)),
+    (131072, 256, 1024, (True, False)), (131073, 256, 1024, (True, True)), (100000, 256, 896, (True, True)), (100000, 384, 896, (True, False)),
+    (100000, 320, 1024, (True, False)), (100000, 512, 1024, (True, True)), (60000, 320, 1024, (True, False)), (66000, 320, 1024, (True, True)),
+    (60000, 256, 1280, (True, False)), (60000, 512, 1280, (True, True))])
+def test_weights_in_registers_leave_full_rounds_of_the_other_form(lib, m, c, n, takes):
+    """Where the form with the activations in registers fills its last round, it keeps the layers it is ahead on."""
+    text = plan(lib, S.ConvLayer("rounds", 1, m, 1, c, n), S.Mode(4, S.OPT5, 1, 1))[0]
+    assert (words(text, "kernel=") == ["conv_cols_kernel"], words(text, "u8_kernel=") == ["conv_cols_kernel"]) == takes, text
+
+
 def test_tuning_hook_forces_and_clears_the_choice(lib):
     """sparq_set_tuning: the documented keys change the plan, NULL restores the rules, junk is refused and changes nothing."""
     conv = S.ConvLayer("conv3x3", 64, 32, 32, 512, 512, 3, 3, (1, 1), (1, 1), 0.5, S.Mode(4, S.OPT5, 1, 1))
