@@ -313,11 +313,15 @@ const ColsVariant* fit_cols(const ConvGeom& g, bool bytes) {
 //   a round of 64 pixels per wavefront three quarters to seven eighths full 1.02-1.08 with all wavefronts at work (256 channels seven eighths of them) and
 //   0.93 else, fuller 0.91 (272 -> 1280, 112981 pixels 59 against 84 us), in half a round 0.95 with idle wavefronts or 320 channels (512: 1.05-1.17);
 //   everywhere else 1.02-1.4.  (70600 timed layers; 1.1 % of those it takes are below 0.95 x, the lowest 0.81.)
+//   Beyond 512 channels a share is 256 outputs, where a tile of the form below has 512, so with an even number of shares it trims twice as often.  Four-byte
+//   results under the trims with the most arithmetic (`heavy`: windows of two or three bits with rounding and pairs) were then 0.94 x from four
+//   rounds on with more than 768 channels (1.06-1.15 between eight and ten, where the form below starts a round), with up to 768 0.93 from twenty
+//   rounds on and 0.97-1.05 between six and eight (768 -> 1024, 80384 pixels, two-bit windows 106 against 149 us).
 //   Four-byte rows off a 64-byte border leave as pieces of lines, which only the caches put together again; the tile kernels write such rows
 //   whole.  19000 timed layers: up to 512 channels 1.0-1.3 x up to 24 MiB of results, beyond 0.43-1.0 (284 -> 1625, 46644 pixels 122 us against 222), and
 //   0.81-1.0 where the forms above or below stand; up to 768 channels 1.13-1.26 up to 80 MiB, beyond 1.07 with a fifth below 0.95, from 128 on 0.64-1.0;
 //   up to 1024 1.16-1.3 up to 128 MiB; rows on a 32-byte border 1.08-1.3 up to 160.
-const ColsVariant* pick_cols(const ConvGeom& g, bool bytes, bool plain, bool rows, bool wide) {
+const ColsVariant* pick_cols(const ConvGeom& g, bool bytes, bool plain, bool heavy, bool rows, bool wide) {
     const ColsVariant* v = g.Cq > 128 && (bytes || rows || !plain || g.Cq > 512) ? fit_cols(g, bytes) : nullptr;
     if (!v) return nullptr;
     const bool two = v->steps <= 16, narrow = two && g.N <= 256;
@@ -336,6 +340,10 @@ const ColsVariant* pick_cols(const ConvGeom& g, bool bytes, bool plain, bool row
         if (last * 8 > 2 * round * 7) return nullptr;
         if (last * 4 > 2 * round * 3 && !(filled && groups * 8 >= shares * per * eighths)) return nullptr;
         if (g.M <= round && v->steps < 16 && !(filled && groups * 8 >= shares * per * 7)) return nullptr;
+    }
+    if (heavy && !two && !bytes && shares % 2 == 0) {
+        const bool slower = v->steps == 24 ? tenths >= 200 || (tenths >= 60 && tenths < 80) : tenths >= 40 && !(tenths >= 80 && tenths < 100);
+        if (slower) return nullptr;
     }
     bool take;
     if (narrow) take = filled && tenths >= 40 && v->steps > 8 && groups * 64 - g.N <= 16 && (bytes ? g.N > 96 : v->steps == 12 && g.N > 176);
@@ -523,11 +531,11 @@ struct ConvPlan {
 
 // forms: the forms other than the two tile kernels may be taken (where the tuning hook asks for a tile kernel, no rule takes them; where
 // it asks for one of them, that one wherever the layer fits it).  Layers with 2:4 pruned weights are planned both ways (make_sparse_plan).
-// bytes: requantised results.  trims: the layer's mode trims (its size queries and descriptors without one do not care).
+// bytes: requantised results.  kind: the layer's mode's trim (size queries and descriptors without one do not care).
 // copy: the channel-padded copy is made (channel counts that are not a multiple of 16).
-ConvPlan make_plan_of(const ConvGeom& g, const Tuning& tune, bool forms, bool bytes, bool trims, bool copy) {
+ConvPlan make_plan_of(const ConvGeom& g, const Tuning& tune, bool forms, bool bytes, TrimKind kind, bool copy) {
     ConvPlan pl;
-    const bool plain = !trims || copy;                           // the kernel itself does not trim (the copy is trimmed already)
+    const bool plain = kind == kTrimNone || copy;                           // the kernel itself does not trim (the copy is trimmed already)
     if (g.fold) {               // at most 4 channels: their own kernel, or 4-channel padded copy, pixel-folded, gather kernel
         pl.pad_bytes = (size_t)round_up((int64_t)g.B * g.H * g.W * 4, 256);
         if (forms && !tune.form && !tune.set()) pl.few = few_geom(g, bytes, device_cu_count());
@@ -551,7 +559,7 @@ ConvPlan make_plan_of(const ConvGeom& g, const Tuning& tune, bool forms, bool by
         pl.rows = pick_rows(gk, bytes, plain);
         if ((!pl.rows || g.K > 256) && (pl.split = pick_split(gk, &pl.pg, &pl.npix)) != nullptr) return pl;
         pl.wide = pick_wide(gk, bytes, plain);
-        pl.cols = pick_cols(gk, bytes, plain, pl.rows != nullptr, pl.wide != nullptr);
+        pl.cols = pick_cols(gk, bytes, plain, kind == kTrimRoundPairWide && !copy, pl.rows != nullptr, pl.wide != nullptr);
     }
     // (units of four blocks and the sparse form's result rows leave LDS for one workgroup per CU, where narrow layers with more tiles
     // than CUs want two: 72 -> 16, expanded to four blocks, 401408 pixels 63 against 54 us in units of two)
@@ -604,7 +612,7 @@ bool staging_outlasts_copy(const ConvGeom& g, const ConvPlan& pl, TrimKind kind)
 ConvPlan make_plan(const ConvGeom& g, const Tuning& tune, bool forms = true, bool bytes = false, TrimKind kind = kTrimFloor) {
     const bool pads = !g.fold && g.Cp != g.C, trims = kind != kTrimNone;
     if (!pads || g.C % 4 == 0) {
-        const ConvPlan pl = make_plan_of(g, tune, forms, bytes, trims, false);
+        const ConvPlan pl = make_plan_of(g, tune, forms, bytes, kind, false);
         if (!pads || !trims) return pl;
         const bool gather = !pl.wide && !pl.split && !pl.block && !pl.rows && !pl.patch;
         const int64_t tiles_m = (g.M + 127) / 128;
@@ -623,7 +631,7 @@ ConvPlan make_plan(const ConvGeom& g, const Tuning& tune, bool forms = true, boo
         }
         if (!once) return pl;
     }
-    return make_plan_of(g, tune, forms, bytes, trims, true);
+    return make_plan_of(g, tune, forms, bytes, kind, true);
 }
 
 // 2:4 pruned weights run on the sparse matrix instruction when the layer's plan is the wave-specialised

@@ -163,6 +163,20 @@ def test_weights_in_registers_leave_full_rounds_of_the_other_form(lib, m, c, n, 
     assert (words(text, "kernel=") == ["conv_cols_kernel"], words(text, "u8_kernel=") == ["conv_cols_kernel"]) == takes, text
 
 
+@pytest.mark.parametrize("m,c,n,takes", [
+    # an even number of 256-output shares: up to 768 channels and up to 1024; then an odd one, and more
+    (24500, 768, 512, True), (24600, 768, 512, False), (32700, 768, 512, False), (32800, 768, 512, True), (81800, 768, 512, True), (81950, 768, 512, False),
+    (80384, 768, 1024, False), (16400, 1024, 512, False), (32700, 1024, 512, False), (32800, 1024, 512, True), (41000, 1024, 512, False),
+    (20400, 1024, 768, True), (60000, 768, 768, True), (3500, 1024, 1024, True)])
+def test_weights_in_registers_leave_trims_that_cost_more_twice(lib, m, c, n, takes):
+    """Windows of two and three bits with rounding and pairs, four-byte results: trimmed once per 256 outputs, where the eight-wavefront form
+    trims once per 512.  Other trims stay."""
+    layer = S.ConvLayer("heavy", 1, m, 1, c, n)
+    for mode in (S.Mode(2, S.OPT7_2B, 1, 1), S.Mode(3, S.OPT6_3B, 1, 1)):
+        assert words(plan(lib, layer, mode)[0], "kernel=") == ["conv_cols_kernel" if takes else "conv_wide_kernel"]
+    assert words(plan(lib, layer, S.Mode(2, S.OPT7_2B, 0, 1))[0], "kernel=") == ["conv_cols_kernel"]
+
+
 def test_tuning_hook_forces_and_clears_the_choice(lib):
     """sparq_set_tuning: the documented keys change the plan, NULL restores the rules, junk is refused and changes nothing."""
     conv = S.ConvLayer("conv3x3", 64, 32, 32, 512, 512, 3, 3, (1, 1), (1, 1), 0.5, S.Mode(4, S.OPT5, 1, 1))
