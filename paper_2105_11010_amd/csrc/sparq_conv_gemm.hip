@@ -291,8 +291,21 @@ const ColsVariant* fit_cols(const ConvGeom& g, bool bytes) {
     return nullptr;
 }
 
-// Weights in registers, against the forms above and below by 32808 timed layers of 129 to 768 channels and 8749 of up to 1024.  `rounds`: 32-pixel fragments for
-// each workgroup of a share of the output channels; `full`: wavefronts that have channels.
+// How its launch splits the output channels: groups of 64 (beyond 512 channels 32) to a wavefront, eight (where two hold the same ones, four) groups to
+// a share; tenths of a round: 32-pixel fragments for each workgroup of a share.
+struct ColsSplit {
+    bool two, narrow;
+    int64_t groups, per, shares, tenths;
+    ColsSplit(const ColsVariant& v, const ConvGeom& g) : two(v.steps <= 16), narrow(two && g.N <= 256) {
+        groups = (g.N + (two ? 63 : 31)) / (two ? 64 : 32);
+        per = narrow ? 4 : 8;
+        shares = (groups + per - 1) / per;
+        tenths = (g.M + 31) / 32 * 10 / (device_cu_count() / (8 * shares) * 8);
+    }
+};
+
+// Weights in registers, against the forms above and below by 32808 timed layers of 129 to 768 channels and 8749 of up to 1024, in rounds (above);
+// `full`: wavefronts that have channels.
 //   Up to 512 channels it walks 512 outputs per share: beyond 256 outputs, with the steps it is built for at least 7/8 filled, 256 channels 1.02-1.17 x
 //   from 1.3 rounds on (before 0.86-1.02), 384 as bytes 1.05-1.28 from 0.5 on, four-byte results 1.06-1.35 from four on (at three 0.97), 512
 //   as bytes 1.08-1.39 from 0.4 on, four-byte results 1.01-1.58 from 0.5 on; less filled (160 and 192, 320 channels) 1.04-1.13 from six rounds on but for
@@ -324,9 +337,9 @@ const ColsVariant* fit_cols(const ConvGeom& g, bool bytes) {
 const ColsVariant* pick_cols(const ConvGeom& g, bool bytes, bool plain, bool heavy, bool rows, bool wide) {
     const ColsVariant* v = g.Cq > 128 && (bytes || rows || !plain || g.Cq > 512) ? fit_cols(g, bytes) : nullptr;
     if (!v) return nullptr;
-    const bool two = v->steps <= 16, narrow = two && g.N <= 256;
-    const int64_t groups = (g.N + (two ? 63 : 31)) / (two ? 64 : 32), per = narrow ? 4 : 8, shares = (groups + per - 1) / per;
-    const int64_t tenths = (g.M + 31) / 32 * 10 / (device_cu_count() / (8 * shares) * 8);      // of a round
+    const ColsSplit split(*v, g);
+    const bool two = split.two, narrow = split.narrow;
+    const int64_t groups = split.groups, per = split.per, shares = split.shares, tenths = split.tenths;
     const bool filled = g.Cq * 8 >= v->steps * 32 * 7, full = groups * 10 >= shares * per * (bytes && v->steps < 16 && tenths >= 40 ? 8 : 7);
     if (!bytes && g.N % 16) {
         const int64_t mib = g.M * g.N * 4 >> 20;
@@ -609,23 +622,30 @@ bool staging_outlasts_copy(const ConvGeom& g, const ConvPlan& pl, TrimKind kind)
 // 1x1 layers trim x once per column tile, which the products of that tile hide in part (`beyond`).  3200 timed layers of 768 to 4600 channels and
 // 2 to 8 columns of 256, in place against the copy, by (instructions - 32) x columns: bytes on the gather kernel 0.95-1.1 x up to 128, 0.92 x at
 // 156, 0.7-0.8 x from 192 on (9739 x 3828 -> 1595, two-bit windows, 105 us against 162); eight wavefronts 1.0-1.4 x up to 255, 0.88-1.0 x beyond.
+// The weights-in-registers form trims x once per share of 256 or 512 outputs and beside the products: in place 1.5 x faster than from the copy (22710 timed
+// layers, 3119 x 776 -> 640 among them; 0.1 % below 0.95 x), but for four-byte results under two- and three-bit windows with rounding and pairs, where
+// shares x tenths of a round from 700 on, from 400 with more than 768 channels, are 0.75-1.0 x.
 ConvPlan make_plan(const ConvGeom& g, const Tuning& tune, bool forms = true, bool bytes = false, TrimKind kind = kTrimFloor) {
     const bool pads = !g.fold && g.Cp != g.C, trims = kind != kTrimNone;
     if (!pads || g.C % 4 == 0) {
         const ConvPlan pl = make_plan_of(g, tune, forms, bytes, kind, false);
         if (!pads || !trims) return pl;
-        const bool gather = !pl.wide && !pl.split && !pl.block && !pl.rows && !pl.patch;
+        const bool gather = !pl.cols && !pl.wide && !pl.split && !pl.block && !pl.rows && !pl.patch;
         const int64_t tiles_m = (g.M + 127) / 128;
         const bool costly = kind == kTrimRound || kind == kTrimRoundPairWide;
         const int beyond = trim_instructions(kind) - 32;         // what the products of one column tile leave uncovered
         bool once = gather && (g.KH * g.KW > 1 || beyond * ((g.N + 255) / 256) > 128);
         if (pl.split && !tune.form) once = costly ? g.K >= 1800 : kind == kTrimRoundPair4 && g.K >= 8000;
-        if (pl.wide && !tune.form) once = tiles_m * ((g.N + 255) / 256) * 2 < device_cu_count();
-        if (pl.wide && !tune.form) {
+        if (pl.cols && !tune.form) {
+            const ColsSplit split(*pl.cols, g);
+            once = kind == kTrimRoundPairWide && !bytes && !split.two && split.shares * split.tenths >= (pl.cols->steps == 24 ? 700 : 400);
+        }
+        if (pl.wide && !pl.cols && !tune.form) {
+            once = tiles_m * ((g.N + 255) / 256) * 2 < device_cu_count();
             const int columns = (g.N + pl.wide->tn - 1) / pl.wide->tn;
             once = once || (costly && columns >= 5) || beyond * columns > 255;
         }
-        if (pl.patch && !pl.wide && !pl.split && !pl.block && !pl.rows) {
+        if (pl.patch && !pl.cols && !pl.wide && !pl.split && !pl.block && !pl.rows) {
             const int64_t staged = tiles_m * ((g.N + pl.variant->tn - 1) / pl.variant->tn) * pl.npix;
             once = (costly && staged > (int64_t)5 * g.B * g.H * g.W) || staging_outlasts_copy(g, pl, kind);
         }

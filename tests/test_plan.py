@@ -310,6 +310,19 @@ def test_1x1_layers_that_would_trim_once_per_column_tile(lib, n, mode, copy):
     assert (copy or words(text, "kernel=") == ["conv_wide_kernel"]) and ("padded_copy" in text) == copy, text
 
 
+@pytest.mark.parametrize("m,c,n,mode,copy", [
+    (3119, 776, 640, S.Mode(4, S.OPT5, 1, 1), False), (3119, 776, 640, S.Mode(2, S.OPT7_2B, 1, 1), False), (36864, 780, 640, S.Mode(3, S.OPT6_3B, 1, 0), False),
+    (1110, 760, 1392, S.Mode(4, S.OPT5, 1, 1), False), (46644, 300, 1632, S.Mode(4, S.OPT5, 1, 1), False), (40000, 660, 1280, S.Mode(4, S.OPT5, 1, 1), False),
+    # two- and three-bit windows with rounding and pairs, trimmed by several shares in many rounds: up to 768 channels, up to 1024
+    (59800, 580, 640, S.Mode(2, S.OPT7_2B, 1, 1), False), (59900, 580, 640, S.Mode(2, S.OPT7_2B, 1, 1), True), (59900, 580, 640, S.Mode(4, S.OPT5, 1, 1), False),
+    (34000, 900, 640, S.Mode(3, S.OPT6_3B, 1, 1), False), (34400, 900, 640, S.Mode(3, S.OPT6_3B, 1, 1), True)])
+def test_weights_in_registers_decide_on_the_copy_themselves(lib, m, c, n, mode, copy):
+    """Channel counts in whole words that the weights-in-registers form takes are read where they are, by what that form trims and not by what the
+    forms behind it would."""
+    text = plan(lib, S.ConvLayer("words", 1, m, 1, c, n), mode)[0]
+    assert words(text, "kernel=") == ["conv_cols_kernel"] and ("padded_copy" in text) == copy, text
+
+
 def test_layers_in_turn_do_not_walk_their_tiles_again(lib):
     """The largest patch of a layer comes from a walk over its tile positions (193 us for 147 x 147 pixels) and is kept per
     geometry.  These two geometries share the low nine bits of the cache's hash: called in turn, neither pushes the other out."""
