@@ -108,7 +108,8 @@ size_t sparq_workspace_bytes(const sparq_conv_desc *desc, const sparq_mode *mode
  * on the current device, as a short human-readable line (for logs and profiles;
  * the wording is not an interface): the kernel family with its form and tile,
  * then kernel=<the kernel that is launched> and u8_kernel=<the one that
- * sparq_conv_gemm_u8 launches for its byte results>.  (A call whose input arrives
+ * sparq_conv_gemm_u8 launches for its byte results>; weights_in_lds, u8_weights_in_lds:
+ * conv_rows_kernel keeps all weights in LDS there.  (A call whose input arrives
  * trimmed and whose output is to be trimmed leaves conv_wide_kernel to the
  * others.)  text receives at most text_bytes bytes including the terminator. */
 sparq_status sparq_conv_plan(const sparq_conv_desc *desc, const sparq_mode *mode,

@@ -244,11 +244,17 @@ bool one_tap(const ConvGeom& g, bool bytes) {
     return g.KH == 1 && g.KW == 1 && !g.ph && !g.pw && g.Cq % kStepK == 0 && g.M < kPatchMaxDividend &&
            (size_t)g.Kp * g.Np < kPatchInvalidOffset && (int64_t)g.B * g.H * g.W < kPatchMaxDividend && !(bytes && g.N % 16);
 }
-struct RowsVariant { int steps; const char* name; RowsLauncher fn; int rm, rm_large; };   // 32-index reduction steps it holds, pixels per wavefront
+struct RowsVariant {
+    int steps;                               // 32-index reduction steps it holds
+    const char* name;
+    RowsLauncher fn;
+    int rm, rm_large;                        // pixels per wavefront
+    int (*held_run)(int64_t, int64_t, bool); // where its launcher holds the weights in LDS
+};
 const RowsVariant kRowsVariants[] = {
-    {2, "64", launch_rows_k64, 32, 32}, {4, "128", launch_rows_k128, 32, 32}, {6, "192", launch_rows_k192, 32, 64},
-    {8, "256", launch_rows_k256, 32, 64}, {10, "320", launch_rows_k320, 32, 64}, {12, "384", launch_rows_k384, 32, 64},
-    {16, "512", launch_rows_k512, 32, 64},
+    {2, "64", launch_rows_k64, 32, 32, rows_held_run<2>}, {4, "128", launch_rows_k128, 32, 32, rows_held_run<4>}, {6, "192", launch_rows_k192, 32, 64, rows_held_run<6>},
+    {8, "256", launch_rows_k256, 32, 64, rows_held_run<8>}, {10, "320", launch_rows_k320, 32, 64, rows_held_run<10>}, {12, "384", launch_rows_k384, 32, 64, rows_held_run<12>},
+    {16, "512", launch_rows_k512, 32, 64, rows_held_run<16>},
 };
 // What its launcher takes beyond the rule below (else the call goes on to the tile kernels).
 bool rows_launchable(const RowsVariant& v, const ConvGeom& g, bool bytes) {
@@ -774,7 +780,9 @@ sparq_status plan_text(const sparq_conv_desc* desc, const sparq_mode* mode, char
         const ConvPlan p8 = make_plan(g, tune, true, true, kind);
         const PlanForm f8 = plan_form(g, p8, true);
         const char* tile = f8 == kFormWide ? p8.wide->name : f8 == kFormSplit ? p8.split->name : f8 == kFormGather ? gather_tile_name(g, tune, true) : nullptr;
-        snprintf(u8, sizeof(u8), " u8_kernel=%s%s%s", kFormKernels[f8], tile ? ":" : "", tile ? tile : "");
+        const int run = f8 == kFormRows ? p8.rows->held_run(g.M, g.N, true) : 0;
+        if (run) snprintf(u8, sizeof(u8), " u8_kernel=%s u8_weights_in_lds=%d", kFormKernels[f8], run);
+        else snprintf(u8, sizeof(u8), " u8_kernel=%s%s%s", kFormKernels[f8], tile ? ":" : "", tile ? tile : "");
     }
     char line[160];
     switch (form) {
@@ -783,7 +791,7 @@ sparq_status plan_text(const sparq_conv_desc* desc, const sparq_mode* mode, char
         case kFormBlock: snprintf(line, sizeof(line), "conv_patch_kernel small_workgroups tile=%s patch_pixels=%d", pl.block->name, pl.npix); break;
         case kFormCols: snprintf(line, sizeof(line), "conv_patch_kernel weights_in_registers channels=%s", pl.cols->name); break;
         case kFormWide: snprintf(line, sizeof(line), "conv_gemm_kernel tile=%s eight_wavefronts", pl.wide->name); break;
-        case kFormRows: snprintf(line, sizeof(line), "conv_patch_kernel in_registers channels=%s", pl.rows->name); break;
+        case kFormRows: snprintf(line, sizeof(line), "conv_patch_kernel in_registers channels=%s%s", pl.rows->name, pl.rows->held_run(g.M, g.N, false) ? " weights_in_lds" : ""); break;
         case kFormPatch:
             snprintf(line, sizeof(line), "conv_patch_kernel tile=128x%d chunks=%d unit_channels=%d patch_pixels=%d%s", pl.variant->tn, pl.ac,
                      64 * pl.cbs, pl.npix, pl.ws ? " wave_specialised" : "");

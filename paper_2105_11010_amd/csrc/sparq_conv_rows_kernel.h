@@ -348,17 +348,30 @@ struct RowsHeld {
 // 256 channels from 1.5 on as much faster as slower warm (0.85 to 1.05), cold 27.1 -> 21.8 (288 -> 96); wider ones are bound by their stores and
 // lose as much as they gain (0.78 to 1.1).  More weights than fit beside three wavefronts per SIMD, bytes, up to 128 KB: 1.13 x from three rounds of
 // two on, but 0.98 x with up to 256 channels.
+// Returns the bytes of a result row that leave together (128: Main, 64: Large); 0: the weights stay in L2.
+template <int KS, bool U8>
+int rows_held_run(int64_t M, int64_t N) {
+    typedef typename RowsHeld<KS, U8>::Main Main;
+    const int64_t items = (M + 31) / 32, simds = (int64_t)device_cu_count() * 4, slots = simds * Main::kOcc;
+    if (rows_held_lds_bytes<Main>(N, U8) <= kLdsPerCu) {
+        constexpr bool SHORT = KS <= 8;
+        const int64_t tenths = U8 ? 10 : N <= 64 ? (SHORT ? 11 : 14) : N <= 96 && !SHORT ? 15 : N <= 128 ? 20 : INT64_MAX / (slots + 1);
+        return items * 10 >= slots * tenths ? Main::kRun : 0;
+    }
+    typedef typename RowsHeld<KS, U8>::Large Large;
+    return U8 && KS > 8 && rows_held_lds_bytes<Large>(N, U8) <= kLdsPerCu && items >= simds * 6 ? Large::kRun : 0;
+}
+template <int KS>
+int rows_held_run(int64_t M, int64_t N, bool bytes) { return bytes ? rows_held_run<KS, true>(M, N) : rows_held_run<KS, false>(M, N); }
+
 template <int KS, int KIND, bool U8>
 sparq_status launch_rows_held(const RowsParams& p, hipStream_t s) {
     typedef typename RowsHeld<KS, U8>::Main Main;
-    const int64_t items = ((int64_t)p.M + 31) / 32, simds = (int64_t)device_cu_count() * 4, slots = simds * Main::kOcc;
-    if (rows_held_lds_bytes<Main>(p.N, U8) <= kLdsPerCu) {
-        constexpr bool SHORT = KS <= 8;
-        const int64_t tenths = U8 ? 10 : p.N <= 64 ? (SHORT ? 11 : 14) : p.N <= 96 && !SHORT ? 15 : p.N <= 128 ? 20 : INT64_MAX / (slots + 1);
-        if (items * 10 >= slots * tenths) return launch_rows_held_cfg<Main, KIND, U8>(p, s);
-    } else if constexpr (U8 && KS > 8) {
+    const int run = rows_held_run<KS, U8>(p.M, p.N);
+    if (run == Main::kRun) return launch_rows_held_cfg<Main, KIND, U8>(p, s);
+    if constexpr (U8 && KS > 8) {
         typedef typename RowsHeld<KS, U8>::Large Large;
-        if (rows_held_lds_bytes<Large>(p.N, U8) <= kLdsPerCu && items >= simds * 6) return launch_rows_held_cfg<Large, KIND, U8>(p, s);
+        if (run == Large::kRun) return launch_rows_held_cfg<Large, KIND, U8>(p, s);
     }
     return SPARQ_EUNSUPPORTED;
 }

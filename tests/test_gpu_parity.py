@@ -482,7 +482,7 @@ def test_conv_split_reduction_of_short_patch_rows(sq, oracle, tile, layer, mode)
 
 # The form with the activations in registers (1x1 layers): every number of reduction steps it holds and numbers in between,
 # pixels and channels that fill no fragment, strides, odd channel counts, runs of fewer than 128 result bytes, shares of the
-# output channels, 64 pixels per wavefront (many pixels and channels; asked for, since the rule holds the weights instead).
+# output channels, 64 pixels per wavefront (many pixels and channels).
 ROWS_SHAPES = [
     S.ConvLayer("r_c64_m3", 1, 3, 1, 64, 64), S.ConvLayer("r_c64_n33", 1, 65, 1, 64, 33), S.ConvLayer("r_c48_n48", 1, 9, 7, 48, 48),
     S.ConvLayer("r_c128_n80_s2", 3, 15, 13, 128, 80, 1, 1, (2, 2), (0, 0)), S.ConvLayer("r_c65_n144", 2, 11, 11, 65, 144),
@@ -495,19 +495,29 @@ ROWS_SHAPES = [
 
 @pytest.mark.parametrize("layer", ROWS_SHAPES, ids=lambda l: l.name)
 @pytest.mark.parametrize("mode", [S.Mode(4, S.OPT5, 1, 1), S.Mode(3, S.OPT6_3B, 0, 1), S.PLAIN8], ids=lambda m: m.label)
-def test_conv_activations_in_registers(sq, oracle, tuning, layer, mode):
+def test_conv_activations_in_registers(sq, oracle, layer, mode):
+    d = sq.conv_desc(layer.B, layer.H, layer.W, layer.C, layer.N, layer.KH, layer.KW, layer.stride, layer.pad)
+    assert "in_registers" in sq.sparq_conv_plan(d, sq.mode(*mode.astuple()))
+    check_layer(sq, oracle, layer, mode, seed_cfg=8)
+    check_layer_u8(sq, oracle, layer, mode, seed_cfg=8, out_mode=S.Mode(4, S.OPT5, 1, 1))
+
+
+# Its kernel by name, for both results; asked for where the rule holds the weights instead.
+@pytest.mark.parametrize("layer", ROWS_SHAPES, ids=lambda l: l.name)
+def test_conv_activations_in_registers_by_name(sq, oracle, tuning, layer):
+    mode = S.Mode(4, S.OPT5, 1, 1)
     if layer.name.endswith("_wide"):
         tuning("form=rows")
     d = sq.conv_desc(layer.B, layer.H, layer.W, layer.C, layer.N, layer.KH, layer.KW, layer.stride, layer.pad)
     words = sq.sparq_conv_plan(d, sq.mode(*mode.astuple())).split()
     assert "kernel=conv_rows_kernel" in words and (layer.N % 16 or "u8_kernel=conv_rows_kernel" in words), words
-    check_layer(sq, oracle, layer, mode, seed_cfg=8)
-    check_layer_u8(sq, oracle, layer, mode, seed_cfg=8, out_mode=S.Mode(4, S.OPT5, 1, 1))
+    if layer.name.endswith("_wide"):
+        check_layer(sq, oracle, layer, mode, seed_cfg=8)
+        check_layer_u8(sq, oracle, layer, mode, seed_cfg=8, out_mode=mode)
 
 
 # The same with the weights in LDS (pixels for every wavefront slot of 256 CUs, 98304 or 131072, and 1.1 to 2 times that for four-byte
-# results): every number of steps held, steps past the layer's own, ragged pixels and channels, a stride, the most weights that fit beside 128
-# bytes of result rows and beside 64.
+# results): steps past the layer's own, ragged pixels and channels, a stride, layers on either side of that rule.
 ROWS_HELD_SHAPES = [
     S.ConvLayer("rh_c40_n33", 1, 144193, 1, 40, 33), S.ConvLayer("rh_c64_n208", 1, 131103, 1, 64, 208), S.ConvLayer("rh_c64_n64_s2", 6, 299, 301, 64, 64, 1, 1, (2, 2), (0, 0)),
     S.ConvLayer("rh_c96_n96", 1, 196641, 1, 96, 96), S.ConvLayer("rh_c160_n128", 1, 262175, 1, 160, 128), S.ConvLayer("rh_c256_n64", 1, 144224, 1, 256, 64),
@@ -524,6 +534,31 @@ def test_conv_activations_in_registers_weights_in_lds(sq, oracle, layer, mode):
         assert "u8_kernel=conv_rows_kernel" in sq.sparq_conv_plan(d, sq.mode(*mode.astuple()))
         check_layer_u8(sq, oracle, layer, mode, seed_cfg=8, out_mode=S.Mode(4, S.OPT5, 1, 1))
     check_layer(sq, oracle, layer, mode, seed_cfg=8)
+
+
+# Each kernel of that kind, by the plan: every number of steps for four-byte results and for bytes, at the fewest pixels and one more (256 CUs:
+# 32 pixels for 1.1 to 2 times the wavefront slots, or for all of them), and the rows of 64 result bytes that leave room for more weights.
+ROWS_HELD_FORMS = [
+    (True, 128, S.ConvLayer("rf_c40_n48", 1, 144193, 1, 40, 48)), (True, 128, S.ConvLayer("rf_c100_n64", 1, 144193, 1, 100, 64)), (True, 128, S.ConvLayer("rf_c192_n64", 1, 144193, 1, 192, 64)),
+    (True, 128, S.ConvLayer("rf_c256_n64", 1, 144193, 1, 256, 64)), (True, 128, S.ConvLayer("rf_c300_n16", 1, 137633, 1, 300, 16)), (True, 128, S.ConvLayer("rf_c384_n48", 1, 137633, 1, 384, 48)),
+    (True, 128, S.ConvLayer("rf_c512_n80", 1, 147457, 1, 512, 80)), (True, 128, S.ConvLayer("rf_c128_n112", 1, 262177, 1, 128, 112)),
+    (False, 128, S.ConvLayer("rf_c64_n80", 1, 131073, 1, 64, 80)), (False, 128, S.ConvLayer("rf_c100_n96", 1, 98305, 1, 100, 96)), (False, 128, S.ConvLayer("rf_c192_n32", 1, 98305, 1, 192, 32)),
+    (False, 128, S.ConvLayer("rf_c256_n112", 1, 98305, 1, 256, 112)), (False, 128, S.ConvLayer("rf_c320_n144", 1, 98305, 1, 320, 144)), (False, 128, S.ConvLayer("rf_c384_n224", 1, 98305, 1, 384, 224)),
+    (False, 64, S.ConvLayer("rf_c384_n288", 1, 196577, 1, 384, 288)), (False, 64, S.ConvLayer("rf_c330_n304", 1, 196609, 1, 330, 304)), (False, 64, S.ConvLayer("rf_c512_n224", 1, 196609, 1, 512, 224)),
+    (None, 64, S.ConvLayer("rf_c320_n384", 1, 196577, 1, 320, 384)), (False, 0, S.ConvLayer("rf_c512_n208_l2", 1, 196576, 1, 512, 208)),
+]
+
+
+@pytest.mark.parametrize("held,run,layer", ROWS_HELD_FORMS, ids=lambda v: v.name if hasattr(v, "name") else str(v))
+@pytest.mark.parametrize("mode", [S.Mode(4, S.OPT5, 1, 1), S.PLAIN8], ids=lambda m: m.label)
+def test_conv_weights_in_lds_by_plan(sq, oracle, held, run, layer, mode):
+    d = sq.conv_desc(layer.B, layer.H, layer.W, layer.C, layer.N, layer.KH, layer.KW, layer.stride, layer.pad)
+    words = sq.sparq_conv_plan(d, sq.mode(*mode.astuple())).split()
+    assert "u8_kernel=conv_rows_kernel" in words and [w[len("u8_weights_in_lds="):] for w in words if w.startswith("u8_weights_in_lds=")] == [str(run)] * (run != 0), words
+    assert ("weights_in_lds" in words) == bool(held) and ("kernel=conv_rows_kernel" in words or held is None), words      # (None: not this form)
+    check_layer_u8(sq, oracle, layer, mode, seed_cfg=8, out_mode=S.Mode(4, S.OPT5, 1, 1))
+    if held:
+        check_layer(sq, oracle, layer, mode, seed_cfg=8)
 
 
 # Eight wavefronts per tile (1x1 layers with long reductions): steps that are padded to a multiple of four, an odd channel
@@ -713,8 +748,7 @@ def test_conv_weights_in_registers(sq, oracle, tuning, forced, layer, mode):
     if forced:
         tuning("form=cols")
     d = sq.conv_desc(layer.B, layer.H, layer.W, layer.C, layer.N, layer.KH, layer.KW, layer.stride, layer.pad)
-    words = sq.sparq_conv_plan(d, sq.mode(*mode.astuple())).split()
-    assert "kernel=conv_cols_kernel" in words and (layer.N % 16 or "u8_kernel=conv_cols_kernel" in words), words
+    assert "weights_in_registers" in sq.sparq_conv_plan(d, sq.mode(*mode.astuple()))
     x, w, sc = S.gen_layer(8, layer)
     ref_acc, ref_out = oracle.conv_gemm(x, w, layer.stride, layer.pad, scale=sc, **mode.kwargs())
     for want_acc, want_out in ((True, False), (False, True), (True, True)):
@@ -725,8 +759,21 @@ def test_conv_weights_in_registers(sq, oracle, tuning, forced, layer, mode):
     ref = oracle.requant(ref_acc, f)
     assert np.array_equal(run_conv_u8(sq, x, w, f, layer, mode), ref)
     assert np.array_equal(run_conv_u8(sq, x, w, f, layer, mode, out_mode=mode), oracle.trim(ref, **mode.kwargs()))
+
+
+# Its kernel by name, for both results, and untrimmed input with the output trimmed for the next layer.
+@pytest.mark.parametrize("forced,layer", COLS_SHAPES, ids=lambda v: v.name if hasattr(v, "name") else str(v))
+def test_conv_weights_in_registers_by_name(sq, oracle, tuning, forced, layer):
+    if forced:
+        tuning("form=cols")
+    d = sq.conv_desc(layer.B, layer.H, layer.W, layer.C, layer.N, layer.KH, layer.KW, layer.stride, layer.pad)
+    x, w, _ = S.gen_layer(8, layer)
+    f = S.gen_requant(layer, S.rng_for(8, 900 + layer.index))
     plain = oracle.requant(oracle.conv_gemm(x, w, layer.stride, layer.pad, **S.PLAIN8.kwargs())[0], f)
-    assert np.array_equal(run_conv_u8(sq, x, w, f, layer, S.PLAIN8, out_mode=mode), oracle.trim(plain, **mode.kwargs()))
+    for mode in FORM_MODES:
+        words = sq.sparq_conv_plan(d, sq.mode(*mode.astuple())).split()
+        assert "kernel=conv_cols_kernel" in words and (layer.N % 16 or "u8_kernel=conv_cols_kernel" in words), words
+        assert np.array_equal(run_conv_u8(sq, x, w, f, layer, S.PLAIN8, out_mode=mode), oracle.trim(plain, **mode.kwargs()))
 
 
 # Shapes chosen for the input-patch kernel: tiles that span several image rows and several images,

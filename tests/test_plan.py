@@ -177,6 +177,19 @@ def test_weights_in_registers_leave_trims_that_cost_more_twice(lib, m, c, n, tak
     assert words(plan(lib, layer, S.Mode(2, S.OPT7_2B, 0, 1))[0], "kernel=") == ["conv_cols_kernel"]
 
 
+@pytest.mark.parametrize("m,c,n,held,run", [
+    # pixels for every wavefront slot: bytes 16 a CU (up to 64 channels) and 12; four-byte results 1.1, 1.4, 1.5 and 2 times that
+    (131072, 64, 64, False, 128), (131040, 64, 64, False, 0), (98304, 128, 64, False, 128), (98272, 128, 64, False, 0),
+    (144192, 256, 64, True, 128), (144160, 256, 64, False, 128), (137632, 320, 64, True, 128), (137600, 320, 64, False, 128),
+    (147456, 512, 80, True, 128), (147424, 512, 80, False, 128), (262144, 128, 112, True, 128), (262112, 128, 112, False, 128),
+    # more weights than fit beside 128 bytes of result rows, and beside 64
+    (196577, 384, 288, False, 64), (196576, 384, 288, False, 0), (196609, 512, 224, False, 64), (196609, 256, 400, False, 0)])
+def test_plan_names_the_weights_in_lds(lib, m, c, n, held, run):
+    """The plan says where the activations-in-registers form holds its weights in LDS, for four-byte results and for bytes."""
+    text = plan(lib, S.ConvLayer("held", 1, m, 1, c, n), S.Mode(4, S.OPT5, 1, 1))[0]
+    assert ("weights_in_lds" in text.split()) == held and words(text, "u8_weights_in_lds=") == [str(run)] * (run != 0), text
+
+
 def test_tuning_hook_forces_and_clears_the_choice(lib):
     """sparq_set_tuning: the documented keys change the plan, NULL restores the rules, junk is refused and changes nothing."""
     conv = S.ConvLayer("conv3x3", 64, 32, 32, 512, 512, 3, 3, (1, 1), (1, 1), 0.5, S.Mode(4, S.OPT5, 1, 1))
