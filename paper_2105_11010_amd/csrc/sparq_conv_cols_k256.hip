@@ -2,5 +2,5 @@
 #include "sparq_conv_cols_kernel.h"
 
 namespace sparq {
-SPARQ_DECLARE_ROWS(launch_cols_k256) { return launch_cols_kind<ColsCfg<8, 2, 1, 2>, ColsCfg<8, 2, 2, 1>>(kind, p, s); }
+SPARQ_DECLARE_ROWS(launch_cols_k256) { return launch_cols_kind<ColsCfg<8, 2, 1, 2>>(kind, p, s); }
 }  // namespace sparq

@@ -2,5 +2,5 @@
 #include "sparq_conv_cols_kernel.h"
 
 namespace sparq {
-SPARQ_DECLARE_ROWS(launch_cols_k512) { return launch_cols_kind<ColsCfg<16, 2, 1, 1>, ColsCfg<16, 2, 2, 1>>(kind, p, s); }
+SPARQ_DECLARE_ROWS(launch_cols_k512) { return launch_cols_kind<ColsCfg<16, 2, 1, 1>, ColsCfg<16, 2, 2, 1>, ColsCfg<16, 2, 1, 1>>(kind, p, s); }
 }  // namespace sparq

@@ -320,26 +320,27 @@ sparq_status launch_cols_cfg(const RowsParams& p, hipStream_t s) {
     return launch_status();
 }
 
-// One: a wavefront for each 32 FN channels; Two: two for narrow layers, which would leave the others idle (512 -> 128, 200704 pixels, bytes
-// 45 -> 39 us).
-template <class One, class Two, int KIND>
+// One: a wavefront for each 32 FN channels; Bytes, Words: what layers of up to four groups take for bytes and for four-byte results, where the rule
+// has two wavefronts for the same channels, which One would leave idle (512 -> 128, 200704 pixels, bytes 45 -> 39 us).
+template <class One, class Bytes, class Words, int KIND>
 sparq_status launch_cols_out(const RowsParams& p, hipStream_t s) {
-    if (!std::is_same_v<One, Two> && p.N <= 4 * 32 * Two::kFN)
-        return p.out_u8 ? launch_cols_cfg<Two, KIND, true>(p, s) : launch_cols_cfg<Two, KIND, false>(p, s);
+    const bool narrow = p.N <= 4 * 32 * One::kFN;
+    if (!std::is_same_v<One, Bytes> && narrow && p.out_u8) return launch_cols_cfg<Bytes, KIND, true>(p, s);
+    if (!std::is_same_v<One, Words> && narrow && !p.out_u8) return launch_cols_cfg<Words, KIND, false>(p, s);
     return p.out_u8 ? launch_cols_cfg<One, KIND, true>(p, s) : launch_cols_cfg<One, KIND, false>(p, s);
 }
 
-template <class One, class Two = One>
+template <class One, class Bytes = One, class Words = Bytes>
 sparq_status launch_cols_kind(TrimKind kind, const RowsParams& p, hipStream_t s) {
     switch (kind) {
-        case kTrimNone: return launch_cols_out<One, Two, kTrimNone>(p, s);
-        case kTrimFloor: return launch_cols_out<One, Two, kTrimFloor>(p, s);
-        case kTrimFloorPair: return launch_cols_out<One, Two, kTrimFloorPair>(p, s);
-        case kTrimFloorPairWide: return launch_cols_out<One, Two, kTrimFloorPairWide>(p, s);
-        case kTrimRound: return launch_cols_out<One, Two, kTrimRound>(p, s);
-        case kTrimRound4: return launch_cols_out<One, Two, kTrimRound4>(p, s);
-        case kTrimRoundPairWide: return launch_cols_out<One, Two, kTrimRoundPairWide>(p, s);
-        case kTrimRoundPair4: return launch_cols_out<One, Two, kTrimRoundPair4>(p, s);
+        case kTrimNone: return launch_cols_out<One, Bytes, Words, kTrimNone>(p, s);
+        case kTrimFloor: return launch_cols_out<One, Bytes, Words, kTrimFloor>(p, s);
+        case kTrimFloorPair: return launch_cols_out<One, Bytes, Words, kTrimFloorPair>(p, s);
+        case kTrimFloorPairWide: return launch_cols_out<One, Bytes, Words, kTrimFloorPairWide>(p, s);
+        case kTrimRound: return launch_cols_out<One, Bytes, Words, kTrimRound>(p, s);
+        case kTrimRound4: return launch_cols_out<One, Bytes, Words, kTrimRound4>(p, s);
+        case kTrimRoundPairWide: return launch_cols_out<One, Bytes, Words, kTrimRoundPairWide>(p, s);
+        case kTrimRoundPair4: return launch_cols_out<One, Bytes, Words, kTrimRoundPair4>(p, s);
         default: return SPARQ_EUNSUPPORTED;
     }
 }
