@@ -597,18 +597,17 @@ ConvPlan make_plan_of(const ConvGeom& g, const Tuning& tune, bool forms, bool by
     return pl;
 }
 
-// Vector instructions that trim 16 bytes (kTrimFloor by its timings: it has 32), as of the timings below; the four with rounding have
-// since come down to 68, 108, 64 and 76.
+// Vector instructions that trim 16 bytes (kTrimFloor by its timings: it has 32).
 int trim_instructions(TrimKind kind) {
-    static const int instructions[kTrimKinds] = {0, 40, 48, 64, 80, 128, 68, 84};
+    static const int instructions[kTrimKinds] = {0, 40, 48, 64, 68, 108, 64, 76};
     return instructions[kind];
 }
 
 // What trimming while staging adds to a tile kernel, against the copy: the trim's instructions for the patch beyond those that the taps'
 // matrix instructions cover, tile after tile on the busiest CU, and a launch and the tensor written and read once more (1/32 ns and
-// 2 us + 0.25 ns per KB).  Of 950 timed layers with up to 2500 channels none is left more than 5 % behind the better of the two; where all
-// were trimmed in place 119 of the first 500 were, by up to 2.3 x (15 x 15 x 1396 -> 96 1x7/2, seven images, three-bit windows, 38 against
-// 86 us; 7 x 7 x 2148 -> 349 1x7/2, sixteen, 57 against 112: few tiles, each a patch of its own, leave the trim to a few CUs).
+// 2 us + 0.25 ns per KB).  4500 timed layers of up to 2800 channels, trims with rounding: 0.6 % behind the better of the two in the mean, 4.5 % of them
+// more than 5 % behind (0.67 at worst); all trimmed in place 0.41 x at worst (15 x 15 x 1396 -> 96 1x7/2, seven images, three-bit windows, 38
+// against 86 us; 7 x 7 x 2148 -> 349 1x7/2, sixteen, 57 against 112: few tiles, each a patch of its own, leave the trim to a few CUs).
 bool staging_outlasts_copy(const ConvGeom& g, const ConvPlan& pl, TrimKind kind) {
     const int64_t tn = pl.variant->tn, tiles = (g.M + kPatchTM - 1) / kPatchTM * ((g.N + tn - 1) / tn), cus = device_cu_count();
     const int64_t beyond = (int64_t)pl.npix * trim_instructions(kind) - (int64_t)34 * g.KH * g.KW * (tn < 128 ? tn : 128);
@@ -622,12 +621,13 @@ bool staging_outlasts_copy(const ConvGeom& g, const ConvPlan& pl, TrimKind kind)
 // pixels 45 -> 39), but for the few whose kernel would trim the same bytes over and over, which keep the copy: several taps in the
 // gather kernel (5x5 on 69 x 69 x 264 52 against 97 us), 128-pixel tiles of long 1x1 reductions for less than half the CUs
 // (2978 x 4312 -> 304 29 against 39), tile kernels whose staging is the longer side (above), and, the trims with the most arithmetic
-// (windows of two or three bits with rounding, 20 and 32 instructions for four bytes), tile kernels that stage more than five bytes for
-// one of x (35 x 35 x 908 -> 736 3x3/2 45 against 66), five column tiles of the eight-wavefront form (9167 x 1276 -> 1216 32 against 38)
-// and long reductions of the split form, which stages all of its patch before the first product (154 x 3364 -> 656 10.6 against 12.4).
-// 1x1 layers trim x once per column tile, which the products of that tile hide in part (`beyond`).  3200 timed layers of 768 to 4600 channels and
-// 2 to 8 columns of 256, in place against the copy, by (instructions - 32) x columns: bytes on the gather kernel 0.95-1.1 x up to 128, 0.92 x at
-// 156, 0.7-0.8 x from 192 on (9739 x 3828 -> 1595, two-bit windows, 105 us against 162); eight wavefronts 1.0-1.4 x up to 255, 0.88-1.0 x beyond.
+// (windows of two or three bits with rounding, 17 and 27 instructions for four bytes), five column tiles of the eight-wavefront form (without
+// pairs 0.98 as bytes, 1.02) and long reductions of the split form, which stages all of its patch before the first product (154 x 3364 -> 656 10.6 against
+// 12.4).  (Tile kernels that stage more than five bytes for one of x kept it as well under those trims: 1400 such layers are 1.09 x faster in place.)
+// 1x1 layers trim x once per column tile, which the products of that tile hide in part (`beyond`).  4400 timed layers of 520 to 4600 channels under the
+// trims with rounding, in place against the copy, by (instructions - 32) x columns: bytes on the gather kernel 1.0-1.06 x up to 108, 0.95-1.0 x from
+// 128 on, 0.7-0.93 x from 176 on; eight wavefronts 1.05-1.1 x up to 176, even from 200 to 264 (pairs at 220 and 228 0.98-1.03, without
+// them at 224 0.99-1.03), 0.92-0.96 x at 288, 0.79-0.91 x from 380 on.
 // The weights-in-registers form trims x once per share of 256 or 512 outputs and beside the products: in place 1.5 x faster than from the copy (22710 timed
 // layers, 3119 x 776 -> 640 among them; 0.1 % below 0.95 x), but for four-byte results under two- and three-bit windows with rounding and pairs, where
 // shares x tenths of a round from 700 on, from 400 with more than 768 channels, are 0.75-1.0 x.
@@ -649,11 +649,10 @@ ConvPlan make_plan(const ConvGeom& g, const Tuning& tune, bool forms = true, boo
         if (pl.wide && !pl.cols && !tune.form) {
             once = tiles_m * ((g.N + 255) / 256) * 2 < device_cu_count();
             const int columns = (g.N + pl.wide->tn - 1) / pl.wide->tn;
-            once = once || (costly && columns >= 5) || beyond * columns > 255;
+            once = once || (costly && columns >= 5) || beyond * columns > (trim_kind_pairs(kind) ? 215 : 255);
         }
         if (pl.patch && !pl.cols && !pl.wide && !pl.split && !pl.block && !pl.rows) {
-            const int64_t staged = tiles_m * ((g.N + pl.variant->tn - 1) / pl.variant->tn) * pl.npix;
-            once = (costly && staged > (int64_t)5 * g.B * g.H * g.W) || staging_outlasts_copy(g, pl, kind);
+            once = staging_outlasts_copy(g, pl, kind);
         }
         if (!once) return pl;
     }

@@ -323,6 +323,25 @@ def test_1x1_layers_that_would_trim_once_per_column_tile(lib, n, mode, copy):
     assert (copy or words(text, "kernel=") == ["conv_wide_kernel"]) and ("padded_copy" in text) == copy, text
 
 
+@pytest.mark.parametrize("shape,k,stride,mode,copy", [
+    # trims of two and three bits with rounding: patches that tiles stage more than five times over, and those that outlast the copy
+    ((2, 54, 54, 116, 131), (3, 3), 1, S.Mode(2, S.OPT7_2B, 1, 1), False), ((3, 21, 21, 60, 274), (3, 1), 1, S.Mode(3, S.OPT6_3B, 1, 0), False),
+    ((35, 35, 35, 908, 736), (3, 3), 2, S.Mode(3, S.OPT6_3B, 1, 1), True), ((9, 31, 31, 2724, 375), (1, 3), 1, S.Mode(2, S.OPT7_2B, 1, 1), True)], ids=str)
+def test_costly_trims_in_tile_kernels_copy_where_staging_outlasts_it(lib, shape, k, stride, mode, copy):
+    """The trims with the most arithmetic are decided on as the others are, by the present instruction counts."""
+    text = plan(lib, S.ConvLayer("words", *shape, *k, (stride, stride), (k[0] // 2, k[1] // 2)), mode)[0]
+    assert words(text, "kernel=") == ["conv_patch_kernel"] and ("padded_copy" in text) == copy, text
+
+
+@pytest.mark.parametrize("n,mode,copy", [
+    (1100, S.Mode(3, S.OPT6_3B, 1, 0), True), (1000, S.Mode(3, S.OPT6_3B, 1, 0), False), (1000, S.Mode(4, S.OPT5, 1, 1), False),
+    (500, S.Mode(2, S.OPT7_2B, 1, 1), False), (600, S.Mode(2, S.OPT7_2B, 1, 1), True)], ids=str)
+def test_1x1_columns_by_the_present_instruction_counts(lib, n, mode, copy):
+    """Either side of the column tiles from which a 1x1 layer's trims outlast the copy: four and five, two and three."""
+    text = plan(lib, S.ConvLayer("columns", 1, 11669, 1, 3444, n), mode)[0]
+    assert ("padded_copy" in text) == copy, text
+
+
 @pytest.mark.parametrize("m,c,n,mode,copy", [
     (3119, 776, 640, S.Mode(4, S.OPT5, 1, 1), False), (3119, 776, 640, S.Mode(2, S.OPT7_2B, 1, 1), False), (36864, 780, 640, S.Mode(3, S.OPT6_3B, 1, 0), False),
     (1110, 760, 1392, S.Mode(4, S.OPT5, 1, 1), False), (46644, 300, 1632, S.Mode(4, S.OPT5, 1, 1), False), (40000, 660, 1280, S.Mode(4, S.OPT5, 1, 1), False),
