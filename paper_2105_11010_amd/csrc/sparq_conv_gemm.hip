@@ -605,13 +605,13 @@ int trim_instructions(TrimKind kind) {
 
 // What trimming while staging adds to a tile kernel, against the copy: the trim's instructions for the patch beyond those that the taps'
 // matrix instructions cover, tile after tile on the busiest CU, and a launch and the tensor written and read once more (1/32 ns and
-// 2 us + 0.25 ns per KB).  4500 timed layers of up to 2800 channels, trims with rounding: 0.6 % behind the better of the two in the mean, 4.5 % of them
-// more than 5 % behind (0.67 at worst); all trimmed in place 0.41 x at worst (15 x 15 x 1396 -> 96 1x7/2, seven images, three-bit windows, 38
+// 1.9 us + 0.25 ns per KB; 1.4 to 2.2 us are as good).  4500 timed layers of up to 2800 channels, trims with rounding: 0.65 % behind the better of the two in the mean, 4.7 %
+// of them more than 5 % (0.67 at worst); all trimmed in place 0.41 x at worst (15 x 15 x 1396 -> 96 1x7/2, seven images, three-bit windows, 38
 // against 86 us; 7 x 7 x 2148 -> 349 1x7/2, sixteen, 57 against 112: few tiles, each a patch of its own, leave the trim to a few CUs).
 bool staging_outlasts_copy(const ConvGeom& g, const ConvPlan& pl, TrimKind kind) {
     const int64_t tn = pl.variant->tn, tiles = (g.M + kPatchTM - 1) / kPatchTM * ((g.N + tn - 1) / tn), cus = device_cu_count();
     const int64_t beyond = (int64_t)pl.npix * trim_instructions(kind) - (int64_t)34 * g.KH * g.KW * (tn < 128 ? tn : 128);
-    return (tiles + cus - 1) / cus * (g.Cq / kStepK) * beyond > 64000 + (int64_t)g.x_bytes / 125;
+    return (tiles + cus - 1) / cus * (g.Cq / kStepK) * beyond > 60000 + (int64_t)g.x_bytes / 125;
 }
 
 // Channel counts that are no multiple of four are contracted from a channel-padded copy, trimmed as it is written.  The others are
