@@ -626,8 +626,8 @@ bool staging_outlasts_copy(const ConvGeom& g, const ConvPlan& pl, TrimKind kind)
 // 12.4).  (Tile kernels that stage more than five bytes for one of x kept it as well under those trims: 1400 such layers are 1.09 x faster in place.)
 // 1x1 layers trim x once per column tile, which the products of that tile hide in part (`beyond`).  4400 timed layers of 520 to 4600 channels under the
 // trims with rounding, in place against the copy, by (instructions - 32) x columns: bytes on the gather kernel 1.0-1.06 x up to 108, 0.95-1.0 x from
-// 128 on, 0.7-0.93 x from 176 on; eight wavefronts 1.05-1.1 x up to 176, even from 200 to 264 (pairs at 220 and 228 0.98-1.03, without
-// them at 224 0.99-1.03), 0.92-0.96 x at 288, 0.79-0.91 x from 380 on.
+// 128 on, 0.7-0.93 x from 176 on; eight wavefronts 1.05-1.1 x up to 176, even from 200 to 264 (rounding with pairs at 220 and 228
+// 0.98-1.03, without them at 224 0.99-1.03), 0.92-0.96 x at 288, 0.79-0.91 x from 380 on.
 // The weights-in-registers form trims x once per share of 256 or 512 outputs and beside the products: in place 1.5 x faster than from the copy (22710 timed
 // layers, 3119 x 776 -> 640 among them; 0.1 % below 0.95 x), but for four-byte results under two- and three-bit windows with rounding and pairs, where
 // shares x tenths of a round from 700 on, from 400 with more than 768 channels, are 0.75-1.0 x.
@@ -649,7 +649,7 @@ ConvPlan make_plan(const ConvGeom& g, const Tuning& tune, bool forms = true, boo
         if (pl.wide && !pl.cols && !tune.form) {
             once = tiles_m * ((g.N + 255) / 256) * 2 < device_cu_count();
             const int columns = (g.N + pl.wide->tn - 1) / pl.wide->tn;
-            once = once || (costly && columns >= 5) || beyond * columns > (trim_kind_pairs(kind) ? 215 : 255);
+            once = once || (costly && columns >= 5) || beyond * columns > (kind == kTrimRoundPair4 || kind == kTrimRoundPairWide ? 215 : 255);
         }
         if (pl.patch && !pl.cols && !pl.wide && !pl.split && !pl.block && !pl.rows) {
             once = staging_outlasts_copy(g, pl, kind);

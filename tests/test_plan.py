@@ -335,9 +335,11 @@ def test_costly_trims_in_tile_kernels_copy_where_staging_outlasts_it(lib, shape,
 
 @pytest.mark.parametrize("n,mode,copy", [
     (1100, S.Mode(3, S.OPT6_3B, 1, 0), True), (1000, S.Mode(3, S.OPT6_3B, 1, 0), False), (1000, S.Mode(4, S.OPT5, 1, 1), False),
-    (500, S.Mode(2, S.OPT7_2B, 1, 1), False), (600, S.Mode(2, S.OPT7_2B, 1, 1), True)], ids=str)
+    (500, S.Mode(2, S.OPT7_2B, 1, 1), False), (600, S.Mode(2, S.OPT7_2B, 1, 1), True),
+    (3500, S.Mode(2, S.OPT7_2B, 0, 1), False)], ids=str)
 def test_1x1_columns_by_the_present_instruction_counts(lib, n, mode, copy):
-    """Either side of the column tiles from which a 1x1 layer's trims outlast the copy: four and five, two and three."""
+    """Either side of the column tiles from which a 1x1 layer's trims outlast the copy: four and five, two and three; windows that
+    round down with pairs as before, at seven."""
     text = plan(lib, S.ConvLayer("columns", 1, 11669, 1, 3444, n), mode)[0]
     assert ("padded_copy" in text) == copy, text
 
