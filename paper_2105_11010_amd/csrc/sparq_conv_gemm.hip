@@ -340,7 +340,13 @@ struct ColsSplit {
 //   whole.  19000 timed layers: up to 512 channels 1.0-1.3 x up to 24 MiB of results, beyond 0.43-1.0 (284 -> 1625, 46644 pixels 122 us against 222), and
 //   0.81-1.0 where the forms above or below stand; up to 768 channels 1.13-1.26 up to 80 MiB, beyond 1.07 with a fifth below 0.95, from 128 on 0.64-1.0;
 //   up to 1024 1.16-1.3 up to 128 MiB; rows on a 32-byte border 1.08-1.3 up to 160.
-const ColsVariant* pick_cols(const ConvGeom& g, bool bytes, bool plain, bool heavy, bool rows, bool wide) {
+//   In its first rounds a trim with little arithmetic leaves the forms above and below less to win against (84500 timed layers of 133 to 512 channels).  448
+//   and 512 channels, four-byte results: untrimmed up to 1.3 rounds 0.81-0.98 (0.67 at worst; 512 channels with all wavefronts at work 1.03), up to 2.5 where the
+//   form below stands 0.94; windows that round down between 1.0 and 1.3 0.94 (all at work beside the form above 1.01); 193 to 256 channels from 1.6 to 2.2 with a
+//   tenth of the wavefronts idle 0.93-0.97.  What rounds is 1.02-1.2 there.
+// `trim`: what the kernel itself trims with (none beside the padded copy).
+const ColsVariant* pick_cols(const ConvGeom& g, bool bytes, TrimKind trim, bool rows, bool wide) {
+    const bool plain = trim == kTrimNone, light = trim <= kTrimFloorPairWide, heavy = trim == kTrimRoundPairWide;
     const ColsVariant* v = g.Cq > 128 && (bytes || rows || !plain || g.Cq > 512) ? fit_cols(g, bytes) : nullptr;
     if (!v) return nullptr;
     const ColsSplit split(*v, g);
@@ -363,6 +369,12 @@ const ColsVariant* pick_cols(const ConvGeom& g, bool bytes, bool plain, bool hea
     if (heavy && !two && !bytes && shares % 2 == 0) {
         const bool slower = v->steps == 24 ? tenths >= 200 || (tenths >= 60 && tenths < 80) : tenths >= 40 && !(tenths >= 80 && tenths < 100);
         if (slower) return nullptr;
+    }
+    if (!bytes && two && !narrow && light) {
+        const bool all = groups == shares * per;
+        if (v->steps == 16 && plain && ((tenths < 13 && !(all && g.Cq > 448)) || (wide && tenths < 25))) return nullptr;
+        if (v->steps == 16 && !plain && tenths >= 10 && tenths < 13 && !(all && rows)) return nullptr;
+        if (v->steps == 8 && tenths >= 16 && tenths < 22 && groups * 10 < shares * per * 9) return nullptr;
     }
     bool take;
     if (narrow) take = filled && tenths >= 40 && v->steps > 8 && groups * 64 - g.N <= 16 && (bytes ? g.N > 96 : v->steps == 12 && g.N > 176);
@@ -578,7 +590,7 @@ ConvPlan make_plan_of(const ConvGeom& g, const Tuning& tune, bool forms, bool by
         pl.rows = pick_rows(gk, bytes, plain);
         if ((!pl.rows || g.K > 256) && (pl.split = pick_split(gk, &pl.pg, &pl.npix)) != nullptr) return pl;
         pl.wide = pick_wide(gk, bytes, plain);
-        pl.cols = pick_cols(gk, bytes, plain, kind == kTrimRoundPairWide && !copy, pl.rows != nullptr, pl.wide != nullptr);
+        pl.cols = pick_cols(gk, bytes, copy ? kTrimNone : kind, pl.rows != nullptr, pl.wide != nullptr);
     }
     // (units of four blocks and the sparse form's result rows leave LDS for one workgroup per CU, where narrow layers with more tiles
     // than CUs want two: 72 -> 16, expanded to four blocks, 401408 pixels 63 against 54 us in units of two)

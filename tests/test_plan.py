@@ -94,7 +94,7 @@ def test_plan_names_the_kernel_of_either_result(lib, shape, kernel, u8_kernel):
     assert words(text, "kernel=") == [kernel] and words(text, "u8_kernel=") == [u8_kernel], text
 
 
-M45, PLAIN = S.Mode(4, S.OPT5, 1, 1), S.PLAIN8
+M45, PLAIN, FLOOR = S.Mode(4, S.OPT5, 1, 1), S.PLAIN8, S.Mode(4, S.OPT3, 0, 0)
 
 
 @pytest.mark.parametrize("form,shape,mode,takes", [
@@ -161,6 +161,20 @@ def test_weights_in_registers_leave_full_rounds_of_the_other_form(lib, m, c, n, 
     """Where the form with the activations in registers fills its last round, it keeps the layers it is ahead on."""
     text = plan(lib, S.ConvLayer("rounds", 1, m, 1, c, n), S.Mode(4, S.OPT5, 1, 1))[0]
     assert (words(text, "kernel=") == ["conv_cols_kernel"], words(text, "u8_kernel=") == ["conv_cols_kernel"]) == takes, text
+
+
+@pytest.mark.parametrize("m,c,n,mode,takes", [
+    # 448 and 512 channels, four-byte results: untrimmed up to 1.3 rounds but where all wavefronts are at work, and up to 2.5 beside the eight-wavefront form
+    (2600, 448, 1088, PLAIN, False), (3600, 448, 1088, PLAIN, True), (4000, 448, 720, PLAIN, False), (4200, 512, 512, PLAIN, True), (8487, 464, 512, PLAIN, False),
+    (5156, 512, 1248, PLAIN, False), (2600, 448, 1088, M45, True),
+    # windows that round down, between 1.0 and 1.3 rounds
+    (2600, 448, 1088, FLOOR, False), (2300, 448, 1088, FLOOR, True), (3600, 448, 1088, FLOOR, True), (4352, 448, 1024, FLOOR, True),
+    # 193 to 256 channels: from 1.6 to 2.2 rounds with a tenth of the wavefronts idle
+    (14060, 256, 432, FLOOR, False), (14060, 256, 512, FLOOR, True), (14060, 256, 432, PLAIN, False), (12800, 256, 432, PLAIN, True), (18100, 256, 432, PLAIN, True), (14060, 256, 432, M45, True)])
+def test_weights_in_registers_leave_trims_with_little_arithmetic(lib, m, c, n, mode, takes):
+    """The first rounds of four-byte results, where the trim does not fill them: the forms above and below keep these."""
+    text = plan(lib, S.ConvLayer("light", 1, m, 1, c, n), mode)[0]
+    assert (words(text, "kernel=") == ["conv_cols_kernel"]) == takes and words(text, "u8_kernel=") == ["conv_cols_kernel"], text
 
 
 @pytest.mark.parametrize("m,c,n,takes", [
