@@ -340,10 +340,11 @@ struct ColsSplit {
 //   whole.  19000 timed layers: up to 512 channels 1.0-1.3 x up to 24 MiB of results, beyond 0.43-1.0 (284 -> 1625, 46644 pixels 122 us against 222), and
 //   0.81-1.0 where the forms above or below stand; up to 768 channels 1.13-1.26 up to 80 MiB, beyond 1.07 with a fifth below 0.95, from 128 on 0.64-1.0;
 //   up to 1024 1.16-1.3 up to 128 MiB; rows on a 32-byte border 1.08-1.3 up to 160.
-//   In its first rounds a trim with little arithmetic leaves the forms above and below less to win against (84500 timed layers of 133 to 512 channels).  448
-//   and 512 channels, four-byte results: untrimmed up to 1.3 rounds 0.81-0.98 (0.67 at worst; 512 channels with all wavefronts at work 1.03), up to 2.5 where the
-//   form below stands 0.94; windows that round down between 1.0 and 1.3 0.94 (all at work beside the form above 1.01); 193 to 256 channels from 1.6 to 2.2 with a
-//   tenth of the wavefronts idle 0.93-0.97.  What rounds is 1.02-1.2 there.
+//   In its first rounds a trim with little arithmetic leaves the forms above and below less to win against (84500 timed layers of 133 to 512 channels on the same
+//   buffers, 44200 on 16 in turn; the latter): four-byte results of 448 and 512 channels, untrimmed 0.90-0.92 x below one round (0.69 at worst; 512 channels with
+//   all wavefronts at work 1.03) and 1.04 up to 1.3, beside the form below 0.87-0.98 up to 2.5; windows that round down 0.96-0.98 between 1.0 and 1.3
+//   (on the same buffers 0.94; all at work beside the form above 1.01); 193 to 256 channels from 1.6 to 2.2 rounds with a tenth of the wavefronts idle
+//   0.96-1.01 (0.92-0.96).  What rounds is 1.02-1.2 there.
 // `trim`: what the kernel itself trims with (none beside the padded copy).
 const ColsVariant* pick_cols(const ConvGeom& g, bool bytes, TrimKind trim, bool rows, bool wide) {
     const bool plain = trim == kTrimNone, light = trim <= kTrimFloorPairWide, heavy = trim == kTrimRoundPairWide;
@@ -372,7 +373,7 @@ const ColsVariant* pick_cols(const ConvGeom& g, bool bytes, TrimKind trim, bool 
     }
     if (!bytes && two && !narrow && light) {
         const bool all = groups == shares * per;
-        if (v->steps == 16 && plain && ((tenths < 13 && !(all && g.Cq > 448)) || (wide && tenths < 25))) return nullptr;
+        if (v->steps == 16 && plain && ((tenths < 10 && !(all && g.Cq > 448)) || (wide && tenths < 25))) return nullptr;
         if (v->steps == 16 && !plain && tenths >= 10 && tenths < 13 && !(all && rows)) return nullptr;
         if (v->steps == 8 && tenths >= 16 && tenths < 22 && groups * 10 < shares * per * 9) return nullptr;
     }
