@@ -335,11 +335,13 @@ struct ColsSplit {
 //   Beyond 512 channels a share is 256 outputs, where a tile of the form below has 512, so with an even number of shares it trims twice as often.  Four-byte
 //   results under the trims with the most arithmetic (`heavy`: windows of two or three bits with rounding and pairs) were then 0.94 x from four
 //   rounds on with more than 768 channels (1.06-1.15 between eight and ten, where the form below starts a round), with up to 768 0.93 from twenty
-//   rounds on and 0.97-1.05 between six and eight (768 -> 1024, 80384 pixels, two-bit windows 106 against 149 us).
+//   rounds on and 0.97-1.05 between six and eight (768 -> 1024, 80384 pixels, two-bit windows 106 against 149 us; rows off a 64-byte border, which the
+//   form below writes as slowly, 1.16-1.25).
 //   Four-byte rows off a 64-byte border leave as pieces of lines, which only the caches put together again; the tile kernels write such rows
 //   whole.  19000 timed layers: up to 512 channels 1.0-1.3 x up to 24 MiB of results, beyond 0.43-1.0 (284 -> 1625, 46644 pixels 122 us against 222), and
-//   0.81-1.0 where the forms above or below stand; up to 768 channels 1.13-1.26 up to 80 MiB, beyond 1.07 with a fifth below 0.95, from 128 on 0.64-1.0;
-//   up to 1024 1.16-1.3 up to 128 MiB; rows on a 32-byte border 1.08-1.3 up to 160.
+//   0.81-1.0 where the forms above or below stand; up to 768 channels 1.13-1.26 up to 80 MiB.  From there on, 1500 layers on up to 16 buffers in turn: up to 768
+//   channels 1.05-1.1 up to 140 MiB, then even (0.97-1.03; on the same buffers 0.9 from there on), rows on a 32-byte border 1.02-1.08 up to 384; up to 1024
+//   channels 1.06-1.18 up to the most that the lines below let through (160).
 //   In its first rounds a trim with little arithmetic leaves the forms above and below less to win against (84500 timed layers of 133 to 512 channels on the same
 //   buffers, 44200 on 16 in turn; the latter): four-byte results of 448 and 512 channels, untrimmed 0.90-0.92 x below one round (0.69 at worst; 512 channels with
 //   all wavefronts at work 1.03) and 1.04 up to 1.3, beside the form below 0.87-0.98 up to 2.5; windows that round down 0.96-0.98 between 1.0 and 1.3
@@ -356,7 +358,7 @@ const ColsVariant* pick_cols(const ConvGeom& g, bool bytes, TrimKind trim, bool 
     const bool filled = g.Cq * 8 >= v->steps * 32 * 7, full = groups * 10 >= shares * per * (bytes && v->steps < 16 && tenths >= 40 ? 8 : 7);
     if (!bytes && g.N % 16) {
         const int64_t mib = g.M * g.N * 4 >> 20;
-        if (two ? rows || wide || mib >= 24 : mib >= (g.N % 8 == 0 ? 160 : v->steps == 24 ? 80 : 128)) return nullptr;
+        if (two ? rows || wide || mib >= 24 : v->steps == 24 && mib >= (g.N % 8 == 0 ? 384 : 140)) return nullptr;
     }
     const int64_t round = (int64_t)device_cu_count() * 256, last = (g.M - 1) % (2 * round) + 1;
     const bool fills = g.M <= round >> (shares - 1) && g.M * 4 > (round >> (shares - 1)) * 3;
@@ -367,7 +369,7 @@ const ColsVariant* pick_cols(const ConvGeom& g, bool bytes, TrimKind trim, bool 
         if (last * 4 > 2 * round * 3 && !(filled && groups * 8 >= shares * per * eighths)) return nullptr;
         if (g.M <= round && v->steps < 16 && !(filled && groups * 8 >= shares * per * 7)) return nullptr;
     }
-    if (heavy && !two && !bytes && shares % 2 == 0) {
+    if (heavy && !two && !bytes && g.N % 16 == 0 && shares % 2 == 0) {
         const bool slower = v->steps == 24 ? tenths >= 200 || (tenths >= 60 && tenths < 80) : tenths >= 40 && !(tenths >= 80 && tenths < 100);
         if (slower) return nullptr;
     }

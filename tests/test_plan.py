@@ -137,8 +137,8 @@ def test_rules_leave_layers_to_the_tile_kernels(lib, form, shape, mode, takes):
 
 @pytest.mark.parametrize("m,c,n,takes", [
     (46644, 284, 1625, False), (46644, 320, 1632, True), (13900, 256, 450, True), (14100, 256, 450, False), (163072, 432, 493, False),
-    (726180, 352, 190, False), (4100, 512, 500, False), (4200, 512, 512, True), (57900, 768, 362, True), (58000, 768, 362, False),
-    (110000, 768, 376, True), (112000, 768, 376, False), (33500, 1024, 1001, True), (33600, 1024, 1001, False)])
+    (726180, 352, 190, False), (4100, 512, 500, False), (4200, 512, 512, True), (101300, 768, 362, True), (101400, 768, 362, False),
+    (267600, 768, 376, True), (267800, 768, 376, False), (33600, 1024, 1001, True)])
 def test_weights_in_registers_leave_rows_off_a_line(lib, m, c, n, takes):
     """Four-byte rows off a 64-byte border leave that kernel as pieces of lines: up to the results that the caches put together."""
     text = plan(lib, S.ConvLayer("rows", 1, m, 1, c, n), S.Mode(4, S.OPT5, 1, 1))[0]
@@ -189,6 +189,8 @@ def test_weights_in_registers_leave_trims_that_cost_more_twice(lib, m, c, n, tak
     for mode in (S.Mode(2, S.OPT7_2B, 1, 1), S.Mode(3, S.OPT6_3B, 1, 1)):
         assert words(plan(lib, layer, mode)[0], "kernel=") == ["conv_cols_kernel" if takes else "conv_wide_kernel"]
     assert words(plan(lib, layer, S.Mode(2, S.OPT7_2B, 0, 1))[0], "kernel=") == ["conv_cols_kernel"]
+    # (rows off a 64-byte border)
+    assert words(plan(lib, S.ConvLayer("heavy", 1, 17000, 1, 1024, 501), S.Mode(2, S.OPT7_2B, 1, 1))[0], "kernel=") == ["conv_cols_kernel"]
 
 
 @pytest.mark.parametrize("m,c,n,held,run", [
