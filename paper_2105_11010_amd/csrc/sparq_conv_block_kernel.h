@@ -9,7 +9,7 @@
 // instead: ahead beyond 64 of them, except where rows are wide (35 x 35 x 64 -> 96 3x3, batch 128, bytes 21.1 -> 19.1 us; the tile
 // kernel 23.5).  A patch pixel's address is worked out once per tile, into
 // LDS.  Requantised results: weights as the row operand (see sparq_conv_rows_kernel.h), rows leave through LDS.
-// Bound by vector issue (60 % of the cycles by the counters, the matrix pipeline 30) and the phases' waits (40 % of a wavefront's
+// Bound by vector issue (66 % of the cycles by the counters, the matrix pipeline 30) and the phases' waits (40 % of a wavefront's
 // life): 56 x 56 x 64 -> 64 3x3, batch 256, bytes: 78 -> 52 us (memory alone 21, the
 // matrix instructions 18); three workgroups per CU with twice the weights requested ahead: 63; 128 pixels per tile: 77.  Waits that count
 // exactly -- no request under a condition, none of the staging's left when the taps begin, fragments and weights asked for where it is

@@ -13,7 +13,8 @@
 // 512 -> 1024/2, 50176 pixels 48.1 -> 36.0; 512 -> 2048, 12544 pixels 26.1 -> 22.5; 1024 -> 256, 50176 pixels 30.0 -> 26.7; fp32, 768 -> 192, 36992
 // pixels 22.8 -> 18.4.
 // Bound by vector arithmetic and the stores: per pixel 256 -> 1024 takes 1.4 times as long as a copy of its bytes, and 7 us are the first
-// loads, weights and trim.  (Vector issue 52 % of the cycles, matrix pipeline 27 %.  Two tiles requested ahead, with the tiles a round of requests
+// loads, weights and trim.  (Vector issue 53 % of the cycles, the matrix pipeline 29, waits 34 % of a wavefront's
+// life; 1024 channels 48, 26 and 38.  Two tiles requested ahead, with the tiles a round of requests
 // leaves empty: up to 7 % slower; 16 wavefronts' worth of outputs in two walks instead of two workgroups: within 3 % of this.)
 #pragma once
 #include "sparq_conv_rows_kernel.h"

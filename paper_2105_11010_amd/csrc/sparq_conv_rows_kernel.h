@@ -13,8 +13,9 @@
 // pieces straight from the registers 64 -> 256 channels took 118 us, this way 58).  int32 / fp32 results: the activations
 // are the row operand and a store writes whole runs.
 // Many pixels and few enough weights: one workgroup per CU holds all of them in LDS, and memory is what bounds the layer (launch_rows_held,
-// where the figures are).  Otherwise the weights come from L2, and with 256 channels and more they and the trim's vector instructions do
-// (192 -> 512: vector issue 45 to 53 % of the cycles, waits 25 % of a wavefront's life); wide layers of 256 channels and more hold the weights instead (sparq_conv_cols_kernel.h).
+// where the figures are).  Otherwise the weights come from L2, and with 256 channels and more they and the trim's vector instructions
+// bound it; wide layers of 256 channels and more hold the weights instead (sparq_conv_cols_kernel.h).  By the counters, bytes, weights in LDS: 64 channels
+// vector issue 67 % of the cycles, the matrix pipeline 13, waits 35 % of a wavefront's life; 256 channels 59, 12 and 20.
 #pragma once
 #include "sparq_conv_patch_kernel.h"
 
@@ -345,7 +346,8 @@ struct RowsHeld {
 // 48 -> 41; fp32, 288 -> 48, 156800 pixels 25.8 -> 20.9, 192 -> 48 17.5 -> 13.2.  Warm, 2321 drawn layers with pixels for every slot:
 // bytes 1.08 x (7 of 1403 below 0.95, the lowest 0.91; 0.94 x with half the pixels).  Four-byte results up to 64 outputs 1.05 x, but with more
 // than 256 channels 0.96 x up to 1.3 rounds (lowest 0.86, the second round nearly empty); up to 128 from two rounds on 1.04, up to 96 of more than
-// 256 channels from 1.5 on as much faster as slower warm (0.85 to 1.05), cold 27.1 -> 21.8 (288 -> 96); wider ones are bound by their stores and
+// 256 channels from 1.5 on as much faster as slower warm (0.85 to 1.05), cold 27.1 -> 21.8 (288 -> 96; 26328 layers
+// of up to 128 outputs on 16 buffers in turn: 33 outputs and more in up to 2.5 rounds 1.04-1.2, on the same ones 0.95-1.03); wider ones are bound by their stores and
 // lose as much as they gain (0.78 to 1.1).  More weights than fit beside three wavefronts per SIMD, bytes, up to 128 KB: 1.13 x from three rounds of
 // two on, but 0.98 x with up to 256 channels.
 // Returns the bytes of a result row that leave together (128: Main, 64: Large); 0: the weights stay in L2.

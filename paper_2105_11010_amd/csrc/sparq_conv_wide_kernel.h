@@ -11,8 +11,8 @@
 // The trim goes between the matrix instructions in quarters of a step, by hand: left to the scheduler it bunches (65536 x
 // 4608 x 512, int32: 188 us, this way 172; the gather kernel 197; bytes 154 against 233).  Bound by the step's traffic beside the
 // matrix pipeline (without any trim 144): 32 KB of weights through L1 and 64 KB of fragments through LDS per 1024 cycles
-// of matrix instructions, and by the result stores, which both tiles of a CU wait for (18 us of int32 results).  Counters: matrix pipeline busy 54 %
-// of the cycles, vector issue 50, LDS 23, a quarter of a wavefront's life in waits.
+// of matrix instructions, and by the result stores, which both tiles of a CU wait for (18 us of int32 results).  Counters: matrix pipeline busy 56 %
+// of the cycles, vector issue 48, LDS 23, a quarter of a wavefront's life in waits.
 #pragma once
 #include "sparq_conv_patch_kernel.h"
 
