@@ -94,7 +94,8 @@ def test_plan_names_the_kernel_of_either_result(lib, shape, kernel, u8_kernel):
     assert words(text, "kernel=") == [kernel] and words(text, "u8_kernel=") == [u8_kernel], text
 
 
-M45, PLAIN, FLOOR = S.Mode(4, S.OPT5, 1, 1), S.PLAIN8, S.Mode(4, S.OPT3, 0, 0)
+M45, PLAIN = S.Mode(4, S.OPT5, 1, 1), S.PLAIN8
+FLOOR = S.Mode(4, S.OPT3, 0, 0)
 
 
 @pytest.mark.parametrize("form,shape,mode,takes", [
